@@ -264,16 +264,13 @@ int het_last_evicted(het_cache *c, int64_t *ids, int64_t *n);
  * loops, harnesses that forbid hipMalloc): het_lookup of a cache created with HET_POLICY_NONE,
  * without a cache object.  out[i][:] = table[ids[i]][:] for ids (device, int64[n]) inside
  * [0, vocab), zero rows for the others; table is float[vocab][dim] (device, or pinned host memory
- * mapped into the device), out float[n][dim] (device).  The ids go through the same sort, run
- * marking and gather kernels as het_lookup; their workspaces (sort buffers, per-position arrays,
- * scalars) live in a static device array of about 1.8 MB that every GPU the library runs on holds
- * until the process ends, so the call allocates and frees nothing, on the device or through any
- * library.  n may be at most HET_NOALLOC_MAX_IDS; dim as for het_cache_configure; vocab below
- * 2^31.  The work is enqueued on hip_stream (a hipStream_t, NULL = the default stream) and the
+ * mapped into the device), out float[n][dim] (device).  One kernel gathers the rows where the ids
+ * stand (a read needs no order), with no workspace: the call allocates and frees nothing, and calls
+ * may overlap freely.  n may be at most HET_NOALLOC_MAX_IDS; dim as for het_cache_configure; vocab
+ * below 2^31.  The work is enqueued on hip_stream (a hipStream_t, NULL = the default stream) and the
  * call returns without waiting.  err_bits (device, uint32, may be NULL) receives, in stream order,
- * 1 if some id was outside the vocabulary, else 0.  All calls on one GPU share the array: calls
- * whose work overlaps on one GPU (two streams, two threads) race and must be serialised by the
- * caller.  HET_EINVAL: a size out of range or a NULL pointer.  HET_EHIP: the runtime refused.
+ * 1 if some id was outside the vocabulary, else 0 (calls that overlap need one each).
+ * HET_EINVAL: a size out of range or a NULL pointer.  HET_EHIP: the runtime refused.
  */
 #define HET_NOALLOC_MAX_IDS 65536
 int het_lookup_nocache_static(const float *table, int64_t vocab, int32_t dim, const int64_t *ids, int64_t n,

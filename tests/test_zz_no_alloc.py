@@ -57,3 +57,27 @@ def test_sizes_beyond_the_static_scratch_are_refused():
     assert hc.lookup_nocache_static(table, ids[:0], out) == hc.HET_OK          # nothing to do
     wide = torch.zeros(4, 5000, device=dev)
     assert hc.lookup_nocache_static(wide, ids[:4], torch.zeros(4, 5000, device=dev)) == hc.HET_EINVAL
+
+
+@pytest.mark.parametrize("n,dim,bad_at", [(1, 64, None), (1, 64, 0), (255, 10, 254), (4_097, 130, None), (8_192, 16, 8_191),
+                                          (8_193, 16, 8_192), (40_000, 260, 39_999), (65_536, 4, None), (65_536, 1_023, 17)])
+def test_every_variant_of_the_static_lookup_copies_rows_exactly(n, dim, bad_at):
+    """Rows are copied, so the result is exact: whole 16-byte pieces or single floats, one piece per lane or
+    several, the ids checked inside the launch (up to 8192) or behind a clear."""
+    dev = torch.device("cuda:0")
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(n)
+    V = 3_001
+    table = torch.randn(V, dim, generator=gen, device=dev)
+    ids = torch.randint(0, V, (n,), generator=gen, device=dev)
+    if bad_at is not None:
+        ids[bad_at] = V
+    err = torch.full((1,), 77, dtype=torch.int32, device=dev)
+    want = torch.where((ids < V)[:, None], table[ids.clamp(max=V - 1)], torch.zeros((), device=dev))
+    for _ in range(2):
+        got = torch.full((n, dim), float("nan"), device=dev)
+        assert hc.lookup_nocache_static(table, ids, got, err) == hc.HET_OK
+        assert torch.equal(got, want)
+        assert int(err.item()) == (0 if bad_at is None else 1)
+    assert hc.lookup_nocache_static(table, ids, got.zero_()) == hc.HET_OK          # nobody asks for the error bits
+    assert torch.equal(got, want)
