@@ -122,10 +122,16 @@ __device__ __forceinline__ void count2(unsigned long long *a, unsigned long long
 // The victims are the m = size - capacity cached rows smallest in (last_use, slot) [LRU] or
 // (freq, last_use, slot) [LFU].  A most-significant-digit radix select finds the policy key
 // tau of the m-th smallest row; rows below tau go, and of the rows equal to tau the first few in
-// slot order.  `bits` is the width of last_use / freq values (both are at most t).
+// slot order.
+// Under LFU only rows of use count 1 can go: a trim never has more to drop than the lookup before it
+// fetched (the cache was within its capacity before), and the rows that lookup fetched all have
+// count 1, so the m-th smallest has count 1 too.  So the policy key is last_use under both policies,
+// `bits` wide (last_use is at most t), and LFU's select simply passes over the rows of a higher
+// count.  (With (freq, last_use) as the key a select had three passes and a kernel of its own for
+// its last stage from iteration 2048 on: 11.4 us of an 87 us step at 206 000 slots.)
 constexpr int SEL_BITS = 11;
 constexpr int SEL_BINS = 1 << SEL_BITS;
-constexpr int SEL_MAX_PASSES = 6;
+constexpr int SEL_MAX_PASSES = 3;     // last_use has at most 32 bits
 constexpr int TRIM_THREADS = 256;
 constexpr int TRIM_WAVES = TRIM_THREADS / WAVE;
 constexpr int TRIM_ITEMS = 4;
@@ -133,8 +139,7 @@ constexpr int TRIM_TILE = TRIM_THREADS * TRIM_ITEMS;   // 1024 slots per countin
 
 struct TrimPlan {
     int lfu;          // policy
-    int bits;         // bits per policy field
-    int key_bits;     // bits of the packed policy key
+    int key_bits;     // bits of the policy key (last_use)
     int passes;       // select passes
     int h0_kept;      // the first pass's histogram is kept up to date between trims (by the probe and the eviction), not counted anew
     uint32_t *hist;   // [SEL_MAX_PASSES][SEL_BINS] followed by sup_cnt: zeroed together before the first pass
@@ -149,11 +154,9 @@ struct TrimPlan {
                                        // every row that Read touched will hold updates when the step is done, whether its clock has moved yet or not
 };
 
-__device__ __forceinline__ uint64_t policy_key(const TrimPlan &tp, const uint4 &meta)
-{
-    const uint64_t lu = meta.z;
-    return tp.lfu ? (((uint64_t)meta.w << tp.bits) | lu) : lu;
-}
+__device__ __forceinline__ uint32_t policy_key(const uint4 &meta) { return meta.z; }
+// Can the row be evicted at all?  (See above: under LFU only rows used once.)
+__device__ __forceinline__ bool evictable(const TrimPlan &tp, const uint4 &meta) { return !tp.lfu || meta.w == 1u; }
 
 __device__ __forceinline__ int sel_shift(const TrimPlan &tp, int pass)
 {
@@ -169,7 +172,7 @@ __device__ __forceinline__ int sel_width(const TrimPlan &tp, int pass)
 // Replays the select decisions of passes [0, upto): returns the key prefix chosen so far
 // (in the high bits of `prefix`) and how many victims remain to be found inside it.
 // Every thread of the block gets the same answer.
-__device__ __forceinline__ void sel_replay(const TrimPlan &tp, int upto, uint32_t m, uint64_t &prefix,
+__device__ __forceinline__ void sel_replay(const TrimPlan &tp, int upto, uint32_t m, uint32_t &prefix,
                                            uint32_t &remaining, uint32_t *lds_pick, uint32_t *lds_scan)
 {
     prefix = 0; remaining = m;
@@ -196,7 +199,7 @@ __device__ __forceinline__ void sel_replay(const TrimPlan &tp, int upto, uint32_
         __syncthreads();
         const uint32_t digit = lds_pick[0], below = lds_pick[1];
         __syncthreads();
-        prefix |= (uint64_t)digit << sel_shift(tp, p);
+        prefix |= digit << sel_shift(tp, p);
         remaining -= below;
     }
 }
@@ -246,40 +249,40 @@ __device__ __forceinline__ void trim_hist_body(const CacheView &cv, const TrimPl
 {
     const int32_t over = cv.ds->size - (int32_t)cv.capacity;
     if (over <= 0 && !always) return;
-    uint64_t prefix; uint32_t remaining;
+    uint32_t prefix, remaining;
     sel_replay(tp, pass, (uint32_t)over, prefix, remaining, l.pick, l.scan);
     for (int b = threadIdx.x; b < SEL_BINS; b += TRIM_THREADS) l.bins[b] = 0;
     __syncthreads();
     const int shift = sel_shift(tp, pass), width = sel_width(tp, pass);
     const int decided = shift + width;                 // bits above are fixed by the prefix
     if (beside_fill && vblock == 0 && threadIdx.x == 0 && new_rows) {
-        const uint64_t k = policy_key(tp, make_uint4(0, 0, t_now, 1));
-        if (decided >= 64 || (k >> decided) == (prefix >> decided))
-            atomicAdd(&tp.hist[pass * SEL_BINS + ((uint32_t)(k >> shift) & ((1u << width) - 1u))], new_rows);
+        if (decided >= 32 || (t_now >> decided) == (prefix >> decided))
+            atomicAdd(&tp.hist[pass * SEL_BINS + ((t_now >> shift) & ((1u << width) - 1u))], new_rows);
     }
     for (uint32_t slot = vblock * TRIM_THREADS + threadIdx.x; slot < cv.n_slots; slot += nblocks * TRIM_THREADS) {
         const uint32_t sk = cv.slot_key[slot];
         const uint4 m = load_meta(cv.meta, slot);
         const bool skip = beside_fill ? cv.was_free[slot] != 0 : sk == KEY_NONE;
-        if (skip) continue;
-        const uint64_t k = policy_key(tp, m);
-        if (decided < 64 && (k >> decided) != (prefix >> decided)) continue;
-        atomicAdd(&l.bins[(uint32_t)(k >> shift) & ((1u << width) - 1u)], 1u);
+        if (skip || !evictable(tp, m)) continue;
+        const uint32_t k = policy_key(m);
+        if (decided < 32 && (k >> decided) != (prefix >> decided)) continue;
+        atomicAdd(&l.bins[(k >> shift) & ((1u << width) - 1u)], 1u);
     }
     __syncthreads();
     for (int b = threadIdx.x; b < SEL_BINS; b += TRIM_THREADS)
         if (l.bins[b]) atomicAdd(&tp.hist[pass * SEL_BINS + b], l.bins[b]);
 }
 
-// The first pass's histogram (policy keys of all cached rows by their top digit) need not be
+// The first pass's histogram (policy keys of all evictable rows by their top digit) need not be
 // counted anew for every trim: a Read changes the keys of the rows it finds and adds the rows it
 // fetches, a trim removes its victims, nothing else touches policy keys.  So the probe moves the
 // rows it touches from their old bin to their new one, and the eviction takes its victims out
-// (h0_remove_victims); the select of the next trim starts at its second pass.  The digit layout
-// depends on the width of the iteration count: when that grows, the histogram is counted afresh.
-__device__ __forceinline__ uint32_t h0_bin(const TrimPlan &tp, uint64_t key)
+// (h0_remove_victims); the select of the next trim starts at its second pass (up to iteration 2047
+// there is none: the first digit is the whole key).  The digit's place depends on the width of the
+// iteration count: when it moves, the histogram is counted afresh.
+__device__ __forceinline__ uint32_t h0_bin(const TrimPlan &tp, uint32_t key)
 {
-    return (uint32_t)(key >> sel_shift(tp, 0)) & ((1u << sel_width(tp, 0)) - 1u);
+    return (key >> sel_shift(tp, 0)) & ((1u << sel_width(tp, 0)) - 1u);
 }
 
 // All rows in bins below the threshold's first digit were evicted, and of that digit's bin as
@@ -288,7 +291,7 @@ __device__ __forceinline__ void h0_remove_victims(const CacheView &cv, const Tri
 {
     const int32_t over = cv.ds->over;
     if (over <= 0) return;
-    uint64_t prefix; uint32_t remaining;
+    uint32_t prefix, remaining;
     sel_replay(tp, 1, (uint32_t)over, prefix, remaining, lds_pick, lds_scan);       // (ends with a barrier: every thread has read its bins)
     const uint32_t d0 = h0_bin(tp, prefix);
     for (uint32_t b = threadIdx.x; b < d0; b += TRIM_THREADS) tp.hist[b] = 0;
@@ -352,13 +355,13 @@ __device__ __forceinline__ void trim_count_body(const CacheView &cv, const TrimP
     uint32_t key[COUNT_ITEMS];
     uint4 meta[COUNT_ITEMS];
     load_slots<COUNT_ITEMS>(cv, vblock * COUNT_SLOTS + threadIdx.x * COUNT_ITEMS, key, meta);      // loads first: they overlap the replay
-    uint64_t tau; uint32_t take_eq;
+    uint32_t tau, take_eq;
     sel_replay(tp, tp.passes, (uint32_t)over, tau, take_eq, l.pick, l.scan);
     uint32_t lt = 0, eq = 0, dlt = 0, deq = 0;
 #pragma unroll
     for (int i = 0; i < COUNT_ITEMS; ++i) {
-        const bool cached = key[i] != KEY_NONE;
-        const uint64_t pk = policy_key(tp, meta[i]);
+        const bool cached = key[i] != KEY_NONE && evictable(tp, meta[i]);
+        const uint32_t pk = policy_key(meta[i]);
         const bool dirty = meta[i].y > meta[i].x || (tp.dirty_stamp && meta[i].z == tp.dirty_stamp);
         if (cached && pk < tau) { lt += 1; dlt += dirty; }
         else if (cached && pk == tau) { eq += 1; deq += dirty; }
@@ -512,9 +515,10 @@ __global__ __launch_bounds__(PT_THREADS) void probe_kernel(CacheView cv, Workspa
                             hit = valid; stale = !valid;
                             const bool upkeep = !(cv.freq_cap && m.w >= cv.freq_cap);        // (light-weight LFU: frequent enough, left alone)
                             if (upkeep) store_meta(cv.meta, (uint32_t)slot, m.x, m.y, t_now, m.w + 1);   // one use per key per Read
-                            if (keep_h0 && upkeep) {
-                                const uint32_t b_old = h0_bin(tp, policy_key(tp, m)), b_new = h0_bin(tp, policy_key(tp, make_uint4(0, 0, t_now, m.w + 1)));
-                                if (b_old != b_new) { atomicSub(&h0_delta[b_old], 1u); atomicAdd(&h0_delta[b_new], 1u); }
+                            if (keep_h0 && upkeep && evictable(tp, m)) {
+                                const uint32_t b_old = h0_bin(tp, policy_key(m)), b_new = h0_bin(tp, t_now);
+                                if (tp.lfu) atomicSub(&h0_delta[b_old], 1u);                  // used twice now: out of reach
+                                else if (b_old != b_new) { atomicSub(&h0_delta[b_old], 1u); atomicAdd(&h0_delta[b_new], 1u); }
                             }
                         }
                         ws.cls[j] = (uint8_t)(miss ? CLS_MISS : (stale ? CLS_STALE : CLS_HIT));
@@ -551,7 +555,7 @@ __global__ __launch_bounds__(PT_THREADS) void probe_kernel(CacheView cv, Workspa
             count2(&cv.last->miss, &ds->total.miss, tot_miss);
             count2(&cv.last->unique, &ds->total.unique, tot_heads);
             if (tot_miss) atomicAdd(&ds->size, (int32_t)tot_miss);
-            if (keep_h0 && tot_miss) atomicAdd(&h0_delta[h0_bin(tp, policy_key(tp, make_uint4(0, 0, t_now, 1)))], tot_miss);   // the rows being fetched
+            if (keep_h0 && tot_miss) atomicAdd(&h0_delta[h0_bin(tp, t_now)], tot_miss);   // the rows being fetched
         }
         if (keep_h0) {
             __syncthreads();
@@ -1707,7 +1711,7 @@ __global__ __launch_bounds__(TRIM_THREADS) void trim_evict_kernel(CacheView cv, 
     const uint32_t slot0 = blk * EV_SLOTS + threadIdx.x * EV_ITEMS;
     // everything this thread may need, requested at once
     const int32_t over = ds->over;                     // snapshot taken by the select
-    const uint64_t tau = ds->sel_tau;
+    const uint32_t tau = ds->sel_tau;
     const uint32_t take_eq = ds->sel_take;
     uint32_t key[EV_ITEMS];
     uint4 meta[EV_ITEMS];
@@ -1737,8 +1741,8 @@ __global__ __launch_bounds__(TRIM_THREADS) void trim_evict_kernel(CacheView cv, 
     uint32_t n_lt = 0, n_eq = 0, n_free = 0;
 #pragma unroll
     for (int i = 0; i < EV_ITEMS; ++i) {
-        const bool cached = key[i] != KEY_NONE && over > 0;
-        const uint64_t pk = policy_key(tp, meta[i]);
+        const bool cached = key[i] != KEY_NONE && over > 0 && evictable(tp, meta[i]);
+        const uint32_t pk = policy_key(meta[i]);
         lt[i] = cached && pk < tau; eq[i] = cached && pk == tau;
         n_lt += lt[i]; n_eq += eq[i];
         n_free += (slot0 + i < cv.n_slots && key[i] == KEY_NONE) ? 1u : 0u;

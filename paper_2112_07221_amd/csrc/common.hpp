@@ -30,9 +30,8 @@ struct DState {
     uint32_t err;        // sticky ERRBIT_*
     uint32_t ev_n[2];    // ids recorded by a trim; trims alternate, the lookup in between clears the idle count
     uint32_t sel_take;   // trim: how many of the rows whose policy key equals sel_tau are evicted (in slot order)
-    unsigned long long sel_tau;   // trim: policy key of the last row to evict
+    uint32_t sel_tau;    // trim: policy key of the last row to evict
     int32_t over;        // trim: rows above capacity when the select ran (what the eviction removes)
-    int32_t pad1;
     uint32_t push_n[2];  // host-backed table: rows a trim staged for write-back; trims alternate like ev_n
     uint32_t pf_n[2];    // host-backed table: keys of a coming batch listed for fetching ahead; the lists alternate
     Counters call[2];    // per-call counters: calls alternate between the two, the idle one is cleared meanwhile

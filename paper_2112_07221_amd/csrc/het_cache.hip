@@ -70,7 +70,7 @@ struct het_cache {
     int n_ann = 0;
     TrimPlan sel_tp{};               // the select plan of the rows now cached (fixed at the lookup)
     int sel_next = 1;                // first stage of that select which the lookup's kernels did not carry
-    int h0_bits = 0;                 // iteration-count width the kept first-pass histogram was counted for (0: not counted yet)
+    int h0_shift = -1;               // place of the digit the kept first-pass histogram was counted for (-1: not counted yet)
     bool last_trim_skipped = false;  // the last update had nothing to trim: its evicted-id list is empty
     int cslot = 0;                   // which of the two per-call counter blocks the current call uses
     uint32_t *inv = nullptr;
@@ -351,8 +351,7 @@ TrimPlan make_trim_plan(const het_cache *c)
 {
     TrimPlan tp = c->tp;
     tp.lfu = c->policy == HET_POLICY_LFU || c->policy == HET_POLICY_LFU_LIGHT;
-    tp.bits = std::max(1, bit_width(c->t_host));
-    tp.key_bits = tp.lfu ? 2 * tp.bits : tp.bits;
+    tp.key_bits = std::max(1, bit_width(c->t_host));
     tp.passes = (tp.key_bits + SEL_BITS - 1) / SEL_BITS;
     tp.sup_cnt = reinterpret_cast<uint4 *>(tp.hist + SEL_MAX_PASSES * SEL_BINS);
     return tp;
@@ -495,11 +494,12 @@ int run_lookup(het_cache *c, const int64_t *ids, uint32_t n, const int64_t *offs
     }
     const uint32_t ptiles = cdiv(n, PT_TILE), stiles = cdiv(c->cv.n_slots, PT_TILE);
     // The select plan of the trim that follows this lookup.  Its first pass's histogram is kept
-    // between trims as long as the digit layout (the width of the iteration count) stays the same;
-    // otherwise this lookup counts it afresh, beside its fetches.
+    // between trims as long as its digit's place in the key stays the same (it moves when the
+    // iteration count reaches 2048, 4096, ...); otherwise this lookup counts it afresh, beside its fetches.
     c->sel_tp = make_trim_plan(c);
-    c->sel_tp.h0_kept = c->h0_bits == c->sel_tp.bits;
-    c->h0_bits = c->sel_tp.bits;
+    const int h0_shift = std::max(0, c->sel_tp.key_bits - SEL_BITS);
+    c->sel_tp.h0_kept = c->h0_shift == h0_shift;
+    c->h0_shift = h0_shift;
     const TrimPlan &tp = c->sel_tp;
     const uint32_t kept_words = tp.h0_kept ? (uint32_t)SEL_BINS : 0u;
     LAUNCH(c, K_PROBE, probe_kernel<true><<<ptiles + (match >= 0 ? ptiles : 0u) + stiles, PT_THREADS, 0, c->stream>>>(
@@ -635,7 +635,7 @@ int launch_apply_tile2(het_cache *c, bool verify, const int64_t *ids, uint32_t n
     int next = c->sel_next;
     int stage = -1;
     if (trim && next < tp.passes) stage = next++;
-    else if (trim && next == tp.passes && verify && !c->cv.freq_cap) { stage = next++; tp.dirty_stamp = (uint32_t)c->t_host; }    // (light-weight LFU leaves some rows of the batch unstamped)
+    else if (trim && next == tp.passes && verify && c->cv.freq_cap != 1) { stage = next++; tp.dirty_stamp = (uint32_t)c->t_host; }    // (light-weight LFU with a cap of 1 leaves rows of the batch unstamped that can be evicted; with a larger cap those it leaves unstamped cannot)
     const uint32_t extra = stage >= 0 ? stage_blocks(c, tp, stage) : 0u;
     const Rides ride = next_rides(c);
     const int fresh = verify && c->fetch_owed ? 1 : 0;          // (verify: this update reuses the lookup's order)
