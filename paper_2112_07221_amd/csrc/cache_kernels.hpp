@@ -229,8 +229,8 @@ __device__ __forceinline__ bool run_carried(const SortStage &a, const SortStage 
         const bool first = bid < a.blocks;
         const SortStage &st = first ? a : b;
         const uint32_t tile = first ? bid : bid - a.blocks;
-        if (HIST_ONLY) { __builtin_amdgcn_s_setprio(3); sort_hist_body(st, tile, lds); }
-        else sort_stage_body(st, tile, lds);
+        if (HIST_ONLY) { __builtin_amdgcn_s_setprio(3); sort_hist_body<SORT_THREADS>(st, tile, lds); }
+        else sort_stage_body<SORT_THREADS>(st, tile, lds);
         return true;
     }
     bid -= a.blocks + b.blocks; nblk -= a.blocks + b.blocks;

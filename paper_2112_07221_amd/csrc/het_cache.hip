@@ -38,6 +38,7 @@ struct Announced {
     const int64_t *ids = nullptr;
     uint32_t n = 0;
     int set = 0;
+    int max_bits = 0;                // widest digit its sort may use (see sort_bits_ahead)
     int next_stage = 0;              // stages [0, next_stage) are enqueued; 2 * passes stages in all
 };
 
@@ -236,35 +237,61 @@ uint32_t row_grid(const RowGeom &g, uint64_t items)
     return std::max(1u, std::min(cdiv(items, per_block), 256u * 8u));      // at most 8 workgroups per CU
 }
 
-SortPlan make_sort_plan(const het_cache *c, uint32_t n, int set)
+// A sort that runs in kernels of its own: up to 256 tiles digits of up to 11 bits and 1024 threads to a
+// tile, because a stage costs a kernel boundary and a chain of barriers whatever its width; beyond that adding
+// up the wide histograms' rows is most of a stage, and narrow digits (256 threads to a tile) are faster.
+// All stages together, us, wide / narrow: 106496 ids of 20 bits 25 / 31, 114688 of 22 bits 32 / 34,
+// 200000 of 20 bits 31 / 34, 409600 of 20 bits 56 / 43, 1048576 of 20 bits 118 / 94.
+constexpr int SORT_NARROW_BITS = 8;
+constexpr uint32_t SORT_WIDE_TILES = 256;
+int sort_bits_alone(uint32_t n) { return cdiv(n, SORT_TILE) <= SORT_WIDE_TILES ? SORT_MAX_BITS : SORT_NARROW_BITS; }
+
+// Digits of a sort: as few passes as max_bits allows, of equal width.
+SortPlan make_sort_plan(const het_cache *c, uint32_t n, int set, int max_bits)
 {
     SortPlan sp{};
     sp.n = n;
     sp.vocab = c->cv.vocab;
     const int bits = bit_width(sp.vocab);               // the key `vocab` itself marks a bad id
-    sp.passes = std::max(1, (bits + SORT_MAX_BITS - 1) / SORT_MAX_BITS);
+    sp.passes = std::max(1, (bits + max_bits - 1) / max_bits);
     sp.width = std::max(SORT_MIN_BITS, (bits + sp.passes - 1) / sp.passes);
     sp.ntiles = cdiv(n, SORT_TILE);
+    // narrow digits: rows are short, and a histogram stage of one tile per workgroup is the quickest to carry (a
+    // step of 62393 ids without a cache 42 us, with 4 tiles 49 us) until there are hundreds of rows (a step of
+    // 409600 ids 327 us, with 4 tiles 314 us); wide ones: few rows to add up (106496 ids: 25.1 us with 4 tiles, 26.5 with 8)
+    sp.super = sp.width <= SORT_NARROW_BITS ? (sp.ntiles <= 128 ? 1u : 4u) : (sp.ntiles <= 128 ? 4u : 8u);
+    sp.nsupers = cdiv(sp.ntiles, sp.super);
     sp.hist = c->sort_hist[set];
     return sp;
 }
 
-int sort_stages(const het_cache *c) { return 2 * make_sort_plan(c, 1, 0).passes; }
-int sort_result_buffer(const het_cache *c) { return (make_sort_plan(c, 1, 0).passes - 1) & 1; }
+// Digits of an announced batch's sort.  A batch announced one ahead meets three kernels that carry a
+// stage before its lookup (two without a cache): two wide passes are nearly all carried.  Announced two ahead
+// it meets them twice: narrow digits are carried just as completely, and their stages are shorter and
+// need less LDS, so the carrying kernels keep their occupancy (114688 ids of 22 bits: the update 40 us with
+// stages of 8 bits, 48 us with stages of 11).
+int sort_bits_ahead(const het_cache *c, uint32_t n)
+{
+    const int carried = c->n_ann >= 2 ? (c->cv.direct ? 4 : 6) : 0;
+    return 2 * make_sort_plan(c, n, 0, SORT_NARROW_BITS).passes <= carried ? SORT_NARROW_BITS : sort_bits_alone(n);
+}
+
+int sort_stages(const het_cache *c, int max_bits) { return 2 * make_sort_plan(c, 1, 0, max_bits).passes; }
+int sort_result_buffer(const het_cache *c, int max_bits) { return (make_sort_plan(c, 1, 0, max_bits).passes - 1) & 1; }
 
 // Stage `stage` of the sort of ids[n] into buffer set `set`.  Pass p writes buffer p & 1 of the
 // set and reads the other one; stage 0 leaves the ids, converted to keys, where pass 0 reads.
-SortStage make_stage(const het_cache *c, const int64_t *ids, uint32_t n, int set, int stage)
+SortStage make_stage(const het_cache *c, const int64_t *ids, uint32_t n, int set, int max_bits, int stage)
 {
     SortStage s{};
-    s.sp = make_sort_plan(c, n, set);
+    s.sp = make_sort_plan(c, n, set, max_bits);
     const int pass = stage >> 1, out = pass & 1, in = 1 - out;
     s.ids = ids;
     s.keys_in = c->keys[set][in]; s.idx_in = c->idx[set][in];
     s.keys_out = stage == 0 ? c->keys[set][in] : c->keys[set][out];
     s.idx_out = c->idx[set][out];
     s.stage = stage;
-    s.blocks = s.sp.ntiles;
+    s.blocks = stage & 1 ? s.sp.ntiles : s.sp.nsupers;
     return s;
 }
 
@@ -283,12 +310,34 @@ void begin_call(het_cache *c)
     c->cv.next_call = &c->cv.ds->call[1 - c->cslot];
 }
 
-// Stages [first_stage, end) of a sort as kernels of their own.
-void sort_now(het_cache *c, const int64_t *ids, uint32_t n, int set, int first_stage)
+template <int ITEMS>
+void launch_solo(het_cache *c, const int64_t *ids, uint32_t n, uint32_t *keys_out, uint32_t *idx_out)
 {
-    for (int st = first_stage; st < sort_stages(c); ++st) {
-        const SortStage s = make_stage(c, ids, n, set, st);
-        LAUNCH(c, K_SORT_STAGE, sort_stage_kernel<<<s.blocks, SORT_THREADS, sort_stage_lds_bytes(s.sp.width, s.stage), c->stream>>>(s));
+    const int bits = std::max(SORT_MIN_BITS, bit_width(c->cv.vocab)), passes = solo_passes(bits), width = (bits + passes - 1) / passes;
+    LAUNCH(c, K_SORT_STAGE, sort_solo_kernel<ITEMS><<<1, SOLO_THREADS, solo_lds_bytes(ITEMS, width), c->stream>>>(ids, n, c->cv.vocab, passes, width, keys_out, idx_out));
+}
+
+// What is left of a sort (stages [first_stage, end)), in kernels of its own; or, for a small batch, all of
+// it by one workgroup in one launch, from the ids.  That one's time is the ballots' on one compute unit and
+// grows with the ids (20 bits: 4.9 us for 200, 7.7 for 2048, 11.9 for 4096, 19.9 for 8192), a stage's hardly does
+// (3.3 us histogram, 6.8 us scatter): SOLO_MAX ids against four stages, proportionally fewer against fewer.
+void sort_now(het_cache *c, const int64_t *ids, uint32_t n, int set, int max_bits, int first_stage)
+{
+    const int end = sort_stages(c, max_bits);
+    if (3ull * n <= (uint64_t)SOLO_MAX * (uint32_t)std::max(0, std::min(3, end - first_stage - 1))) {
+        uint32_t *k = c->keys[set][sort_result_buffer(c, max_bits)], *i = c->idx[set][sort_result_buffer(c, max_bits)];
+        if (n <= SOLO_THREADS) launch_solo<1>(c, ids, n, k, i);
+        else if (n <= 2 * SOLO_THREADS) launch_solo<2>(c, ids, n, k, i);
+        else if (n <= 4 * SOLO_THREADS) launch_solo<4>(c, ids, n, k, i);
+        else launch_solo<8>(c, ids, n, k, i);
+        return;
+    }
+    for (int st = first_stage; st < end; ++st) {
+        const SortStage s = make_stage(c, ids, n, set, max_bits, st);
+        if (s.sp.ntiles <= SORT_WIDE_TILES)
+            LAUNCH(c, K_SORT_STAGE, sort_stage_kernel<SORT_THREADS_ALONE><<<s.blocks, SORT_THREADS_ALONE, sort_stage_lds_bytes(s.sp.width, s.sp.super, s.stage, SORT_THREADS_ALONE), c->stream>>>(s));
+        else
+            LAUNCH(c, K_SORT_STAGE, sort_stage_kernel<SORT_THREADS><<<s.blocks, SORT_THREADS, sort_stage_lds_bytes(s.sp.width, s.sp.super, s.stage, SORT_THREADS), c->stream>>>(s));
     }
 }
 
@@ -297,7 +346,7 @@ void sort_now(het_cache *c, const int64_t *ids, uint32_t n, int set, int first_s
 SortStage next_ride_of(het_cache *c, int a)
 {
     Announced &an = c->ann[a];
-    return make_stage(c, an.ids, an.n, an.set, an.next_stage++);
+    return make_stage(c, an.ids, an.n, an.set, an.max_bits, an.next_stage++);
 }
 
 // What the kernel about to be launched carries: the next stage of the oldest announced batch whose
@@ -314,8 +363,8 @@ struct Rides {
 uint32_t lds_bytes(size_t own, const Rides &r)
 {
     uint32_t need = (uint32_t)own;
-    if (r.a.blocks) need = std::max(need, sort_stage_lds_bytes(r.a.sp.width, r.a.stage));
-    if (r.b.blocks) need = std::max(need, sort_stage_lds_bytes(r.b.sp.width, r.b.stage));
+    if (r.a.blocks) need = std::max(need, sort_stage_lds_bytes(r.a.sp.width, r.a.sp.super, r.a.stage, SORT_THREADS));
+    if (r.b.blocks) need = std::max(need, sort_stage_lds_bytes(r.b.sp.width, r.b.sp.super, r.b.stage, SORT_THREADS));
     return need;
 }
 
@@ -324,7 +373,7 @@ Rides next_rides(het_cache *c)
     Rides r{no_stage(), no_stage()};
     int got = 0;
     for (int a = 0; a < c->n_ann && got < 2; ++a) {
-        if (c->ann[a].next_stage >= sort_stages(c)) continue;
+        if (c->ann[a].next_stage >= sort_stages(c, c->ann[a].max_bits)) continue;
         (got == 0 ? r.a : r.b) = next_ride_of(c, a);
         ++got;
     }
@@ -337,9 +386,9 @@ void drop_oldest_announcement(het_cache *c)
     c->n_ann -= 1;
 }
 
-void use_order(het_cache *c, int set)
+void use_order(het_cache *c, int set, int max_bits)
 {
-    const int buf = sort_result_buffer(c);
+    const int buf = sort_result_buffer(c, max_bits);
     c->sort_set = set;
     c->ws.skey = c->keys[set][buf];
     c->ws.perm = c->idx[set][buf];
@@ -463,11 +512,11 @@ int run_lookup(het_cache *c, const int64_t *ids, uint32_t n, const int64_t *offs
         for (int a = 0; a < match; ++a) drop_oldest_announcement(c);
         const Announced an = c->ann[0];
         drop_oldest_announcement(c);
-        sort_now(c, ids, n, an.set, an.next_stage);
-        use_order(c, an.set);
+        sort_now(c, ids, n, an.set, an.max_bits, an.next_stage);
+        use_order(c, an.set, an.max_bits);
     } else {
-        sort_now(c, ids, n, c->sort_set, 0);             // over the previous batch's order: it is not needed any more
-        use_order(c, c->sort_set);
+        sort_now(c, ids, n, c->sort_set, sort_bits_alone(n), 0);             // over the previous batch's order: it is not needed any more
+        use_order(c, c->sort_set, sort_bits_alone(n));
     }
     const uint32_t t_now = (uint32_t)c->t_host;
     if (c->cv.direct) {
@@ -575,12 +624,12 @@ int run_lookup(het_cache *c, const int64_t *ids, uint32_t n, const int64_t *offs
         if (push_blocks) c->push_pending = false;
         ah = Ahead{};
         if (next) {
-            if (next->next_stage < sort_stages(c)) {         // what is left of its sort runs now
-                sort_now(c, next->ids, next->n, next->set, next->next_stage);
-                next->next_stage = sort_stages(c);
+            if (next->next_stage < sort_stages(c, next->max_bits)) {         // what is left of its sort runs now
+                sort_now(c, next->ids, next->n, next->set, next->max_bits, next->next_stage);
+                next->next_stage = sort_stages(c, next->max_bits);
             }
             c->pf_serial = (c->pf_serial % 0x7FFFFFFFu) + 1;
-            ah.skey = c->keys[next->set][sort_result_buffer(c)];
+            ah.skey = c->keys[next->set][sort_result_buffer(c, next->max_bits)];
             ah.n = next->n;
             ah.blocks = cdiv(next->n, 256);
             ah.list_tag = 0x80000000u | c->pf_serial;
@@ -680,8 +729,8 @@ int run_update(het_cache *c, const int64_t *ids, uint32_t n, const int64_t *offs
     const bool reuse = c->order_valid && ids == c->order_ids && n == c->order_n;
     if (!reuse) {
         if ((rc = settle_fetch(c)) != HET_OK) return rc;
-        sort_now(c, ids, n, c->sort_set, 0);
-        use_order(c, c->sort_set);
+        sort_now(c, ids, n, c->sort_set, sort_bits_alone(n), 0);
+        use_order(c, c->sort_set, sort_bits_alone(n));
         if (c->cv.direct)
             LAUNCH(c, K_PROBE, direct_probe_kernel<false><<<cdiv(n, PT_TILE), PT_THREADS, 0, c->stream>>>(c->cv, c->ws, n, (uint32_t)c->t_host, cdiv(n, PT_TILE), nullptr));
         else
@@ -828,7 +877,7 @@ static int configure_impl(het_cache *c, int64_t max_batch_ids, int32_t optimizer
     for (int set = 0; set < SORT_SETS; ++set) {
         for (int i = 0; i < 2; ++i)
             if ((rc = dev_alloc(c, &c->keys[set][i], N)) || (rc = dev_alloc(c, &c->idx[set][i], N))) return rc;
-        if ((rc = dev_alloc(c, &c->sort_hist[set], sort_tiles * (SORT_MAX_BINS / 2)))) return rc;
+        if ((rc = dev_alloc(c, &c->sort_hist[set], std::max(2 * sort_tiles * ((size_t)1 << (SORT_NARROW_BITS - 1)), (sort_tiles + cdiv(sort_tiles, 4)) * (SORT_MAX_BINS / 2))))) return rc;
     }
     c->cv.last = &cv.ds->call[0];
     c->cv.next_call = &cv.ds->call[1];
@@ -852,6 +901,10 @@ static int configure_impl(het_cache *c, int64_t max_batch_ids, int32_t optimizer
     }
     HIP_TRY(hipMemsetAsync(c->tile_free[1], 0, slot_tiles * sizeof(uint32_t), c->stream));
 
+    // the sort's own kernels ask for more LDS than a launch gets unasked
+    const int max_lds = 160 * 1024;
+    HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(&sort_stage_kernel<SORT_THREADS_ALONE>), hipFuncAttributeMaxDynamicSharedMemorySize, max_lds));
+    HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(&sort_solo_kernel<8>), hipFuncAttributeMaxDynamicSharedMemorySize, max_lds));
     HIP_TRY(hipMemsetAsync(c->bd.arrived, 0, ap_tiles * 3 * sizeof(uint32_t), c->stream));
     HIP_TRY(hipMemsetAsync(cv.ds, 0, sizeof(DState), c->stream));
     init_cache_kernel<<<1024, 256, 0, c->stream>>>(cv, c->n_buckets * BUCKET_ENTRIES, c->n_buckets);
@@ -984,7 +1037,7 @@ int het_prefetch(het_cache *c, const int64_t *ids, int64_t n)
         for (int a = 0; a < c->n_ann; ++a) taken = taken || c->ann[a].set == set;
         if (taken) continue;
         Announced an;
-        an.ids = ids; an.n = (uint32_t)n; an.set = set; an.next_stage = 0;
+        an.ids = ids; an.n = (uint32_t)n; an.set = set; an.max_bits = sort_bits_ahead(c, an.n); an.next_stage = 0;
         c->ann[c->n_ann++] = an;
         break;
     }

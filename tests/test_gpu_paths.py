@@ -29,3 +29,42 @@ def test_light_weight_lfu_where_the_select_gains_a_pass(cap):
         p.flush_and_compare()
     finally:
         p.close()
+
+
+@pytest.mark.parametrize("ahead", [0, 1, 2])
+@pytest.mark.parametrize("n,vocab", [(1, 5), (1_024, 2_047), (1_025, 2_048), (2_730, 300), (2_731, 300), (5_461, 70_000), (5_462, 70_000),
+                                     (8_192, 1_000_000), (8_193, 1_000_000), (131_072, 4_000_000), (131_073, 4_194_304),
+                                     (262_144, 100_000), (262_145, 100_000), (20_000, 8_400_000)])
+def test_every_way_a_batch_is_sorted(n, vocab, ahead):
+    """One workgroup or stages, one to three passes, wide and narrow digits, super-tiles of 1, 4 and 8 tiles,
+    stages carried or alone: the distinct keys and the gradient sums of a no-cache step.  Gradients are
+    small integers and lr is 1, so every sum is exact."""
+    from paper_2112_07221_amd import hetcache as hc
+    dev = torch.device("cuda:0")
+    rng = np.random.default_rng(n + ahead)
+    steps = 4
+    ids = [rng.integers(0, vocab, n) if t % 2 else np.minimum((rng.random(n) ** 6 * vocab).astype(np.int64), vocab - 1) for t in range(steps)]
+    ids[1][n // 2] = -1 if n > 1 else ids[1][0]                       # (an id outside the vocabulary sorts behind every key)
+    g = [torch.from_numpy(rng.integers(-8, 9, (n, 4)).astype(np.float32)).to(dev) for _ in range(steps)]
+    table = torch.zeros(vocab, 4, device=dev)
+    want = np.zeros((vocab, 4))
+    cache = hc.HetCache(1, 4, 0, hc.POLICY_NONE, n, hc.OPT_SGD)
+    try:
+        cache.attach_backing(table, None, torch.zeros(vocab, dtype=torch.int32, device=dev))
+        d_ids = [torch.from_numpy(x).to(dev) for x in ids]
+        out = torch.empty(n, 4, device=dev)
+        for t in range(1, ahead):
+            cache.prefetch(d_ids[t])
+        for t in range(steps):
+            if ahead and t + ahead < steps:
+                cache.prefetch(d_ids[t + ahead])
+            cache.lookup(d_ids[t], out)
+            cache.update(d_ids[t], g[t], 1.0)
+            ok = ids[t] >= 0
+            got = out.cpu().numpy()
+            assert np.array_equal(got[ok], want[ids[t][ok]]) and not got[~ok].any()
+            assert np.array_equal(cache.last_lookup()[0], np.unique(ids[t][ok]))
+            np.add.at(want, ids[t][ok], -g[t].cpu().numpy()[ok].astype(np.float64))
+        assert np.array_equal(table.cpu().numpy(), want.astype(np.float32))
+    finally:
+        cache.close()
