@@ -10,7 +10,6 @@
 // order of atomics, and no workgroup ever waits for another.
 #pragma once
 #include "common.hpp"
-#include "hash_table.hpp"
 #include "sort_unique.hpp"
 
 namespace het {
@@ -74,7 +73,13 @@ struct CacheView {
     uint32_t capacity;
     uint32_t max_ids;
     int64_t s;            // staleness bound
-    HashTable ht;
+    // Find (Algorithm 2): the slot of every key of the table, SLOT_NONE where it is not cached.  One 4-byte load, which
+    // a wave's sorted keys share lines of, in flight beside the key's global clock; one store to insert or erase.
+    // With a hash table of the cached keys (buckets of 16 entries in 128 bytes) every Find was eight 16-byte loads
+    // of a line no other lane wanted, every insert and erase a search: probe 13 -> 10.4 us and eviction 13 -> 10.2 us
+    // at 106496 ids; a step of 3328 ids 42.9 -> 38.1 us, of 106496 ids 74.7 -> 71.3 us, of 409600 ids in bags
+    // 316 -> 302 us.  4 bytes per row of the table, in HBM mostly a fraction of its clocks' and rows' own.
+    int32_t *slot_of;
     uint32_t *free_list;  // free slots in ascending order (first max_ids of them)
     uint8_t *was_free;    // per slot: free when the current lookup began (its fetches may be filling it now)
     DState *ds;
@@ -494,7 +499,7 @@ __global__ __launch_bounds__(PT_THREADS) void probe_kernel(CacheView cv, Workspa
             finder = head || (LOOKUP && lane_id() == 0);
             if (finder) {
                 const uint32_t cg = LOOKUP ? cv.Cg[key] : 0u;        // in flight together with the probe's loads
-                const int32_t slot = ht_find(cv.ht, key);
+                const int32_t slot = cv.slot_of[key];
                 int32_t src = slot == SLOT_NONE ? SRC_BACKING : slot;
                 bool valid = true;
                 uint4 m = make_uint4(0, 0, 0, 0);
@@ -847,7 +852,7 @@ __device__ __forceinline__ void ahead_list_body(const CacheView &cv, const Ahead
     if (j < ah.n) {
         key = ah.skey[j];
         const bool head = key != cv.vocab && (j == 0 || ah.skey[j - 1] != key);
-        if (head && ht_find(cv.ht, key) == SLOT_NONE) {
+        if (head && cv.slot_of[key] == SLOT_NONE) {
             want = true;
             // a row the last trim evicted, whose write-back is still to come: the staged copy is the row
             const uint64_t pe = cv.hl.pend[key];
@@ -1092,18 +1097,29 @@ __global__ __launch_bounds__(256) void fill_gather_kernel(CacheView cv, Workspac
     // copies above (done by the same lanes it would stand behind them: two more dependent steps)
     if (bid < fill_blocks + ins_blocks) {
         const uint32_t tl = bid - fill_blocks;
+        constexpr int KEYS = PT_TILE / 256;
         const uint32_t here = ws.tile_miss[tl];
+        uint2 jks[KEYS];                         // (they and the clocks are on their way while the tiles before are added up)
+        uint32_t cgs[KEYS];
+#pragma unroll
+        for (int i = 0; i < KEYS; ++i) {
+            const uint32_t ml = threadIdx.x + 256u * i;
+            jks[i] = ml < here ? ws.miss_stage[tl * PT_TILE + ml] : make_uint2(0, 0);
+        }
+#pragma unroll
+        for (int i = 0; i < KEYS; ++i) cgs[i] = threadIdx.x + 256u * i < here ? cv.Cg[jks[i].y] : 0u;
         const uint32_t before = block_sum_array<4>(ws.tile_miss, tl, lds_as<FillLds>().scan);
-        for (uint32_t ml = threadIdx.x; ml < here; ml += 256u) {
-            const uint2 jk = ws.miss_stage[tl * PT_TILE + ml];
+#pragma unroll
+        for (int i = 0; i < KEYS; ++i) {
+            const uint32_t ml = threadIdx.x + 256u * i;
+            if (ml >= here) continue;
             const uint32_t slot = cv.free_list[before + ml];
-            const uint32_t j = jk.x, key = jk.y;
-            const uint32_t cg = cv.Cg[key];
+            const uint32_t j = jks[i].x, key = jks[i].y, cg = cgs[i];
             store_meta(cv.meta, slot, cg, cg, t_now, 1u);                    // c_s = c_c = c_g; first use
             if (cv.early_cc) cv.early_cc[slot] = fetch_mode == 1 ? cg + 1u : 0u;    // (the update that fetches the row will make it c_g + 1)
             cv.slot_key[slot] = key;
             ws.head_slot[j] = (int32_t)slot;
-            if (!ht_insert(cv.ht, key, slot)) atomicOr(&cv.ds->err, ERRBIT_INTERNAL);
+            cv.slot_of[key] = (int32_t)slot;
             // host-backed table: the gather runs after this kernel and reads the cached copy
             if (cv.Cg_host) for (uint32_t jj = j; jj < n && ws.skey[jj] == key; ++jj) ws.src[jj] = (int32_t)slot;
         }
@@ -1774,9 +1790,9 @@ __global__ __launch_bounds__(TRIM_THREADS) void trim_evict_kernel(CacheView cv, 
         if (victim[i]) {
         const uint32_t slot = slot0 + i, k = key[i], my_cc = meta[i].y;
         tp.ev_ids[ev_at++] = k;
-        const uint32_t cg = dirty[i] ? cv.Cg[k] : 0u;                         // in flight together with the erase's loads
+        const uint32_t cg = dirty[i] ? cv.Cg[k] : 0u;
         const uint32_t early = dirty[i] && cv.early_cc ? cv.early_cc[slot] : 0u;
-        ht_erase(cv.ht, k);
+        cv.slot_of[k] = SLOT_NONE;
         cv.slot_key[slot] = KEY_NONE;
         // host-backed table: rows below tau that hold updates are staged in slot order, then one
         // place per tied victim (left empty by those without updates)
@@ -1934,16 +1950,14 @@ __global__ __launch_bounds__(256) void foreign_update_kernel(CacheView cv, const
     }
 }
 
-// Initial free list (every slot free) and empty slots / hash table.
-__global__ __launch_bounds__(256) void init_cache_kernel(CacheView cv, uint32_t n_entries, uint32_t n_buckets)
+// Initial free list (every slot free) and empty slots.
+__global__ __launch_bounds__(256) void init_cache_kernel(CacheView cv)
 {
     const uint32_t i0 = blockIdx.x * 256u + threadIdx.x, stride = gridDim.x * 256u;
     for (uint32_t i = i0; i < cv.n_slots; i += stride) {
         cv.slot_key[i] = KEY_NONE; store_meta(cv.meta, i, 0, 0, 0, 0);
     }
     for (uint32_t i = i0; i < cv.max_ids; i += stride) cv.free_list[i] = i;
-    for (uint32_t i = i0; i < n_entries; i += stride) cv.ht.entries[i] = ENTRY_EMPTY;
-    for (uint32_t i = i0; i < n_buckets; i += stride) cv.ht.reach[i] = 0;
 }
 
 } // namespace het

@@ -11,7 +11,6 @@ constexpr int32_t SLOT_NONE = -1;
 
 constexpr uint32_t ERRBIT_RANGE = 1u;        // an id outside [0, vocab)
 constexpr uint32_t ERRBIT_STATE = 2u;        // update of a key that is not cached
-constexpr uint32_t ERRBIT_INTERNAL = 4u;     // hash table could not place a key (never expected)
 
 constexpr int CLS_HIT = 0, CLS_STALE = 1, CLS_MISS = 2;
 

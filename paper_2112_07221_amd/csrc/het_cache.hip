@@ -78,7 +78,7 @@ struct het_cache {
     uint32_t *tile_free[2] = {nullptr, nullptr};   // free slots per tile, left by a trim; trims alternate between the two
     int tf_last = 0;                 // the one the last trim filled (initially: every slot free)
     uint32_t *ev_ids[2] = {nullptr, nullptr};      // evicted ids of the last two trims, alternating like tile_free
-    uint32_t n_buckets = 0;
+    void *index_host = nullptr;      // the key index, if it found no room in HBM
     int max_chunks_per_lane = 1;     // row chunks one lane handles in the apply kernel
     std::vector<void *> owned;       // every device allocation, for destroy
     char *arena = nullptr;           // one allocation that holds all the small arrays side by side (see dev_alloc)
@@ -139,6 +139,12 @@ void free_owned_from(het_cache *c, size_t keep, size_t arena_mark)
     if (c->arena) c->arena_used = arena_mark;
 }
 
+void free_index_host(het_cache *c)
+{
+    if (c->index_host) (void)hipHostFree(c->index_host);
+    c->index_host = nullptr;
+}
+
 constexpr size_t ARENA_BYTES = (size_t)128 << 20, ARENA_ITEM_MAX = 8u << 20;
 
 // Arrays of up to 8 MB lie side by side in one allocation of 128 MB; larger ones, and whatever does
@@ -188,7 +194,6 @@ inline uint32_t pow2_at_least(uint64_t v)
 
 int status_from_bits(uint32_t bits)
 {
-    if (bits & ERRBIT_INTERNAL) return HET_EHIP;
     if (bits & ERRBIT_RANGE) return HET_ERANGE;
     if (bits & ERRBIT_STATE) return HET_ESTATE;
     return HET_OK;
@@ -860,14 +865,6 @@ static int configure_impl(het_cache *c, int64_t max_batch_ids, int32_t optimizer
     if ((rc = dev_alloc(c, &cv.slot_key, P)) || (rc = dev_alloc(c, &cv.meta, P))) return rc;
     if ((rc = dev_alloc(c, &cv.free_list, (size_t)max_batch_ids)) || (rc = dev_alloc(c, &cv.was_free, P))) return rc;
     if ((rc = dev_alloc(c, &cv.ds, 1))) return rc;
-    // hash table: at most a quarter of the entries are ever used
-    c->n_buckets = pow2_at_least(std::max<uint64_t>(1, cdiv(P * 4, BUCKET_ENTRIES)));
-    cv.ht.bucket_mask = c->n_buckets - 1;
-    cv.ht.shift = 32u - (uint32_t)(bit_width(c->n_buckets) - 1);
-    if ((rc = dev_alloc(c, &cv.ht.entries, (size_t)c->n_buckets * BUCKET_ENTRIES)) ||
-        (rc = dev_alloc(c, &cv.ht.reach, c->n_buckets)))
-        return rc;
-
     // workspaces
     Workspace &ws = c->ws;
     const size_t N = (size_t)max_batch_ids;
@@ -907,7 +904,7 @@ static int configure_impl(het_cache *c, int64_t max_batch_ids, int32_t optimizer
     HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(&sort_solo_kernel<8>), hipFuncAttributeMaxDynamicSharedMemorySize, max_lds));
     HIP_TRY(hipMemsetAsync(c->bd.arrived, 0, ap_tiles * 3 * sizeof(uint32_t), c->stream));
     HIP_TRY(hipMemsetAsync(cv.ds, 0, sizeof(DState), c->stream));
-    init_cache_kernel<<<1024, 256, 0, c->stream>>>(cv, c->n_buckets * BUCKET_ENTRIES, c->n_buckets);
+    init_cache_kernel<<<1024, 256, 0, c->stream>>>(cv);
     if ((rc = launch_ok())) return rc;
     HIP_TRY(hipStreamSynchronize(c->stream));
     c->configured = true;
@@ -920,6 +917,21 @@ int het_cache_configure(het_cache *c, int64_t max_batch_ids, int32_t optimizer, 
     const int rc = configure_impl(c, max_batch_ids, optimizer, eps, hip_stream);
     if (rc != HET_OK && c && !c->configured) free_owned_from(c, keep, mark);     // a retry starts from nothing
     return rc;
+}
+
+// The key index: 4 bytes per row of the table, nothing cached yet.  In pinned host memory if HBM has no room for
+// it (a table that fills HBM to the last): Find then crosses the host link.
+static int alloc_index(het_cache *c, int64_t vocab)
+{
+    const size_t bytes = (size_t)vocab * sizeof(int32_t);
+    if (dev_alloc(c, &c->cv.slot_of, (size_t)vocab) != HET_OK) {
+        (void)hipGetLastError();
+        if (hipHostMalloc(&c->index_host, bytes, hipHostMallocDefault) != hipSuccess) { (void)hipGetLastError(); c->index_host = nullptr; return HET_ENOMEM; }
+        c->cv.slot_of = static_cast<int32_t *>(c->index_host);
+    }
+    static_assert(SLOT_NONE == -1, "filled byte by byte");
+    HIP_TRY(hipMemsetAsync(c->cv.slot_of, 0xFF, bytes, c->stream));
+    return HET_OK;
 }
 
 static int attach_impl(het_cache *c, float *table, float *state, uint32_t *cg, int64_t vocab, int32_t location)
@@ -939,6 +951,10 @@ static int attach_impl(het_cache *c, float *table, float *state, uint32_t *cg, i
         table = static_cast<float *>(dt); cg = static_cast<uint32_t *>(dcg); state = static_cast<float *>(dst);
     }
     c->cv.W = table; c->cv.A = state; c->cv.Cg = cg; c->cv.Cg_host = nullptr; c->cv.vocab = (uint32_t)vocab;
+    if (!c->cv.direct) {
+        const int rc = alloc_index(c, vocab);
+        if (rc) return rc;
+    }
     if (c->cv.direct) {
         if (vocab >= (1ll << 31)) return HET_EINVAL;        // a key stands for its own slot
         c->cv.rows = table; c->cv.acc = state;
@@ -980,6 +996,7 @@ int het_attach_backing(het_cache *c, float *table, float *state, uint32_t *cg, i
     const int rc = attach_impl(c, table, state, cg, vocab, location);
     if (rc != HET_OK && c && !was) {
         free_owned_from(c, keep, mark);
+        free_index_host(c);
         if (c->ev_main) { (void)hipEventDestroy(c->ev_main); c->ev_main = nullptr; }
         if (c->ev_link) { (void)hipEventDestroy(c->ev_link); c->ev_link = nullptr; }
         if (c->side) { (void)hipStreamDestroy(c->side); c->side = nullptr; }
@@ -1323,6 +1340,7 @@ int het_cache_destroy(het_cache *c)
     if (c->side) (void)hipStreamDestroy(c->side);
     for (void *p : c->owned)
         if (hipFree(p) != hipSuccess) rc = HET_EHIP;
+    free_index_host(c);
     delete c;
     return rc;
 }

@@ -68,3 +68,41 @@ def test_every_way_a_batch_is_sorted(n, vocab, ahead):
         assert np.array_equal(table.cpu().numpy(), want.astype(np.float32))
     finally:
         cache.close()
+
+
+@pytest.mark.parametrize("full", [False, True])
+def test_key_index_in_hbm_and_where_hbm_has_no_room(full):
+    """The index of a table's keys goes to pinned host memory if HBM has no room for it when the table is
+    attached; lookups and updates that fetch, hit and evict read the same either way (whole numbers, so sums are
+    exact)."""
+    from paper_2112_07221_amd import hetcache as hc
+    dev = torch.device("cuda:0")
+    vocab, n, cap = 64_000_000, 3_000, 2_000                          # (an index of 256 MB)
+    rng = np.random.default_rng(3)
+    table, clock = torch.zeros(vocab, 4, device=dev), torch.zeros(vocab, dtype=torch.int32, device=dev)
+    out = torch.empty(n, 4, device=dev)
+    cache = hc.HetCache(cap, 4, 100, hc.POLICY_LRU, n, hc.OPT_SGD)
+    try:
+        torch.cuda.synchronize()
+        torch.cuda.empty_cache()
+        filler = torch.empty(torch.cuda.mem_get_info()[0] - (200 << 20), dtype=torch.uint8, device=dev) if full else None
+        cache.attach_backing(table, None, clock)
+        del filler
+        torch.cuda.empty_cache()
+        want = {}
+        for t in range(6):
+            ids = np.concatenate([rng.integers(0, vocab, n - 1_000), rng.integers(0, 600, 999), [vocab - 1]])
+            g = rng.integers(-8, 9, (n, 4)).astype(np.float32)
+            d = torch.from_numpy(ids).to(dev)
+            cache.lookup(d, out)
+            assert np.array_equal(out.cpu().numpy(), np.array([want.get(i, np.zeros(4)) for i in ids.tolist()]))
+            cache.update(d, torch.from_numpy(g).to(dev), 1.0)
+            for i, row in zip(ids.tolist(), g):
+                want[i] = want.get(i, np.zeros(4)) - row
+        assert cache.stats()["resident"] == cap
+        assert cache.flush() == hc.HET_OK
+        keys = np.array(sorted(want))
+        assert np.array_equal(table[torch.from_numpy(keys).to(dev)].cpu().numpy(), np.array([want[k] for k in keys.tolist()]))
+        assert float(table.abs().sum(dtype=torch.float64)) == float(np.abs(np.array(list(want.values()))).sum())
+    finally:
+        cache.close()
