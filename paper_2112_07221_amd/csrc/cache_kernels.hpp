@@ -1248,13 +1248,18 @@ __device__ __forceinline__ void apply_step(const CacheView &cv, uint32_t slot, i
 // sorted positions, brings their keys, gradient rows' numbers and slots into LDS and lists the
 // tile's segments (stretches of equal keys; a run of equal keys is one segment unless it crosses a
 // tile border).  Work then goes by segment, not by position:
-//   - a segment of up to AP_SOLO positions is summed by one row group, a few gradient rows (ap_batch) in
+//   - a segment of up to AP_ROWS positions is summed by one row group, a few gradient rows (ap_batch) in
 //     flight at a time, in order of position, in fp64 (the kernel is bound by reading the
 //     gradients; summing wide makes a long run of a popular key lose no digits), rounded once;
+//   - one of up to AP_SOLO by the row groups of one wave: contiguous shares, added through shuffles (by one row group
+//     it was up to eleven rounds of loads in a row, and the kernel waits for its slowest tiles: with the run beyond the border, 106496 ids 71.3 -> 69.2 us a step,
+//     60.7 -> 59.1 without a cache, 8658 ids 40.2 -> 39.0);
 //   - a longer one by all row groups of the workgroup together: contiguous shares, added in group
 //     order through LDS.
 // A segment that is a whole run gets the optimizer step and its clock at once: no partial sum ever
-// leaves the workgroup.  Only a run that crosses a tile border (at most two per tile) leaves one
+// leaves the workgroup.  A run of up to AP_SOLO positions that crosses a tile border belongs to the tile it begins
+// in, which sums it beyond the border; the tile it ends in passes over it (both see AP_SOLO positions on either side
+// of their own and so agree on its length).  Only a longer run that crosses a border (at most two per tile) leaves one
 // fp64 partial sum per tile it touches in `ApplyBorders::part`, and the tile that arrives last at
 // the run's counter adds them up in tile order and applies the step: which tile is last varies,
 // the order of the additions does not.  Nobody waits for anybody.
@@ -1274,20 +1279,24 @@ constexpr int AP_THREADS = 256;
 __host__ __device__ constexpr int ap_batch(int ap_tile, bool early) { return ap_tile == 64 ? (early ? 3 : 4) : (early ? 4 : 6); }
 __host__ __device__ constexpr int ap_waves(int ap_tile) { return ap_tile == 64 ? 7 : 6; }
 constexpr int AP_SOLO = 32;
+constexpr int AP_ROWS = 8;
 // Positions per tile (template parameter AP_TILE): 64 where a workgroup has eight row groups or
 // more (rows up to 128 floats), 128 for wider rows, whose fewer row groups would otherwise stand
 // idle beside the popular keys' long segments and pay for twice as many border crossings.
 __host__ __device__ constexpr int ap_tile_for(int lanes) { return lanes <= 32 ? 64 : 128; }
 
+// Everything below that names a position of the tile counts it from AP_SOLO positions before the tile's first.
 template <int VEC, int AP_TILE> struct ApplyLds {
-    static_assert(AP_TILE + 2 <= AP_THREADS && AP_TILE % WAVE == 0, "one thread per position of the tile, two more for the keys outside it");
+    static constexpr int WIN = AP_TILE + 2 * AP_SOLO;
+    static_assert(WIN <= AP_THREADS && AP_TILE % WAVE == 0 && AP_SOLO * 2 == WAVE, "one thread per position of the window; those before the tile are half of its first wave, those behind it half of its last");
     double share[AP_THREADS * VEC];      // the row groups' shares of a long segment
-    uint32_t key[AP_TILE + 2];           // [0]: key before the tile, [1 + i]: position i, [AP_TILE + 1]: key behind the tile
-    uint32_t grow[AP_TILE];              // gradient row of each position
-    int32_t slot[AP_TILE];               // slot of the key, valid at run heads
-    uint32_t seg_start[AP_TILE + 1];     // first position (within the tile) of every segment, then the tile's count
-    uint32_t wave_heads[AP_TILE / WAVE];
-    uint64_t fresh[AP_TILE / WAVE];      // per position: a run head whose key missed in the lookup and whose row is fetched here
+    uint32_t key[WIN];                   // KEY_NONE where there is no valid position
+    uint32_t grow[WIN];                  // gradient row of each position (tile and behind it)
+    int32_t slot[WIN];                   // slot of the key, valid at run heads of the tile
+    uint32_t seg_start[AP_TILE + 1];     // first position of every segment, then the end of the last
+    uint32_t wave_heads[WIN / WAVE];     // segments that begin in each wave's positions
+    uint64_t fresh[WIN / WAVE];          // per position: a run head whose key missed in the lookup and whose row is fetched here
+    uint32_t front_open, back_open;      // a run of more than AP_SOLO positions comes in through the tile's front border / goes on behind its back border
 };
 
 // How many of the conditions cond(1), cond(2), ... hold before the first that does not; found by
@@ -1345,7 +1354,7 @@ __device__ __forceinline__ void sum_positions(const CacheView &cv, const float *
 }
 
 struct SegWork {
-    uint32_t a, b;             // positions [a, b) of the tile
+    uint32_t a, b;             // positions [a, b) of the window
     int32_t slot;
     uint32_t from_key;         // KEY_NONE, or the key whose row has not been fetched yet (fresh)
     bool is_front, is_back;    // the run began in an earlier tile / goes on in a later one
@@ -1461,52 +1470,66 @@ __global__ __launch_bounds__(AP_THREADS) __attribute__((amdgpu_waves_per_eu(MAXC
     ApplyLds<VEC, AP_TILE> &l = lds_as<ApplyLds<VEC, AP_TILE>>();
     const uint32_t T = bid, j0 = T * AP_TILE;
     const uint32_t *skey = ws.skey;
-    {   // the tile: one position per thread, and the keys just outside it
-        const uint32_t i = threadIdx.x;
-        if (i < AP_TILE) {
-            const uint32_t j = j0 + i;
-            const bool in = j < n_ids;
+    constexpr uint32_t WIN = ApplyLds<VEC, AP_TILE>::WIN, W0 = AP_SOLO, WAVES = WIN / WAVE;
+    bool missed = false;
+    {   // the tile and what lies beside it: one position per thread
+        const uint32_t i = threadIdx.x, j = j0 + i - W0;   // (wraps before the first position)
+        if (i < WIN) {
+            const bool in = j < n_ids, own = in && i >= W0 && i < W0 + AP_TILE;      // (not nv: that is on its way itself)
             const uint32_t k = in ? skey[j] : KEY_NONE;
-            uint32_t pm = in ? ws.perm[j] : 0u;
-            const int32_t hs = in ? ws.head_slot[j] : SLOT_NONE;
+            uint32_t pm = in && i >= W0 ? ws.perm[j] : 0u;
+            const int32_t hs = own ? ws.head_slot[j] : SLOT_NONE;
             // fresh_rows: the lookup left the fetch of its missed keys' rows to this kernel
-            const bool fresh = fresh_rows && in && ws.cls[j] == (uint8_t)CLS_MISS && (j == 0 || skey[j - 1] != k);
+            missed = fresh_rows && own && ws.cls[j] == (uint8_t)CLS_MISS;
             if (grad_row && in) pm = grad_row[pm];
-            l.key[1 + i] = j < nv ? k : KEY_NONE;
+            l.key[i] = j < nv ? k : KEY_NONE;
             l.grow[i] = pm;
             l.slot[i] = hs;
-            const uint64_t fm = __ballot(fresh);
-            if (lane_id() == 0) l.fresh[i / WAVE] = fm;
-        } else if (i == AP_TILE) {
-            l.key[0] = j0 > 0 && j0 < n_ids ? skey[j0 - 1] : KEY_NONE;
-        } else if (i == AP_TILE + 1) {
-            const uint32_t jn = j0 + AP_TILE;
-            const uint32_t k = jn < n_ids ? skey[jn] : KEY_NONE;
-            l.key[AP_TILE + 1] = jn < nv ? k : KEY_NONE;
         }
     }
     if (j0 >= nv) return;                                  // (uniform: nothing valid in this tile)
     const uint32_t cnt = min((uint32_t)AP_TILE, nv - j0);
     __syncthreads();
+    uint32_t nseg = 0;
     {   // the segments, in order
-        const uint32_t i = threadIdx.x;
-        const bool head = i < cnt && (i == 0 || l.key[i] != l.key[1 + i]);
-        const uint64_t m = __ballot(head);
-        const uint32_t w = i / WAVE;
-        if (i < AP_TILE && lane_id() == 0) l.wave_heads[w] = (uint32_t)__popcll(m);
+        const uint32_t i = threadIdx.x, w = i / WAVE;
+        bool start = false;
+        uint64_t m = 0;
+        uint32_t end = 0;
+        if (w < WAVES) {
+            const bool head = i == 0 || l.key[i] != l.key[i - 1];
+            const uint64_t heads = __ballot(head);
+            start = head && i >= W0 && i < W0 + cnt;       // (tile positions begin and end at half a wave)
+            if (w == 0) {
+                // keys ascend: a run is longer than AP_SOLO if the position AP_SOLO behind its first has its key
+                // (one that began before the window is; position 0 stands for its first)
+                const uint32_t first = 31u - (uint32_t)__clz((uint32_t)heads);
+                const bool open = !(heads >> W0 & 1ull) && l.key[first + AP_SOLO] == l.key[W0];
+                if (i == W0) start = head || open;
+                if (i == 0) l.front_open = open;
+            }
+            if (w == WAVES - 1) {
+                const uint32_t behind = (uint32_t)(heads >> W0);       // run heads behind the tile
+                const bool cross = cnt == AP_TILE && !(behind & 1u);
+                const uint32_t more = behind ? (uint32_t)__ffs(behind) - 1u : (uint32_t)AP_SOLO;
+                const bool open = cross && l.key[W0 + AP_TILE + more - 1 - AP_SOLO] == l.key[W0 + AP_TILE - 1];
+                end = W0 + cnt + (cross && !open ? more : 0u);
+                if (lane_id() == 0) l.back_open = open;
+            }
+            m = __ballot(start);
+            const uint64_t fm = __ballot(missed && head);
+            if (lane_id() == 0) { l.wave_heads[w] = (uint32_t)__popcll(m); l.fresh[w] = fm; }
+        }
         __syncthreads();
-        uint32_t before = 0, total = 0;
+        uint32_t before = 0;
 #pragma unroll
-        for (int ww = 0; ww < AP_TILE / WAVE; ++ww) { const uint32_t c = l.wave_heads[ww]; before += (uint32_t)ww < w ? c : 0u; total += c; }
-        if (head) l.seg_start[before + mask_rank(m)] = i;
-        if (i == 0) l.seg_start[total] = cnt;
+        for (uint32_t ww = 0; ww < WAVES; ++ww) { const uint32_t c = l.wave_heads[ww]; before += ww < w ? c : 0u; nseg += c; }
+        if (start) l.seg_start[before + mask_rank(m)] = i;
+        if (i == WIN - WAVE) l.seg_start[nseg] = end;
         __syncthreads();
     }
-    uint32_t nseg = 0;
-#pragma unroll
-    for (int ww = 0; ww < AP_TILE / WAVE; ++ww) nseg += l.wave_heads[ww];
-    const bool front_open = l.key[0] != KEY_NONE && l.key[0] == l.key[1];                   // the first segment's run began in an earlier tile
-    const bool back_open = cnt == AP_TILE && l.key[AP_TILE + 1] != KEY_NONE && l.key[AP_TILE + 1] == l.key[AP_TILE];   // the last one's goes on
+    const bool front_open = l.front_open != 0;             // the first segment's run began in an earlier tile
+    const bool back_open = l.back_open != 0;               // the last one's goes on
     const size_t pstride = (size_t)g.dim;
     // Which tiles the runs that cross this tile's borders touch is asked now, by the two waves that
     // will finish them (see below), so that the answer is there when the sums are.
@@ -1515,7 +1538,7 @@ __global__ __launch_bounds__(AP_THREADS) __attribute__((amdgpu_waves_per_eu(MAXC
     const bool do_front = wave == 0 && front_open, do_back = wave == 1 && back_open && !through;
     uint32_t T0 = T, T1 = T;
     if (do_front || do_back) {
-        const uint32_t key = do_front ? l.key[1] : l.key[AP_TILE];
+        const uint32_t key = do_front ? l.key[W0] : l.key[W0 + AP_TILE - 1];
         if (do_front)            // tiles before this one that the run also entered through their front border
             T0 = T - 1 - wave_count_leading([&](uint32_t i) { return i < T && skey[(size_t)(T - i) * AP_TILE - 1] == key; });
         if (do_back || through)  // tiles behind this one that the run also leaves through their back border
@@ -1525,13 +1548,12 @@ __global__ __launch_bounds__(AP_THREADS) __attribute__((amdgpu_waves_per_eu(MAXC
     // (does any segment need the whole workgroup?  every thread looks at one)
     const bool any_long = __syncthreads_or(threadIdx.x < nseg && l.seg_start[threadIdx.x + 1] - l.seg_start[threadIdx.x] > AP_SOLO) != 0;
 
-    // segments of up to AP_SOLO positions: one row group each
     auto seg_work = [&](uint32_t sg) {
         SegWork w;
         w.a = l.seg_start[sg]; w.b = l.seg_start[sg + 1];
         w.is_front = sg == 0 && front_open; w.is_back = sg + 1 == nseg && back_open;
         w.slot = w.is_front ? SLOT_NONE : l.slot[w.a];
-        w.from_key = !w.is_front && ((l.fresh[w.a / WAVE] >> (w.a % WAVE)) & 1ull) ? l.key[1 + w.a] : KEY_NONE;
+        w.from_key = !w.is_front && ((l.fresh[w.a / WAVE] >> (w.a % WAVE)) & 1ull) ? l.key[w.a] : KEY_NONE;
         return w;
     };
     // what is left to do once the segment's sum for row piece cidx is there
@@ -1553,10 +1575,34 @@ __global__ __launch_bounds__(AP_THREADS) __attribute__((amdgpu_waves_per_eu(MAXC
         }
         if (w.is_front || w.is_back) stores_acknowledged();   // the partial sum, before this tile is counted as arrived
     };
+    // segments of more than AP_ROWS and up to AP_SOLO positions: one wave each, where it holds several row groups
+    const uint32_t alone = MAXC == 1 && g.lanes < WAVE ? AP_ROWS : AP_SOLO;
+    if constexpr (MAXC == 1) {
+        const uint32_t wave_group = lane_id() / g.lanes, wave_groups = WAVE / g.lanes;
+        uint32_t count = 0;
+        for (uint32_t s0 = 0; s0 < nseg; s0 += WAVE) {
+            const uint32_t mine = s0 + lane_id(), len = mine < nseg ? l.seg_start[mine + 1] - l.seg_start[mine] : 0u;
+            for (uint64_t todo = __ballot(len > alone && len <= AP_SOLO); todo; todo &= todo - 1) {
+                if (count++ % (AP_THREADS / WAVE) != wave) continue;
+                const SegWork w = seg_work(s0 + (uint32_t)__builtin_ctzll(todo));
+                const bool step = !w.is_front && !w.is_back && w.slot != SLOT_NONE, act = gl < g.chunks;
+                const uint32_t per = (w.b - w.a + wave_groups - 1) / wave_groups;
+                const uint32_t lo = min(w.a + wave_group * per, w.b), hi = min(lo + per, w.b);
+                double acc64[VEC];
+                V xr{}, ar{};
+                sum_positions<VEC, BATCH>(cv, grads, l.grow, lo, hi, gl, act, acc64, step && wave_group == 0, (uint32_t)w.slot, xr, ar, w.from_key);
+                for (int o = g.lanes; o < WAVE; o <<= 1)
+#pragma unroll
+                    for (int e = 0; e < VEC; ++e) acc64[e] += __shfl_xor(acc64[e], o, WAVE);
+                if (wave_group == 0) { finish_piece(w, gl, act, acc64, xr, ar); finish_segment(w); }
+            }
+        }
+    }
     {
+        // the shorter ones: one row group each
         for (uint32_t sg = group; sg < nseg; sg += ngroups) {
             const SegWork w = seg_work(sg);
-            if (w.b - w.a > AP_SOLO) continue;
+            if (w.b - w.a > alone) continue;
             const bool step = !w.is_front && !w.is_back && w.slot != SLOT_NONE;
 #pragma unroll
             for (int q = 0; q < MAXC; ++q) {
@@ -1578,7 +1624,7 @@ __global__ __launch_bounds__(AP_THREADS) __attribute__((amdgpu_waves_per_eu(MAXC
             if (b - a <= AP_SOLO) continue;
             const bool is_front = sg == 0 && front_open, is_back = sg + 1 == nseg && back_open;
             const int32_t slot = is_front ? SLOT_NONE : l.slot[a];
-            const uint32_t from_key = !is_front && ((l.fresh[a / WAVE] >> (a % WAVE)) & 1ull) ? l.key[1 + a] : KEY_NONE;
+            const uint32_t from_key = !is_front && ((l.fresh[a / WAVE] >> (a % WAVE)) & 1ull) ? l.key[a] : KEY_NONE;
             const bool closed = !is_front && !is_back;
             const bool step = closed && slot != SLOT_NONE;
             const uint32_t per = (b - a + ngroups - 1) / ngroups;

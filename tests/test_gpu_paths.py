@@ -106,3 +106,33 @@ def test_key_index_in_hbm_and_where_hbm_has_no_room(full):
         assert float(table.abs().sum(dtype=torch.float64)) == float(np.abs(np.array(list(want.values()))).sum())
     finally:
         cache.close()
+
+
+@pytest.mark.parametrize("dim", [3, 4, 64, 132])
+@pytest.mark.parametrize("length", [1, 30, 31, 32, 33, 34, 63, 64, 65, 97, 161])
+def test_runs_of_every_length_over_tile_borders(length, dim):
+    """Runs of one length at every offset from the update's tiles (of 64 or 128 sorted positions): a run of up to 32
+    positions is summed beyond the border by the tile it begins in, a longer one in parts.  Whole numbers and lr 1,
+    so sums are exact; the last tile ends in invalid ids."""
+    from paper_2112_07221_amd import hetcache as hc
+    dev = torch.device("cuda:0")
+    vocab = 4_000
+    rng = np.random.default_rng(length)
+    keys = np.repeat(np.arange(2_000, 2_200), length)
+    batches = [np.concatenate([np.arange(o), keys, np.full(7, -1)]) for o in range(0, 129, 16 if length > 40 else 8)]     # (o other keys shift the runs)
+    for policy in (hc.POLICY_NONE, hc.POLICY_LRU):
+        cache = hc.HetCache(300, dim, 0, policy, len(batches[-1]), hc.OPT_SGD)
+        table, want = torch.zeros(vocab, dim, device=dev), np.zeros((vocab, dim))
+        try:
+            cache.attach_backing(table, None, torch.zeros(vocab, dtype=torch.int32, device=dev))
+            for b in batches:
+                ids = rng.permutation(b)
+                g = rng.integers(-8, 9, (len(ids), dim)).astype(np.float32)
+                d = torch.from_numpy(ids).to(dev)
+                cache.lookup(d, torch.empty(len(ids), dim, device=dev))
+                cache.update(d, torch.from_numpy(g).to(dev), 1.0)
+                np.add.at(want, ids[ids >= 0], -g[ids >= 0].astype(np.float64))
+            assert cache.flush() == hc.HET_ERANGE                      # (the ids of -1)
+            assert np.array_equal(table.cpu().numpy(), want.astype(np.float32))
+        finally:
+            cache.close()
