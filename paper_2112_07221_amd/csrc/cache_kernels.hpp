@@ -226,7 +226,7 @@ template <typename T> __device__ __forceinline__ T &lds_as() { return *reinterpr
 // Up to two sort stages, of two different announced batches, travel in one kernel.  Returns
 // true if this workgroup ran one of them; otherwise bid / nblk number the kernel's own workgroups.
 // HIST_ONLY: both are known to be histogram stages (cheap in registers).
-template <bool HIST_ONLY = false>
+template <bool HIST_ONLY = false, int THREADS = SORT_THREADS>
 __device__ __forceinline__ bool run_carried(const SortStage &a, const SortStage &b, uint32_t &bid, uint32_t &nblk)
 {
     uint32_t *lds = reinterpret_cast<uint32_t *>(dyn_lds);
@@ -234,8 +234,8 @@ __device__ __forceinline__ bool run_carried(const SortStage &a, const SortStage 
         const bool first = bid < a.blocks;
         const SortStage &st = first ? a : b;
         const uint32_t tile = first ? bid : bid - a.blocks;
-        if (HIST_ONLY) { __builtin_amdgcn_s_setprio(3); sort_hist_body<SORT_THREADS>(st, tile, lds); }
-        else sort_stage_body<SORT_THREADS>(st, tile, lds);
+        if (HIST_ONLY) { __builtin_amdgcn_s_setprio(3); sort_hist_body<THREADS>(st, tile, lds); }
+        else sort_stage_body<THREADS>(st, tile, lds);
         return true;
     }
     bid -= a.blocks + b.blocks; nblk -= a.blocks + b.blocks;
@@ -438,14 +438,25 @@ __device__ __forceinline__ void check_order_body(const CacheView &cv, const Work
     if (__any(changed) && lane_id() == 0) atomicOr(&cv.ds->err, ERRBIT_STATE);
 }
 
-template <bool LOOKUP>
-__global__ __launch_bounds__(PT_THREADS) void probe_kernel(CacheView cv, Workspace ws, uint32_t n, uint32_t t_now, uint32_t ptiles,
+// RIDE: carries sort stages of announced batches, in workgroups of a thread per key, behind its own (they end first).
+// (96 scalar registers: with the 102 that the stages' arguments would take, a SIMD holds seven waves, and a compute unit one workgroup instead of two.)
+template <bool LOOKUP, bool RIDE>
+__global__ __launch_bounds__(PT_THREADS) __attribute__((amdgpu_num_sgpr(96))) void probe_kernel(CacheView cv, Workspace ws, uint32_t n, uint32_t t_now, uint32_t ptiles,
                                                            const uint32_t *tile_free, uint32_t *tile_free_idle, uint32_t ev_idle,
                                                            uint32_t *zero_from, uint32_t zero_words, TrimPlan tp,
-                                                           const int64_t *__restrict__ check_ids, int pf_idle = -1,
-                                                           uint32_t *__restrict__ inv = nullptr)
+                                                           const int64_t *__restrict__ check_ids, int pf_idle,
+                                                           uint32_t *__restrict__ inv, SortStage ride, SortStage ride2)
 {
     __shared__ uint32_t lds[PT_WAVES + 1];
+    uint32_t own_blocks = gridDim.x;
+    if (RIDE) {
+        own_blocks -= ride.blocks + ride2.blocks;
+        if (blockIdx.x >= own_blocks) {
+            uint32_t bid = blockIdx.x - own_blocks, nblk = gridDim.x;
+            run_carried<false, PT_THREADS>(ride, ride2, bid, nblk);
+            return;
+        }
+    }
     __shared__ uint32_t h0_delta[LOOKUP ? SEL_BINS : 1];       // rows entering (+) and leaving (-) each bin of the kept histogram
     const uint32_t check_blocks = LOOKUP && check_ids ? ptiles : 0u;
     if (blockIdx.x >= ptiles && blockIdx.x < ptiles + check_blocks) {
@@ -458,7 +469,7 @@ __global__ __launch_bounds__(PT_THREADS) void probe_kernel(CacheView cv, Workspa
     if (blockIdx.x >= ptiles) {          // extra workgroups of a lookup: the free list for the fill kernel
         // ... and clean select histograms for the trim that follows this lookup
         const uint32_t first = ptiles + check_blocks;
-        for (uint32_t i = (blockIdx.x - first) * PT_THREADS + threadIdx.x; i < zero_words; i += (gridDim.x - first) * PT_THREADS) zero_from[i] = 0;
+        for (uint32_t i = (blockIdx.x - first) * PT_THREADS + threadIdx.x; i < zero_words; i += (own_blocks - first) * PT_THREADS) zero_from[i] = 0;
         free_list_body(cv, tile_free, tile_free_idle, ev_idle, blockIdx.x - first, lds);
         return;
     }
@@ -576,11 +587,19 @@ __global__ __launch_bounds__(PT_THREADS) void probe_kernel(CacheView cv, Workspa
 
 // No cache (the paper's baseline "Hybrid (w/o Cache)", Section 5): Read and Write go straight to
 // the global table.  The sorted order is used as it is; a key stands for its own row.
-template <bool LOOKUP>
-__global__ __launch_bounds__(PT_THREADS) void direct_probe_kernel(CacheView cv, Workspace ws, uint32_t n, uint32_t t_now, uint32_t ptiles,
-                                                                  const int64_t *__restrict__ check_ids, uint32_t *__restrict__ inv = nullptr)
+template <bool LOOKUP, bool RIDE>
+__global__ __launch_bounds__(PT_THREADS) __attribute__((amdgpu_num_sgpr(96))) void direct_probe_kernel(CacheView cv, Workspace ws, uint32_t n, uint32_t t_now, uint32_t ptiles,
+                                                                  const int64_t *__restrict__ check_ids, uint32_t *__restrict__ inv, SortStage ride, SortStage ride2)
 {
     __shared__ uint32_t lds[PT_WAVES + 1];
+    if (RIDE) {
+        const uint32_t own_blocks = gridDim.x - (ride.blocks + ride2.blocks);
+        if (blockIdx.x >= own_blocks) {
+            uint32_t bid = blockIdx.x - own_blocks, nblk = gridDim.x;
+            run_carried<false, PT_THREADS>(ride, ride2, bid, nblk);
+            return;
+        }
+    }
     if (blockIdx.x >= ptiles) { check_order_body(cv, ws, check_ids, n, blockIdx.x - ptiles); return; }     // (an order sorted ahead, see probe_kernel)
     const uint32_t j = blockIdx.x * PT_TILE + threadIdx.x;
     if (LOOKUP && inv && j < n) inv[ws.perm[j]] = j;         // pooled lookup (see probe_kernel)

@@ -270,14 +270,14 @@ SortPlan make_sort_plan(const het_cache *c, uint32_t n, int set, int max_bits)
     return sp;
 }
 
-// Digits of an announced batch's sort.  A batch announced one ahead meets three kernels that carry a
-// stage before its lookup (two without a cache): two wide passes are nearly all carried.  Announced two ahead
+// Digits of an announced batch's sort.  A batch announced one ahead meets three or four kernels that carry a
+// stage before its lookup: two wide passes are (nearly) all carried.  Announced two ahead
 // it meets them twice: narrow digits are carried just as completely, and their stages are shorter and
 // need less LDS, so the carrying kernels keep their occupancy (114688 ids of 22 bits: the update 40 us with
 // stages of 8 bits, 48 us with stages of 11).
 int sort_bits_ahead(const het_cache *c, uint32_t n)
 {
-    const int carried = c->n_ann >= 2 ? (c->cv.direct ? 4 : 6) : 0;
+    const int carried = c->n_ann >= 2 ? 6 : 0;
     return 2 * make_sort_plan(c, n, 0, SORT_NARROW_BITS).passes <= carried ? SORT_NARROW_BITS : sort_bits_alone(n);
 }
 
@@ -365,12 +365,22 @@ struct Rides {
 };
 
 // LDS a kernel needs: its own roles' or, if larger, a carried stage's.
-uint32_t lds_bytes(size_t own, const Rides &r)
+uint32_t lds_bytes(size_t own, const Rides &r, int threads = SORT_THREADS)
 {
     uint32_t need = (uint32_t)own;
-    if (r.a.blocks) need = std::max(need, sort_stage_lds_bytes(r.a.sp.width, r.a.sp.super, r.a.stage, SORT_THREADS));
-    if (r.b.blocks) need = std::max(need, sort_stage_lds_bytes(r.b.sp.width, r.b.sp.super, r.b.stage, SORT_THREADS));
+    if (r.a.blocks) need = std::max(need, sort_stage_lds_bytes(r.a.sp.width, r.a.sp.super, r.a.stage, threads));
+    if (r.b.blocks) need = std::max(need, sort_stage_lds_bytes(r.b.sp.width, r.b.sp.super, r.b.stage, threads));
     return need;
+}
+
+// Must the probe carry a stage?  The kernels behind it carry them for less (the probe's workgroups are large ones of
+// its own size: 409600 ids 311 -> 328 us a step where nothing needed it), so only where an announced batch would
+// meet too few of those before its lookup: 2 a step without a cache, else 3.
+bool probe_must_ride(const het_cache *c, bool evict_kernel)
+{
+    for (int a = 0; a < c->n_ann; ++a)
+        if (sort_stages(c, c->ann[a].max_bits) - c->ann[a].next_stage > (a + 1) * (evict_kernel ? 3 : 2)) return true;
+    return false;
 }
 
 Rides next_rides(het_cache *c)
@@ -526,8 +536,15 @@ int run_lookup(het_cache *c, const int64_t *ids, uint32_t n, const int64_t *offs
     const uint32_t t_now = (uint32_t)c->t_host;
     if (c->cv.direct) {
         // no cache: mark the runs, then gather straight from the global table
-        LAUNCH(c, K_PROBE, direct_probe_kernel<true><<<cdiv(n, PT_TILE) * (match >= 0 ? 2u : 1u), PT_THREADS, 0, c->stream>>>(c->cv, c->ws, n, t_now, cdiv(n, PT_TILE), match >= 0 ? ids : nullptr,
-                                                                                                                              offsets ? c->inv : nullptr));
+        const uint32_t dtiles = cdiv(n, PT_TILE), dblocks = dtiles * (match >= 0 ? 2u : 1u);
+        {
+            const Rides ride = probe_must_ride(c, false) ? next_rides(c) : Rides{no_stage(), no_stage()};
+#define DIRECT_PROBE(RIDE)                                                                                                                       \
+    LAUNCH(c, K_PROBE, direct_probe_kernel<true, RIDE><<<dblocks + ride.blocks(), PT_THREADS, lds_bytes(0, ride, PT_THREADS), c->stream>>>(        \
+                           c->cv, c->ws, n, t_now, dtiles, match >= 0 ? ids : nullptr, offsets ? c->inv : nullptr, ride.a, ride.b))
+            if (ride.blocks()) DIRECT_PROBE(true); else DIRECT_PROBE(false);
+#undef DIRECT_PROBE
+        }
         const Rides ride = next_rides(c);
         const uint32_t grid = ride.blocks() + row_grid(c->cv.geom, offsets ? n_bags : cdiv(n, GATHER_ROWS));
         const uint32_t lds = lds_bytes(std::max(sizeof(FillLds), sizeof(TrimLds)), ride);
@@ -556,10 +573,17 @@ int run_lookup(het_cache *c, const int64_t *ids, uint32_t n, const int64_t *offs
     c->h0_shift = h0_shift;
     const TrimPlan &tp = c->sel_tp;
     const uint32_t kept_words = tp.h0_kept ? (uint32_t)SEL_BINS : 0u;
-    LAUNCH(c, K_PROBE, probe_kernel<true><<<ptiles + (match >= 0 ? ptiles : 0u) + stiles, PT_THREADS, 0, c->stream>>>(
-                           c->cv, c->ws, n, t_now, ptiles, c->tile_free[c->tf_last], c->tile_free[1 - c->tf_last], (uint32_t)(1 - c->tf_last),
-                           c->tp.hist + kept_words, c->tp.zero_words - kept_words, tp, match >= 0 ? ids : nullptr,
-                           c->side ? c->pf_slot_next : -1, offsets ? c->inv : nullptr));
+    {
+        const Rides ride = probe_must_ride(c, true) ? next_rides(c) : Rides{no_stage(), no_stage()};
+        const uint32_t blocks = ptiles + (match >= 0 ? ptiles : 0u) + stiles;
+#define PROBE(RIDE)                                                                                                                              \
+    LAUNCH(c, K_PROBE, probe_kernel<true, RIDE><<<blocks + ride.blocks(), PT_THREADS, lds_bytes(0, ride, PT_THREADS), c->stream>>>(                \
+                           c->cv, c->ws, n, t_now, ptiles, c->tile_free[c->tf_last], c->tile_free[1 - c->tf_last], (uint32_t)(1 - c->tf_last),    \
+                           c->tp.hist + kept_words, c->tp.zero_words - kept_words, tp, match >= 0 ? ids : nullptr, c->side ? c->pf_slot_next : -1, offsets ? c->inv : nullptr, ride.a, ride.b))
+        if (ride.blocks()) PROBE(true); else PROBE(false);
+#undef PROBE
+    }
+
     const int hist_pass = tp.h0_kept ? 1 : 0;                  // this pass of the select rides with the fetches
     // (the update has one kernel to carry a stage: with the first pass kept, a select of two passes
     // is over when that kernel ends: second pass here, tie count there)
@@ -737,10 +761,10 @@ int run_update(het_cache *c, const int64_t *ids, uint32_t n, const int64_t *offs
         sort_now(c, ids, n, c->sort_set, sort_bits_alone(n), 0);
         use_order(c, c->sort_set, sort_bits_alone(n));
         if (c->cv.direct)
-            LAUNCH(c, K_PROBE, direct_probe_kernel<false><<<cdiv(n, PT_TILE), PT_THREADS, 0, c->stream>>>(c->cv, c->ws, n, (uint32_t)c->t_host, cdiv(n, PT_TILE), nullptr));
+            LAUNCH(c, K_PROBE, direct_probe_kernel<false, false><<<cdiv(n, PT_TILE), PT_THREADS, 0, c->stream>>>(c->cv, c->ws, n, (uint32_t)c->t_host, cdiv(n, PT_TILE), nullptr, nullptr, no_stage(), no_stage()));
         else
-            LAUNCH(c, K_PROBE, probe_kernel<false><<<cdiv(n, PT_TILE), PT_THREADS, 0, c->stream>>>(
-                                   c->cv, c->ws, n, (uint32_t)c->t_host, cdiv(n, PT_TILE), nullptr, nullptr, 0u, nullptr, 0u, TrimPlan{}, nullptr));
+            LAUNCH(c, K_PROBE, probe_kernel<false, false><<<cdiv(n, PT_TILE), PT_THREADS, 0, c->stream>>>(
+                                   c->cv, c->ws, n, (uint32_t)c->t_host, cdiv(n, PT_TILE), nullptr, nullptr, 0u, nullptr, 0u, TrimPlan{}, nullptr, -1, nullptr, no_stage(), no_stage()));
     }
     const uint32_t *grad_row = nullptr;
     if (offsets) {
@@ -898,9 +922,11 @@ static int configure_impl(het_cache *c, int64_t max_batch_ids, int32_t optimizer
     }
     HIP_TRY(hipMemsetAsync(c->tile_free[1], 0, slot_tiles * sizeof(uint32_t), c->stream));
 
-    // the sort's own kernels ask for more LDS than a launch gets unasked
+    // the sort's own kernels, and those that carry wide digits in workgroups as large, ask for more LDS than a launch gets unasked
     const int max_lds = 160 * 1024;
     HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(&sort_stage_kernel<SORT_THREADS_ALONE>), hipFuncAttributeMaxDynamicSharedMemorySize, max_lds));
+    HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(&probe_kernel<true, true>), hipFuncAttributeMaxDynamicSharedMemorySize, max_lds - 16 * 1024));      // (it has LDS of its own)
+    HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(&direct_probe_kernel<true, true>), hipFuncAttributeMaxDynamicSharedMemorySize, max_lds - 16 * 1024));
     HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(&sort_solo_kernel<8>), hipFuncAttributeMaxDynamicSharedMemorySize, max_lds));
     HIP_TRY(hipMemsetAsync(c->bd.arrived, 0, ap_tiles * 3 * sizeof(uint32_t), c->stream));
     HIP_TRY(hipMemsetAsync(cv.ds, 0, sizeof(DState), c->stream));

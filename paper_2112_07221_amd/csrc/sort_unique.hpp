@@ -357,7 +357,7 @@ __device__ __forceinline__ void sort_scatter_alone(const SortStage &s, uint32_t 
 template <int THREADS>
 __device__ __forceinline__ void sort_stage_body(const SortStage &s, uint32_t tile, uint32_t *lds)
 {
-    // few workgroups with a long chain of dependent steps, among the many of the carrying kernel:
+    // (256 threads) few workgroups with a long chain of dependent steps, among the many of the carrying kernel:
     // their waves go first when a SIMD has to choose
     if (THREADS == SORT_THREADS) __builtin_amdgcn_s_setprio(3);
     if (!(s.stage & 1)) sort_hist_body<THREADS>(s, tile, lds);

@@ -136,3 +136,12 @@ def test_runs_of_every_length_over_tile_borders(length, dim):
             assert np.array_equal(table.cpu().numpy(), want.astype(np.float32))
         finally:
             cache.close()
+
+
+@pytest.mark.parametrize("mode", ["before", "between", "after"])
+@pytest.mark.parametrize("batch,vocab,policy", [(315, 70_000, 1), (316, 1_000_000, 0), (600, 2_500_000, 1), (1_300, 300_000, 1)])
+def test_sort_stages_carried_by_every_kernel_of_a_step(batch, vocab, policy, mode):
+    """Announced one or two ahead: the probe carries stages too, in workgroups of 1024 threads, where the kernels behind
+    it are too few."""
+    w = wl.WORKLOADS[1].scaled(batch=batch, vocab=vocab, capacity=9_000, s=4, policy=policy, dim=8)
+    run_workload(w, 7, state_every=2, prefetch=mode)
