@@ -212,8 +212,8 @@ def trace_kernels(args, w, dev):
     cache = hc.HetCache(w.capacity, w.dim, w.s, w.policy, w.n, w.optimizer, w.eps)
     cache.attach_backing(Wt, At, Cg, hc.BACKING_HBM)
     cap = 1 << 15
-    kernels = {"apply_kernel": {1: "carried sort stage", 2: "select stage", 3: "id check", 4: "update tile"},
-               "fill_gather_kernel": {1: "carried sort stage", 2: "fetch", 3: "bookkeeping of the fetched keys", 4: "select stage",
+    kernels = {"apply_kernel": {1: "carried sort stage", 2: "eviction, or the count before it", 3: "id check", 4: "update tile"},
+               "fill_gather_kernel": {1: "carried sort stage", 2: "fetch", 3: "bookkeeping of the fetched keys", 4: "count of the rows to evict",
                                       5: "gather", 6: "host link"}}
     rec = {k: torch.zeros(cap, hc.TRACE_WORDS, dtype=torch.int64, device=dev) for k in kernels}
 

@@ -280,7 +280,8 @@ int het_lookup_nocache_static(const float *table, int64_t vocab, int32_t dim, co
 /*
  * Per-kernel timing for benchmarks.  Between het_profile_begin and het_profile_end every kernel
  * the library launches for this cache is bracketed by a pair of HIP events on the cache's
- * stream (this slows the calls down slightly and creates events: not for timed regions).
+ * stream (this slows the calls down slightly and creates events: not for timed regions), and the
+ * eviction that otherwise runs beside the update runs in a kernel of its own.
  * het_profile_end waits for the stream and adds up, per kernel index, the elapsed milliseconds
  * into total_ms[n_kernels] and the launch count into launches[n_kernels] (host arrays).
  * het_profile_kernel_count / het_profile_kernel_name give the index space.

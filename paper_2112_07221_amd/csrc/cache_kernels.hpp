@@ -128,15 +128,18 @@ __device__ __forceinline__ void count2(unsigned long long *a, unsigned long long
 // (freq, last_use, slot) [LFU].  A most-significant-digit radix select finds the policy key
 // tau of the m-th smallest row; rows below tau go, and of the rows equal to tau the first few in
 // slot order.
+// The two first digits' histograms are kept from call to call (see kept_bin), so up to 4 million iterations the
+// select is a look-up and one count of the rows below and at tau.
 // Under LFU only rows of use count 1 can go: a trim never has more to drop than the lookup before it
 // fetched (the cache was within its capacity before), and the rows that lookup fetched all have
 // count 1, so the m-th smallest has count 1 too.  So the policy key is last_use under both policies,
-// `bits` wide (last_use is at most t), and LFU's select simply passes over the rows of a higher
+// `key_bits` wide (last_use is at most t), and LFU's select simply passes over the rows of a higher
 // count.  (With (freq, last_use) as the key a select had three passes and a kernel of its own for
 // its last stage from iteration 2048 on: 11.4 us of an 87 us step at 206 000 slots.)
 constexpr int SEL_BITS = 11;
 constexpr int SEL_BINS = 1 << SEL_BITS;
-constexpr int SEL_MAX_PASSES = 3;     // last_use has at most 32 bits
+constexpr int KEPT_BITS = 2 * SEL_BITS;                       // the policy key's top digits, counted in the kept histograms
+constexpr uint32_t KEPT_WORDS = SEL_BINS + (1u << KEPT_BITS); // their words: [SEL_BINS] by the first digit, then [SEL_BINS][SEL_BINS]
 constexpr int TRIM_THREADS = 256;
 constexpr int TRIM_WAVES = TRIM_THREADS / WAVE;
 constexpr int TRIM_ITEMS = 4;
@@ -144,10 +147,12 @@ constexpr int TRIM_TILE = TRIM_THREADS * TRIM_ITEMS;   // 1024 slots per countin
 
 struct TrimPlan {
     int lfu;          // policy
-    int key_bits;     // bits of the policy key (last_use)
-    int passes;       // select passes
-    int h0_kept;      // the first pass's histogram is kept up to date between trims (by the probe and the eviction), not counted anew
-    uint32_t *hist;   // [SEL_MAX_PASSES][SEL_BINS] followed by sup_cnt: zeroed together before the first pass
+    int key_bits;     // bits of the policy key (last_use): KEPT_BITS, or as many as the iteration has beyond that
+    int passes;       // its digits: 2, or 3 beyond KEPT_BITS bits
+    uint32_t t_now;   // iteration of the Read that left the overflow
+    uint32_t *coarse, *fine;           // the kept histograms of all evictable rows, by the first digit and by both (see kept_bin)
+    uint32_t *hist;                    // [SEL_BINS]: third digit, of the rows that share tau's first two
+    uint32_t *zero_from;               // cleared by every Read: sup_cnt and, if there is a third digit, hist behind it
     uint32_t zero_words;
     uint4 *blk_cnt, *sup_cnt;          // per 1024 slots, and per EV_SUPER such blocks: cached rows with a policy key
                                        // below the threshold (x), equal to it (y), and those of each that hold updates (z, w)
@@ -155,6 +160,7 @@ struct TrimPlan {
     uint32_t *ev_ids;                  // ids dropped by this trim
     int ev_slot;                       // which of the two evicted-id counts (and staging buffers) this trim appends to
     uint32_t push_seq;                 // host-backed table: serial number of this trim (never 0)
+    int fetched_dirty;                 // the count ran beside the lookup's fetches, and the batch has been updated since
     uint32_t dirty_stamp;              // the tie count runs beside the optimizer step of the Read of this iteration's keys (0: it does not):
                                        // every row that Read touched will hold updates when the step is done, whether its clock has moved yet or not
 };
@@ -163,50 +169,63 @@ __device__ __forceinline__ uint32_t policy_key(const uint4 &meta) { return meta.
 // Can the row be evicted at all?  (See above: under LFU only rows used once.)
 __device__ __forceinline__ bool evictable(const TrimPlan &tp, const uint4 &meta) { return !tp.lfu || meta.w == 1u; }
 
-__device__ __forceinline__ int sel_shift(const TrimPlan &tp, int pass)
+// The kept histograms count every evictable row by the top KEPT_BITS bits of its policy key.  They need not be
+// counted anew for every trim: a Read changes the keys of the rows it finds and adds the rows it fetches, a
+// trim removes its victims, nothing else touches policy keys.  So the probe moves the rows it touches from
+// their old bin to their new one, and the eviction takes its victims out (kept_remove_victims).  Up to iteration
+// 2^22 a bin is one iteration and tau is known as soon as the probe has ended, so the rows below and at
+// it are counted beside the lookup's fetches (16 MB; with the first digit's histogram kept alone, the second was
+// counted beside the fetches and the rows by the update or, between two Reads, by a kernel of their own: lookups of
+// 53248 ids 60.5 -> 58.4 us; and the eviction could not run beside the update, see evict_body).
+// Beyond, the bins widen by a factor of two at iterations 2^22, 2^23, ...; kept_recount_kernel then counts them afresh.
+__device__ __forceinline__ uint32_t kept_bin(const TrimPlan &tp, uint32_t key) { return key >> (tp.key_bits - KEPT_BITS); }
+
+// The digit whose cumulative count first reaches `remaining`, which becomes what is left to find inside it.
+// c: the counts of the thread's SEL_BINS / TRIM_THREADS consecutive digits.  Every thread gets the same answer.
+constexpr int SEL_PER = SEL_BINS / TRIM_THREADS;
+static_assert(SEL_PER == 8, "a thread's share of a histogram is two 16-byte loads");
+__device__ __forceinline__ void sel_load(const uint32_t *hist, uint32_t (&c)[SEL_PER])
 {
-    const int sh = tp.key_bits - SEL_BITS * (pass + 1);
-    return sh < 0 ? 0 : sh;
+    const uint4 a = reinterpret_cast<const uint4 *>(hist)[2 * threadIdx.x], b = reinterpret_cast<const uint4 *>(hist)[2 * threadIdx.x + 1];
+    c[0] = a.x; c[1] = a.y; c[2] = a.z; c[3] = a.w; c[4] = b.x; c[5] = b.y; c[6] = b.z; c[7] = b.w;
 }
-__device__ __forceinline__ int sel_width(const TrimPlan &tp, int pass)
+__device__ __forceinline__ uint32_t sel_pick(const uint32_t (&c)[SEL_PER], uint32_t &remaining, uint32_t *lds_pick, uint32_t *lds_scan)
 {
-    const int hi = tp.key_bits - SEL_BITS * pass;       // bits not yet decided
-    return hi < SEL_BITS ? hi : SEL_BITS;
+    uint32_t s = 0, tot;
+#pragma unroll
+    for (int q = 0; q < SEL_PER; ++q) s += c[q];
+    uint32_t run = block_excl_scan<TRIM_WAVES>(s, lds_scan, tot);
+#pragma unroll
+    for (int q = 0; q < SEL_PER; ++q) {
+        if (c[q] && run < remaining && remaining <= run + c[q]) { lds_pick[0] = threadIdx.x * SEL_PER + q; lds_pick[1] = run; }
+        run += c[q];
+    }
+    __syncthreads();
+    const uint32_t digit = lds_pick[0] & (SEL_BINS - 1);
+    remaining -= lds_pick[1];
+    __syncthreads();
+    return digit;
 }
 
-// Replays the select decisions of passes [0, upto): returns the key prefix chosen so far
-// (in the high bits of `prefix`) and how many victims remain to be found inside it.
-// Every thread of the block gets the same answer.
-__device__ __forceinline__ void sel_replay(const TrimPlan &tp, int upto, uint32_t m, uint32_t &prefix,
-                                           uint32_t &remaining, uint32_t *lds_pick, uint32_t *lds_scan)
+// Replays the select's decisions on its first `upto` digits (2 or 3): the key prefix chosen (in the high bits),
+// how many of the m victims share the first digit (in_coarse) and how many the whole prefix (remaining).
+// tau mostly has the present iteration's first digit, so that row of `fine` is asked for along with `coarse`.
+__device__ __forceinline__ void sel_replay(const TrimPlan &tp, int upto, uint32_t m, uint32_t &prefix, uint32_t &in_coarse, uint32_t &remaining,
+                                           uint32_t *lds_pick, uint32_t *lds_scan)
 {
-    prefix = 0; remaining = m;
-    for (int p = 0; p < upto; ++p) {
-        const int width = sel_width(tp, p), bins = 1 << width;
-        uint32_t local[SEL_BINS / TRIM_THREADS];
-        uint32_t s = 0;
-#pragma unroll
-        for (int q = 0; q < SEL_BINS / TRIM_THREADS; ++q) {
-            const int b = threadIdx.x * (SEL_BINS / TRIM_THREADS) + q;
-            local[q] = b < bins ? tp.hist[p * SEL_BINS + b] : 0u;
-            s += local[q];
-        }
-        uint32_t tot;
-        uint32_t run = block_excl_scan<TRIM_WAVES>(s, lds_scan, tot);
-        __syncthreads();
-#pragma unroll
-        for (int q = 0; q < SEL_BINS / TRIM_THREADS; ++q) {
-            const int b = threadIdx.x * (SEL_BINS / TRIM_THREADS) + q;
-            // the digit whose cumulative count first reaches `remaining`
-            if (local[q] && run < remaining && remaining <= run + local[q]) { lds_pick[0] = (uint32_t)b; lds_pick[1] = run; }
-            run += local[q];
-        }
-        __syncthreads();
-        const uint32_t digit = lds_pick[0], below = lds_pick[1];
-        __syncthreads();
-        prefix |= digit << sel_shift(tp, p);
-        remaining -= below;
-    }
+    uint32_t c[SEL_PER], f[SEL_PER];
+    const uint32_t guess = kept_bin(tp, tp.t_now) >> SEL_BITS;
+    sel_load(tp.coarse, c);
+    sel_load(tp.fine + (size_t)guess * SEL_BINS, f);
+    remaining = m;
+    const uint32_t d0 = sel_pick(c, remaining, lds_pick, lds_scan);
+    in_coarse = remaining;
+    if (d0 != guess) sel_load(tp.fine + (size_t)d0 * SEL_BINS, f);
+    const uint32_t d1 = sel_pick(f, remaining, lds_pick, lds_scan);
+    prefix = (d0 << SEL_BITS | d1) << (tp.key_bits - KEPT_BITS);
+    if (upto < 3) return;
+    sel_load(tp.hist, c);
+    prefix |= sel_pick(c, remaining, lds_pick, lds_scan);
 }
 
 // LDS of one select stage (a workgroup of TRIM_THREADS threads).
@@ -242,65 +261,71 @@ __device__ __forceinline__ bool run_carried(const SortStage &a, const SortStage 
     return false;
 }
 
-// One histogram pass of the select over the rows whose key matches the prefix chosen so far.
-// Runs in `nblocks` workgroups of TRIM_THREADS threads; `vblock` is this one's index.
-// `beside_fill` (the pass runs beside the lookup's fetches): slots that were free when the lookup
-// began are skipped - they are being filled right now - and the rows fetched into them, which
-// all carry the policy key (freq 1, last_use t_now), are counted from their number `new_rows`.
-// `always`: counts even if nothing has to be evicted (the first pass's histogram is kept from
-// here on, see h0_shift).
-__device__ __forceinline__ void trim_hist_body(const CacheView &cv, const TrimPlan &tp, int pass, uint32_t vblock, uint32_t nblocks, TrimLds &l,
-                                               bool beside_fill = false, uint32_t new_rows = 0, uint32_t t_now = 0, bool always = false)
+// The third digit's histogram, over the rows whose first two are tau's.  Runs in `nblocks` workgroups of
+// TRIM_THREADS threads; `vblock` is this one's index.
+// It runs beside the lookup's fetches: slots that were free when the lookup began are skipped (they are being
+// filled right now), and the rows fetched into them, which all carry the policy key t_now, are counted from
+// their number.
+__device__ __forceinline__ void trim_hist_body(const CacheView &cv, const TrimPlan &tp, uint32_t vblock, uint32_t nblocks, TrimLds &l)
 {
     const int32_t over = cv.ds->size - (int32_t)cv.capacity;
-    if (over <= 0 && !always) return;
-    uint32_t prefix, remaining;
-    sel_replay(tp, pass, (uint32_t)over, prefix, remaining, l.pick, l.scan);
+    if (over <= 0) return;
+    const uint32_t new_rows = (uint32_t)cv.last->miss;
+    uint32_t prefix, in_coarse, remaining;
+    sel_replay(tp, 2, (uint32_t)over, prefix, in_coarse, remaining, l.pick, l.scan);
     for (int b = threadIdx.x; b < SEL_BINS; b += TRIM_THREADS) l.bins[b] = 0;
     __syncthreads();
-    const int shift = sel_shift(tp, pass), width = sel_width(tp, pass);
-    const int decided = shift + width;                 // bits above are fixed by the prefix
-    if (beside_fill && vblock == 0 && threadIdx.x == 0 && new_rows) {
-        if (decided >= 32 || (t_now >> decided) == (prefix >> decided))
-            atomicAdd(&tp.hist[pass * SEL_BINS + ((t_now >> shift) & ((1u << width) - 1u))], new_rows);
-    }
+    const int width = tp.key_bits - KEPT_BITS;         // 1 to 10 bits
+    const uint32_t mask = (1u << width) - 1u;
+    if (vblock == 0 && threadIdx.x == 0 && new_rows && (tp.t_now >> width) == (prefix >> width)) atomicAdd(&tp.hist[tp.t_now & mask], new_rows);
     for (uint32_t slot = vblock * TRIM_THREADS + threadIdx.x; slot < cv.n_slots; slot += nblocks * TRIM_THREADS) {
-        const uint32_t sk = cv.slot_key[slot];
+        const bool skip = cv.was_free[slot] != 0;
         const uint4 m = load_meta(cv.meta, slot);
-        const bool skip = beside_fill ? cv.was_free[slot] != 0 : sk == KEY_NONE;
-        if (skip || !evictable(tp, m)) continue;
-        const uint32_t k = policy_key(m);
-        if (decided < 32 && (k >> decided) != (prefix >> decided)) continue;
-        atomicAdd(&l.bins[(k >> shift) & ((1u << width) - 1u)], 1u);
+        if (skip || !evictable(tp, m) || (policy_key(m) >> width) != (prefix >> width)) continue;
+        atomicAdd(&l.bins[policy_key(m) & mask], 1u);
     }
     __syncthreads();
     for (int b = threadIdx.x; b < SEL_BINS; b += TRIM_THREADS)
-        if (l.bins[b]) atomicAdd(&tp.hist[pass * SEL_BINS + b], l.bins[b]);
+        if (l.bins[b]) atomicAdd(&tp.hist[b], l.bins[b]);
 }
 
-// The first pass's histogram (policy keys of all evictable rows by their top digit) need not be
-// counted anew for every trim: a Read changes the keys of the rows it finds and adds the rows it
-// fetches, a trim removes its victims, nothing else touches policy keys.  So the probe moves the
-// rows it touches from their old bin to their new one, and the eviction takes its victims out
-// (h0_remove_victims); the select of the next trim starts at its second pass (up to iteration 2047
-// there is none: the first digit is the whole key).  The digit's place depends on the width of the
-// iteration count: when it moves, the histogram is counted afresh.
-__device__ __forceinline__ uint32_t h0_bin(const TrimPlan &tp, uint32_t key)
-{
-    return (key >> sel_shift(tp, 0)) & ((1u << sel_width(tp, 0)) - 1u);
-}
-
-// All rows in bins below the threshold's first digit were evicted, and of that digit's bin as
-// many as the select still had to find there.  One workgroup of TRIM_THREADS threads.
-__device__ __forceinline__ void h0_remove_victims(const CacheView &cv, const TrimPlan &tp, uint32_t *lds_pick, uint32_t *lds_scan)
+// All rows in bins below tau's were evicted, and of that bin as many as the select still had to find there.  One
+// workgroup of TRIM_THREADS threads, after every other reader of the kept histograms.
+__device__ __forceinline__ void kept_remove_victims(const CacheView &cv, const TrimPlan &tp, uint32_t *lds_pick, uint32_t *lds_scan)
 {
     const int32_t over = cv.ds->over;
     if (over <= 0) return;
-    uint32_t prefix, remaining;
-    sel_replay(tp, 1, (uint32_t)over, prefix, remaining, lds_pick, lds_scan);       // (ends with a barrier: every thread has read its bins)
-    const uint32_t d0 = h0_bin(tp, prefix);
-    for (uint32_t b = threadIdx.x; b < d0; b += TRIM_THREADS) tp.hist[b] = 0;
-    if (threadIdx.x == 0) tp.hist[d0] -= remaining;
+    uint32_t prefix, in_coarse, remaining;
+    sel_replay(tp, 2, (uint32_t)over, prefix, in_coarse, remaining, lds_pick, lds_scan);       // (ends with a barrier: every thread has read its bins)
+    const uint32_t bin = kept_bin(tp, prefix), d0 = bin >> SEL_BITS, d1 = bin & (SEL_BINS - 1);
+    for (uint32_t b0 = 0; b0 < d0; b0 += TRIM_THREADS) {
+        const uint32_t b = b0 + threadIdx.x;
+        const uint32_t rows = b < d0 ? tp.coarse[b] : 0u;
+        if (rows) tp.coarse[b] = 0;
+        for (uint64_t m = __ballot(rows != 0); m; m &= m - 1) {           // (few: the rows of a first digit are evicted together once)
+            uint4 *f = reinterpret_cast<uint4 *>(tp.fine + (size_t)(b - lane_id() + (uint32_t)__builtin_ctzll(m)) * SEL_BINS);
+            for (uint32_t i = lane_id(); i < SEL_BINS / 4; i += WAVE) f[i] = make_uint4(0, 0, 0, 0);
+        }
+    }
+    for (uint32_t b = threadIdx.x; b < d1; b += TRIM_THREADS) tp.fine[(size_t)d0 * SEL_BINS + b] = 0;
+    if (threadIdx.x == 0) { tp.fine[bin] -= remaining; tp.coarse[d0] -= in_coarse; }
+}
+
+// The kept histograms from nothing, for the rows cached before a Read (its probe moves on from there).
+__global__ __launch_bounds__(TRIM_THREADS) void kept_recount_kernel(CacheView cv, TrimPlan tp)
+{
+    for (uint32_t slot = blockIdx.x * TRIM_THREADS + threadIdx.x; slot < cv.n_slots; slot += gridDim.x * TRIM_THREADS) {
+        const uint4 m = load_meta(cv.meta, slot);
+        if (cv.slot_key[slot] == KEY_NONE || !evictable(tp, m)) continue;
+        const uint32_t bin = kept_bin(tp, policy_key(m));
+        atomicAdd(&tp.fine[bin], 1u);
+        atomicAdd(&tp.coarse[bin >> SEL_BITS], 1u);
+    }
+}
+
+__global__ __launch_bounds__(256) void clear_words_kernel(uint32_t *p, uint32_t words)
+{
+    for (uint32_t i = blockIdx.x * 256u + threadIdx.x; i < words; i += gridDim.x * 256u) p[i] = 0;
 }
 
 // Sums eight values per thread over the block at once (every thread gets all sums).
@@ -352,16 +377,32 @@ __device__ __forceinline__ void load_slots(const CacheView &cv, uint32_t slot0, 
     }
 }
 
-__device__ __forceinline__ void trim_count_body(const CacheView &cv, const TrimPlan &tp, uint32_t vblock, TrimLds &l)
+// beside_fill: the count runs beside the lookup's fetches (the host allows it where no row of the batch but a
+// fetched one can be a victim: see count_beside_fill).  Slots that were free when the lookup began are being filled
+// right now; those up to the last one taken hold the fetched rows, whose policy key is t_now and which hold no
+// updates yet (the eviction knows if they do by then).
+__device__ __forceinline__ void trim_count_body(const CacheView &cv, const TrimPlan &tp, uint32_t vblock, TrimLds &l, bool beside_fill = false)
 {
     const int32_t over = cv.ds->size - (int32_t)cv.capacity;
-    if (vblock == 0 && threadIdx.x == 0) cv.ds->over = over;
+    if (vblock == 0 && threadIdx.x == 0) { cv.ds->over = over; cv.ds->cut_slot = -1; }
     if (over <= 0) return;
     uint32_t key[COUNT_ITEMS];
     uint4 meta[COUNT_ITEMS];
-    load_slots<COUNT_ITEMS>(cv, vblock * COUNT_SLOTS + threadIdx.x * COUNT_ITEMS, key, meta);      // loads first: they overlap the replay
-    uint32_t tau, take_eq;
-    sel_replay(tp, tp.passes, (uint32_t)over, tau, take_eq, l.pick, l.scan);
+    const uint32_t slot0 = vblock * COUNT_SLOTS + threadIdx.x * COUNT_ITEMS;
+    load_slots<COUNT_ITEMS>(cv, slot0, key, meta);      // loads first: they overlap the replay
+    uint32_t last_new = 0, misses = 0;
+    bool any_new = false;
+    if (beside_fill) {
+        misses = (uint32_t)cv.last->miss;
+        any_new = misses != 0;
+        last_new = any_new ? cv.free_list[misses - 1] : 0u;
+#pragma unroll
+        for (int i = 0; i < COUNT_ITEMS; ++i)
+            if (slot0 + i < cv.n_slots && cv.was_free[slot0 + i]) key[i] = KEY_NONE;
+    }
+    uint32_t tau, in_coarse, take_eq;
+    sel_replay(tp, tp.passes, (uint32_t)over, tau, in_coarse, take_eq, l.pick, l.scan);
+    const bool new_tied = beside_fill && any_new && tau == tp.t_now;
     uint32_t lt = 0, eq = 0, dlt = 0, deq = 0;
 #pragma unroll
     for (int i = 0; i < COUNT_ITEMS; ++i) {
@@ -370,6 +411,7 @@ __device__ __forceinline__ void trim_count_body(const CacheView &cv, const TrimP
         const bool dirty = meta[i].y > meta[i].x || (tp.dirty_stamp && meta[i].z == tp.dirty_stamp);
         if (cached && pk < tau) { lt += 1; dlt += dirty; }
         else if (cached && pk == tau) { eq += 1; deq += dirty; }
+        else if (new_tied && key[i] == KEY_NONE && slot0 + i <= last_new) eq += 1;      // (a free slot up to the last one taken)
     }
     // counts of an eviction block stay below 2^16: two to a word
     const uint32_t a = wave_sum(lt | (eq << 16));
@@ -384,22 +426,17 @@ __device__ __forceinline__ void trim_count_body(const CacheView &cv, const TrimP
         if (c.z) atomicAdd(&sup[2], c.z);
         if (c.w) atomicAdd(&sup[3], c.w);
     }
-    if (vblock == 0 && threadIdx.x == 0) { cv.ds->sel_tau = tau; cv.ds->sel_take = take_eq; }
+    if (vblock == 0 && threadIdx.x == 0) {
+        cv.ds->sel_tau = tau; cv.ds->sel_take = take_eq;
+        if (new_tied && take_eq) cv.ds->cut_slot = (int32_t)cv.free_list[min(take_eq, misses) - 1];     // (only fetched rows are tied: they took the first free slots in order)
+    }
 }
 
-// Stage `stage` of the select: the histogram passes first, then the count.  Kernels that have
-// nothing to do with the trim (the optimizer step) carry a stage in extra workgroups, because
-// at minibatch size a kernel boundary costs more than the stage's work.
-__device__ __forceinline__ void trim_stage_body(const CacheView &cv, const TrimPlan &tp, int stage, uint32_t vblock, uint32_t nblocks, TrimLds &l)
-{
-    if (stage < tp.passes) trim_hist_body(cv, tp, stage, vblock, nblocks, l);
-    else trim_count_body(cv, tp, vblock, l);
-}
-
-__global__ __launch_bounds__(TRIM_THREADS) void trim_stage_kernel(CacheView cv, TrimPlan tp, int stage)
+// The count where no kernel carries it.
+__global__ __launch_bounds__(TRIM_THREADS) void trim_stage_kernel(CacheView cv, TrimPlan tp)
 {
     __shared__ TrimLds l;
-    trim_stage_body(cv, tp, stage, blockIdx.x, gridDim.x, l);
+    trim_count_body(cv, tp, blockIdx.x, l);
 }
 
 // Lists the free slots of one 1024-slot tile in ascending order behind those of the earlier
@@ -443,7 +480,7 @@ __device__ __forceinline__ void check_order_body(const CacheView &cv, const Work
 template <bool LOOKUP, bool RIDE>
 __global__ __launch_bounds__(PT_THREADS) __attribute__((amdgpu_num_sgpr(96))) void probe_kernel(CacheView cv, Workspace ws, uint32_t n, uint32_t t_now, uint32_t ptiles,
                                                            const uint32_t *tile_free, uint32_t *tile_free_idle, uint32_t ev_idle,
-                                                           uint32_t *zero_from, uint32_t zero_words, TrimPlan tp,
+                                                           TrimPlan tp,
                                                            const int64_t *__restrict__ check_ids, int pf_idle,
                                                            uint32_t *__restrict__ inv, SortStage ride, SortStage ride2)
 {
@@ -457,7 +494,9 @@ __global__ __launch_bounds__(PT_THREADS) __attribute__((amdgpu_num_sgpr(96))) vo
             return;
         }
     }
-    __shared__ uint32_t h0_delta[LOOKUP ? SEL_BINS : 1];       // rows entering (+) and leaving (-) each bin of the kept histogram
+    // rows entering (+) and leaving (-) the kept bins: by how many bins they lie before the present one, and by the
+    // first digit the same way (the present one and the one before: what lies further back goes to memory at once)
+    __shared__ uint32_t kept_delta[LOOKUP ? SEL_BINS : 1], coarse_delta[2];
     const uint32_t check_blocks = LOOKUP && check_ids ? ptiles : 0u;
     if (blockIdx.x >= ptiles && blockIdx.x < ptiles + check_blocks) {
         // An order that was sorted ahead of this call (an announced batch) is checked against the ids
@@ -467,9 +506,9 @@ __global__ __launch_bounds__(PT_THREADS) __attribute__((amdgpu_num_sgpr(96))) vo
         return;
     }
     if (blockIdx.x >= ptiles) {          // extra workgroups of a lookup: the free list for the fill kernel
-        // ... and clean select histograms for the trim that follows this lookup
+        // ... and clean counts for the trim that follows this lookup
         const uint32_t first = ptiles + check_blocks;
-        for (uint32_t i = (blockIdx.x - first) * PT_THREADS + threadIdx.x; i < zero_words; i += (own_blocks - first) * PT_THREADS) zero_from[i] = 0;
+        for (uint32_t i = (blockIdx.x - first) * PT_THREADS + threadIdx.x; i < tp.zero_words; i += (own_blocks - first) * PT_THREADS) tp.zero_from[i] = 0;
         free_list_body(cv, tile_free, tile_free_idle, ev_idle, blockIdx.x - first, lds);
         return;
     }
@@ -478,9 +517,10 @@ __global__ __launch_bounds__(PT_THREADS) __attribute__((amdgpu_num_sgpr(96))) vo
     const uint32_t j = tile * PT_TILE + threadIdx.x;
     DState *ds = cv.ds;
     if (LOOKUP && inv && j < n) inv[ws.perm[j]] = j;         // pooled lookup: the sorted position of every original position
-    const bool keep_h0 = LOOKUP && tp.h0_kept;
-    if (keep_h0) {
-        for (int b = threadIdx.x; b < SEL_BINS; b += PT_THREADS) h0_delta[b] = 0;
+    const uint32_t bin_now = LOOKUP ? kept_bin(tp, t_now) : 0u;
+    if (LOOKUP) {
+        for (int b = threadIdx.x; b < SEL_BINS; b += PT_THREADS) kept_delta[b] = 0;
+        if (threadIdx.x < 2) coarse_delta[threadIdx.x] = 0;
         __syncthreads();
     }
 
@@ -495,7 +535,7 @@ __global__ __launch_bounds__(PT_THREADS) __attribute__((amdgpu_num_sgpr(96))) vo
     // Find runs once per key, not once per position: by the head of every run of equal keys, and by
     // each wave's first lane (its run may have begun in the wave before); the other positions of a
     // run take where their row comes from from the nearest such lane below them.
-    bool head = false, miss = false, stale = false, hit = false, absent = false, bad = false, finder = false;
+    bool head = false, miss = false, stale = false, hit = false, absent = false, bad = false, finder = false, moved = false;
     int32_t my_src = SRC_ZERO;
     if (j < n) {
         const uint32_t key = ws.skey[j];
@@ -531,10 +571,13 @@ __global__ __launch_bounds__(PT_THREADS) __attribute__((amdgpu_num_sgpr(96))) vo
                             hit = valid; stale = !valid;
                             const bool upkeep = !(cv.freq_cap && m.w >= cv.freq_cap);        // (light-weight LFU: frequent enough, left alone)
                             if (upkeep) store_meta(cv.meta, (uint32_t)slot, m.x, m.y, t_now, m.w + 1);   // one use per key per Read
-                            if (keep_h0 && upkeep && evictable(tp, m)) {
-                                const uint32_t b_old = h0_bin(tp, policy_key(m)), b_new = h0_bin(tp, t_now);
-                                if (tp.lfu) atomicSub(&h0_delta[b_old], 1u);                  // used twice now: out of reach
-                                else if (b_old != b_new) { atomicSub(&h0_delta[b_old], 1u); atomicAdd(&h0_delta[b_new], 1u); }
+                            if (upkeep && evictable(tp, m)) {
+                                const uint32_t bin_old = kept_bin(tp, policy_key(m)), back = bin_now - bin_old;
+                                if (tp.lfu || back) {                    // (LFU: used twice now, out of reach)
+                                    moved = !tp.lfu;
+                                    if (back < (uint32_t)SEL_BINS) atomicSub(&kept_delta[back], 1u);
+                                    else { atomicSub(&tp.fine[bin_old], 1u); atomicSub(&tp.coarse[bin_old >> SEL_BITS], 1u); }
+                                }
                             }
                         }
                         ws.cls[j] = (uint8_t)(miss ? CLS_MISS : (stale ? CLS_STALE : CLS_HIT));
@@ -554,6 +597,8 @@ __global__ __launch_bounds__(PT_THREADS) __attribute__((amdgpu_num_sgpr(96))) vo
 
     if (__any(bad) && lane_id() == 0) atomicOr(&ds->err, ERRBIT_RANGE);
     if (LOOKUP) {
+        const uint64_t mv = __ballot(moved);
+        if (mv && lane_id() == 0) atomicAdd(&kept_delta[0], (uint32_t)__popcll(mv));
         // stage this tile's missed and stale keys, in key order, for the fill kernel
         // (a tile has 1024 positions: two counts to a word, one pass of barriers for each pair)
         uint32_t tot_ms;
@@ -571,13 +616,18 @@ __global__ __launch_bounds__(PT_THREADS) __attribute__((amdgpu_num_sgpr(96))) vo
             count2(&cv.last->miss, &ds->total.miss, tot_miss);
             count2(&cv.last->unique, &ds->total.unique, tot_heads);
             if (tot_miss) atomicAdd(&ds->size, (int32_t)tot_miss);
-            if (keep_h0 && tot_miss) atomicAdd(&h0_delta[h0_bin(tp, t_now)], tot_miss);   // the rows being fetched
+            if (tot_miss) atomicAdd(&kept_delta[0], tot_miss);            // the rows being fetched
         }
-        if (keep_h0) {
-            __syncthreads();
-            for (int b = threadIdx.x; b < SEL_BINS; b += PT_THREADS)
-                if (h0_delta[b]) atomicAdd(&tp.hist[b], h0_delta[b]);          // (differences, modulo 2^32)
+        __syncthreads();
+        for (uint32_t b = threadIdx.x; b < (uint32_t)SEL_BINS; b += PT_THREADS) {
+            const uint32_t d = kept_delta[b];
+            if (d) {                                                      // (differences, modulo 2^32)
+                atomicAdd(&tp.fine[bin_now - b], d);
+                atomicAdd(&coarse_delta[(bin_now >> SEL_BITS) - ((bin_now - b) >> SEL_BITS)], d);
+            }
         }
+        __syncthreads();
+        if (threadIdx.x < 2 && coarse_delta[threadIdx.x]) atomicAdd(&tp.coarse[(bin_now >> SEL_BITS) - threadIdx.x], coarse_delta[threadIdx.x]);
     } else {
         if (__any(absent) && lane_id() == 0) atomicOr(&ds->err, ERRBIT_STATE);
         const uint32_t tot_heads = block_sum<PT_WAVES>(head ? 1u : 0u, lds);
@@ -1010,7 +1060,7 @@ template <int VEC, bool POOLED, int RIDE, bool TRACE>
 __global__ __launch_bounds__(256) void fill_gather_kernel(CacheView cv, Workspace ws, uint32_t n, uint32_t t_now, uint32_t ptiles, uint32_t fill_blocks,
                                                           TrimPlan tp, uint32_t hist_blocks, float *__restrict__ out, const int64_t *__restrict__ offsets, uint32_t n_bags,
                                                           const uint32_t *__restrict__ inv, SortStage ride, SortStage ride2,
-                                                          uint32_t push_blocks, int push_buf, uint32_t push_seq, int hist_pass, Ahead ah,
+                                                          uint32_t push_blocks, int push_buf, uint32_t push_seq, Ahead ah,
                                                           KernelTrace tr_arg, int fetch_mode)
 {
     using V = typename VecT<VEC>::type;
@@ -1147,12 +1197,10 @@ __global__ __launch_bounds__(256) void fill_gather_kernel(CacheView cv, Workspac
     }
     bid -= ins_blocks; nblk -= ins_blocks;
     if (bid < fill_blocks + hist_blocks) {
-        // a pass of the coming trim's select (the first, or the second if the first pass's histogram
-        // is kept), over the rows cached before this lookup plus the rows being fetched right now
-        // (counted, not read)
-        TrimLds &tl = lds_as<TrimLds>();
-        const uint32_t new_rows = block_sum_array<TRIM_WAVES>(ws.tile_miss, ptiles, tl.scan);
-        trim_hist_body(cv, tp, hist_pass, bid - fill_blocks, hist_blocks, tl, true, new_rows, t_now, hist_pass == 0);
+        // the coming trim's select, over the rows cached before this lookup plus the rows being fetched right now
+        // (known by their number and slots, not read): the count or, where there is a third digit, its histogram
+        if (tp.passes == 2) trim_count_body(cv, tp, bid - fill_blocks, lds_as<TrimLds>(), true);
+        else trim_hist_body(cv, tp, bid - fill_blocks, hist_blocks, lds_as<TrimLds>());
         tr.role(4); tr.end();
         return;
     }
@@ -1228,10 +1276,11 @@ __device__ __forceinline__ float rowwise_rcp(const CacheView &cv, uint32_t slot,
 }
 
 // `from_key` other than KEY_NONE: the row has not been fetched yet (see apply_kernel, "fresh"): it is
-// read from the global table at that key and written to the slot (EARLY: and to the global table).
+// read from the global table at that key and written to the slot (EARLY: and to the global table), or, if
+// the trim that follows drops it (gone), to the global table alone.
 template <int VEC, bool EARLY = false>
 __device__ __forceinline__ void apply_step(const CacheView &cv, uint32_t slot, int c, const double *g64, float lr, float eps, bool act = true,
-                                           uint32_t from_key = KEY_NONE)
+                                           uint32_t from_key = KEY_NONE, bool gone = false)
 {
     using V = typename VecT<VEC>::type;
     float G[VEC];
@@ -1253,14 +1302,255 @@ __device__ __forceinline__ void apply_step(const CacheView &cv, uint32_t slot, i
         float *a = reinterpret_cast<float *>(&av);
 #pragma unroll
         for (int k = 0; k < VEC; ++k) { a[k] += G[k] * G[k]; x[k] -= lr * G[k] * fast_rcp(fast_sqrt(a[k]) + eps); }
-        *ap = av;
-        if (EARLY && fresh) reinterpret_cast<V *>(cv.A + (size_t)from_key * cv.geom.dim)[c] = av;
+        if (!gone) *ap = av;
+        if (gone || (EARLY && fresh)) reinterpret_cast<V *>(cv.A + (size_t)from_key * cv.geom.dim)[c] = av;
     } else {
 #pragma unroll
         for (int k = 0; k < VEC; ++k) x[k] -= lr * G[k];
     }
-    *xp = xv;
-    if (EARLY && fresh) reinterpret_cast<V *>(cv.W + (size_t)from_key * cv.geom.dim)[c] = xv;     // early push
+    if (!gone) *xp = xv;
+    if (gone || (EARLY && fresh)) reinterpret_cast<V *>(cv.W + (size_t)from_key * cv.geom.dim)[c] = xv;     // the push
+}
+
+// Drops the victims among 1024 consecutive slots, four per thread: erase the key, free the slot,
+// raise c_g; then one row group per victim that holds updates copies its row (and accumulator)
+// to the global table: Evict's push (Section 3.1).  Where a victim goes in the evicted-id list
+// and (host-backed table) in the staging buffer follows from the select's per-block counts, so
+// the kernel has no counter that every workgroup would have to add to: at a few nanoseconds
+// per addition to one address, thousands of workgroups made those additions the kernel's
+// duration.  The workgroup that holds the last victim among the rows tied at the threshold
+// writes the call's counters.
+struct EvictLds {
+    uint32_t scan[TRIM_WAVES * 8 + 8];
+    uint32_t v_slot[EV_SLOTS], v_key[EV_SLOTS], v_cg[EV_SLOTS], v_at[EV_SLOTS];
+    uint32_t n_push;
+};
+// MANY: several workers over the table (the push adds what this worker changed to the server's row:
+// three more rows in flight per victim, which the one-worker kernel does not pay registers for).
+// BESIDE: runs beside the update of the batch whose lookup left the overflow (see evict_beside in the host code).
+// No row of the batch is a victim but fetched ones tied at tau; those the update itself writes to the global
+// table (DState::cut_slot), and their clock will be the one they were fetched at plus one.  No other row's clock moves.
+// With a kernel less, and rows fetched and dropped by one step written once: 106496 ids 68.9 -> 60.4 us a step, 114688
+// ids of 128 floats 99.8 -> 92.7, 409600 ids in bags, 256 floats, 296 -> 251.
+// Runs in nblk_ workgroups of TRIM_THREADS threads; `blk` is this one's index.
+template <int VEC, bool MANY, bool BESIDE>
+__device__ __forceinline__ void evict_body(const CacheView &cv, const TrimPlan &tp, uint32_t blk, uint32_t nblk_)
+{
+    EvictLds &el = lds_as<EvictLds>();
+    uint32_t *scan = el.scan, *v_slot = el.v_slot, *v_key = el.v_key, *v_cg = el.v_cg, *v_at = el.v_at;
+    if (blk + 1 == nblk_) { kept_remove_victims(cv, tp, v_slot, scan); return; }
+    DState *ds = cv.ds;
+    const uint32_t slot0 = blk * EV_SLOTS + threadIdx.x * EV_ITEMS;
+    // everything this thread may need, requested at once
+    const int32_t over = ds->over;                     // snapshot taken by the select
+    const uint32_t tau = ds->sel_tau;
+    const uint32_t take_eq = ds->sel_take;
+    uint32_t key[EV_ITEMS];
+    uint4 meta[EV_ITEMS];
+    load_slots<EV_ITEMS>(cv, slot0, key, meta);
+    // counts over the blocks before this one (whole supers, then the blocks of this super), and over all blocks
+    // (rows counted as they were fetched, and updated since: all the tied ones, if tau is their policy key)
+    const bool tied_dirty = tp.fetched_dirty && tau == tp.t_now;
+    uint32_t c8[8] = {0, 0, 0, 0, 0, 0, 0, 0};         // before: lt, eq, dirty lt, dirty eq;  all: dirty lt
+    {
+        const uint32_t nblocks = (cv.n_slots + EV_SLOTS - 1) / EV_SLOTS, nsup = (nblocks + EV_SUPER - 1) / EV_SUPER;
+        const uint32_t sup = blk / EV_SUPER;
+        for (uint32_t i = threadIdx.x; i < nsup; i += TRIM_THREADS) {
+            const uint4 v = tp.sup_cnt[i];
+            c8[4] += v.z;
+            if (i < sup) { c8[0] += v.x; c8[1] += v.y; c8[2] += v.z; c8[3] += tied_dirty ? v.y : v.w; }
+        }
+        const uint32_t b = sup * EV_SUPER + threadIdx.x;
+        if (threadIdx.x < EV_SUPER && b < blk) {
+            const uint4 v = tp.blk_cnt[b];
+            c8[0] += v.x; c8[1] += v.y; c8[2] += v.z; c8[3] += tied_dirty ? v.y : v.w;
+        }
+    }
+    block_sum8(c8, scan);
+    const uint32_t lt_before = c8[0], eq_before = c8[1], dlt_before = c8[2], deq_before = c8[3], dlt_total = c8[4];
+    if (threadIdx.x == 0) el.n_push = 0;
+
+    // this thread's four slots: below tau / tied with tau, in slot order
+    bool lt[EV_ITEMS], eq[EV_ITEMS];
+    uint32_t n_lt = 0, n_eq = 0, n_free = 0;
+#pragma unroll
+    for (int i = 0; i < EV_ITEMS; ++i) {
+        const bool cached = key[i] != KEY_NONE && over > 0 && evictable(tp, meta[i]);
+        const uint32_t pk = policy_key(meta[i]);
+        lt[i] = cached && pk < tau; eq[i] = cached && pk == tau;
+        n_lt += lt[i]; n_eq += eq[i];
+        n_free += (slot0 + i < cv.n_slots && key[i] == KEY_NONE) ? 1u : 0u;
+    }
+    uint32_t tot1;
+    const uint32_t ex1 = block_excl_scan<TRIM_WAVES>(n_lt | (n_eq << 16), scan, tot1);
+    uint32_t eq_rank = eq_before + (ex1 >> 16);        // rank of the thread's first tied row among all tied rows
+    const uint32_t eq_here = tot1 >> 16;
+    bool victim[EV_ITEMS], dirty[EV_ITEMS];
+    uint32_t eq_at[EV_ITEMS];
+    uint32_t n_vic = 0, n_dlt = 0, n_deq_vic = 0;
+#pragma unroll
+    for (int i = 0; i < EV_ITEMS; ++i) {
+        eq_at[i] = eq_rank;
+        victim[i] = lt[i] || (eq[i] && eq_rank < take_eq);
+        dirty[i] = victim[i] && (meta[i].y > meta[i].x || (BESIDE && meta[i].z == tp.t_now));
+        eq_rank += eq[i];
+        n_vic += victim[i]; n_dlt += dirty[i] && lt[i]; n_deq_vic += dirty[i] && eq[i];
+    }
+    uint32_t tot2;
+    const uint32_t ex2 = block_excl_scan<TRIM_WAVES>(n_vic | (n_dlt << 16), scan, tot2);
+    const uint32_t nv = tot2 & 0xFFFFu;
+    // victims in earlier blocks: their rows below tau, and their tied rows up to the cut
+    uint32_t ev_at = lt_before + min(eq_before, take_eq) + (ex2 & 0xFFFFu);
+    uint32_t dlt_at = dlt_before + (ex2 >> 16);
+    const int buf = tp.ev_slot;
+#pragma unroll
+    for (int i = 0; i < EV_ITEMS; ++i) {
+        if (victim[i]) {
+        const bool by_update = BESIDE && meta[i].z == tp.t_now;
+        const uint32_t slot = slot0 + i, k = key[i], my_cc = by_update ? meta[i].x + 1u : meta[i].y;
+        tp.ev_ids[ev_at++] = k;
+        const uint32_t cg = dirty[i] ? cv.Cg[k] : 0u;
+        const uint32_t early = dirty[i] && cv.early_cc ? cv.early_cc[slot] : 0u;
+        cv.slot_of[k] = SLOT_NONE;
+        cv.slot_key[slot] = KEY_NONE;
+        // host-backed table: rows below tau that hold updates are staged in slot order, then one
+        // place per tied victim (left empty by those without updates)
+        const uint32_t stage_at = lt[i] ? dlt_at : dlt_total + eq_at[i];
+        if (dirty[i]) {
+            if (my_cc > cg) cv.Cg[k] = my_cc;                                 // c_g = max(c_g, c_c)
+            // (pushed early by the update that fetched it, not updated since, and nobody else has pushed: the row is there already)
+            const bool travelled = by_update || (early == my_cc && cg == meta[i].x);
+            if (!travelled) {
+                const uint32_t at = atomicAdd(&el.n_push, 1u);
+                v_slot[at] = slot; v_key[at] = k; v_cg[at] = my_cc > cg ? my_cc : cg; v_at[at] = stage_at;
+            }
+            dlt_at += lt[i];
+        } else if (cv.Cg_host && eq[i]) {
+            cv.hl.keys_of(buf)[stage_at] = KEY_NONE;
+        }
+        }
+    }
+    uint32_t s2[8] = {n_free, n_deq_vic, 0, 0, 0, 0, 0, 0};
+    block_sum8(s2, scan);                              // also makes the push list visible to every thread
+    const uint32_t free_here = s2[0], deq_vic_here = s2[1];
+    const uint32_t np = el.n_push;
+    const int lanes = cv.geom.lanes;
+    const int group = threadIdx.x / lanes, gl = threadIdx.x % lanes, ngroups = TRIM_THREADS / lanes;
+    const RowGeom g = cv.geom;
+    // Evict's push, PUSH_ROWS victims per row group at a time (all their loads before the first
+    // store).  Host-backed table: the rows go to the staging buffer instead; the next Read's fetch
+    // kernel (or a waiting call) sends them over the host link.
+    using V = typename VecT<VEC>::type;
+    if constexpr (BESIDE) {
+        // (table in HBM; two victims at a time: the update's kernel has no registers for four)
+        using RV = typename RawVecT<VEC>::type;
+        for (uint32_t v0 = group * 2; v0 < np; v0 += ngroups * 2) {
+            const uint32_t v1 = min(v0 + 1, np - 1);                 // (past the end: the last row again, the same values to the same place)
+            const size_t f0 = (size_t)v_slot[v0] * g.dim, f1 = (size_t)v_slot[v1] * g.dim, t0 = (size_t)v_key[v0] * g.dim, t1 = (size_t)v_key[v1] * g.dim;
+            for (int c = gl; c < g.chunks; c += g.lanes) {
+                const RV x0 = reinterpret_cast<const RV *>(cv.rows + f0)[c], x1 = reinterpret_cast<const RV *>(cv.rows + f1)[c];
+                if (cv.adagrad) {
+                    const RV a0 = reinterpret_cast<const RV *>(cv.acc + f0)[c], a1 = reinterpret_cast<const RV *>(cv.acc + f1)[c];
+                    reinterpret_cast<RV *>(cv.A + t0)[c] = a0; reinterpret_cast<RV *>(cv.A + t1)[c] = a1;
+                }
+                reinterpret_cast<RV *>(cv.W + t0)[c] = x0; reinterpret_cast<RV *>(cv.W + t1)[c] = x1;
+            }
+        }
+    } else {
+    constexpr int PUSH_ROWS = 4;
+    static_assert(PUSH_ROWS == 4, "the copy below is written out for four rows");
+    const bool host = cv.Cg_host != nullptr;
+    const float *src_x = cv.rows, *src_a = cv.acc;
+    float *dst_x = host ? cv.hl.rows_of(buf) : cv.W, *dst_a = host ? cv.hl.acc_of(buf) : cv.A;
+    for (uint32_t v0 = group * PUSH_ROWS; v0 < np; v0 += ngroups * PUSH_ROWS) {
+        uint32_t from[PUSH_ROWS], to[PUSH_ROWS];
+#pragma unroll
+        for (int r = 0; r < PUSH_ROWS; ++r) {
+            const uint32_t v = min(v0 + r, np - 1);
+            from[r] = v_slot[v];
+            to[r] = host ? v_at[v] : v_key[v];
+            if (host && gl == 0 && v0 + r < np) {
+                const uint32_t vk = v_key[v];
+                cv.hl.keys_of(buf)[to[r]] = vk;
+                cv.hl.cg_of(buf)[to[r]] = v_cg[v];
+                cv.hl.pend[vk] = ((uint64_t)tp.push_seq << 32) | (uint64_t)to[r];
+            }
+        }
+        const bool adagrad = cv.adagrad != 0;
+        for (int c = gl; c < g.chunks; c += g.lanes) {
+            V x0, x1, x2, x3, a0{}, a1{}, a2{}, a3{};
+            x0 = reinterpret_cast<const V *>(src_x + (size_t)from[0] * g.dim)[c];
+            x1 = reinterpret_cast<const V *>(src_x + (size_t)from[1] * g.dim)[c];
+            x2 = reinterpret_cast<const V *>(src_x + (size_t)from[2] * g.dim)[c];
+            x3 = reinterpret_cast<const V *>(src_x + (size_t)from[3] * g.dim)[c];
+            if (adagrad) {
+                a0 = reinterpret_cast<const V *>(src_a + (size_t)from[0] * g.dim)[c];
+                a1 = reinterpret_cast<const V *>(src_a + (size_t)from[1] * g.dim)[c];
+                a2 = reinterpret_cast<const V *>(src_a + (size_t)from[2] * g.dim)[c];
+                a3 = reinterpret_cast<const V *>(src_a + (size_t)from[3] * g.dim)[c];
+            }
+            if (MANY) {
+                // several workers: the server adds what this worker accumulated since its Fetch
+                // (rows past the end repeat the last one: only the first of the repeats adds)
+                const bool r1 = v0 + 1 < np, r2 = v0 + 2 < np, r3 = v0 + 3 < np;
+                const V w0 = reinterpret_cast<const V *>(dst_x + (size_t)to[0] * g.dim)[c], b0 = reinterpret_cast<const V *>(cv.rows0 + (size_t)from[0] * g.dim)[c];
+                const V w1 = reinterpret_cast<const V *>(dst_x + (size_t)to[1] * g.dim)[c], b1 = reinterpret_cast<const V *>(cv.rows0 + (size_t)from[1] * g.dim)[c];
+                const V w2 = reinterpret_cast<const V *>(dst_x + (size_t)to[2] * g.dim)[c], b2 = reinterpret_cast<const V *>(cv.rows0 + (size_t)from[2] * g.dim)[c];
+                const V w3 = reinterpret_cast<const V *>(dst_x + (size_t)to[3] * g.dim)[c], b3 = reinterpret_cast<const V *>(cv.rows0 + (size_t)from[3] * g.dim)[c];
+                x0 = delta_add(w0, x0, b0);
+                x1 = r1 ? delta_add(w1, x1, b1) : x0; x2 = r2 ? delta_add(w2, x2, b2) : x1; x3 = r3 ? delta_add(w3, x3, b3) : x2;
+                if (adagrad) {
+                    const V u0 = reinterpret_cast<const V *>(dst_a + (size_t)to[0] * g.dim)[c], d0 = reinterpret_cast<const V *>(cv.acc0 + (size_t)from[0] * g.dim)[c];
+                    const V u1 = reinterpret_cast<const V *>(dst_a + (size_t)to[1] * g.dim)[c], d1 = reinterpret_cast<const V *>(cv.acc0 + (size_t)from[1] * g.dim)[c];
+                    const V u2 = reinterpret_cast<const V *>(dst_a + (size_t)to[2] * g.dim)[c], d2 = reinterpret_cast<const V *>(cv.acc0 + (size_t)from[2] * g.dim)[c];
+                    const V u3 = reinterpret_cast<const V *>(dst_a + (size_t)to[3] * g.dim)[c], d3 = reinterpret_cast<const V *>(cv.acc0 + (size_t)from[3] * g.dim)[c];
+                    a0 = delta_add(u0, a0, d0);
+                    a1 = r1 ? delta_add(u1, a1, d1) : a0; a2 = r2 ? delta_add(u2, a2, d2) : a1; a3 = r3 ? delta_add(u3, a3, d3) : a2;
+                }
+            }
+            // rows past the end repeat the last one: the same values to the same place
+            reinterpret_cast<V *>(dst_x + (size_t)to[0] * g.dim)[c] = x0;
+            reinterpret_cast<V *>(dst_x + (size_t)to[1] * g.dim)[c] = x1;
+            reinterpret_cast<V *>(dst_x + (size_t)to[2] * g.dim)[c] = x2;
+            reinterpret_cast<V *>(dst_x + (size_t)to[3] * g.dim)[c] = x3;
+            if (adagrad) {
+                reinterpret_cast<V *>(dst_a + (size_t)to[0] * g.dim)[c] = a0;
+                reinterpret_cast<V *>(dst_a + (size_t)to[1] * g.dim)[c] = a1;
+                reinterpret_cast<V *>(dst_a + (size_t)to[2] * g.dim)[c] = a2;
+                reinterpret_cast<V *>(dst_a + (size_t)to[3] * g.dim)[c] = a3;
+            }
+        }
+        if (cv.rowwise && gl == 0) {                 // (one accumulator per row; such a table is in HBM)
+#pragma unroll
+            for (int r = 0; r < PUSH_ROWS; ++r) cv.A[to[r]] = cv.acc[from[r]];
+        }
+    }
+    }
+    if (threadIdx.x == 0) {
+        if (free_here + nv) atomicAdd(&tp.tile_free[blk / (TRIM_TILE / EV_SLOTS)], free_here + nv);     // (zero when the trim starts; a few workgroups per tile)
+        // the call's counters: written by the block that holds the last tied victim (block 0 if there is none)
+        const bool closes = over <= 0 ? blk == 0
+                          : (take_eq == 0 ? blk == 0 : (eq_before < take_eq && take_eq <= eq_before + eq_here));
+        if (closes) {
+            const uint32_t evicted = over > 0 ? (uint32_t)over : 0u;
+            const uint32_t evicted_dirty = over > 0 ? dlt_total + deq_before + deq_vic_here : 0u;
+            ds->ev_n[buf] = evicted;
+            ds->push_n[buf] = over > 0 ? dlt_total + take_eq : 0u;
+            if (evicted) {
+                ds->size -= (int32_t)evicted;
+                cv.last->evicted = evicted; ds->total.evicted += evicted;
+                cv.last->evicted_dirty = evicted_dirty; ds->total.evicted_dirty += evicted_dirty;
+            }
+        }
+    }
+}
+
+template <int VEC, bool RIDE, bool MANY>
+__global__ __launch_bounds__(TRIM_THREADS) void trim_evict_kernel(CacheView cv, TrimPlan tp, SortStage ride, SortStage ride2)
+{
+    uint32_t bid = blockIdx.x, nblk = gridDim.x;
+    if (RIDE && run_carried(ride, ride2, bid, nblk)) return;
+    evict_body<VEC, MANY, false>(cv, tp, bid, nblk);
 }
 
 // Update + Clock (Algorithm 3) in one kernel.  A workgroup takes a tile of AP_TILE consecutive
@@ -1286,10 +1576,13 @@ __device__ __forceinline__ void apply_step(const CacheView &cv, uint32_t slot, i
 // this kernel (table in HBM, one worker): where a run's key was a miss, the row and accumulator are
 // read from the global table instead of the slot; the step's result goes to the slot as always.
 // Fetch and Update of Algorithms 2 and 3 in one read and one write of the row.
-// VERIFY: the ids must be the ones the sorted order was built from (an update that reuses the
-// preceding lookup's order); extra workgroups compare them and flag any difference.
+// MODE: AP_SORTED, the update sorted its own ids.  AP_REUSED, it reuses the preceding lookup's order: the ids must
+// be the ones that order was built from; extra workgroups compare them and flag any difference, others may count
+// the coming trim's rows.  AP_REUSED_EVICT, it also carries the eviction (a variant of its own, without the count, because
+// its arguments and registers made every other update 2 % slower).
 // MAXC: row pieces per lane (dim / VEC / lanes, rounded up).
 constexpr int AP_THREADS = 256;
+constexpr int AP_SORTED = 0, AP_REUSED = 1, AP_REUSED_EVICT = 2;
 // Gradient rows in flight per row group, and waves per SIMD the kernel is held to (rows of one piece
 // per lane).  Tiles of 64 positions: seven waves (72 registers), so that all tiles of a batch of
 // config 2's or 4's size are resident from the start, with four rows in flight (three where the
@@ -1376,13 +1669,14 @@ struct SegWork {
     uint32_t a, b;             // positions [a, b) of the window
     int32_t slot;
     uint32_t from_key;         // KEY_NONE, or the key whose row has not been fetched yet (fresh)
+    bool gone;                 // the trim that runs beside the update drops that row
     bool is_front, is_back;    // the run began in an earlier tile / goes on in a later one
 };
 
 // The optimizer step from a row already in registers.
 template <int VEC, bool EARLY = false>
 __device__ __forceinline__ void apply_loaded(const CacheView &cv, uint32_t slot, int cidx, const double *g64, float lr, float eps,
-                                             typename VecT<VEC>::type xv, typename VecT<VEC>::type av, bool act, uint32_t from_key = KEY_NONE)
+                                             typename VecT<VEC>::type xv, typename VecT<VEC>::type av, bool act, uint32_t from_key, bool gone)
 {
     using V = typename VecT<VEC>::type;
     float *x = reinterpret_cast<float *>(&xv), *a = reinterpret_cast<float *>(&av);
@@ -1399,9 +1693,11 @@ __device__ __forceinline__ void apply_loaded(const CacheView &cv, uint32_t slot,
         else if (cv.adagrad) { a[e] += G * G; x[e] -= lr * G * fast_rcp(fast_sqrt(a[e]) + eps); }
         else x[e] -= lr * G;
     }
-    reinterpret_cast<V *>(cv.rows + (size_t)slot * cv.geom.dim)[cidx] = xv;
-    if (cv.adagrad) reinterpret_cast<V *>(cv.acc + (size_t)slot * cv.geom.dim)[cidx] = av;
-    if (EARLY && from_key != KEY_NONE) {                // early push: a row fetched by this update goes to the global table as well
+    if (!gone) {
+        reinterpret_cast<V *>(cv.rows + (size_t)slot * cv.geom.dim)[cidx] = xv;
+        if (cv.adagrad) reinterpret_cast<V *>(cv.acc + (size_t)slot * cv.geom.dim)[cidx] = av;
+    }
+    if (gone || (EARLY && from_key != KEY_NONE)) {      // a row fetched by this update and dropped by the trim beside it goes to the global table; early push: any row fetched by it, too
         reinterpret_cast<V *>(cv.W + (size_t)from_key * cv.geom.dim)[cidx] = xv;
         if (cv.adagrad) reinterpret_cast<V *>(cv.A + (size_t)from_key * cv.geom.dim)[cidx] = av;
     }
@@ -1434,13 +1730,14 @@ struct ApplyBorders {
 };
 constexpr uint32_t AP_GROUP = 16;
 
-template <int VEC, int MAXC, bool VERIFY, int AP_TILE, bool EARLY>
+template <int VEC, int MAXC, int MODE, int AP_TILE, bool EARLY>
 __global__ __launch_bounds__(AP_THREADS) __attribute__((amdgpu_waves_per_eu(MAXC == 1 ? ap_waves(AP_TILE) : 1))) void apply_kernel(CacheView cv, Workspace ws, ApplyBorders bd, const int64_t *__restrict__ ids,
                                                            const float *__restrict__ grads, const uint32_t *__restrict__ grad_row,
-                                                           float lr, float eps, uint32_t n_ids, uint32_t work_blocks, TrimPlan tp, int stage,
+                                                           float lr, float eps, uint32_t n_ids, uint32_t work_blocks, TrimPlan tp, uint32_t trim_blocks,
                                                            SortStage ride, SortStage ride2, KernelTrace tr, int fresh_rows)
 {
     using V = typename VecT<VEC>::type;
+    constexpr bool VERIFY = MODE != AP_SORTED;
     constexpr int BATCH = ap_batch(AP_TILE, EARLY);
     // The tiles' workgroups live longest, so they take the first places; the carried stages, the select
     // stage and the id check follow in the places they leave (the other way round the step was 1 to 2 %
@@ -1449,13 +1746,15 @@ __global__ __launch_bounds__(AP_THREADS) __attribute__((amdgpu_waves_per_eu(MAXC
     tr.stamp(0);
     if (run_carried(ride, ride2, bid, nblk)) { tr.role(1); tr.end(); return; }
     const uint32_t verify_blocks = VERIFY ? (n_ids + VERIFY_TILE - 1) / VERIFY_TILE : 0u;
-    const uint32_t stage_blocks = nblk - work_blocks - verify_blocks;
-    if (bid < stage_blocks) {            // extra workgroups: a stage of the coming trim's select
-        trim_stage_body(cv, tp, stage, bid, stage_blocks, lds_as<TrimLds>());
-        tr.role(2); tr.end();
-        return;
+    if (MODE != AP_SORTED) {             // extra workgroups: the eviction, or the count of the coming trim's rows
+        if (bid < trim_blocks) {
+            if constexpr (MODE == AP_REUSED_EVICT) evict_body<VEC, false, true>(cv, tp, bid, trim_blocks);
+            else trim_count_body(cv, tp, bid, lds_as<TrimLds>());
+            tr.role(2); tr.end();
+            return;
+        }
+        bid -= trim_blocks;
     }
-    bid -= stage_blocks;
     if (VERIFY && bid < verify_blocks) {
         // The ids must be the ones the sorted order was built from: every position's id against the
         // sorted key, by workgroups of their own.  A difference is flagged; the update goes on.
@@ -1476,6 +1775,8 @@ __global__ __launch_bounds__(AP_THREADS) __attribute__((amdgpu_waves_per_eu(MAXC
     const uint32_t group = threadIdx.x / g.lanes, ngroups = AP_THREADS / g.lanes;
     const int gl = threadIdx.x % g.lanes;
     const uint32_t nv = cv.ds->n_valid;
+    const int32_t cut_slot = MODE == AP_REUSED_EVICT ? cv.ds->cut_slot : -1;
+    auto is_gone = [&](uint32_t from_key, int32_t slot) { return MODE == AP_REUSED_EVICT && from_key != KEY_NONE && slot <= cut_slot; };
     if (VERIFY && bid == 0 && threadIdx.x == 0) {
         // this call did not sort: its per-call counters start here, with the lookup's key count
         DState *ds = cv.ds;
@@ -1573,13 +1874,14 @@ __global__ __launch_bounds__(AP_THREADS) __attribute__((amdgpu_waves_per_eu(MAXC
         w.is_front = sg == 0 && front_open; w.is_back = sg + 1 == nseg && back_open;
         w.slot = w.is_front ? SLOT_NONE : l.slot[w.a];
         w.from_key = !w.is_front && ((l.fresh[w.a / WAVE] >> (w.a % WAVE)) & 1ull) ? l.key[w.a] : KEY_NONE;
+        w.gone = is_gone(w.from_key, w.slot);
         return w;
     };
     // what is left to do once the segment's sum for row piece cidx is there
     auto finish_piece = [&](const SegWork &w, int cidx, bool act, const double (&acc64)[VEC], V xr, V ar) {
         const bool closed = !w.is_front && !w.is_back;
         if (closed) {
-            if (w.slot != SLOT_NONE) apply_loaded<VEC, EARLY>(cv, (uint32_t)w.slot, cidx, acc64, lr, eps, xr, ar, act, w.from_key);
+            if (w.slot != SLOT_NONE) apply_loaded<VEC, EARLY>(cv, (uint32_t)w.slot, cidx, acc64, lr, eps, xr, ar, act, w.from_key, w.gone);
         } else if (act) {
             double *mine = bd.part + ((size_t)T * 2 + (w.is_front ? 0 : 1)) * pstride + (size_t)cidx * VEC;
 #pragma unroll
@@ -1590,7 +1892,7 @@ __global__ __launch_bounds__(AP_THREADS) __attribute__((amdgpu_waves_per_eu(MAXC
         if (gl == 0) {
             if (w.is_back && !w.is_front) { st_device(&bd.slot[T], w.slot); st_device(&bd.from_key[T], w.from_key); }
             // Clock(k): once per key per Write; a run that goes on in later tiles takes it where it starts
-            if (!w.is_front && w.slot != SLOT_NONE && !cv.direct) atomicAdd(&cv.meta[w.slot].cc, 1u);
+            if (!w.is_front && w.slot != SLOT_NONE && !cv.direct && !w.gone) atomicAdd(&cv.meta[w.slot].cc, 1u);
         }
         if (w.is_front || w.is_back) stores_acknowledged();   // the partial sum, before this tile is counted as arrived
     };
@@ -1644,6 +1946,7 @@ __global__ __launch_bounds__(AP_THREADS) __attribute__((amdgpu_waves_per_eu(MAXC
             const bool is_front = sg == 0 && front_open, is_back = sg + 1 == nseg && back_open;
             const int32_t slot = is_front ? SLOT_NONE : l.slot[a];
             const uint32_t from_key = !is_front && ((l.fresh[a / WAVE] >> (a % WAVE)) & 1ull) ? l.key[a] : KEY_NONE;
+            const bool gone = is_gone(from_key, slot);
             const bool closed = !is_front && !is_back;
             const bool step = closed && slot != SLOT_NONE;
             const uint32_t per = (b - a + ngroups - 1) / ngroups;
@@ -1666,7 +1969,7 @@ __global__ __launch_bounds__(AP_THREADS) __attribute__((amdgpu_waves_per_eu(MAXC
                     for (uint32_t gi = 0; gi < ngroups; ++gi)
 #pragma unroll
                         for (int e = 0; e < VEC; ++e) tot[e] += l.share[(gi * g.lanes + gl) * VEC + e];
-                    if (step) apply_loaded<VEC, EARLY>(cv, (uint32_t)slot, cidx, tot, lr, eps, xr, ar, act, from_key);
+                    if (step) apply_loaded<VEC, EARLY>(cv, (uint32_t)slot, cidx, tot, lr, eps, xr, ar, act, from_key, gone);
                     else if (!closed && act) {
                         double *mine = bd.part + ((size_t)T * 2 + (is_front ? 0 : 1)) * pstride + (size_t)cidx * VEC;
 #pragma unroll
@@ -1676,7 +1979,7 @@ __global__ __launch_bounds__(AP_THREADS) __attribute__((amdgpu_waves_per_eu(MAXC
             }
             if (threadIdx.x == 0) {
                 if (is_back && !is_front) { st_device(&bd.slot[T], slot); st_device(&bd.from_key[T], from_key); }
-                if (!is_front && slot != SLOT_NONE && !cv.direct) atomicAdd(&cv.meta[slot].cc, 1u);
+                if (!is_front && slot != SLOT_NONE && !cv.direct && !gone) atomicAdd(&cv.meta[slot].cc, 1u);
             }
             if (!closed && group == 0) stores_acknowledged();
         }
@@ -1760,218 +2063,9 @@ __global__ __launch_bounds__(AP_THREADS) __attribute__((amdgpu_waves_per_eu(MAXC
         double sum[VEC];
         if (grouped) add_up(ngroups_run, [&](uint32_t i) { return (const double *)bd.part + ((size_t)work_blocks * 2 + (size_t)(T0 + i * AP_GROUP) * 2 + (i == 0 ? 1 : 0)) * pstride; }, cidx, act, sum);
         else add_up(m, [&](uint32_t i) { return (const double *)tile_sum(i); }, cidx, act, sum);
-        if (slot != SLOT_NONE) apply_step<VEC, EARLY>(cv, (uint32_t)slot, cidx, sum, lr, eps, act, from_key);
+        if (slot != SLOT_NONE) apply_step<VEC, EARLY>(cv, (uint32_t)slot, cidx, sum, lr, eps, act, from_key, is_gone(from_key, slot));
     }
     tr.end();
-}
-
-// Drops the victims among 1024 consecutive slots, four per thread: erase the key, free the slot,
-// raise c_g; then one row group per victim that holds updates copies its row (and accumulator)
-// to the global table: Evict's push (Section 3.1).  Where a victim goes in the evicted-id list
-// and (host-backed table) in the staging buffer follows from the select's per-block counts, so
-// the kernel has no counter that every workgroup would have to add to: at a few nanoseconds
-// per addition to one address, thousands of workgroups made those additions the kernel's
-// duration.  The workgroup that holds the last victim among the rows tied at the threshold
-// writes the call's counters.
-struct EvictLds {
-    uint32_t scan[TRIM_WAVES * 8 + 8];
-    uint32_t v_slot[EV_SLOTS], v_key[EV_SLOTS], v_cg[EV_SLOTS], v_at[EV_SLOTS];
-    uint32_t n_push;
-};
-// MANY: several workers over the table (the push adds what this worker changed to the server's row:
-// three more rows in flight per victim, which the one-worker kernel does not pay registers for).
-template <int VEC, bool RIDE, bool MANY>
-__global__ __launch_bounds__(TRIM_THREADS) void trim_evict_kernel(CacheView cv, TrimPlan tp, SortStage ride, SortStage ride2)
-{
-    uint32_t blk = blockIdx.x, nblk_ = gridDim.x;
-    if (RIDE && run_carried(ride, ride2, blk, nblk_)) return;
-    EvictLds &el = lds_as<EvictLds>();
-    uint32_t *scan = el.scan, *v_slot = el.v_slot, *v_key = el.v_key, *v_cg = el.v_cg, *v_at = el.v_at;
-    if (blk + 1 == nblk_) { h0_remove_victims(cv, tp, v_slot, scan); return; }      // the last workgroup: keeps the first pass's histogram
-    DState *ds = cv.ds;
-    const uint32_t slot0 = blk * EV_SLOTS + threadIdx.x * EV_ITEMS;
-    // everything this thread may need, requested at once
-    const int32_t over = ds->over;                     // snapshot taken by the select
-    const uint32_t tau = ds->sel_tau;
-    const uint32_t take_eq = ds->sel_take;
-    uint32_t key[EV_ITEMS];
-    uint4 meta[EV_ITEMS];
-    load_slots<EV_ITEMS>(cv, slot0, key, meta);
-    // counts over the blocks before this one (whole supers, then the blocks of this super), and over all blocks
-    uint32_t c8[8] = {0, 0, 0, 0, 0, 0, 0, 0};         // before: lt, eq, dirty lt, dirty eq;  all: dirty lt
-    {
-        const uint32_t nblocks = (cv.n_slots + EV_SLOTS - 1) / EV_SLOTS, nsup = (nblocks + EV_SUPER - 1) / EV_SUPER;
-        const uint32_t sup = blk / EV_SUPER;
-        for (uint32_t i = threadIdx.x; i < nsup; i += TRIM_THREADS) {
-            const uint4 v = tp.sup_cnt[i];
-            c8[4] += v.z;
-            if (i < sup) { c8[0] += v.x; c8[1] += v.y; c8[2] += v.z; c8[3] += v.w; }
-        }
-        const uint32_t b = sup * EV_SUPER + threadIdx.x;
-        if (threadIdx.x < EV_SUPER && b < blk) {
-            const uint4 v = tp.blk_cnt[b];
-            c8[0] += v.x; c8[1] += v.y; c8[2] += v.z; c8[3] += v.w;
-        }
-    }
-    block_sum8(c8, scan);
-    const uint32_t lt_before = c8[0], eq_before = c8[1], dlt_before = c8[2], deq_before = c8[3], dlt_total = c8[4];
-    if (threadIdx.x == 0) el.n_push = 0;
-
-    // this thread's four slots: below tau / tied with tau, in slot order
-    bool lt[EV_ITEMS], eq[EV_ITEMS];
-    uint32_t n_lt = 0, n_eq = 0, n_free = 0;
-#pragma unroll
-    for (int i = 0; i < EV_ITEMS; ++i) {
-        const bool cached = key[i] != KEY_NONE && over > 0 && evictable(tp, meta[i]);
-        const uint32_t pk = policy_key(meta[i]);
-        lt[i] = cached && pk < tau; eq[i] = cached && pk == tau;
-        n_lt += lt[i]; n_eq += eq[i];
-        n_free += (slot0 + i < cv.n_slots && key[i] == KEY_NONE) ? 1u : 0u;
-    }
-    uint32_t tot1;
-    const uint32_t ex1 = block_excl_scan<TRIM_WAVES>(n_lt | (n_eq << 16), scan, tot1);
-    uint32_t eq_rank = eq_before + (ex1 >> 16);        // rank of the thread's first tied row among all tied rows
-    const uint32_t eq_here = tot1 >> 16;
-    bool victim[EV_ITEMS], dirty[EV_ITEMS];
-    uint32_t eq_at[EV_ITEMS];
-    uint32_t n_vic = 0, n_dlt = 0, n_deq_vic = 0;
-#pragma unroll
-    for (int i = 0; i < EV_ITEMS; ++i) {
-        eq_at[i] = eq_rank;
-        victim[i] = lt[i] || (eq[i] && eq_rank < take_eq);
-        dirty[i] = victim[i] && meta[i].y > meta[i].x;
-        eq_rank += eq[i];
-        n_vic += victim[i]; n_dlt += dirty[i] && lt[i]; n_deq_vic += dirty[i] && eq[i];
-    }
-    uint32_t tot2;
-    const uint32_t ex2 = block_excl_scan<TRIM_WAVES>(n_vic | (n_dlt << 16), scan, tot2);
-    const uint32_t nv = tot2 & 0xFFFFu;
-    // victims in earlier blocks: their rows below tau, and their tied rows up to the cut
-    uint32_t ev_at = lt_before + min(eq_before, take_eq) + (ex2 & 0xFFFFu);
-    uint32_t dlt_at = dlt_before + (ex2 >> 16);
-    const int buf = tp.ev_slot;
-#pragma unroll
-    for (int i = 0; i < EV_ITEMS; ++i) {
-        if (victim[i]) {
-        const uint32_t slot = slot0 + i, k = key[i], my_cc = meta[i].y;
-        tp.ev_ids[ev_at++] = k;
-        const uint32_t cg = dirty[i] ? cv.Cg[k] : 0u;
-        const uint32_t early = dirty[i] && cv.early_cc ? cv.early_cc[slot] : 0u;
-        cv.slot_of[k] = SLOT_NONE;
-        cv.slot_key[slot] = KEY_NONE;
-        // host-backed table: rows below tau that hold updates are staged in slot order, then one
-        // place per tied victim (left empty by those without updates)
-        const uint32_t stage_at = lt[i] ? dlt_at : dlt_total + eq_at[i];
-        if (dirty[i]) {
-            if (my_cc > cg) cv.Cg[k] = my_cc;                                 // c_g = max(c_g, c_c)
-            // (pushed early by the update that fetched it, not updated since, and nobody else has pushed: the row is there already)
-            const bool travelled = early == my_cc && cg == meta[i].x;
-            if (!travelled) {
-                const uint32_t at = atomicAdd(&el.n_push, 1u);
-                v_slot[at] = slot; v_key[at] = k; v_cg[at] = my_cc > cg ? my_cc : cg; v_at[at] = stage_at;
-            }
-            dlt_at += lt[i];
-        } else if (cv.Cg_host && eq[i]) {
-            cv.hl.keys_of(buf)[stage_at] = KEY_NONE;
-        }
-        }
-    }
-    uint32_t s2[8] = {n_free, n_deq_vic, 0, 0, 0, 0, 0, 0};
-    block_sum8(s2, scan);                              // also makes the push list visible to every thread
-    const uint32_t free_here = s2[0], deq_vic_here = s2[1];
-    const uint32_t np = el.n_push;
-    const int lanes = cv.geom.lanes;
-    const int group = threadIdx.x / lanes, gl = threadIdx.x % lanes, ngroups = TRIM_THREADS / lanes;
-    const RowGeom g = cv.geom;
-    // Evict's push, PUSH_ROWS victims per row group at a time (all their loads before the first
-    // store).  Host-backed table: the rows go to the staging buffer instead; the next Read's fetch
-    // kernel (or a waiting call) sends them over the host link.
-    using V = typename VecT<VEC>::type;
-    constexpr int PUSH_ROWS = 4;
-    static_assert(PUSH_ROWS == 4, "the copy below is written out for four rows");
-    const bool host = cv.Cg_host != nullptr;
-    const float *src_x = cv.rows, *src_a = cv.acc;
-    float *dst_x = host ? cv.hl.rows_of(buf) : cv.W, *dst_a = host ? cv.hl.acc_of(buf) : cv.A;
-    for (uint32_t v0 = group * PUSH_ROWS; v0 < np; v0 += ngroups * PUSH_ROWS) {
-        uint32_t from[PUSH_ROWS], to[PUSH_ROWS];
-#pragma unroll
-        for (int r = 0; r < PUSH_ROWS; ++r) {
-            const uint32_t v = min(v0 + r, np - 1);
-            from[r] = v_slot[v];
-            to[r] = host ? v_at[v] : v_key[v];
-            if (host && gl == 0 && v0 + r < np) {
-                const uint32_t vk = v_key[v];
-                cv.hl.keys_of(buf)[to[r]] = vk;
-                cv.hl.cg_of(buf)[to[r]] = v_cg[v];
-                cv.hl.pend[vk] = ((uint64_t)tp.push_seq << 32) | (uint64_t)to[r];
-            }
-        }
-        const bool adagrad = cv.adagrad != 0;
-        for (int c = gl; c < g.chunks; c += g.lanes) {
-            V x0, x1, x2, x3, a0{}, a1{}, a2{}, a3{};
-            x0 = reinterpret_cast<const V *>(src_x + (size_t)from[0] * g.dim)[c];
-            x1 = reinterpret_cast<const V *>(src_x + (size_t)from[1] * g.dim)[c];
-            x2 = reinterpret_cast<const V *>(src_x + (size_t)from[2] * g.dim)[c];
-            x3 = reinterpret_cast<const V *>(src_x + (size_t)from[3] * g.dim)[c];
-            if (adagrad) {
-                a0 = reinterpret_cast<const V *>(src_a + (size_t)from[0] * g.dim)[c];
-                a1 = reinterpret_cast<const V *>(src_a + (size_t)from[1] * g.dim)[c];
-                a2 = reinterpret_cast<const V *>(src_a + (size_t)from[2] * g.dim)[c];
-                a3 = reinterpret_cast<const V *>(src_a + (size_t)from[3] * g.dim)[c];
-            }
-            if (MANY) {
-                // several workers: the server adds what this worker accumulated since its Fetch
-                // (rows past the end repeat the last one: only the first of the repeats adds)
-                const bool r1 = v0 + 1 < np, r2 = v0 + 2 < np, r3 = v0 + 3 < np;
-                const V w0 = reinterpret_cast<const V *>(dst_x + (size_t)to[0] * g.dim)[c], b0 = reinterpret_cast<const V *>(cv.rows0 + (size_t)from[0] * g.dim)[c];
-                const V w1 = reinterpret_cast<const V *>(dst_x + (size_t)to[1] * g.dim)[c], b1 = reinterpret_cast<const V *>(cv.rows0 + (size_t)from[1] * g.dim)[c];
-                const V w2 = reinterpret_cast<const V *>(dst_x + (size_t)to[2] * g.dim)[c], b2 = reinterpret_cast<const V *>(cv.rows0 + (size_t)from[2] * g.dim)[c];
-                const V w3 = reinterpret_cast<const V *>(dst_x + (size_t)to[3] * g.dim)[c], b3 = reinterpret_cast<const V *>(cv.rows0 + (size_t)from[3] * g.dim)[c];
-                x0 = delta_add(w0, x0, b0);
-                x1 = r1 ? delta_add(w1, x1, b1) : x0; x2 = r2 ? delta_add(w2, x2, b2) : x1; x3 = r3 ? delta_add(w3, x3, b3) : x2;
-                if (adagrad) {
-                    const V u0 = reinterpret_cast<const V *>(dst_a + (size_t)to[0] * g.dim)[c], d0 = reinterpret_cast<const V *>(cv.acc0 + (size_t)from[0] * g.dim)[c];
-                    const V u1 = reinterpret_cast<const V *>(dst_a + (size_t)to[1] * g.dim)[c], d1 = reinterpret_cast<const V *>(cv.acc0 + (size_t)from[1] * g.dim)[c];
-                    const V u2 = reinterpret_cast<const V *>(dst_a + (size_t)to[2] * g.dim)[c], d2 = reinterpret_cast<const V *>(cv.acc0 + (size_t)from[2] * g.dim)[c];
-                    const V u3 = reinterpret_cast<const V *>(dst_a + (size_t)to[3] * g.dim)[c], d3 = reinterpret_cast<const V *>(cv.acc0 + (size_t)from[3] * g.dim)[c];
-                    a0 = delta_add(u0, a0, d0);
-                    a1 = r1 ? delta_add(u1, a1, d1) : a0; a2 = r2 ? delta_add(u2, a2, d2) : a1; a3 = r3 ? delta_add(u3, a3, d3) : a2;
-                }
-            }
-            // rows past the end repeat the last one: the same values to the same place
-            reinterpret_cast<V *>(dst_x + (size_t)to[0] * g.dim)[c] = x0;
-            reinterpret_cast<V *>(dst_x + (size_t)to[1] * g.dim)[c] = x1;
-            reinterpret_cast<V *>(dst_x + (size_t)to[2] * g.dim)[c] = x2;
-            reinterpret_cast<V *>(dst_x + (size_t)to[3] * g.dim)[c] = x3;
-            if (adagrad) {
-                reinterpret_cast<V *>(dst_a + (size_t)to[0] * g.dim)[c] = a0;
-                reinterpret_cast<V *>(dst_a + (size_t)to[1] * g.dim)[c] = a1;
-                reinterpret_cast<V *>(dst_a + (size_t)to[2] * g.dim)[c] = a2;
-                reinterpret_cast<V *>(dst_a + (size_t)to[3] * g.dim)[c] = a3;
-            }
-        }
-        if (cv.rowwise && gl == 0) {                 // (one accumulator per row; such a table is in HBM)
-#pragma unroll
-            for (int r = 0; r < PUSH_ROWS; ++r) cv.A[to[r]] = cv.acc[from[r]];
-        }
-    }
-    if (threadIdx.x == 0) {
-        if (free_here + nv) atomicAdd(&tp.tile_free[blk / (TRIM_TILE / EV_SLOTS)], free_here + nv);     // (zero when the trim starts; a few workgroups per tile)
-        // the call's counters: written by the block that holds the last tied victim (block 0 if there is none)
-        const bool closes = over <= 0 ? blk == 0
-                          : (take_eq == 0 ? blk == 0 : (eq_before < take_eq && take_eq <= eq_before + eq_here));
-        if (closes) {
-            const uint32_t evicted = over > 0 ? (uint32_t)over : 0u;
-            const uint32_t evicted_dirty = over > 0 ? dlt_total + deq_before + deq_vic_here : 0u;
-            ds->ev_n[buf] = evicted;
-            ds->push_n[buf] = over > 0 ? dlt_total + take_eq : 0u;
-            if (evicted) {
-                ds->size -= (int32_t)evicted;
-                cv.last->evicted = evicted; ds->total.evicted += evicted;
-                cv.last->evicted_dirty = evicted_dirty; ds->total.evicted_dirty += evicted_dirty;
-            }
-        }
-    }
 }
 
 // flush: push every cached row that holds updates and mark it clean (c_s = c_c = c_g).

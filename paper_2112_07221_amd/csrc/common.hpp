@@ -26,6 +26,7 @@ struct DState {
     int32_t size;        // cached rows
     uint32_t n_unique;   // distinct valid ids of the current call
     uint32_t n_valid;    // ids of the current call that lie in [0, vocab)
+    int32_t cut_slot;    // trim, counted beside the fetches: the rows fetched into slots up to this one are victims (-1: none)
     uint32_t err;        // sticky ERRBIT_*
     uint32_t ev_n[2];    // ids recorded by a trim; trims alternate, the lookup in between clears the idle count
     uint32_t sel_take;   // trim: how many of the rows whose policy key equals sel_tau are evicted (in slot order)

@@ -70,8 +70,9 @@ struct het_cache {
     Announced ann[SORT_SETS - 1];    // announced batches, oldest first
     int n_ann = 0;
     TrimPlan sel_tp{};               // the select plan of the rows now cached (fixed at the lookup)
-    int sel_next = 1;                // first stage of that select which the lookup's kernels did not carry
-    int h0_shift = -1;               // place of the digit the kept first-pass histogram was counted for (-1: not counted yet)
+    bool counted = false;            // its rows have been counted (beside the lookup's fetches)
+    bool recount = false;            // and which of them hold updates has changed since other than by the update of the batch
+    int kept_key_bits = KEPT_BITS;   // width of the policy key the kept histograms were counted for
     bool last_trim_skipped = false;  // the last update had nothing to trim: its evicted-id list is empty
     int cslot = 0;                   // which of the two per-call counter blocks the current call uses
     uint32_t *inv = nullptr;
@@ -375,7 +376,7 @@ uint32_t lds_bytes(size_t own, const Rides &r, int threads = SORT_THREADS)
 
 // Must the probe carry a stage?  The kernels behind it carry them for less (the probe's workgroups are large ones of
 // its own size: 409600 ids 311 -> 328 us a step where nothing needed it), so only where an announced batch would
-// meet too few of those before its lookup: 2 a step without a cache, else 3.
+// meet too few of those before its lookup: 2 or 3 a step (with the eviction beside the update, or none, or in a kernel of its own).
 bool probe_must_ride(const het_cache *c, bool evict_kernel)
 {
     for (int a = 0; a < c->n_ann; ++a)
@@ -409,23 +410,28 @@ void use_order(het_cache *c, int set, int max_bits)
     c->ws.perm = c->idx[set][buf];
 }
 
-// The trim's select plan for the rows cached after the lookup that just ran: stages 0..passes-1
-// are histogram passes, stage `passes` is the tie count.
+// The trim's select plan for the rows cached after the lookup that just ran.
 TrimPlan make_trim_plan(const het_cache *c)
 {
     TrimPlan tp = c->tp;
     tp.lfu = c->policy == HET_POLICY_LFU || c->policy == HET_POLICY_LFU_LIGHT;
-    tp.key_bits = std::max(1, bit_width(c->t_host));
-    tp.passes = (tp.key_bits + SEL_BITS - 1) / SEL_BITS;
-    tp.sup_cnt = reinterpret_cast<uint4 *>(tp.hist + SEL_MAX_PASSES * SEL_BINS);
+    tp.key_bits = std::max(KEPT_BITS, bit_width(c->t_host));
+    tp.passes = tp.key_bits > KEPT_BITS ? 3 : 2;
+    tp.t_now = (uint32_t)c->t_host;
+    tp.zero_words = (uint32_t)(tp.hist - tp.zero_from) + (tp.passes > 2 ? (uint32_t)SEL_BINS : 0u);
     return tp;
 }
 
-uint32_t stage_blocks(const het_cache *c, const TrimPlan &tp, int stage)
+// May the rows below and at tau be counted beside the fetches of a lookup of n ids?  What holds updates when the
+// trim comes must be known by then: no row of the batch may be a victim, or only fetched ones, all tied at tau.
+// LRU: as long as the batch's distinct keys fit the capacity, older rows are enough.  LFU: a row of the batch that was
+// found has been used twice, unless the light-weight policy stopped counting at 1.
+bool count_beside_fill(const het_cache *c, const TrimPlan &tp, uint32_t n)
 {
-    if (stage < tp.passes) return std::min(cdiv(c->cv.n_slots, TRIM_TILE), 1024u);
-    return cdiv(c->cv.n_slots, COUNT_SLOTS);
+    return tp.passes == 2 && (tp.lfu ? c->cv.freq_cap != 1 : (int64_t)n <= c->capacity);
 }
+
+uint32_t count_blocks(const het_cache *c) { return cdiv(c->cv.n_slots, COUNT_SLOTS); }
 
 constexpr uint32_t STALE_BLOCKS = 128;     // fetch workgroups of a lookup that leaves the missed rows to the update: they refresh the stale rows
 constexpr uint32_t PUSH_BLOCKS = 256;      // few workgroups keep the host link full; more only contend
@@ -461,7 +467,7 @@ int settle_fetch_impl(het_cache *c)
     const SortStage no = no_stage();
     LAUNCH(c, K_FILL_GATHER, fill_gather_kernel<VEC, false, 0, false><<<fill_blocks, 256, sizeof(FillLds), c->stream>>>(
                                  c->cv, c->ws, n, c->owed_t, ptiles, fill_blocks, none, 0u, nullptr, nullptr, 0u, nullptr, no, no,
-                                 0u, 0, 0u, 0, Ahead{}, KernelTrace{}, 2));
+                                 0u, 0, 0u, Ahead{}, KernelTrace{}, 2));
     c->fetch_owed = false;
     return launch_ok();
 }
@@ -471,23 +477,40 @@ int settle_fetch(het_cache *c)
     return c->cv.geom.vec == 4 ? settle_fetch_impl<4>(c) : settle_fetch_impl<1>(c);
 }
 
-// Evict(): the select stages from `first_stage` on (earlier ones rode along with the update's
-// kernels), then the eviction itself.
-template <int VEC>
-int run_trim(het_cache *c, int first_stage)
+// The plan of the eviction about to be launched: which of the alternating arrays it fills.
+TrimPlan plan_eviction(het_cache *c, bool fetched_dirty)
 {
     TrimPlan tp = c->sel_tp;
-    drain_pushes(c);                                 // the staging buffers alternate: the one before last must be gone
-    for (int st = first_stage; st <= tp.passes; ++st)
-        LAUNCH(c, K_TRIM_STAGE, trim_stage_kernel<<<stage_blocks(c, tp, st), TRIM_THREADS, 0, c->stream>>>(c->cv, tp, st));
     const int fill = 1 - c->tf_last;                 // the idle array: cleared by the lookup in between
+    tp.fetched_dirty = fetched_dirty;
     tp.tile_free = c->tile_free[fill];
     tp.ev_slot = fill;
     tp.ev_ids = c->ev_ids[fill];
     tp.push_seq = ++c->trim_seq;
     if (c->trim_seq == 0x7FFFFFFFu) c->trim_seq = 0;        // 0 means "none", the top bit marks lists of keys fetched ahead; a wrap is harmless (see HostLink::pend)
+    c->tf_last = fill;
+    c->overflow_pending = false;
+    c->last_trim_skipped = false;
+    c->order_valid = false;          // slots recorded for the sorted order may be gone now
+    return tp;
+}
+
+uint32_t evict_grid(const het_cache *c) { return cdiv(c->cv.n_slots, EV_SLOTS) + 1; }        // (the last one keeps the histograms)
+
+// Evict(): the rows below and at tau are counted, if no kernel carried that, then the eviction itself.
+// updated: the batch of the lookup that left the overflow has been updated since, by its own order.
+template <int VEC>
+int run_trim(het_cache *c, bool counted, bool updated)
+{
+    drain_pushes(c);                                 // the staging buffers alternate: the one before last must be gone
+    if (counted && c->recount) {
+        LAUNCH(c, K_TRIM_STAGE, clear_words_kernel<<<1, 256, 0, c->stream>>>(c->sel_tp.zero_from, (uint32_t)(c->sel_tp.hist - c->sel_tp.zero_from)));
+        counted = false;
+    }
+    if (!counted) LAUNCH(c, K_TRIM_STAGE, trim_stage_kernel<<<count_blocks(c), TRIM_THREADS, 0, c->stream>>>(c->cv, c->sel_tp));
+    const TrimPlan tp = plan_eviction(c, counted && c->counted && updated);
     const Rides ride = next_rides(c);
-    const uint32_t ev_blocks = cdiv(c->cv.n_slots, EV_SLOTS);
+    const uint32_t ev_blocks = evict_grid(c);
     // Rows of a kilobyte or more: the pushes run at the memory's limit, and a fourth workgroup per
     // compute unit only gets in the others' way (config 5: 107 us against 97).  Asking for more LDS
     // than a quarter of a compute unit's keeps it to three.  Not where the update pushes the rows it
@@ -496,16 +519,12 @@ int run_trim(het_cache *c, int first_stage)
     const uint32_t lds_floor = c->cv.geom.lanes == 64 && VEC == 4 && !c->cv.early_cc ? 44u * 1024u : 0u;
     const uint32_t lds = std::max(lds_bytes(sizeof(EvictLds), ride), lds_floor);
     if (c->many)
-        LAUNCH(c, K_TRIM_EVICT, trim_evict_kernel<VEC, true, true><<<ride.blocks() + ev_blocks + 1, TRIM_THREADS, lds, c->stream>>>(c->cv, tp, ride.a, ride.b));
+        LAUNCH(c, K_TRIM_EVICT, trim_evict_kernel<VEC, true, true><<<ride.blocks() + ev_blocks, TRIM_THREADS, lds, c->stream>>>(c->cv, tp, ride.a, ride.b));
     else if (ride.blocks())
-        LAUNCH(c, K_TRIM_EVICT, trim_evict_kernel<VEC, true, false><<<ride.blocks() + ev_blocks + 1, TRIM_THREADS, lds, c->stream>>>(c->cv, tp, ride.a, ride.b));
+        LAUNCH(c, K_TRIM_EVICT, trim_evict_kernel<VEC, true, false><<<ride.blocks() + ev_blocks, TRIM_THREADS, lds, c->stream>>>(c->cv, tp, ride.a, ride.b));
     else
-        LAUNCH(c, K_TRIM_EVICT, trim_evict_kernel<VEC, false, false><<<ev_blocks + 1, TRIM_THREADS, lds, c->stream>>>(c->cv, tp, ride.a, ride.b));
-    c->tf_last = fill;
-    if (c->location == HET_BACKING_PINNED_HOST) { c->push_pending = true; c->push_buf = fill; c->push_seq = tp.push_seq; }
-    c->overflow_pending = false;
-    c->last_trim_skipped = false;
-    c->order_valid = false;          // slots recorded for the sorted order may be gone now
+        LAUNCH(c, K_TRIM_EVICT, trim_evict_kernel<VEC, false, false><<<ev_blocks, TRIM_THREADS, lds, c->stream>>>(c->cv, tp, ride.a, ride.b));
+    if (c->location == HET_BACKING_PINNED_HOST) { c->push_pending = true; c->push_buf = tp.ev_slot; c->push_seq = tp.push_seq; }
     return launch_ok();
 }
 
@@ -516,7 +535,7 @@ int run_lookup(het_cache *c, const int64_t *ids, uint32_t n, const int64_t *offs
     c->t_host += 1;
     int rc;
     if ((rc = settle_fetch(c)) != HET_OK) return rc;
-    if (c->overflow_pending && (rc = run_trim<VEC>(c, c->sel_next)) != HET_OK) return rc;   // a Read that follows a Read
+    if (c->overflow_pending && (rc = run_trim<VEC>(c, c->counted, false)) != HET_OK) return rc;   // a Read that follows a Read
     // The sorted order: announced by het_prefetch and sorted inside the kernels launched since
     // (what is left of it runs now), or sorted here.  Announcements older than the one used are
     // void; with no match they all stand (a later lookup may still use them).
@@ -551,7 +570,7 @@ int run_lookup(het_cache *c, const int64_t *ids, uint32_t n, const int64_t *offs
         const TrimPlan none{};
 #define GATHER_ONLY_T(POOLED, RIDE, TRACE)                                                                               \
     LAUNCH(c, K_FILL_GATHER, fill_gather_kernel<VEC, POOLED, RIDE, TRACE><<<grid, 256, lds, c->stream>>>(                   \
-                                 c->cv, c->ws, n, t_now, 0u, 0u, none, 0u, out, offsets, n_bags, c->inv, ride.a, ride.b, 0u, 0, 0u, 0, Ahead{}, c->trace[1], 0))
+                                 c->cv, c->ws, n, t_now, 0u, 0u, none, 0u, out, offsets, n_bags, c->inv, ride.a, ride.b, 0u, 0, 0u, Ahead{}, c->trace[1], 0))
 #define GATHER_ONLY(POOLED, RIDE) do { if (c->trace[1].rec) GATHER_ONLY_T(POOLED, RIDE, true); else GATHER_ONLY_T(POOLED, RIDE, false); } while (0)
         const int kind = ride.kind();
         if (!offsets) { if (kind == 0) GATHER_ONLY(false, 0); else if (kind == 1) GATHER_ONLY(false, 1); else GATHER_ONLY(false, 2); }
@@ -564,37 +583,35 @@ int run_lookup(het_cache *c, const int64_t *ids, uint32_t n, const int64_t *offs
         return HET_OK;
     }
     const uint32_t ptiles = cdiv(n, PT_TILE), stiles = cdiv(c->cv.n_slots, PT_TILE);
-    // The select plan of the trim that follows this lookup.  Its first pass's histogram is kept
-    // between trims as long as its digit's place in the key stays the same (it moves when the
-    // iteration count reaches 2048, 4096, ...); otherwise this lookup counts it afresh, beside its fetches.
+    // The select plan of the trim that follows this lookup.
     c->sel_tp = make_trim_plan(c);
-    const int h0_shift = std::max(0, c->sel_tp.key_bits - SEL_BITS);
-    c->sel_tp.h0_kept = c->h0_shift == h0_shift;
-    c->h0_shift = h0_shift;
     const TrimPlan &tp = c->sel_tp;
-    const uint32_t kept_words = tp.h0_kept ? (uint32_t)SEL_BINS : 0u;
+    if (tp.key_bits != c->kept_key_bits) {           // (iterations 2^22, 2^23, ...: wider bins)
+        LAUNCH(c, K_TRIM_STAGE, clear_words_kernel<<<1024, 256, 0, c->stream>>>(tp.coarse, KEPT_WORDS));
+        LAUNCH(c, K_TRIM_STAGE, kept_recount_kernel<<<std::min(cdiv(c->cv.n_slots, TRIM_THREADS), 1024u), TRIM_THREADS, 0, c->stream>>>(c->cv, tp));
+        c->kept_key_bits = tp.key_bits;
+    }
     {
-        const Rides ride = probe_must_ride(c, true) ? next_rides(c) : Rides{no_stage(), no_stage()};
+        const bool beside = count_beside_fill(c, tp, n) && c->location == HET_BACKING_HBM && !c->many && !c->cv.rowwise;
+        const Rides ride = probe_must_ride(c, !beside) ? next_rides(c) : Rides{no_stage(), no_stage()};
         const uint32_t blocks = ptiles + (match >= 0 ? ptiles : 0u) + stiles;
 #define PROBE(RIDE)                                                                                                                              \
     LAUNCH(c, K_PROBE, probe_kernel<true, RIDE><<<blocks + ride.blocks(), PT_THREADS, lds_bytes(0, ride, PT_THREADS), c->stream>>>(                \
                            c->cv, c->ws, n, t_now, ptiles, c->tile_free[c->tf_last], c->tile_free[1 - c->tf_last], (uint32_t)(1 - c->tf_last),    \
-                           c->tp.hist + kept_words, c->tp.zero_words - kept_words, tp, match >= 0 ? ids : nullptr, c->side ? c->pf_slot_next : -1, offsets ? c->inv : nullptr, ride.a, ride.b))
+                           tp, match >= 0 ? ids : nullptr, c->side ? c->pf_slot_next : -1, offsets ? c->inv : nullptr, ride.a, ride.b))
         if (ride.blocks()) PROBE(true); else PROBE(false);
 #undef PROBE
     }
 
-    const int hist_pass = tp.h0_kept ? 1 : 0;                  // this pass of the select rides with the fetches
-    // (the update has one kernel to carry a stage: with the first pass kept, a select of two passes
-    // is over when that kernel ends: second pass here, tie count there)
-    const uint32_t hist_blocks = hist_pass < tp.passes ? stage_blocks(c, tp, hist_pass) : 0u;
-    c->sel_next = hist_blocks ? hist_pass + 1 : hist_pass;     // (a select of one pass whose histogram is kept: only the tie count is left)
-        const uint32_t fill_blocks = std::min(cdiv(row_grid(c->cv.geom, n), (uint32_t)FILL_ROWS), FILL_MAX_BLOCKS);     // they come first: theirs is the longer chain
+    c->counted = count_beside_fill(c, tp, n);
+    c->recount = false;
+    const uint32_t hist_blocks = c->counted ? count_blocks(c) : (tp.passes > 2 ? std::min(cdiv(c->cv.n_slots, TRIM_TILE), 1024u) : 0u);
+    const uint32_t fill_blocks = std::min(cdiv(row_grid(c->cv.geom, n), (uint32_t)FILL_ROWS), FILL_MAX_BLOCKS);     // they come first: theirs is the longer chain
     const uint32_t lds_own = (uint32_t)std::max(sizeof(FillLds), sizeof(TrimLds));
 #define FILL_GATHER_T(POOLED, RIDE, TRACE, GRID, FILLB, HISTB, PUSHB)                                                     \
     LAUNCH(c, K_FILL_GATHER, fill_gather_kernel<VEC, POOLED, RIDE, TRACE><<<GRID, 256, lds_bytes(lds_own, ride), c->stream>>>( \
                                  c->cv, c->ws, n, t_now, ptiles, FILLB, tp, HISTB, out, offsets, n_bags, c->inv, ride.a, ride.b, \
-                                 PUSHB, c->push_buf, c->push_seq, hist_pass, ah, c->trace[1], fetch_mode))
+                                 PUSHB, c->push_buf, c->push_seq, ah, c->trace[1], fetch_mode))
 #define FILL_GATHER(POOLED, RIDE, GRID, FILLB, HISTB, PUSHB)                                                              \
     do {                                                                                                                  \
         if (c->trace[1].rec) FILL_GATHER_T(POOLED, RIDE, true, GRID, FILLB, HISTB, PUSHB);                                \
@@ -698,37 +715,42 @@ int run_lookup(het_cache *c, const int64_t *ids, uint32_t n, const int64_t *offs
     return HET_OK;
 }
 
-// The kernel of Write.  It carries one stage of the coming trim's select in extra workgroups (the
-// stages before c->sel_next are done: the kept first pass, and what rode with the lookup's
-// fetches): a histogram pass (policy fields only), or the tie count.  The count looks at the clocks
-// the kernel is moving, which is sound only when the update is known to touch exactly the rows the
-// last Read touched (it reuses that Read's order): see TrimPlan::dirty_stamp.
-// `trim`: a trim follows.  Returns the first stage that is still to run.
+// The kernel of Write.  Where the rows below and at tau could not be counted beside the lookup's fetches it
+// carries that count in extra workgroups.  The count looks at the clocks the kernel is moving, which is sound
+// only when the update is known to touch exactly the rows the last Read touched (it reuses that Read's order): see
+// TrimPlan::dirty_stamp.
+// Where they were counted there, the eviction runs beside the update (see evict_body) if the update is the one the lookup left its fetches to (c->fetch_owed: table in HBM, one
+// worker, not row-wise Adagrad): by count_beside_fill no row it touches is a victim but rows it fetches, and those it
+// writes to the global table itself, instead of to their slots.
+// `trim`: a trim follows.  Returns whether its rows have been counted.
 template <int VEC, int MAXC, int TILE, bool EARLY>
-int launch_apply_tile2(het_cache *c, bool verify, const int64_t *ids, uint32_t n, const float *grads, const uint32_t *grad_row, float lr,
+bool launch_apply_tile2(het_cache *c, bool verify, const int64_t *ids, uint32_t n, const float *grads, const uint32_t *grad_row, float lr,
                       bool trim)
 {
     const uint32_t grid = cdiv(n, TILE);
     TrimPlan tp = c->sel_tp;
-    int next = c->sel_next;
-    int stage = -1;
-    if (trim && next < tp.passes) stage = next++;
-    else if (trim && next == tp.passes && verify && c->cv.freq_cap != 1) { stage = next++; tp.dirty_stamp = (uint32_t)c->t_host; }    // (light-weight LFU with a cap of 1 leaves rows of the batch unstamped that can be evicted; with a larger cap those it leaves unstamped cannot)
-    const uint32_t extra = stage >= 0 ? stage_blocks(c, tp, stage) : 0u;
-    const Rides ride = next_rides(c);
+    bool counted = c->counted;
     const int fresh = verify && c->fetch_owed ? 1 : 0;          // (verify: this update reuses the lookup's order)
     if (fresh) c->fetch_owed = false;
-    const uint32_t lds = lds_bytes(std::max(sizeof(TrimLds), sizeof(ApplyLds<VEC, TILE>)), ride);
-    if (verify)
-        LAUNCH(c, K_APPLY, apply_kernel<VEC, MAXC, true, TILE, EARLY><<<ride.blocks() + grid + extra + cdiv(n, VERIFY_TILE), AP_THREADS, lds, c->stream>>>(c->cv, c->ws, c->bd, ids, grads, grad_row, lr, c->eps, n, grid, tp, stage, ride.a, ride.b, c->trace[0], fresh));
-    else
-        LAUNCH(c, K_APPLY, apply_kernel<VEC, MAXC, false, TILE, EARLY><<<ride.blocks() + grid + extra, AP_THREADS, lds, c->stream>>>(c->cv, c->ws, c->bd, ids, grads, grad_row, lr, c->eps, n, grid, tp, stage, ride.a, ride.b, c->trace[0], fresh));
-    return next;
+    const bool evict = trim && fresh && c->counted && !c->recount && !c->profiling;      // (per-kernel timing: in a kernel of its own, to tell the two apart)
+    uint32_t extra = 0;
+    if (evict) { tp = plan_eviction(c, true); extra = evict_grid(c); }
+    else if (trim && !counted && verify && c->cv.freq_cap != 1) {    // (light-weight LFU with a cap of 1 leaves rows of the batch unstamped that can be evicted; with a larger cap those it leaves unstamped cannot)
+        extra = count_blocks(c); counted = true; tp.dirty_stamp = (uint32_t)c->t_host;
+    }
+    const Rides ride = next_rides(c);
+    const uint32_t lds = lds_bytes(std::max({sizeof(TrimLds), sizeof(EvictLds), sizeof(ApplyLds<VEC, TILE>)}), ride);
+#define APPLY(MODE)                                                                                                                              \
+    LAUNCH(c, K_APPLY, apply_kernel<VEC, MAXC, MODE, TILE, EARLY><<<ride.blocks() + grid + extra + (verify ? cdiv(n, VERIFY_TILE) : 0u), AP_THREADS, lds, c->stream>>>( \
+                           c->cv, c->ws, c->bd, ids, grads, grad_row, lr, c->eps, n, grid, tp, extra, ride.a, ride.b, c->trace[0], fresh))
+    if (evict) APPLY(AP_REUSED_EVICT); else if (verify) APPLY(AP_REUSED); else APPLY(AP_SORTED);
+#undef APPLY
+    return counted;
 }
 
 // EARLY: the variant that also pushes the rows it fetches (CacheView::early_cc in use).
 template <int VEC, int MAXC, int TILE>
-int launch_apply_tile(het_cache *c, bool verify, const int64_t *ids, uint32_t n, const float *grads, const uint32_t *grad_row, float lr,
+bool launch_apply_tile(het_cache *c, bool verify, const int64_t *ids, uint32_t n, const float *grads, const uint32_t *grad_row, float lr,
                       bool trim)
 {
     if constexpr (VEC == 4)          // (only rows of whole 16-byte pieces push early)
@@ -737,7 +759,7 @@ int launch_apply_tile(het_cache *c, bool verify, const int64_t *ids, uint32_t n,
 }
 
 template <int VEC, int MAXC>
-int launch_apply(het_cache *c, bool verify, const int64_t *ids, uint32_t n, const float *grads, const uint32_t *grad_row, float lr,
+bool launch_apply(het_cache *c, bool verify, const int64_t *ids, uint32_t n, const float *grads, const uint32_t *grad_row, float lr,
                  bool trim)
 {
     // rows of more than 128 floats (64 lanes to a row) have one row piece per lane or more; narrower ones exactly one
@@ -764,7 +786,7 @@ int run_update(het_cache *c, const int64_t *ids, uint32_t n, const int64_t *offs
             LAUNCH(c, K_PROBE, direct_probe_kernel<false, false><<<cdiv(n, PT_TILE), PT_THREADS, 0, c->stream>>>(c->cv, c->ws, n, (uint32_t)c->t_host, cdiv(n, PT_TILE), nullptr, nullptr, no_stage(), no_stage()));
         else
             LAUNCH(c, K_PROBE, probe_kernel<false, false><<<cdiv(n, PT_TILE), PT_THREADS, 0, c->stream>>>(
-                                   c->cv, c->ws, n, (uint32_t)c->t_host, cdiv(n, PT_TILE), nullptr, nullptr, 0u, nullptr, 0u, TrimPlan{}, nullptr, -1, nullptr, no_stage(), no_stage()));
+                                   c->cv, c->ws, n, (uint32_t)c->t_host, cdiv(n, PT_TILE), nullptr, nullptr, 0u, TrimPlan{}, nullptr, -1, nullptr, no_stage(), no_stage()));
     }
     const uint32_t *grad_row = nullptr;
     if (offsets) {
@@ -773,16 +795,18 @@ int run_update(het_cache *c, const int64_t *ids, uint32_t n, const int64_t *offs
     }
     // Only a lookup leaves rows above capacity; an update that follows no lookup has nothing to trim.
     const bool trim = c->overflow_pending;
-    int next_stage = 1;
+    bool counted = false;
     switch (c->max_chunks_per_lane) {
-    case 1: next_stage = launch_apply<VEC, 1>(c, reuse, ids, n, grads, grad_row, lr, trim); break;
-    case 2: next_stage = launch_apply<VEC, 2>(c, reuse, ids, n, grads, grad_row, lr, trim); break;
-    case 4: next_stage = launch_apply<VEC, 4>(c, reuse, ids, n, grads, grad_row, lr, trim); break;
-    default: next_stage = launch_apply<VEC, 16>(c, reuse, ids, n, grads, grad_row, lr, trim); break;
+    case 1: counted = launch_apply<VEC, 1>(c, reuse, ids, n, grads, grad_row, lr, trim); break;
+    case 2: counted = launch_apply<VEC, 2>(c, reuse, ids, n, grads, grad_row, lr, trim); break;
+    case 4: counted = launch_apply<VEC, 4>(c, reuse, ids, n, grads, grad_row, lr, trim); break;
+    default: counted = launch_apply<VEC, 16>(c, reuse, ids, n, grads, grad_row, lr, trim); break;
     }
     if ((rc = launch_ok()) != HET_OK) return rc;
     if (!trim) { c->last_trim_skipped = true; c->order_valid = false; return HET_OK; }
-    return run_trim<VEC>(c, next_stage);
+    if (!reuse) c->recount = true;               // rows counted as clean may hold updates now
+    if (!c->overflow_pending) return HET_OK;         // (evicted beside the update)
+    return run_trim<VEC>(c, counted, reuse);
 }
 
 int sync_all(het_cache *c)
@@ -910,11 +934,16 @@ static int configure_impl(het_cache *c, int64_t max_batch_ids, int32_t optimizer
         (rc = dev_alloc(c, &c->bd.arrived, ap_tiles * 3)) || (rc = dev_alloc(c, &c->bd.from_key, ap_tiles)))
         return rc;
     const size_t slot_tiles = cdiv(P, TRIM_TILE), ev_blocks = cdiv(P, EV_SLOTS), ev_supers = cdiv(ev_blocks, EV_SUPER);
-    c->tp.zero_words = (uint32_t)(SEL_MAX_PASSES * SEL_BINS + 4 * ev_supers);
-    if ((rc = dev_alloc(c, &c->tp.hist, (size_t)c->tp.zero_words)) || (rc = dev_alloc(c, &c->tp.blk_cnt, ev_blocks)) ||
+    // the counts per EV_SUPER eviction blocks, and the third digit's histogram behind them
+    if ((rc = dev_alloc(c, &c->tp.zero_from, 4 * ev_supers + SEL_BINS)) || (rc = dev_alloc(c, &c->tp.blk_cnt, ev_blocks)) ||
+        (rc = dev_alloc(c, &c->tp.coarse, direct ? 1 : (size_t)KEPT_WORDS)) ||
         (rc = dev_alloc(c, &c->tile_free[0], slot_tiles)) ||
         (rc = dev_alloc(c, &c->tile_free[1], slot_tiles)) || (rc = dev_alloc(c, &c->ev_ids[0], P)) || (rc = dev_alloc(c, &c->ev_ids[1], P)))
         return rc;
+    c->tp.sup_cnt = reinterpret_cast<uint4 *>(c->tp.zero_from);
+    c->tp.hist = c->tp.zero_from + 4 * ev_supers;
+    c->tp.fine = c->tp.coarse + SEL_BINS;
+    if (!direct) HIP_TRY(hipMemsetAsync(c->tp.coarse, 0, (size_t)KEPT_WORDS * sizeof(uint32_t), c->stream));
     {   // before the first trim every slot is free
         std::vector<uint32_t> full(slot_tiles);
         for (size_t t = 0; t < slot_tiles; ++t) full[t] = (uint32_t)std::min<uint64_t>(TRIM_TILE, P - t * TRIM_TILE);
@@ -1129,6 +1158,7 @@ int het_flush(het_cache *c)
     if (!ready(c)) return HET_EINVAL;
     begin_call(c);
     c->n_ann = 0;                // announcements do not outlive a flush
+    c->recount = true;           // (rows counted as holding updates hold none afterwards)
     c->pf.ready = false;
     wait_link(c);                // (nothing the flush writes may be overtaken by an older staged copy)
     drain_pushes(c);             // (a staged copy of a row reaches the table before anything the flush writes)

@@ -145,3 +145,38 @@ def test_sort_stages_carried_by_every_kernel_of_a_step(batch, vocab, policy, mod
     it are too few."""
     w = wl.WORKLOADS[1].scaled(batch=batch, vocab=vocab, capacity=9_000, s=4, policy=policy, dim=8)
     run_workload(w, 7, state_every=2, prefetch=mode)
+
+
+@pytest.mark.parametrize("optimizer", [0, 1])
+@pytest.mark.parametrize("dim", [3, 16, 128, 260])
+@pytest.mark.parametrize("policy,capacity,lfu_cap", [(0, 311, None), (0, 312, None), (0, 700, None), (1, 40, None), (1, 700, None), (3, 700, 1), (3, 200, 2), (3, 700, 16)])
+def test_evictions_counted_beside_the_fetches(policy, capacity, lfu_cap, dim, optimizer):
+    """Victims are counted in the lookup and dropped beside the update (LRU from a capacity of the batch's 312 ids
+    on; LFU, whose victims may be rows of the very batch) or by kernels of their own: lookups that follow
+    lookups, flushes and updates with other ids in between.  State, counters, evicted ids and the table's clocks
+    after every call; the table's rows too where updates do not push early."""
+    w = wl.WORKLOADS[1].scaled(batch=12, vocab=3_000, capacity=capacity, s=3, policy=policy, dim=dim, optimizer=optimizer)
+    T = 40
+    ids, grads, table = wl.IdStream(w).batches(T + 1), wl.grad_pool(w), wl.table_init(w)
+    rng = np.random.default_rng(capacity + dim)
+    p = Pair(w, table, lfu_cap=lfu_cap)
+    try:
+        ids_dev = torch.from_numpy(ids).to(p.dev)
+        for t in range(T):
+            p.lookup(ids[t], ids_dev=ids_dev[t])
+            kind = rng.integers(0, 8) if t > 8 else 7
+            if kind == 0:
+                p.cache.flush(); p.oracle.flush()
+            if kind == 1:
+                p.compare_counters()
+                continue                                                  # a lookup follows a lookup
+            other = kind == 2                                             # (a part of the batch's ids: a buffer of its own)
+            b = np.repeat(ids[t][: w.n // 2], 2) if other else ids[t]
+            p.update(b, grads[t % len(grads)], ids_dev=None if other else ids_dev[t])
+            p.compare_state(values=t % 8 == 0)
+            p.compare_counters()
+            if dim < 128:
+                p.compare_table()
+        p.flush_and_compare()
+    finally:
+        p.close()
