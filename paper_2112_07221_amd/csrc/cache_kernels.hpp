@@ -106,7 +106,7 @@ struct Workspace {
     int32_t *src;                 // per sorted position: slot to gather from, or SRC_*
     int32_t *head_slot;           // at heads: slot of the key (set by fill for a missed key)
     uint8_t *cls;                 // at heads: HIT / STALE / MISS (lookup)
-    uint32_t *tile_miss, *tile_stale;     // per probe tile counts
+    uint32_t *tile_miss, *tile_stale, *tile_hit;     // per probe tile counts
     uint2 *miss_stage, *stale_stage;      // per probe tile: (head position, key) of its missed / stale keys
     uint32_t *bag_of;             // pooled: bag of each original position
 };
@@ -228,7 +228,7 @@ __device__ __forceinline__ void sel_replay(const TrimPlan &tp, int upto, uint32_
     prefix |= sel_pick(c, remaining, lds_pick, lds_scan);
 }
 
-// LDS of one select stage (a workgroup of TRIM_THREADS threads).
+// LDS of the select (a workgroup of TRIM_THREADS threads).
 struct TrimLds {
     uint32_t bins[SEL_BINS];
     uint32_t pick[2];
@@ -266,11 +266,11 @@ __device__ __forceinline__ bool run_carried(const SortStage &a, const SortStage 
 // It runs beside the lookup's fetches: slots that were free when the lookup began are skipped (they are being
 // filled right now), and the rows fetched into them, which all carry the policy key t_now, are counted from
 // their number.
-__device__ __forceinline__ void trim_hist_body(const CacheView &cv, const TrimPlan &tp, uint32_t vblock, uint32_t nblocks, TrimLds &l)
+__device__ __forceinline__ void trim_hist_body(const CacheView &cv, const TrimPlan &tp, const uint32_t *tile_miss, uint32_t ptiles, uint32_t vblock, uint32_t nblocks, TrimLds &l)
 {
-    const int32_t over = cv.ds->size - (int32_t)cv.capacity;
+    const uint32_t new_rows = block_sum_array<TRIM_WAVES>(tile_miss, ptiles, l.scan);
+    const int32_t over = cv.ds->size_before + (int32_t)new_rows - (int32_t)cv.capacity;
     if (over <= 0) return;
-    const uint32_t new_rows = (uint32_t)cv.last->miss;
     uint32_t prefix, in_coarse, remaining;
     sel_replay(tp, 2, (uint32_t)over, prefix, in_coarse, remaining, l.pick, l.scan);
     for (int b = threadIdx.x; b < SEL_BINS; b += TRIM_THREADS) l.bins[b] = 0;
@@ -381,28 +381,30 @@ __device__ __forceinline__ void load_slots(const CacheView &cv, uint32_t slot0, 
 // fetched one can be a victim: see count_beside_fill).  Slots that were free when the lookup began are being filled
 // right now; those up to the last one taken hold the fetched rows, whose policy key is t_now and which hold no
 // updates yet (the eviction knows if they do by then).
-__device__ __forceinline__ void trim_count_body(const CacheView &cv, const TrimPlan &tp, uint32_t vblock, TrimLds &l, bool beside_fill = false)
+__device__ __forceinline__ void trim_count_body(const CacheView &cv, const TrimPlan &tp, uint32_t vblock, TrimLds &l, bool beside_fill = false,
+                                                const uint32_t *tile_miss = nullptr, uint32_t ptiles = 0)
 {
-    const int32_t over = cv.ds->size - (int32_t)cv.capacity;
-    if (vblock == 0 && threadIdx.x == 0) { cv.ds->over = over; cv.ds->cut_slot = -1; }
-    if (over <= 0) return;
     uint32_t key[COUNT_ITEMS];
     uint4 meta[COUNT_ITEMS];
     const uint32_t slot0 = vblock * COUNT_SLOTS + threadIdx.x * COUNT_ITEMS;
     load_slots<COUNT_ITEMS>(cv, slot0, key, meta);      // loads first: they overlap the replay
     uint32_t last_new = 0, misses = 0;
-    bool any_new = false;
+    int32_t over;
     if (beside_fill) {
-        misses = (uint32_t)cv.last->miss;
-        any_new = misses != 0;
-        last_new = any_new ? cv.free_list[misses - 1] : 0u;
 #pragma unroll
         for (int i = 0; i < COUNT_ITEMS; ++i)
             if (slot0 + i < cv.n_slots && cv.was_free[slot0 + i]) key[i] = KEY_NONE;
+        misses = block_sum_array<TRIM_WAVES>(tile_miss, ptiles, l.scan);
+        over = cv.ds->size_before + (int32_t)misses - (int32_t)cv.capacity;
+        if (misses) last_new = cv.free_list[misses - 1];
+    } else {
+        over = cv.ds->size - (int32_t)cv.capacity;
     }
+    if (vblock == 0 && threadIdx.x == 0) { cv.ds->over = over; cv.ds->cut_slot = -1; }
+    if (over <= 0) return;
     uint32_t tau, in_coarse, take_eq;
     sel_replay(tp, tp.passes, (uint32_t)over, tau, in_coarse, take_eq, l.pick, l.scan);
-    const bool new_tied = beside_fill && any_new && tau == tp.t_now;
+    const bool new_tied = misses && tau == tp.t_now;
     uint32_t lt = 0, eq = 0, dlt = 0, deq = 0;
 #pragma unroll
     for (int i = 0; i < COUNT_ITEMS; ++i) {
@@ -529,7 +531,7 @@ __global__ __launch_bounds__(PT_THREADS) __attribute__((amdgpu_num_sgpr(96))) vo
         *cv.next_call = z;
         cv.last->n = n;
         atomicAdd(&ds->total.n, (unsigned long long)n);
-        if (LOOKUP) ds->t = t_now;
+        if (LOOKUP) { ds->t = t_now; ds->size_before = ds->size; }
         if (LOOKUP && pf_idle >= 0) ds->pf_n[pf_idle] = 0;    // the list of keys to fetch ahead that this lookup's second kernel may fill
     }
     // Find runs once per key, not once per position: by the head of every run of equal keys, and by
@@ -606,16 +608,11 @@ __global__ __launch_bounds__(PT_THREADS) __attribute__((amdgpu_num_sgpr(96))) vo
         const uint32_t mo = ms & 0xFFFFu, so = ms >> 16, tot_miss = tot_ms & 0xFFFFu, tot_stale = tot_ms >> 16;
         if (miss) ws.miss_stage[tile * PT_TILE + mo] = make_uint2(j, ws.skey[j]);
         if (stale) ws.stale_stage[tile * PT_TILE + so] = make_uint2(j, ws.skey[j]);
-        const uint32_t tot_hh = block_sum<PT_WAVES>((hit ? 1u : 0u) | (head ? 1u << 16 : 0u), lds);
-        const uint32_t tot_hit = tot_hh & 0xFFFFu, tot_heads = tot_hh >> 16;
+        const uint32_t tot_hit = block_sum<PT_WAVES>(hit ? 1u : 0u, lds);
         if (threadIdx.x == 0) {
             ws.tile_miss[tile] = tot_miss;
             ws.tile_stale[tile] = tot_stale;
-            count2(&cv.last->hit, &ds->total.hit, tot_hit);
-            count2(&cv.last->stale, &ds->total.stale, tot_stale);
-            count2(&cv.last->miss, &ds->total.miss, tot_miss);
-            count2(&cv.last->unique, &ds->total.unique, tot_heads);
-            if (tot_miss) atomicAdd(&ds->size, (int32_t)tot_miss);
+            ws.tile_hit[tile] = tot_hit;              // (the call's counters: added up by a workgroup of the next kernel)
             if (tot_miss) atomicAdd(&kept_delta[0], tot_miss);            // the rows being fetched
         }
         __syncthreads();
@@ -852,11 +849,11 @@ template <> struct RawVecT<4> { using type = raw_float4; };
 
 // Optional time stamps inside the two heavy kernels, one record of TRACE_WORDS words per workgroup
 // (het_profile_trace): [0] start, [5] the last wave's end, [6] role.
-// apply_kernel: roles 1 carried sort stage, 2 select stage, 3 id check, 4 tile of the update; for
+// apply_kernel: roles 1 carried sort stage, 2 eviction or the count before it, 3 id check, 4 tile of the update; for
 // role 4 also [1] tile and segments listed, [2] short segments done, [3] long segments done,
 // [4] past the barrier before the border runs.
 // fill_gather_kernel: roles 1 carried sort stage, 2 fetch, 3 the fetched keys' bookkeeping,
-// 4 select stage, 5 gather, 6 host link (write-back, list of rows to fetch ahead).
+// 4 count of the rows to evict, 5 gather, 6 host link (write-back, list of rows to fetch ahead).
 // Clock: wall_clock64(), 100 MHz.
 constexpr int TRACE_WORDS = 8;
 struct KernelTrace {
@@ -1100,7 +1097,22 @@ __global__ __launch_bounds__(256) void fill_gather_kernel(CacheView cv, Workspac
         const uint32_t tot_stale = tile_prefix_to_lds<4>(ws.tile_stale, ptiles, fl.pre_stale, fl.scan);
         const uint32_t gid = bid * groups_per_block + threadIdx.x / g.lanes;
         const uint32_t ngroups = fill_blocks * groups_per_block;
-        if (bid == 0 && threadIdx.x == 0 && fetch_mode != 2) cv.ds->n_unique = (uint32_t)cv.last->unique;   // for an update that reuses this order
+        if (bid == 0 && fetch_mode != 2 && threadIdx.x < WAVE) {
+            // The lookup's counters, by one wave.  (Added up with atomics by every workgroup of the probe, a hundred and more
+            // to one cache line, they were the last thing the probe waited for: 106496 ids 60.2 -> 58.3 us a step, 409600
+            // ids in bags 251 -> 237, lookups of 53248 ids 58.5 -> 57.5.)
+            uint32_t hits = 0;
+            for (uint32_t i = threadIdx.x; i < ptiles; i += WAVE) hits += ws.tile_hit[i];
+            hits = wave_sum(hits);
+            if (threadIdx.x == 0) {
+                DState *ds = cv.ds;
+                const uint32_t unique = hits + tot_stale + tot_miss;
+                cv.last->hit = hits; cv.last->stale = tot_stale; cv.last->miss = tot_miss; cv.last->unique = unique;
+                ds->total.hit += hits; ds->total.stale += tot_stale; ds->total.miss += tot_miss; ds->total.unique += unique;
+                ds->size = ds->size_before + (int32_t)tot_miss;
+                ds->n_unique = unique;               // for an update that reuses this order
+            }
+        }
         // Fetch(k) into a new slot, FILL_ROWS keys per row group at a time: where each row comes from
         // and goes to is asked for all of them first, then the rows (few workgroups with several
         // rows in flight each leave the chip to the other roles of this kernel from the start)
@@ -1199,8 +1211,8 @@ __global__ __launch_bounds__(256) void fill_gather_kernel(CacheView cv, Workspac
     if (bid < fill_blocks + hist_blocks) {
         // the coming trim's select, over the rows cached before this lookup plus the rows being fetched right now
         // (known by their number and slots, not read): the count or, where there is a third digit, its histogram
-        if (tp.passes == 2) trim_count_body(cv, tp, bid - fill_blocks, lds_as<TrimLds>(), true);
-        else trim_hist_body(cv, tp, bid - fill_blocks, hist_blocks, lds_as<TrimLds>());
+        if (tp.passes == 2) trim_count_body(cv, tp, bid - fill_blocks, lds_as<TrimLds>(), true, ws.tile_miss, ptiles);
+        else trim_hist_body(cv, tp, ws.tile_miss, ptiles, bid - fill_blocks, hist_blocks, lds_as<TrimLds>());
         tr.role(4); tr.end();
         return;
     }

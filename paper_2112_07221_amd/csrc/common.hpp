@@ -24,6 +24,7 @@ struct Counters {
 struct DState {
     uint32_t t;          // iteration = number of non-empty lookups; the LRU time stamp
     int32_t size;        // cached rows
+    int32_t size_before; // those before the current lookup's fetches
     uint32_t n_unique;   // distinct valid ids of the current call
     uint32_t n_valid;    // ids of the current call that lie in [0, vocab)
     int32_t cut_slot;    // trim, counted beside the fetches: the rows fetched into slots up to this one are victims (-1: none)

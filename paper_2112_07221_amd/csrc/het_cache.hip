@@ -927,7 +927,7 @@ static int configure_impl(het_cache *c, int64_t max_batch_ids, int32_t optimizer
     c->cv.last = &cv.ds->call[0];
     c->cv.next_call = &cv.ds->call[1];
     if ((rc = dev_alloc(c, &ws.src, N)) || (rc = dev_alloc(c, &ws.head_slot, N)) || (rc = dev_alloc(c, &ws.cls, N)) ||
-        (rc = dev_alloc(c, &ws.tile_miss, ptiles)) || (rc = dev_alloc(c, &ws.tile_stale, ptiles)) ||
+        (rc = dev_alloc(c, &ws.tile_miss, ptiles)) || (rc = dev_alloc(c, &ws.tile_stale, ptiles)) || (rc = dev_alloc(c, &ws.tile_hit, ptiles)) ||
         (rc = dev_alloc(c, &ws.miss_stage, ptiles * PT_TILE)) || (rc = dev_alloc(c, &ws.stale_stage, ptiles * PT_TILE)) ||
         (rc = dev_alloc(c, &c->inv, N)) || (rc = dev_alloc(c, &ws.bag_of, N)) ||
         (rc = dev_alloc(c, &c->bd.part, ap_tiles * 4 * (size_t)c->dim)) || (rc = dev_alloc(c, &c->bd.slot, ap_tiles)) ||      // (tiles' sums, then groups' sums: see ApplyBorders)

@@ -16,7 +16,7 @@
 // atomics (a popular id would make hundreds of them hit one address).
 // A stage costs a kernel boundary and a chain of some ten LDS and barrier steps whatever its digit's
 // width, so few wide passes beat many narrow ones once the offsets do not have to be added up over
-// every tile; the figures are beside sort_passes in the host code.
+// every tile; the figures are beside sort_bits_alone in the host code.
 //
 // A stage is a device function for workgroups of 256 or 1024 threads, not a kernel: the sort of the
 // NEXT minibatch (Section 4.2: its indices are known in advance) touches no cache state, so
