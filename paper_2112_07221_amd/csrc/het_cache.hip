@@ -316,26 +316,31 @@ void begin_call(het_cache *c)
     c->cv.next_call = &c->cv.ds->call[1 - c->cslot];
 }
 
+// The one-workgroup sort from where stages [0, s.stage) have left it (s: the first stage that is not enqueued).
 template <int ITEMS>
-void launch_solo(het_cache *c, const int64_t *ids, uint32_t n, uint32_t *keys_out, uint32_t *idx_out)
+void launch_solo(het_cache *c, const SortStage &s, uint32_t *keys_out, uint32_t *idx_out)
 {
-    const int bits = std::max(SORT_MIN_BITS, bit_width(c->cv.vocab)), passes = solo_passes(bits), width = (bits + passes - 1) / passes;
-    LAUNCH(c, K_SORT_STAGE, sort_solo_kernel<ITEMS><<<1, SOLO_THREADS, solo_lds_bytes(ITEMS, width), c->stream>>>(ids, n, c->cv.vocab, passes, width, keys_out, idx_out));
+    const int shift = (s.stage >> 1) * s.sp.width;
+    const int bits = std::max(SORT_MIN_BITS, bit_width(s.sp.vocab) - shift), passes = solo_passes(bits), width = (bits + passes - 1) / passes;
+    LAUNCH(c, K_SORT_STAGE, sort_solo_kernel<ITEMS><<<1, SOLO_THREADS, solo_lds_bytes(ITEMS, width), c->stream>>>(
+                                s.ids, s.stage > 0 ? s.keys_in : nullptr, s.stage > 1 ? s.idx_in : nullptr, s.sp.n, s.sp.vocab, shift, passes, width,
+                                keys_out, idx_out));
 }
 
-// What is left of a sort (stages [first_stage, end)), in kernels of its own; or, for a small batch, all of
-// it by one workgroup in one launch, from the ids.  That one's time is the ballots' on one compute unit and
+// What is left of a sort (stages [first_stage, end)), in kernels of its own; or, for a small batch, by
+// one workgroup in one launch.  That one's time is the ballots' on one compute unit and
 // grows with the ids (20 bits: 4.9 us for 200, 7.7 for 2048, 11.9 for 4096, 19.9 for 8192), a stage's hardly does
 // (3.3 us histogram, 6.8 us scatter): SOLO_MAX ids against four stages, proportionally fewer against fewer.
 void sort_now(het_cache *c, const int64_t *ids, uint32_t n, int set, int max_bits, int first_stage)
 {
     const int end = sort_stages(c, max_bits);
     if (3ull * n <= (uint64_t)SOLO_MAX * (uint32_t)std::max(0, std::min(3, end - first_stage - 1))) {
+        const SortStage s = make_stage(c, ids, n, set, max_bits, first_stage);
         uint32_t *k = c->keys[set][sort_result_buffer(c, max_bits)], *i = c->idx[set][sort_result_buffer(c, max_bits)];
-        if (n <= SOLO_THREADS) launch_solo<1>(c, ids, n, k, i);
-        else if (n <= 2 * SOLO_THREADS) launch_solo<2>(c, ids, n, k, i);
-        else if (n <= 4 * SOLO_THREADS) launch_solo<4>(c, ids, n, k, i);
-        else launch_solo<8>(c, ids, n, k, i);
+        if (n <= SOLO_THREADS) launch_solo<1>(c, s, k, i);
+        else if (n <= 2 * SOLO_THREADS) launch_solo<2>(c, s, k, i);
+        else if (n <= 4 * SOLO_THREADS) launch_solo<4>(c, s, k, i);
+        else launch_solo<8>(c, s, k, i);
         return;
     }
     for (int st = first_stage; st < end; ++st) {

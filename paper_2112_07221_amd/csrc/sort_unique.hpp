@@ -7,7 +7,8 @@
 // A run of equal keys in skey is one unique key; its first position is the key's "head".
 // Ids outside [0, vocab) get the key `vocab`, which sorts behind every valid id.
 //
-// Up to SOLO_MAX ids: one workgroup sorts them in LDS, in one launch (sort_solo_kernel).
+// Up to SOLO_MAX ids: one workgroup sorts them in LDS, in one launch (sort_solo_kernel), or what other kernels
+// left of their sort.
 // More: one to three passes of up to 11 bits, two stages per pass: a histogram stage counts the
 // pass's digit per tile of 1024 keys and per super-tile of a few tiles, a scatter stage moves the keys.
 // Every workgroup of a scatter stage derives its output offsets itself from the super-tiles'
@@ -373,8 +374,11 @@ __global__ __launch_bounds__(THREADS) void sort_stage_kernel(SortStage s)
     sort_stage_body<THREADS>(s, blockIdx.x, sort_dyn_lds);
 }
 
-// The whole sort of a small batch by one workgroup: the keys stay in registers, ITEMS per thread, and
-// change places through LDS between the passes.
+// The sort of a small batch by one workgroup: the keys stay in registers, ITEMS per thread, and change
+// places through LDS between the passes.  From the ids (keys_in == nullptr), or from where earlier stages
+// left it: keys_in (and idx_in, or the position where that is nullptr) are in order by their lowest `shift` bits,
+// and ids changed since those stages began are seen as they were then (the order check flags them).
+// keys_out and idx_out may be keys_in and idx_in: every key is in a register before the first is stored.
 constexpr int SOLO_THREADS = 1024;
 constexpr int SOLO_WAVES = SOLO_THREADS / WAVE;
 constexpr int SOLO_MAX_BITS = 9;
@@ -389,8 +393,9 @@ __host__ __device__ inline uint32_t solo_lds_bytes(int items, int width)
 }
 
 template <int ITEMS>
-__global__ __launch_bounds__(SOLO_THREADS) void sort_solo_kernel(const int64_t *__restrict__ ids, uint32_t n, uint32_t vocab, int passes, int width,
-                                                                 uint32_t *__restrict__ keys_out, uint32_t *__restrict__ idx_out)
+__global__ __launch_bounds__(SOLO_THREADS) void sort_solo_kernel(const int64_t *__restrict__ ids, const uint32_t *keys_in, const uint32_t *idx_in,
+                                                                 uint32_t n, uint32_t vocab, int shift, int passes, int width,
+                                                                 uint32_t *keys_out, uint32_t *idx_out)
 {
     extern __shared__ __align__(16) uint32_t sort_dyn_lds[];
     const uint32_t bins = 1u << width, mask = bins - 1u, w = threadIdx.x / WAVE;
@@ -400,10 +405,19 @@ __global__ __launch_bounds__(SOLO_THREADS) void sort_solo_kernel(const int64_t *
     const uint32_t at0 = w * (WAVE * ITEMS) + lane_id();
     uint32_t key[ITEMS], pay[ITEMS], d[ITEMS], rank[ITEMS];
     bool valid[ITEMS];
-    {
+#pragma unroll
+    for (int it = 0; it < ITEMS; ++it) { const uint32_t i = at0 + it * WAVE; valid[it] = i < n; pay[it] = i; }
+    if (keys_in) {
+#pragma unroll
+        for (int it = 0; it < ITEMS; ++it) key[it] = valid[it] ? keys_in[at0 + it * WAVE] : 0u;
+        if (idx_in) {
+#pragma unroll
+            for (int it = 0; it < ITEMS; ++it) pay[it] = valid[it] ? idx_in[at0 + it * WAVE] : 0u;
+        }
+    } else {
         int64_t id[ITEMS];
 #pragma unroll
-        for (int it = 0; it < ITEMS; ++it) { const uint32_t i = at0 + it * WAVE; valid[it] = i < n; id[it] = valid[it] ? ids[i] : 0; pay[it] = i; }
+        for (int it = 0; it < ITEMS; ++it) id[it] = valid[it] ? ids[at0 + it * WAVE] : 0;
 #pragma unroll
         for (int it = 0; it < ITEMS; ++it) key[it] = id_to_key(id[it], vocab);
     }
@@ -411,7 +425,7 @@ __global__ __launch_bounds__(SOLO_THREADS) void sort_solo_kernel(const int64_t *
         for (uint32_t b = threadIdx.x; b < SOLO_WAVES * bins / 2; b += SOLO_THREADS) reinterpret_cast<uint32_t *>(hist)[b] = 0;
         __syncthreads();                                   // (also: the keys of the pass before have been read back)
 #pragma unroll
-        for (int it = 0; it < ITEMS; ++it) d[it] = (key[it] >> (p * width)) & mask;
+        for (int it = 0; it < ITEMS; ++it) d[it] = (key[it] >> (shift + p * width)) & mask;
         if (at0 - lane_id() < n) rank_in_wave<ITEMS>(d, valid, width, hist + w * bins, rank);     // (a wave without keys leaves its counts at zero)
         __syncthreads();
         uint32_t run = 0;

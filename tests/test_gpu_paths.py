@@ -180,3 +180,44 @@ def test_evictions_counted_beside_the_fetches(policy, capacity, lfu_cap, dim, op
         p.flush_and_compare()
     finally:
         p.close()
+
+
+@pytest.mark.parametrize("when", ["before", "between"])
+@pytest.mark.parametrize("policy", [0, 1, 2])
+@pytest.mark.parametrize("n,vocab", [(200, 3_000), (1_024, 5_000_000), (2_700, 5_000_000), (2_731, 100_000), (5_400, 5_000_000)])
+def test_small_batches_whose_sort_was_under_way_when_their_lookup_came(n, vocab, policy, when):
+    """One workgroup finishes what the kernels before the lookup carried of a small batch's sort: from the keys
+    that were taken when it began, so that ids changed since are flagged, whatever was left of it.  Whole numbers
+    and lr 1, so rows are exact."""
+    from paper_2112_07221_amd import hetcache as hc
+    dev = torch.device("cuda:0")
+    rng = np.random.default_rng(n + policy)
+    steps = 6
+    ids = [np.minimum((rng.random(n) ** 3 * vocab).astype(np.int64), vocab - 1) for _ in range(steps)]
+    ids[2][n // 2] = -1
+    table, want = torch.zeros(vocab, 4, device=dev), np.zeros((vocab, 4), dtype=np.float32)
+    cache = hc.HetCache(150, 4, 100, policy, n, hc.OPT_SGD)
+    try:
+        cache.attach_backing(table, None, torch.zeros(vocab, dtype=torch.int32, device=dev))
+        d = [torch.from_numpy(x).to(dev) for x in ids]
+        out = torch.empty(n, 4, device=dev)
+        for t in range(steps):
+            if t and t == steps - 1:
+                d[t][n // 3:] = (d[t][n // 3:] + 1) % vocab               # changed after the kernels of the step before had begun its sort
+            if when == "before" and t + 1 < steps:
+                cache.prefetch(d[t + 1])
+            cache.lookup(d[t], out)
+            if t == steps - 1:
+                break
+            if when == "between":
+                cache.prefetch(d[t + 1])
+            ok = ids[t] >= 0
+            got = out.cpu().numpy()
+            assert np.array_equal(got[ok], want[ids[t][ok]]) and not got[~ok].any()
+            g = rng.integers(-8, 9, (n, 4)).astype(np.float32)
+            cache.update(d[t], torch.from_numpy(g).to(dev), 1.0)
+            np.add.at(want, ids[t][ok], -g[ok])
+            assert cache.stats()["error_bits"] == (1 if t >= 2 else 0)
+        assert cache.stats()["error_bits"] & 2
+    finally:
+        cache.close()
