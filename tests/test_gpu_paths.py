@@ -10,6 +10,17 @@ from parity import Pair, run_workload
 pytestmark = pytest.mark.gpu
 
 
+def fill_hbm(leave):
+    """Takes all of HBM but `leave` bytes (or a little less); returns what holds it."""
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    held = []
+    while torch.cuda.mem_get_info()[0] > leave and len(held) < 64:
+        held.append(torch.empty(max(2 << 20, torch.cuda.mem_get_info()[0] - leave), dtype=torch.uint8, device="cuda:0"))
+    assert 0.9 * leave < torch.cuda.mem_get_info()[0] <= leave
+    return held
+
+
 @pytest.mark.parametrize("cap", [1, 2])
 def test_light_weight_lfu_where_the_select_gains_a_pass(cap):
     """A cap of 1 leaves rows of the batch that can be evicted unstamped (their trim has a kernel of its
@@ -83,10 +94,11 @@ def test_key_index_in_hbm_and_where_hbm_has_no_room(full):
     out = torch.empty(n, 4, device=dev)
     cache = hc.HetCache(cap, 4, 100, hc.POLICY_LRU, n, hc.OPT_SGD)
     try:
-        torch.cuda.synchronize()
-        torch.cuda.empty_cache()
-        filler = torch.empty(torch.cuda.mem_get_info()[0] - (200 << 20), dtype=torch.uint8, device=dev) if full else None
+        filler = fill_hbm(200_000_000) if full else None
+        before = torch.cuda.mem_get_info()[0]
         cache.attach_backing(table, None, clock)
+        taken = before - torch.cuda.mem_get_info()[0]
+        assert taken < 64_000_000 if full else taken > 240_000_000
         del filler
         torch.cuda.empty_cache()
         want = {}
