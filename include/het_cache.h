@@ -117,8 +117,9 @@ int het_cache_set_many_writers(het_cache *c);
  * Fixes the largest number of ids one call may carry, the optimizer het_update applies and the
  * HIP stream (a hipStream_t, NULL = the default stream) all work is enqueued on, and allocates
  * the cache in HBM: capacity + max_batch_ids row slots (rows fetched on a miss are added beyond
- * the capacity and the overflow is trimmed at the end of the update, Algorithm 2 / 3) and the
- * per-call workspaces.  Must be called once, before attach.
+ * the capacity and the overflow is trimmed at the end of the update, Algorithm 2 / 3), the
+ * per-call workspaces and, unless the policy is HET_POLICY_NONE, 16 MB of the eviction's histograms whatever
+ * the capacity (arrays of up to 8 MB share one allocation of 128 MB).  Must be called once, before attach.
  * eps is Adagrad's epsilon (ignored for SGD).  HET_OPT_ADAGRAD_ROWWISE keeps one accumulator per row
  * instead of one per element (half the optimizer state of an embedding table): `state` of
  * het_attach_backing is then float[vocab] and het_export_rows' acc float[n_resident]; the table
@@ -140,7 +141,9 @@ int het_cache_configure(het_cache *c, int64_t max_batch_ids, int32_t optimizer, 
  *   cg     uint32[vocab]: global clock c_g per row, zero-initialised by the caller.
  * location HET_BACKING_HBM: device pointers.  HET_BACKING_PINNED_HOST: pointers to pinned,
  * device-mapped host memory (hipHostMalloc); kernels read and write it over the host link.
- * Allocates the id->slot index, 4 bytes per row of the table (HBM; pinned host memory if HBM is full).
+ * Allocates the id->slot index, 4 bytes per row of the table (HBM; pinned host memory if HBM is full,
+ * and then every Find crosses the host link); for a table in host memory also, in HBM, 12 bytes per row
+ * (a mirror of cg, and where rows on their way are) and staging for three batches of rows.
  * The caller owns the arrays; the library reads and writes them during lookup/update/flush and
  * they must outlive the cache.  Between a lookup and the update that follows it the caller must
  * not write them (with the table in HBM the rows a lookup misses are read from it for the output

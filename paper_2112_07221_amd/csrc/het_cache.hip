@@ -1011,10 +1011,6 @@ static int attach_impl(het_cache *c, float *table, float *state, uint32_t *cg, i
         table = static_cast<float *>(dt); cg = static_cast<uint32_t *>(dcg); state = static_cast<float *>(dst);
     }
     c->cv.W = table; c->cv.A = state; c->cv.Cg = cg; c->cv.Cg_host = nullptr; c->cv.vocab = (uint32_t)vocab;
-    if (!c->cv.direct) {
-        const int rc = alloc_index(c, vocab);
-        if (rc) return rc;
-    }
     if (c->cv.direct) {
         if (vocab >= (1ll << 31)) return HET_EINVAL;        // a key stands for its own slot
         c->cv.rows = table; c->cv.acc = state;
@@ -1043,6 +1039,10 @@ static int attach_impl(het_cache *c, float *table, float *state, uint32_t *cg, i
         HIP_TRY(hipStreamCreateWithFlags(&c->side, hipStreamNonBlocking));
         HIP_TRY(hipEventCreateWithFlags(&c->ev_main, hipEventDisableTiming));
         HIP_TRY(hipEventCreateWithFlags(&c->ev_link, hipEventDisableTiming));
+    }
+    if (!c->cv.direct) {                 // last: the only array that can do without HBM
+        const int rc = alloc_index(c, vocab);
+        if (rc) return rc;
     }
     c->location = location;
     c->attached = true;

@@ -233,3 +233,37 @@ def test_small_batches_whose_sort_was_under_way_when_their_lookup_came(n, vocab,
         assert cache.stats()["error_bits"] & 2
     finally:
         cache.close()
+
+
+def test_a_table_in_host_memory_attaches_where_hbm_has_room_for_all_but_the_key_index():
+    """What only HBM can hold is allocated before the index of the table's keys, which then takes pinned host memory."""
+    from paper_2112_07221_amd import hetcache as hc
+    dev = torch.device("cuda:0")
+    vocab, n, cap = 64_000_000, 3_000, 2_000                          # (index and clocks 256 MB each, rows on their way 512 MB)
+    rng = np.random.default_rng(4)
+    table = torch.zeros(vocab, 1).pin_memory()
+    clock = torch.zeros(vocab, dtype=torch.int32).pin_memory()
+    out = torch.empty(n, 1, device=dev)
+    cache = hc.HetCache(cap, 1, 100, hc.POLICY_LRU, n, hc.OPT_SGD)
+    try:
+        filler = fill_hbm(900_000_000)
+        before = torch.cuda.mem_get_info()[0]
+        cache.attach_backing(table, None, clock, hc.BACKING_PINNED_HOST)
+        assert 740_000_000 < before - torch.cuda.mem_get_info()[0] < 850_000_000
+        del filler
+        torch.cuda.empty_cache()
+        want = {}
+        for t in range(4):
+            ids = np.concatenate([rng.integers(0, vocab, n - 1_000), rng.integers(0, 600, 1_000)])
+            g = rng.integers(-8, 9, (n, 1)).astype(np.float32)
+            d = torch.from_numpy(ids).to(dev)
+            cache.lookup(d, out)
+            assert np.array_equal(out.cpu().numpy()[:, 0], np.array([want.get(i, 0.0) for i in ids.tolist()]))
+            cache.update(d, torch.from_numpy(g).to(dev), 1.0)
+            for i, x in zip(ids.tolist(), g[:, 0].tolist()):
+                want[i] = want.get(i, 0.0) - x
+        assert cache.flush() == hc.HET_OK
+        keys = np.array(sorted(want))
+        assert np.array_equal(table.numpy()[keys, 0], np.array([want[k] for k in keys.tolist()]))
+    finally:
+        cache.close()
