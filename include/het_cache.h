@@ -245,6 +245,15 @@ int het_flush(het_cache *c);
 /* Waits for the stream and fills *out (host). */
 int het_stats(het_cache *c, het_stats_t *out);
 
+/*
+ * The iteration count (het_stats_t.iteration, the LRU time stamp) goes on from `iteration`, as if as many
+ * lookups had gone by that used no cached row: for a worker that takes up a long run again (the stamps' width
+ * decides how the eviction selects: two digits up to iteration 2^22, three beyond).  Takes effect at the next
+ * lookup.  HET_EINVAL: below the present count, 2^32 - 2^20 or more, or a lookup has left rows above the capacity
+ * that no update has trimmed yet.
+ */
+int het_cache_set_iteration(het_cache *c, int64_t iteration);
+
 /* Resets the sticky device error bits. */
 int het_clear_error(het_cache *c);
 

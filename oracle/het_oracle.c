@@ -529,6 +529,8 @@ void het_oracle_stats(const het_oracle *o, int64_t *out)
 
 int64_t het_oracle_size(const het_oracle *o) { return o->size; }
 int64_t het_oracle_iteration(const het_oracle *o) { return (int64_t)o->t; }
+/* Goes on as if `t` non-empty Reads had gone by (t not below the present count). */
+void het_oracle_set_iteration(het_oracle *o, int64_t t) { o->t = (uint32_t)t; }
 int32_t het_oracle_error(const het_oracle *o) { return o->err; }
 void het_oracle_clear_error(het_oracle *o) { o->err = 0; }
 int32_t het_oracle_real_bytes(void) { return (int32_t)sizeof(real); }

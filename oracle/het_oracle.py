@@ -53,6 +53,8 @@ def _load(real: str):
     lib.het_oracle_stats.restype = None
     lib.het_oracle_size.argtypes = [p]
     lib.het_oracle_iteration.argtypes = [p]
+    lib.het_oracle_set_iteration.argtypes = [p, i64]
+    lib.het_oracle_set_iteration.restype = None
     lib.het_oracle_error.argtypes = [p]
     lib.het_oracle_clear_error.argtypes = [p]
     lib.het_oracle_clear_error.restype = None
@@ -175,6 +177,9 @@ class Oracle:
     @property
     def iteration(self):
         return self.lib.het_oracle_iteration(self.h)
+
+    def set_iteration(self, t):
+        self.lib.het_oracle_set_iteration(self.h, t)
 
     @property
     def error(self):

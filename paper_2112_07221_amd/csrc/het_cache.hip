@@ -1078,6 +1078,13 @@ int het_cache_set_many_writers(het_cache *c)
     return HET_OK;
 }
 
+int het_cache_set_iteration(het_cache *c, int64_t iteration)
+{
+    if (!ready(c) || c->overflow_pending || iteration < (int64_t)c->t_host || iteration >= (1ll << 32) - (1ll << 20)) return HET_EINVAL;
+    c->t_host = (uint64_t)iteration;             // (the device takes it from the next lookup, which widens the kept histograms' bins if it must)
+    return HET_OK;
+}
+
 int het_backing_foreign_update(het_cache *c, const int64_t *ids, const float *deltas, int64_t n)
 {
     if (!ready(c) || n < 0 || n >= (1ll << 31) || c->location != HET_BACKING_HBM) return HET_EINVAL;

@@ -30,6 +30,7 @@ EXPORTS = (
     "het_profile_end", "het_profile_kernel_count", "het_profile_kernel_name", "het_profile_rows", "het_profile_trace",
     "het_lookup_nocache_static", "het_build_id", "het_cache_set_many_writers",
     "het_backing_foreign_update", "het_cache_set_lfu_cap",
+    "het_cache_set_iteration",
 )
 
 COUNTER_FIELDS = ("n", "unique", "hit", "stale", "miss", "evicted", "evicted_dirty",
@@ -78,6 +79,7 @@ def load() -> C.CDLL:
     lib.het_prefetch_cancel.argtypes = [p]
     lib.het_cache_set_many_writers.argtypes = [p]
     lib.het_cache_set_lfu_cap.argtypes = [p, C.c_uint32]
+    lib.het_cache_set_iteration.argtypes = [p, i64]
     lib.het_backing_foreign_update.argtypes = [p, p, p, i64]
     lib.het_lookup_pooled.argtypes = [p, p, i64, p, i64, p]
     lib.het_update.argtypes = [p, p, p, i64, C.c_float]
@@ -231,6 +233,9 @@ class HetCache:
         self._rc(self.lib.het_attach_backing(self.h, table.data_ptr(),
                                              state.data_ptr() if state is not None else None,
                                              cg.data_ptr(), V, location), "het_attach_backing")
+
+    def set_iteration(self, iteration):
+        self._rc(self.lib.het_cache_set_iteration(self.h, iteration), "het_cache_set_iteration")
 
     def prefetch(self, ids):
         import torch

@@ -267,3 +267,101 @@ def test_a_table_in_host_memory_attaches_where_hbm_has_room_for_all_but_the_key_
         assert np.array_equal(table.numpy()[keys, 0], np.array([want[k] for k in keys.tolist()]))
     finally:
         cache.close()
+
+
+def go_on_from(p, t):
+    p.cache.set_iteration(t)
+    p.oracle.set_iteration(t)
+
+
+@pytest.mark.parametrize("optimizer,dim", [(0, 16), (1, 128), (2, 8)])
+@pytest.mark.parametrize("policy,capacity,lfu_cap", [(0, 200, None), (0, 700, None), (1, 40, None), (1, 700, None), (3, 700, 1), (3, 200, 2)])
+def test_select_beyond_four_million_iterations(policy, capacity, lfu_cap, optimizer, dim):
+    """From iteration 2^22 the policy key has a third digit of 1, 2, 3 ... bits: the kept histograms' bins widen and
+    are counted afresh at 2^22, 2^23, ..., and the third digit is counted beside the fetches.  Across two of these
+    borders, where one bin holds all rows of the last iterations, and at the last iterations that are taken;
+    with lookups that follow lookups, flushes and updates with other ids in between."""
+    w = wl.WORKLOADS[1].scaled(batch=12, vocab=3_000, capacity=capacity, s=3, policy=policy, dim=dim, optimizer=optimizer)
+    stretches = [(0, 10), (2 ** 22 - 7, 14), (2 ** 23 - 7, 14), (2 ** 27 + 50, 30), (2 ** 32 - 2 ** 20 - 1, 14)]
+    T = sum(n for _, n in stretches)
+    ids, grads, table = wl.IdStream(w).batches(T), wl.grad_pool(w), wl.table_init(w)
+    rng = np.random.default_rng(capacity + dim)
+    p = Pair(w, table, lfu_cap=lfu_cap)
+    try:
+        ids_dev = torch.from_numpy(ids).to(p.dev)
+        t, updated = 0, True
+        for start, n in stretches:
+            go_on_from(p, start)
+            for k in range(n):
+                p.lookup(ids[t], ids_dev=ids_dev[t])
+                kind = rng.integers(0, 8) if t > 8 and k + 1 < n else 7
+                if kind == 0:
+                    p.cache.flush(); p.oracle.flush()
+                if kind != 1:                                             # (1: a lookup follows a lookup)
+                    other = kind == 2
+                    b = np.repeat(ids[t][: w.n // 2], 2) if other else ids[t]
+                    p.update(b, grads[t % len(grads)], ids_dev=None if other else ids_dev[t])
+                    p.compare_state(values=t % 8 == 0)
+                p.compare_counters()
+                t += 1
+        p.flush_and_compare()
+    finally:
+        p.close()
+
+
+@pytest.mark.parametrize("policy,lfu_cap", [(0, None), (1, None), (3, 1), (3, 4)])
+@pytest.mark.parametrize("gap", [2_040, 2_047, 2_048, 2_049, 5_000, 3 * 2_048 * 2_048 // 4])
+def test_rows_used_again_and_evicted_after_thousands_of_iterations(gap, policy, lfu_cap):
+    """Rows that lay unused for so many iterations that the probe moves them in the kept histograms one by one, in
+    memory (2048 and more), and fewer; then rows of old and new stamps are evicted together."""
+    w = wl.WORKLOADS[1].scaled(batch=10, width=26, vocab=5_000, capacity=800, s=50, policy=policy)
+    rng = np.random.default_rng(gap)
+    n, grads = w.n, wl.grad_pool(w)
+    p = Pair(w, wl.table_init(w), lfu_cap=lfu_cap)
+    t = 0
+
+    def step(ids):
+        nonlocal t
+        t += 1
+        d = torch.from_numpy(np.ascontiguousarray(ids)).to(p.dev)
+        p.lookup(ids, ids_dev=d)
+        p.update(ids, grads[t % len(grads)], ids_dev=d)
+        p.compare_state(values=t % 4 == 0)
+        p.compare_counters()
+
+    try:
+        for part in range(3):                                             # 780 rows, each used once
+            step(np.arange(part * n, (part + 1) * n))
+        go_on_from(p, gap)
+        step(rng.permutation(np.repeat(np.arange(0, 3 * n, 6), 2)))       # every sixth of them again
+        go_on_from(p, gap + 2_049)
+        step(rng.permutation(np.repeat(np.arange(1, 3 * n, 12), 4)))      # others, twice as long ago
+        for k in range(12):                                               # and rows are needed
+            step(rng.integers(0, 5_000, n))
+            if k == 5:
+                go_on_from(p, gap + 7_000)
+        assert p.cache.stats()["total"]["evicted"] > 1_000
+        p.flush_and_compare()
+    finally:
+        p.close()
+
+
+def test_the_iteration_count_only_goes_forward_and_not_between_a_lookup_and_its_update():
+    from paper_2112_07221_amd import hetcache as hc
+    w = wl.WORKLOADS[1].scaled(batch=4, capacity=100)
+    ids = wl.IdStream(w).batches(1)
+    p = Pair(w, wl.table_init(w))
+    try:
+        d = torch.from_numpy(ids[0]).to(p.dev)
+        p.lookup(ids[0], ids_dev=d)
+        with pytest.raises(hc.HetError):
+            p.cache.set_iteration(10)
+        p.update(ids[0], wl.grad_pool(w)[0], ids_dev=d)
+        for bad in (-1, 0, 2 ** 32 - 2 ** 20):
+            with pytest.raises(hc.HetError):
+                p.cache.set_iteration(bad)
+        go_on_from(p, 10)
+        p.lookup(ids[0], ids_dev=d)
+        p.compare_counters()
+    finally:
+        p.close()
