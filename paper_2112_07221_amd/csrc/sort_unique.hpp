@@ -9,7 +9,7 @@
 //
 // Up to SOLO_MAX ids: one workgroup sorts them in LDS, in one launch (sort_solo_kernel), or what other kernels
 // left of their sort.
-// More: one to three passes of up to 11 bits, two stages per pass: a histogram stage counts the
+// More: one to four passes of up to 11 bits, two stages per pass: a histogram stage counts the
 // pass's digit per tile of 1024 keys and per super-tile of a few tiles, a scatter stage moves the keys.
 // Every workgroup of a scatter stage derives its output offsets itself from the super-tiles'
 // histograms and those of the tiles before its own in its super-tile ("count at the producer, prefix
@@ -42,7 +42,7 @@ struct SortPlan {
     uint32_t ntiles;       // ceil(n / SORT_TILE)
     uint32_t super;        // tiles per super-tile: a workgroup of a histogram stage counts one (1, 4 or 8)
     uint32_t nsupers;      // ceil(ntiles / super)
-    int passes;            // 1..3
+    int passes;            // 1..4
     int width;             // bits per digit (3..11)
     uint32_t *hist;        // the current pass's digit counts, two 16-bit counts per word: [ntiles][bins / 2], then [nsupers][bins / 2]
 };

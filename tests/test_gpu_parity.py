@@ -179,7 +179,7 @@ def test_config3_pinned_host_backing_reduced():
 def test_announcements_far_ahead_out_of_order_and_too_many():
     """Up to three batches stand announced; a fourth replaces the oldest; lookups may come in another
     order than the announcements, or with ids never announced.  Nothing of it changes a result."""
-    w = wl.WORKLOADS[1].scaled(vocab=100_000, batch=300, capacity=2_000, s=1, policy=wl.LFU)   # 17-bit ids: three passes
+    w = wl.WORKLOADS[1].scaled(vocab=100_000, batch=300, capacity=2_000, s=1, policy=wl.LFU)   # 17-bit ids: two passes of 9 bits, or three of 6
     ids_np = wl.IdStream(w).batches(10)
     g = wl.grad_pool(w)
     p = Pair(w, wl.table_init(w))
@@ -426,9 +426,9 @@ def test_random_call_sequences(seed, host):
 
 
 @pytest.mark.parametrize("policy", [wl.LRU, wl.LFU])
-def test_beyond_2048_iterations_the_select_takes_more_passes(policy):
-    """The policy keys grow with the iteration count: past iteration 2047 they need one more
-    select pass (LRU two, LFU three), and more stages than the update's kernels can carry."""
+def test_beyond_2048_iterations_the_select_has_rows_of_two_first_digits(policy):
+    """From iteration 2048 the first digit of the policy key is no longer the same for all rows: the kept
+    histograms' rows of two first digits are in use side by side while the older one is evicted."""
     w = wl.WORKLOADS[1].scaled(batch=40, capacity=600, s=5, policy=policy, optimizer=wl.ADAGRAD, eps=1e-8)
     T = 2120
     table = wl.table_init(w)
@@ -450,9 +450,9 @@ def test_beyond_2048_iterations_the_select_takes_more_passes(policy):
         p.close()
 
 
-def test_beyond_65536_iterations_lfu_select_of_four_passes():
-    """LFU keys are twice as wide as the iteration count: from iteration 65536 the select has four
-    passes, one stage more than the update's kernels carry.  Most iterations run unchecked (both
+def test_beyond_65536_iterations_lfu_select_over_many_first_digits():
+    """A long run: the kept histograms go through 32 first digits, each of which is cleared by the evictions that
+    leave it behind; what the incremental upkeep got wrong once would stay wrong.  Most iterations run unchecked (both
     sides get the same calls); the integers of the state (keys, slots, clocks, policy fields,
     evicted ids, counters) are compared now and then and over the last 200 iterations.  Row values
     are not: fp32 rounding against the fp64 oracle adds up over 65 000 optimizer steps."""
@@ -559,9 +559,9 @@ def test_smallest_tables_and_caches(vocab, capacity):
         p.close()
 
 
-def test_ids_of_25_bits_sort_in_four_passes():
-    """A vocabulary of 20 M ids: the radix sort takes four passes (the configurations up to 4 M ids
-    take three at most)."""
+def test_ids_of_25_bits():
+    """A vocabulary of 20 M ids: the radix sort takes three passes of nine bits, where the configurations
+    up to 4 M ids take two."""
     w = wl.WORKLOADS[1].scaled(vocab=20_000_000, dim=4, batch=300, capacity=3_000, s=2, policy=wl.LFU,
                                optimizer=wl.ADAGRAD, eps=1e-8)
     st = run_workload(w, 10, state_every=2, values_every=5, prefetch="before")
