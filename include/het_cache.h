@@ -141,9 +141,10 @@ int het_cache_configure(het_cache *c, int64_t max_batch_ids, int32_t optimizer, 
  *   cg     uint32[vocab]: global clock c_g per row, zero-initialised by the caller.
  * location HET_BACKING_HBM: device pointers.  HET_BACKING_PINNED_HOST: pointers to pinned,
  * device-mapped host memory (hipHostMalloc); kernels read and write it over the host link.
- * Allocates the id->slot index, 4 bytes per row of the table (HBM; pinned host memory if HBM is full,
- * and then every Find crosses the host link); for a table in host memory also, in HBM, 12 bytes per row
- * (a mirror of cg, and where rows on their way are) and staging for three batches of rows.
+ * Allocates the id->slot index: 4 bytes per row of the table in HBM; a hash table of 32 to 64 bytes per row slot
+ * if HBM has no room for them (a step then has three small kernels more); 4 bytes per row of pinned host memory
+ * if not even for that (every Find then crosses the host link).  For a table in host memory also, in HBM, 12
+ * bytes per row (a mirror of cg, and where rows on their way are) and staging for three batches of rows.
  * The caller owns the arrays; the library reads and writes them during lookup/update/flush and
  * they must outlive the cache.  Between a lookup and the update that follows it the caller must
  * not write them (with the table in HBM the rows a lookup misses are read from it for the output

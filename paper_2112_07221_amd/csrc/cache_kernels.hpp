@@ -78,7 +78,9 @@ struct CacheView {
     // With a hash table of the cached keys (buckets of 16 entries in 128 bytes) every Find was eight 16-byte loads
     // of a line no other lane wanted, every insert and erase a search: probe 13 -> 10.4 us and eviction 13 -> 10.2 us
     // at 106496 ids; a step of 3328 ids 42.9 -> 38.1 us, of 106496 ids 74.7 -> 71.3 us, of 409600 ids in bags
-    // 316 -> 302 us.  4 bytes per row of the table, in HBM mostly a fraction of its clocks' and rows' own.
+    // 316 -> 302 us.  4 bytes per row of the table, in HBM mostly a fraction of its clocks' and rows' own; a table that
+    // leaves no room for them is searched through the hash table after all (key_hash.hpp), by a kernel before
+    // the one that asks: slot_of then holds its answers by sorted position, and the index is not kept.
     int32_t *slot_of;
     uint32_t *free_list;  // free slots in ascending order (first max_ids of them)
     uint8_t *was_free;    // per slot: free when the current lookup began (its fetches may be filling it now)
@@ -88,6 +90,7 @@ struct CacheView {
     RowGeom geom;
     int adagrad;          // element-wise Adagrad: an accumulator row beside every row
     int rowwise;          // row-wise Adagrad: one accumulator per row (acc[slot], A[key]); rows of at most one piece per lane
+    int by_position;      // what slot_of is indexed by (see there)
     int direct;           // no cache: rows/acc alias the global table, a key is its own slot, there are no clocks
 };
 
@@ -552,7 +555,7 @@ __global__ __launch_bounds__(PT_THREADS) __attribute__((amdgpu_num_sgpr(96))) vo
             finder = head || (LOOKUP && lane_id() == 0);
             if (finder) {
                 const uint32_t cg = LOOKUP ? cv.Cg[key] : 0u;        // in flight together with the probe's loads
-                const int32_t slot = cv.slot_of[key];
+                const int32_t slot = cv.slot_of[cv.by_position ? j : key];
                 int32_t src = slot == SLOT_NONE ? SRC_BACKING : slot;
                 bool valid = true;
                 uint4 m = make_uint4(0, 0, 0, 0);
@@ -918,7 +921,7 @@ __device__ __forceinline__ void ahead_list_body(const CacheView &cv, const Ahead
     if (j < ah.n) {
         key = ah.skey[j];
         const bool head = key != cv.vocab && (j == 0 || ah.skey[j - 1] != key);
-        if (head && cv.slot_of[key] == SLOT_NONE) {
+        if (head && cv.slot_of[cv.by_position ? j : key] == SLOT_NONE) {
             want = true;
             // a row the last trim evicted, whose write-back is still to come: the staged copy is the row
             const uint64_t pe = cv.hl.pend[key];
@@ -1200,7 +1203,7 @@ __global__ __launch_bounds__(256) void fill_gather_kernel(CacheView cv, Workspac
             if (cv.early_cc) cv.early_cc[slot] = fetch_mode == 1 ? cg + 1u : 0u;    // (the update that fetches the row will make it c_g + 1)
             cv.slot_key[slot] = key;
             ws.head_slot[j] = (int32_t)slot;
-            cv.slot_of[key] = (int32_t)slot;
+            if (!cv.by_position) cv.slot_of[key] = (int32_t)slot;
             // host-backed table: the gather runs after this kernel and reads the cached copy
             if (cv.Cg_host) for (uint32_t jj = j; jj < n && ws.skey[jj] == key; ++jj) ws.src[jj] = (int32_t)slot;
         }
@@ -1423,7 +1426,7 @@ __device__ __forceinline__ void evict_body(const CacheView &cv, const TrimPlan &
         tp.ev_ids[ev_at++] = k;
         const uint32_t cg = dirty[i] ? cv.Cg[k] : 0u;
         const uint32_t early = dirty[i] && cv.early_cc ? cv.early_cc[slot] : 0u;
-        cv.slot_of[k] = SLOT_NONE;
+        if (!cv.by_position) cv.slot_of[k] = SLOT_NONE;
         cv.slot_key[slot] = KEY_NONE;
         // host-backed table: rows below tau that hold updates are staged in slot order, then one
         // place per tied victim (left empty by those without updates)

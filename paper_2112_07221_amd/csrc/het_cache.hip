@@ -14,6 +14,7 @@
 #include <vector>
 
 #include "cache_kernels.hpp"
+#include "key_hash.hpp"
 #include "pattern_kernels.hpp"
 #include "static_lookup.hpp"
 
@@ -79,7 +80,8 @@ struct het_cache {
     uint32_t *tile_free[2] = {nullptr, nullptr};   // free slots per tile, left by a trim; trims alternate between the two
     int tf_last = 0;                 // the one the last trim filled (initially: every slot free)
     uint32_t *ev_ids[2] = {nullptr, nullptr};      // evicted ids of the last two trims, alternating like tile_free
-    void *index_host = nullptr;      // the key index, if it found no room in HBM
+    KeyHash key_hash{};              // the cached keys, if the index of the table's found no room in HBM
+    void *index_host = nullptr;      // that index, if neither did
     int max_chunks_per_lane = 1;     // row chunks one lane handles in the apply kernel
     std::vector<void *> owned;       // every device allocation, for destroy
     char *arena = nullptr;           // one allocation that holds all the small arrays side by side (see dev_alloc)
@@ -482,6 +484,25 @@ int settle_fetch(het_cache *c)
     return c->cv.geom.vec == 4 ? settle_fetch_impl<4>(c) : settle_fetch_impl<1>(c);
 }
 
+// Where the key index found no room in HBM, kernels of their own search, fill and clear the hash table of the cached
+// keys (key_hash.hpp): the slots of a sorted order's keys, before a kernel asks for them; the keys a lookup has
+// fetched; the keys a trim has dropped.
+void hash_find(het_cache *c, const uint32_t *skey, uint32_t n)
+{
+    if (!c->key_hash.entries) return;
+    LAUNCH(c, K_MISC, key_find_kernel<<<cdiv(n, 256), 256, 0, c->stream>>>(c->key_hash, skey, n, c->cv.vocab, c->cv.slot_of));
+}
+void hash_insert(het_cache *c, uint32_t n)
+{
+    if (!c->key_hash.entries) return;
+    LAUNCH(c, K_MISC, key_insert_kernel<<<cdiv(n, 256), 256, 0, c->stream>>>(c->key_hash, c->ws.skey, c->ws.cls, c->ws.head_slot, n, c->cv.vocab));
+}
+void hash_erase(het_cache *c, const TrimPlan &tp)
+{
+    if (!c->key_hash.entries) return;
+    LAUNCH(c, K_MISC, key_erase_kernel<<<cdiv(c->last_lookup_n, 256), 256, 0, c->stream>>>(c->key_hash, tp.ev_ids, &c->cv.ds->ev_n[tp.ev_slot]));
+}
+
 // The plan of the eviction about to be launched: which of the alternating arrays it fills.
 TrimPlan plan_eviction(het_cache *c, bool fetched_dirty)
 {
@@ -529,6 +550,7 @@ int run_trim(het_cache *c, bool counted, bool updated)
         LAUNCH(c, K_TRIM_EVICT, trim_evict_kernel<VEC, true, false><<<ride.blocks() + ev_blocks, TRIM_THREADS, lds, c->stream>>>(c->cv, tp, ride.a, ride.b));
     else
         LAUNCH(c, K_TRIM_EVICT, trim_evict_kernel<VEC, false, false><<<ev_blocks, TRIM_THREADS, lds, c->stream>>>(c->cv, tp, ride.a, ride.b));
+    hash_erase(c, tp);
     if (c->location == HET_BACKING_PINNED_HOST) { c->push_pending = true; c->push_buf = tp.ev_slot; c->push_seq = tp.push_seq; }
     return launch_ok();
 }
@@ -597,6 +619,7 @@ int run_lookup(het_cache *c, const int64_t *ids, uint32_t n, const int64_t *offs
         c->kept_key_bits = tp.key_bits;
     }
     {
+        hash_find(c, c->ws.skey, n);
         const bool beside = count_beside_fill(c, tp, n) && c->location == HET_BACKING_HBM && !c->many && !c->cv.rowwise;
         const Rides ride = probe_must_ride(c, !beside) ? next_rides(c) : Rides{no_stage(), no_stage()};
         const uint32_t blocks = ptiles + (match >= 0 ? ptiles : 0u) + stiles;
@@ -649,6 +672,7 @@ int run_lookup(het_cache *c, const int64_t *ids, uint32_t n, const int64_t *offs
         const uint32_t fb = owe ? std::min(fill_blocks, STALE_BLOCKS) : fill_blocks;
         FILL_GATHER_ANY(ride.blocks() + fb + ptiles + hist_blocks + gather_blocks, fb, hist_blocks, 0u);
         if (owe) { c->fetch_owed = true; c->owed_n = n; c->owed_t = t_now; }
+        hash_insert(c, n);
     } else {
         // Host-backed table: the fetches come over the host link, and the last trim's write-back
         // goes the other way in the same kernel; the gather follows and reads the cached copies.
@@ -673,6 +697,7 @@ int run_lookup(het_cache *c, const int64_t *ids, uint32_t n, const int64_t *offs
             FILL_GATHER_ANY(ride.blocks() + push_blocks + fetch_blocks + ptiles + hist_blocks, fetch_blocks, hist_blocks, push_blocks);
         }
         if (push_blocks) c->push_pending = false;
+        hash_insert(c, n);
         ah = Ahead{};
         if (next) {
             if (next->next_stage < sort_stages(c, next->max_bits)) {         // what is left of its sort runs now
@@ -686,6 +711,7 @@ int run_lookup(het_cache *c, const int64_t *ids, uint32_t n, const int64_t *offs
             ah.list_tag = 0x80000000u | c->pf_serial;
             ah.list_slot = c->pf_slot_next;
             ah.pending_seq = c->push_pending ? c->push_seq : 0u;
+            hash_find(c, ah.skey, ah.n);
         }
         {
             const Rides ride = next_rides(c);
@@ -748,7 +774,7 @@ bool launch_apply_tile2(het_cache *c, bool verify, const int64_t *ids, uint32_t 
 #define APPLY(MODE)                                                                                                                              \
     LAUNCH(c, K_APPLY, apply_kernel<VEC, MAXC, MODE, TILE, EARLY><<<ride.blocks() + grid + extra + (verify ? cdiv(n, VERIFY_TILE) : 0u), AP_THREADS, lds, c->stream>>>( \
                            c->cv, c->ws, c->bd, ids, grads, grad_row, lr, c->eps, n, grid, tp, extra, ride.a, ride.b, c->trace[0], fresh))
-    if (evict) APPLY(AP_REUSED_EVICT); else if (verify) APPLY(AP_REUSED); else APPLY(AP_SORTED);
+    if (evict) { APPLY(AP_REUSED_EVICT); hash_erase(c, tp); } else if (verify) APPLY(AP_REUSED); else APPLY(AP_SORTED);
 #undef APPLY
     return counted;
 }
@@ -789,9 +815,11 @@ int run_update(het_cache *c, const int64_t *ids, uint32_t n, const int64_t *offs
         use_order(c, c->sort_set, sort_bits_alone(n));
         if (c->cv.direct)
             LAUNCH(c, K_PROBE, direct_probe_kernel<false, false><<<cdiv(n, PT_TILE), PT_THREADS, 0, c->stream>>>(c->cv, c->ws, n, (uint32_t)c->t_host, cdiv(n, PT_TILE), nullptr, nullptr, no_stage(), no_stage()));
-        else
+        else {
+            hash_find(c, c->ws.skey, n);
             LAUNCH(c, K_PROBE, probe_kernel<false, false><<<cdiv(n, PT_TILE), PT_THREADS, 0, c->stream>>>(
                                    c->cv, c->ws, n, (uint32_t)c->t_host, cdiv(n, PT_TILE), nullptr, nullptr, 0u, TrimPlan{}, nullptr, -1, nullptr, no_stage(), no_stage()));
+        }
     }
     const uint32_t *grad_row = nullptr;
     if (offsets) {
@@ -979,12 +1007,38 @@ int het_cache_configure(het_cache *c, int64_t max_batch_ids, int32_t optimizer, 
     return rc;
 }
 
-// The key index: 4 bytes per row of the table, nothing cached yet.  In pinned host memory if HBM has no room for
-// it (a table that fills HBM to the last): Find then crosses the host link.
+// The hash table of the cached keys, and where its searches leave their answers.
+static int alloc_key_hash(het_cache *c)
+{
+    KeyHash &h = c->key_hash;
+    const uint32_t buckets = pow2_at_least(cdiv((uint64_t)c->cv.n_slots * 4, BUCKET_ENTRIES));
+    const size_t keep = c->owned.size(), mark = c->arena_used;
+    int rc;
+    if ((rc = dev_alloc(c, &h.entries, (size_t)buckets * BUCKET_ENTRIES)) || (rc = dev_alloc(c, &h.reach, buckets)) ||
+        (rc = dev_alloc(c, &c->cv.slot_of, (size_t)c->max_ids))) {
+        free_owned_from(c, keep, mark);
+        h.entries = nullptr;
+        return rc;
+    }
+    h.mask = buckets - 1;
+    h.shift = 64 - (bit_width(buckets) - 1);
+    static_assert(ENTRY_EMPTY == ~0ull, "filled byte by byte");
+    HIP_TRY(hipMemsetAsync(h.entries, 0xFF, (size_t)buckets * BUCKET_ENTRIES * sizeof(uint64_t), c->stream));
+    HIP_TRY(hipMemsetAsync(h.reach, 0, (size_t)buckets * sizeof(uint32_t), c->stream));
+    return HET_OK;
+}
+
+// Find's index, nothing cached yet: 4 bytes per row of the table; if HBM has no room for them (a table that fills it),
+// a hash table of the size of the cache; if not even for that, the former in pinned host memory.
 static int alloc_index(het_cache *c, int64_t vocab)
 {
     const size_t bytes = (size_t)vocab * sizeof(int32_t);
+    c->cv.by_position = 0;
+    c->key_hash.entries = nullptr;
     if (dev_alloc(c, &c->cv.slot_of, (size_t)vocab) != HET_OK) {
+        (void)hipGetLastError();
+        const int rc = alloc_key_hash(c);
+        if (rc != HET_ENOMEM) { c->cv.by_position = 1; return rc; }
         (void)hipGetLastError();
         if (hipHostMalloc(&c->index_host, bytes, hipHostMallocDefault) != hipSuccess) { (void)hipGetLastError(); c->index_host = nullptr; return HET_ENOMEM; }
         c->cv.slot_of = static_cast<int32_t *>(c->index_host);

@@ -17,7 +17,7 @@ def fill_hbm(leave):
     held = []
     while torch.cuda.mem_get_info()[0] > leave and len(held) < 64:
         held.append(torch.empty(max(2 << 20, torch.cuda.mem_get_info()[0] - leave), dtype=torch.uint8, device="cuda:0"))
-    assert 0.9 * leave < torch.cuda.mem_get_info()[0] <= leave
+    assert leave - (8 << 20) < torch.cuda.mem_get_info()[0] <= leave
     return held
 
 
@@ -83,8 +83,8 @@ def test_every_way_a_batch_is_sorted(n, vocab, ahead):
 
 @pytest.mark.parametrize("full", [False, True])
 def test_key_index_in_hbm_and_where_hbm_has_no_room(full):
-    """The index of a table's keys goes to pinned host memory if HBM has no room for it when the table is
-    attached; lookups and updates that fetch, hit and evict read the same either way (whole numbers, so sums are
+    """If HBM has no room for the index of a table's keys when the table is attached, a hash table of the cached keys
+    takes its place; lookups and updates that fetch, hit and evict read the same either way (whole numbers, so sums are
     exact)."""
     from paper_2112_07221_amd import hetcache as hc
     dev = torch.device("cuda:0")
@@ -236,7 +236,7 @@ def test_small_batches_whose_sort_was_under_way_when_their_lookup_came(n, vocab,
 
 
 def test_a_table_in_host_memory_attaches_where_hbm_has_room_for_all_but_the_key_index():
-    """What only HBM can hold is allocated before the index of the table's keys, which then takes pinned host memory."""
+    """What only HBM can hold is allocated before the index of the table's keys, which can do without."""
     from paper_2112_07221_amd import hetcache as hc
     dev = torch.device("cuda:0")
     vocab, n, cap = 64_000_000, 3_000, 2_000                          # (index and clocks 256 MB each, rows on their way 512 MB)
@@ -365,3 +365,88 @@ def test_the_iteration_count_only_goes_forward_and_not_between_a_lookup_and_its_
         p.compare_counters()
     finally:
         p.close()
+
+
+FIND_VOCAB, FIND_IDS = 64_000_000, 3_000                                  # (the direct index: 256 MB)
+# how Find works, policy, table in host memory, one of several workers, capacity
+FIND_KINDS = [("hash table", 1, True, False, 1_700), ("hash table", 0, False, False, 1_700), ("hash table", 1, False, False, 1_700),
+              ("hash table", 3, False, True, 1_700), ("index in host memory", 1, False, False, 400_000)]
+
+
+@pytest.fixture(scope="module")
+def find_pairs():
+    """Of every kind a cache with its index in HBM and one attached when HBM was full, over tables of their own."""
+    from paper_2112_07221_amd import hetcache as hc
+    dev = torch.device("cuda:0")
+    pairs = []
+    for where, policy, host, many, cap in FIND_KINDS:
+        dim, pair = 2 if host else 4, []
+        for k in range(2):
+            make = (lambda *a, **kw: torch.zeros(*a, **kw).pin_memory()) if host else (lambda *a, **kw: torch.zeros(*a, device=dev, **kw))
+            pair.append((hc.HetCache(cap, dim, 4, policy, FIND_IDS, hc.OPT_SGD, many_writers=many), make(FIND_VOCAB, dim), make(FIND_VOCAB, dtype=torch.int32)))
+        pairs.append(pair)
+
+    def attach(entry, host):
+        before = torch.cuda.mem_get_info()[0]
+        entry[0].attach_backing(entry[1], None, entry[2], hc.BACKING_PINNED_HOST if host else hc.BACKING_HBM)
+        return before - torch.cuda.mem_get_info()[0] - (768_000_000 if host else 0)         # (mirror of the clocks, rows on their way)
+
+    try:
+        for pair, (_, _, host, _, _) in zip(pairs, FIND_KINDS):
+            assert attach(pair[0], host) > 230_000_000
+        filler = [fill_hbm(990_000_000)]
+        for pair, (where, _, host, _, _) in zip(pairs, FIND_KINDS):
+            if where == "index in host memory":
+                filler.append(fill_hbm(8 << 20))                          # (no room for a hash table of 17 MB either)
+            assert abs(attach(pair[1], host)) < 50_000_000
+        del filler
+        torch.cuda.empty_cache()
+        yield pairs
+    finally:
+        for pair in pairs:
+            for entry in pair:
+                entry[0].close()
+
+
+@pytest.mark.parametrize("kind", range(len(FIND_KINDS)), ids=["-".join(map(str, k[:4])) for k in FIND_KINDS])
+def test_find_without_room_for_the_key_index_agrees_with_the_index(find_pairs, kind):
+    """Where HBM has no room for 4 bytes per row of the table, a hash table of the cached keys is searched, or the index
+    in host memory: the same calls on a cache that has its index in HBM give the same bits everywhere.  Announced and
+    other batches, lookups that follow lookups, updates with other ids, flushes."""
+    dev = torch.device("cuda:0")
+    _, policy, host, _, cap = FIND_KINDS[kind]
+    caches, tables, clocks = zip(*find_pairs[kind])
+    n, vocab, dim, steps = FIND_IDS, FIND_VOCAB, tables[0].shape[1], 14
+    rng = np.random.default_rng(kind)
+    ids = [np.where(rng.random(n) < 0.6, rng.integers(0, 900, n) * 71_111, rng.integers(0, vocab, n)) for _ in range(steps)]
+    for t in range(3, steps, 3):
+        ids[t][:800] = ids[t - 1][:800]
+    ids[5][7] = vocab
+    d = [torch.from_numpy(x).to(dev) for x in ids]
+    part = [x[::3].flip(0).contiguous() for x in d]
+    grads = [torch.randn(n, dim, device=dev) for _ in range(3)]
+    outs = [torch.empty(n, dim, device=dev) for _ in caches]
+    for t, what in enumerate("uulupufuulpufu"):                           # update; lookup next; update of a part of the ids; flush first
+        for c, out in zip(caches, outs):
+            if t + 1 < steps and t % 4:
+                c.prefetch(d[t + 1])
+            c.lookup(d[t], out)
+        assert torch.equal(outs[0], outs[1])
+        assert all(np.array_equal(a, b) for a, b in zip(caches[0].last_lookup(), caches[1].last_lookup()))
+        if what == "l":
+            continue
+        for c in caches:
+            if what == "f":
+                c.flush()
+            x = part[t] if what == "p" else d[t]
+            c.update(x, grads[t % 3][: x.numel()], 0.5)
+        assert np.array_equal(np.sort(caches[0].last_evicted()), np.sort(caches[1].last_evicted()))
+        a, b = caches[0].export_state(), caches[1].export_state()
+        assert all(np.array_equal(a[col], b[col]) for col in a)
+        assert caches[0].stats() == caches[1].stats()
+    total = caches[0].stats()["total"]
+    assert total["hit"] > 5_000 and total["miss"] > 10_000 and (total["evicted"] > 10_000 or cap > 100_000)
+    for c in caches:
+        c.flush()
+    assert np.array_equal(caches[0].export_rows()[0], caches[1].export_rows()[0])
+    assert torch.equal(tables[0], tables[1]) and torch.equal(clocks[0], clocks[1])
