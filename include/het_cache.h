@@ -311,11 +311,11 @@ const char *het_profile_kernel_name(int index);
  * "fill_gather_kernel" (het_lookup's second kernel).  While `records` (device memory,
  * HET_TRACE_WORDS uint64 per workgroup, room for `capacity` workgroups, zeroed by the caller) is
  * set, every launch of that kernel writes per workgroup: [0] start, [5] the last wave's end,
- * [6] role.  apply_kernel: roles 1 carried sort stage, 2 select stage, 3 id check, 4 tile of the
- * update; for role 4 also [1] tile loaded and segments listed, [2] short segments done, [3] long
+ * [6] role.  apply_kernel: roles 1 carried sort stage, 2 eviction or the count before it, 3 id check,
+ * 4 tile of the update; for role 4 also [1] tile loaded and segments listed, [2] short segments done, [3] long
  * segments done, [4] past the barrier before the runs that cross tile borders (as far as the
  * workgroup got).  fill_gather_kernel: roles 1 carried sort stage, 2 fetch, 3 the fetched keys'
- * bookkeeping, 4 select stage, 5 gather, 6 host link.  Clock: the GPU's constant 100 MHz counter.
+ * bookkeeping, 4 count of the rows to evict, 5 gather, 6 host link.  Clock: the GPU's constant 100 MHz counter.
  * A later launch overwrites the records.  capacity 0 (records ignored) switches the stamps off
  * again.  They cost a few stores per workgroup: not for timed regions.  HET_EINVAL for a bad
  * argument.

@@ -164,7 +164,7 @@ struct TrimPlan {
     int ev_slot;                       // which of the two evicted-id counts (and staging buffers) this trim appends to
     uint32_t push_seq;                 // host-backed table: serial number of this trim (never 0)
     int fetched_dirty;                 // the count ran beside the lookup's fetches, and the batch has been updated since
-    uint32_t dirty_stamp;              // the tie count runs beside the optimizer step of the Read of this iteration's keys (0: it does not):
+    uint32_t dirty_stamp;              // the count runs beside the optimizer step of the Read of this iteration's keys (0: it does not):
                                        // every row that Read touched will hold updates when the step is done, whether its clock has moved yet or not
 };
 
@@ -743,15 +743,6 @@ __device__ __forceinline__ void pull_row(const CacheView &cv, uint32_t key, uint
     if (cv.adagrad)
         row_copy<VEC>(cv.acc + (size_t)slot * g.dim, cv.A + (size_t)key * g.dim, g.chunks, g.lanes, gl);
     if (cv.rowwise && gl == 0) cv.acc[slot] = cv.A[key];
-}
-
-// The same from explicit sources (a staged row).
-template <int VEC>
-__device__ __forceinline__ void pull_row_from(const CacheView &cv, const float *row, const float *acc, uint32_t slot, int gl)
-{
-    const RowGeom g = cv.geom;
-    row_copy<VEC>(cv.rows + (size_t)slot * g.dim, row, g.chunks, g.lanes, gl);
-    if (cv.adagrad) row_copy<VEC>(cv.acc + (size_t)slot * g.dim, acc, g.chunks, g.lanes, gl);
 }
 
 // Host-backed table: writes the rows staged by trim `buf` to the global table, with their clocks.
@@ -1688,8 +1679,12 @@ struct SegWork {
     bool is_front, is_back;    // the run began in an earlier tile / goes on in a later one
 };
 
-// A row piece's store.  STREAM: past the L2, which rows of 512 bytes and more, written once a step, would only clear of
-// the gradients (114688 ids of 128 floats 92.0 -> 90.9 us a step; 409600 ids in bags, 256 floats, 237.6 -> 237.3).
+// A row piece's store.  STREAM: past the L2, which rows written once a step would only clear of the gradients.  Used by
+// the variants that push early (rows of more than 64 floats in whole 16-byte pieces, table in HBM, one worker), the
+// last step of a run over several tiles excepted.  On one box, each side's runs within 0.1 %: 114688 ids of 128 floats, SGD,
+// 91.9 -> 90.8 us a step, 409600 ids in bags, 256 floats, 237.1 -> 236.7; steps of 12 million floats with SGD /
+// Adagrad: rows of 68 floats 58.6 / 67.1 -> 58.7 / 66.8, 100 67.4 / 80.3 -> 67.4 / 80.0, 124 70.5 / 85.3 -> 70.4 / 84.5, 132
+// 86.3 / 94.1 -> 86.6 / 94.1, 256 80.3 / 88.2 -> 79.8 / 87.4, 512 110.7 / 124.4 -> 110.6 / 124.9.
 template <int VEC, bool STREAM>
 __device__ __forceinline__ void store_piece(typename VecT<VEC>::type *p, const typename VecT<VEC>::type &v)
 {

@@ -149,13 +149,4 @@ __device__ __forceinline__ void row_copy(float *dst, const float *src, int chunk
     for (int c = gl; c < chunks; c += lanes) d[c] = s[c];
 }
 
-template <int VEC>
-__device__ __forceinline__ void row_zero(float *dst, int chunks, int lanes, int gl)
-{
-    using V = typename VecT<VEC>::type;
-    V *d = reinterpret_cast<V *>(dst);
-    V z{};
-    for (int c = gl; c < chunks; c += lanes) d[c] = z;
-}
-
 } // namespace het

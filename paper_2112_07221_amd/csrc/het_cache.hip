@@ -273,11 +273,13 @@ SortPlan make_sort_plan(const het_cache *c, uint32_t n, int set, int max_bits)
     return sp;
 }
 
-// Digits of an announced batch's sort.  A batch announced one ahead meets three or four kernels that carry a
-// stage before its lookup: two wide passes are (nearly) all carried.  Announced two ahead
-// it meets them twice: narrow digits are carried just as completely, and their stages are shorter and
+// Digits of an announced batch's sort.  A step has two kernels that carry a stage (the lookup's second one and the
+// update), three where the eviction has one of its own, and the probe for what these cannot (probe_must_ride).
+// A batch announced one ahead meets them once: two wide passes are (nearly) all carried.  Announced two ahead
+// it meets them twice: six narrow stages are carried just as completely, and they are shorter and
 // need less LDS, so the carrying kernels keep their occupancy (114688 ids of 22 bits: the update 40 us with
-// stages of 8 bits, 48 us with stages of 11).
+// stages of 8 bits, 48 us with stages of 11).  With the eviction beside the update that takes the probe in every
+// step (106496 ids: 12.1 us, 7.7 without a stage; 409600 ids: 29.8 and 18.2).
 int sort_bits_ahead(const het_cache *c, uint32_t n)
 {
     const int carried = c->n_ann >= 2 ? 6 : 0;
@@ -382,8 +384,9 @@ uint32_t lds_bytes(size_t own, const Rides &r, int threads = SORT_THREADS)
 }
 
 // Must the probe carry a stage?  The kernels behind it carry them for less (the probe's workgroups are large ones of
-// its own size: 409600 ids 311 -> 328 us a step where nothing needed it), so only where an announced batch would
-// meet too few of those before its lookup: 2 or 3 a step (with the eviction beside the update, or none, or in a kernel of its own).
+// its own size: 409600 ids 311 -> 328 us a step where nothing needed it, while the eviction still had a kernel of its
+// own), so only where an announced batch would meet too few of those before its lookup: 2 or 3 a step (with the
+// eviction beside the update, or none, or in a kernel of its own).
 bool probe_must_ride(const het_cache *c, bool evict_kernel)
 {
     for (int a = 0; a < c->n_ann; ++a)
@@ -934,8 +937,8 @@ static int configure_impl(het_cache *c, int64_t max_batch_ids, int32_t optimizer
     if (!direct && cv.adagrad && (rc = dev_alloc(c, &cv.acc, row_elems))) return rc;
     if (!direct && cv.rowwise && (rc = dev_alloc(c, &cv.acc, (size_t)P))) return rc;
     cv.many = c->many;
-    // Early push where rows have 128 floats or more (measured: config 4 1.4 %, config 5 6 % faster; with
-    // rows of 64 floats the update loses what the eviction gains).
+    // Early push where rows have more than 64 floats, in whole 16-byte pieces (measured: rows of 128 floats 1.4 %,
+    // of 256 floats 6 % faster; with rows of 64 floats the update loses what the eviction gains).
     if (!direct && !c->many && !cv.rowwise && g.vec == 4 && g.lanes >= 32) {          // (dropped again at attach if the table is behind the host link)
         if ((rc = dev_alloc(c, &cv.early_cc, (size_t)P))) return rc;
         HIP_TRY(hipMemsetAsync(cv.early_cc, 0, (size_t)P * sizeof(uint32_t), c->stream));
