@@ -41,6 +41,7 @@ struct Announced {
     int set = 0;
     int max_bits = 0;                // widest digit its sort may use (see sort_bits_ahead)
     int next_stage = 0;              // stages [0, next_stage) are enqueued; 2 * passes stages in all
+    int result = -1;                 // the buffer that holds the finished order (-1: not finished by sort_now)
 };
 
 struct het_cache {
@@ -331,21 +332,45 @@ void launch_solo(het_cache *c, const SortStage &s, uint32_t *keys_out, uint32_t 
                                 keys_out, idx_out));
 }
 
-// What is left of a sort (stages [first_stage, end)), in kernels of its own; or, for a small batch, by
-// one workgroup in one launch.  That one's time is the ballots' on one compute unit and
-// grows with the ids (20 bits: 4.9 us for 200, 7.7 for 2048, 11.9 for 4096, 19.9 for 8192), a stage's hardly does
-// (3.3 us histogram, 6.8 us scatter): SOLO_MAX ids against four stages, proportionally fewer against fewer.
-void sort_now(het_cache *c, const int64_t *ids, uint32_t n, int set, int max_bits, int first_stage)
+// A batch sorted in ranges (see SortRanges): its plan.  The tiles' order lies in buffer 0, the result in buffer 1, and what
+// the launches hand on where the general sort has its histograms.  Ranges for 400 to 1000 keys each: 26624 ids
+// 12.4 us with 64, 12.6 with 128; 53248 ids 14.9 and 14.2; 106496 ids 19.3 and 18.9.
+SortRanges make_ranges(const het_cache *c, uint32_t n, int set)
 {
-    const int end = sort_stages(c, max_bits);
+    SortRanges sr{};
+    sr.n = n; sr.vocab = c->cv.vocab;
+    sr.ranges = n <= 32768 ? 64 : SR_MAX_RANGES;
+    sr.ntiles = cdiv(n, SORT_TILE);
+    sr.cuts = c->sort_hist[set];
+    sr.begin = reinterpret_cast<uint16_t *>(sr.cuts + SR_MAX_RANGES);
+    sr.keys = c->keys[set][0]; sr.idx = c->idx[set][0];
+    return sr;
+}
+
+// What is left of a sort (stages [first_stage, end)), in kernels of its own.  Up to SOLO_MAX ids by one workgroup in one
+// launch: its time is the ballots' on one compute unit and grows with the ids (20 bits: 4.9 us for 200,
+// 7.7 for 2048, 11.9 for 4096, 19.9 for 8192).  Up to SR_MAX ids in ranges, if three stages or more are left: two
+// launches from the ids, or the keys that stage 0 left, against a stage's 3.3 us (histogram) and 6.8 us (scatter): 8658 ids
+// 11.7 us, 26624 12.4 (four stages 22), 53248 14.2 (24), 106496 18.9 (25), 200000 26.5 (31; but there a range
+// now and then holds more than a workgroup sorts at a time, and then it is 70).
+// Returns which buffer of the set holds the order.
+int sort_now(het_cache *c, const int64_t *ids, uint32_t n, int set, int max_bits, int first_stage)
+{
+    const int end = sort_stages(c, max_bits), result = sort_result_buffer(c, max_bits);
+    if (end - first_stage >= 3 && n > SOLO_ALONE && n <= SR_MAX) {
+        const SortRanges sr = make_ranges(c, n, set);
+        LAUNCH(c, K_SORT_STAGE, sort_part_kernel<<<sr.ntiles, SOLO_THREADS, 0, c->stream>>>(ids, first_stage > 0 ? c->keys[set][1] : nullptr, sr));
+        LAUNCH(c, K_SORT_STAGE, sort_range_kernel<<<sr.ranges, SOLO_THREADS, sizeof(SortRangeLds), c->stream>>>(sr, c->keys[set][1], c->idx[set][1]));
+        return 1;
+    }
     if (3ull * n <= (uint64_t)SOLO_MAX * (uint32_t)std::max(0, std::min(3, end - first_stage - 1))) {
         const SortStage s = make_stage(c, ids, n, set, max_bits, first_stage);
-        uint32_t *k = c->keys[set][sort_result_buffer(c, max_bits)], *i = c->idx[set][sort_result_buffer(c, max_bits)];
+        uint32_t *k = c->keys[set][result], *i = c->idx[set][result];
         if (n <= SOLO_THREADS) launch_solo<1>(c, s, k, i);
         else if (n <= 2 * SOLO_THREADS) launch_solo<2>(c, s, k, i);
         else if (n <= 4 * SOLO_THREADS) launch_solo<4>(c, s, k, i);
         else launch_solo<8>(c, s, k, i);
-        return;
+        return result;
     }
     for (int st = first_stage; st < end; ++st) {
         const SortStage s = make_stage(c, ids, n, set, max_bits, st);
@@ -354,6 +379,7 @@ void sort_now(het_cache *c, const int64_t *ids, uint32_t n, int set, int max_bit
         else
             LAUNCH(c, K_SORT_STAGE, sort_stage_kernel<SORT_THREADS><<<s.blocks, SORT_THREADS, sort_stage_lds_bytes(s.sp.width, s.sp.super, s.stage, SORT_THREADS), c->stream>>>(s));
     }
+    return result;
 }
 
 // The next stage of the oldest announced batch whose sort is not complete yet, for the kernel
@@ -412,9 +438,8 @@ void drop_oldest_announcement(het_cache *c)
     c->n_ann -= 1;
 }
 
-void use_order(het_cache *c, int set, int max_bits)
+void use_order(het_cache *c, int set, int buf)
 {
-    const int buf = sort_result_buffer(c, max_bits);
     c->sort_set = set;
     c->ws.skey = c->keys[set][buf];
     c->ws.perm = c->idx[set][buf];
@@ -576,11 +601,9 @@ int run_lookup(het_cache *c, const int64_t *ids, uint32_t n, const int64_t *offs
         for (int a = 0; a < match; ++a) drop_oldest_announcement(c);
         const Announced an = c->ann[0];
         drop_oldest_announcement(c);
-        sort_now(c, ids, n, an.set, an.max_bits, an.next_stage);
-        use_order(c, an.set, an.max_bits);
+        use_order(c, an.set, an.result >= 0 ? an.result : sort_now(c, ids, n, an.set, an.max_bits, an.next_stage));
     } else {
-        sort_now(c, ids, n, c->sort_set, sort_bits_alone(n), 0);             // over the previous batch's order: it is not needed any more
-        use_order(c, c->sort_set, sort_bits_alone(n));
+        use_order(c, c->sort_set, sort_now(c, ids, n, c->sort_set, sort_bits_alone(n), 0));             // over the previous batch's order: it is not needed any more
     }
     const uint32_t t_now = (uint32_t)c->t_host;
     if (c->cv.direct) {
@@ -703,12 +726,12 @@ int run_lookup(het_cache *c, const int64_t *ids, uint32_t n, const int64_t *offs
         hash_insert(c, n);
         ah = Ahead{};
         if (next) {
-            if (next->next_stage < sort_stages(c, next->max_bits)) {         // what is left of its sort runs now
-                sort_now(c, next->ids, next->n, next->set, next->max_bits, next->next_stage);
+            if (next->result < 0) {                                          // what is left of its sort runs now
+                next->result = sort_now(c, next->ids, next->n, next->set, next->max_bits, next->next_stage);
                 next->next_stage = sort_stages(c, next->max_bits);
             }
             c->pf_serial = (c->pf_serial % 0x7FFFFFFFu) + 1;
-            ah.skey = c->keys[next->set][sort_result_buffer(c, next->max_bits)];
+            ah.skey = c->keys[next->set][next->result];
             ah.n = next->n;
             ah.blocks = cdiv(next->n, 256);
             ah.list_tag = 0x80000000u | c->pf_serial;
@@ -814,8 +837,7 @@ int run_update(het_cache *c, const int64_t *ids, uint32_t n, const int64_t *offs
     const bool reuse = c->order_valid && ids == c->order_ids && n == c->order_n;
     if (!reuse) {
         if ((rc = settle_fetch(c)) != HET_OK) return rc;
-        sort_now(c, ids, n, c->sort_set, sort_bits_alone(n), 0);
-        use_order(c, c->sort_set, sort_bits_alone(n));
+        use_order(c, c->sort_set, sort_now(c, ids, n, c->sort_set, sort_bits_alone(n), 0));
         if (c->cv.direct)
             LAUNCH(c, K_PROBE, direct_probe_kernel<false, false><<<cdiv(n, PT_TILE), PT_THREADS, 0, c->stream>>>(c->cv, c->ws, n, (uint32_t)c->t_host, cdiv(n, PT_TILE), nullptr, nullptr, no_stage(), no_stage()));
         else {
@@ -992,6 +1014,7 @@ static int configure_impl(het_cache *c, int64_t max_batch_ids, int32_t optimizer
     HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(&sort_stage_kernel<SORT_THREADS_ALONE>), hipFuncAttributeMaxDynamicSharedMemorySize, max_lds));
     HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(&probe_kernel<true, true>), hipFuncAttributeMaxDynamicSharedMemorySize, max_lds - 16 * 1024));      // (it has LDS of its own)
     HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(&direct_probe_kernel<true, true>), hipFuncAttributeMaxDynamicSharedMemorySize, max_lds - 16 * 1024));
+    HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(&sort_range_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, max_lds));
     HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(&sort_solo_kernel<8>), hipFuncAttributeMaxDynamicSharedMemorySize, max_lds));
     HIP_TRY(hipMemsetAsync(c->bd.arrived, 0, ap_tiles * 3 * sizeof(uint32_t), c->stream));
     HIP_TRY(hipMemsetAsync(cv.ds, 0, sizeof(DState), c->stream));

@@ -81,6 +81,62 @@ def test_every_way_a_batch_is_sorted(n, vocab, ahead):
         cache.close()
 
 
+def drawn_positions(n):
+    """The positions whose ids cut a batch into ranges (sort_part_kernel's sample)."""
+    t = np.arange(256, dtype=np.uint64)
+    lo, hi = t * n // 256, (t + 1) * n // 256
+    return (lo + ((t * 0x9E3779B9 % 2**32) * (hi - lo) >> np.uint64(32))).astype(np.int64)
+
+
+@pytest.mark.parametrize("policy", [0, 2])
+@pytest.mark.parametrize("n,vocab", [(4_097, 2_100), (9_000, 3_000_000), (32_768, 1_000_000), (32_769, 4_000_000), (131_072, 70_000)])
+def test_batches_sorted_in_ranges(n, vocab, policy):
+    """Ranges of one key, of no key and of more keys than a workgroup sorts at a time (all drawn positions hold other keys
+    than the rest of the batch), ids outside the vocabulary, keys at both ends of it.  Whole numbers and lr 1, so rows are exact."""
+    from paper_2112_07221_amd import hetcache as hc
+    dev = torch.device("cuda:0")
+    rng = np.random.default_rng(n)
+    drawn = drawn_positions(n)
+    misled = rng.integers(vocab // 2, vocab // 2 + min(vocab // 2, 3 * n), n)
+    misled[rng.random(n) < 0.3] = vocab // 2 + 5
+    misled[drawn] = rng.integers(0, 256, 256)
+    popular = np.minimum((rng.random(n) ** 4 * vocab).astype(np.int64), vocab - 1)
+    popular[rng.random(n) < 0.4] = vocab - 1
+    popular[rng.random(n) < 0.2] = 0
+    bad = rng.integers(0, vocab, n)
+    bad[rng.random(n) < 0.3] = -7
+    bad[rng.random(n) < 0.1] = vocab
+    bad[0] = 1 << 40
+    same = np.full(n, vocab // 3)
+    batches = [rng.integers(0, vocab, n), misled, popular, same, np.sort(misled), bad, np.full(n, -1), popular[::-1].copy()]
+    table, want = torch.zeros(vocab, 4, device=dev), np.zeros((vocab, 4))
+    cache = hc.HetCache(1 if policy == 2 else n // 3, 4, 100, policy, n, hc.OPT_SGD)
+    try:
+        cache.attach_backing(table, None, torch.zeros(vocab, dtype=torch.int32, device=dev))
+        out = torch.empty(n, 4, device=dev)
+        for t, ids in enumerate(batches):
+            d, g = torch.from_numpy(ids).to(dev), rng.integers(-8, 9, (n, 4)).astype(np.float32)
+            cache.lookup(d, out)
+            ok = (ids >= 0) & (ids < vocab)
+            got = out.cpu().numpy()
+            assert np.array_equal(got[ok], want[ids[ok]]) and not got[~ok].any(), t
+            assert np.array_equal(cache.last_lookup()[0], np.unique(ids[ok])), t
+            cache.update(d, torch.from_numpy(g).to(dev), 1.0)
+            np.add.at(want, ids[ok], -g[ok].astype(np.float64))
+        assert cache.flush() == hc.HET_ERANGE                          # (the ids outside)
+        assert np.array_equal(table.cpu().numpy(), want.astype(np.float32))
+    finally:
+        cache.close()
+
+
+@pytest.mark.parametrize("policy,s", [(0, 3), (1, 3), (3, 0)])
+@pytest.mark.parametrize("batch,vocab,capacity", [(158, 60_000, 9_000), (1_260, 300_000, 20_000), (1_261, 300_000, 40_000)])
+def test_lookups_of_batches_sorted_in_ranges(batch, vocab, capacity, policy, s):
+    """Classes, slots, clocks and victims of batches nobody announced, of 64 and of 128 ranges."""
+    w = wl.WORKLOADS[1].scaled(batch=batch, vocab=vocab, capacity=capacity, s=s, policy=policy, dim=8)
+    run_workload(w, 7, state_every=1)
+
+
 @pytest.mark.parametrize("full", [False, True])
 def test_key_index_in_hbm_and_where_hbm_has_no_room(full):
     """If HBM has no room for the index of a table's keys when the table is attached, a hash table of the cached keys
