@@ -69,6 +69,7 @@ struct het_cache {
     uint32_t *keys[SORT_SETS][2] = {}, *idx[SORT_SETS][2] = {};
     uint32_t *sort_hist[SORT_SETS] = {};
     int sort_set = 0;                // the set that holds the current batch's order
+    uint32_t sorted_n = 0;           // how many ids that order has (0: there is none yet)
     Announced ann[SORT_SETS - 1];    // announced batches, oldest first
     int n_ann = 0;
     TrimPlan sel_tp{};               // the select plan of the rows now cached (fixed at the lookup)
@@ -333,26 +334,27 @@ void launch_solo(het_cache *c, const SortStage &s, uint32_t *keys_out, uint32_t 
 }
 
 // A batch sorted in ranges (see SortRanges): its plan.  The tiles' order lies in buffer 0, the result in buffer 1, and what
-// the launches hand on where the general sort has its histograms.  Ranges for 400 to 1000 keys each: 26624 ids
-// 12.4 us with 64, 12.6 with 128; 53248 ids 14.9 and 14.2; 106496 ids 19.3 and 18.9.
+// the launches hand on where the general sort has its histograms.  Ranges for some 500 keys each.
+// The order sorted before tells where ranges begin, unless it lies where the tiles' order goes.
 SortRanges make_ranges(const het_cache *c, uint32_t n, int set)
 {
     SortRanges sr{};
     sr.n = n; sr.vocab = c->cv.vocab;
-    sr.ranges = n <= 32768 ? 64 : SR_MAX_RANGES;
+    sr.ranges = n <= 16384 ? 64 : (n <= 65536 ? 128 : SR_MAX_RANGES);
     sr.ntiles = cdiv(n, SORT_TILE);
     sr.cuts = c->sort_hist[set];
     sr.begin = reinterpret_cast<uint16_t *>(sr.cuts + SR_MAX_RANGES);
     sr.keys = c->keys[set][0]; sr.idx = c->idx[set][0];
+    if (c->sorted_n && c->ws.skey != sr.keys) { sr.known = c->ws.skey; sr.n_known = c->sorted_n; }
     return sr;
 }
 
 // What is left of a sort (stages [first_stage, end)), in kernels of its own.  Up to SOLO_MAX ids by one workgroup in one
 // launch: its time is the ballots' on one compute unit and grows with the ids (20 bits: 4.9 us for 200,
 // 7.7 for 2048, 11.9 for 4096, 19.9 for 8192).  Up to SR_MAX ids in ranges, if three stages or more are left: two
-// launches from the ids, or the keys that stage 0 left, against a stage's 3.3 us (histogram) and 6.8 us (scatter): 8658 ids
-// 11.7 us, 26624 12.4 (four stages 22), 53248 14.2 (24), 106496 18.9 (25), 200000 26.5 (31; but there a range
-// now and then holds more than a workgroup sorts at a time, and then it is 70).
+// launches from the ids, or the keys that stage 0 left, against a stage's 3.3 us (histogram) and 6.8 us (scatter): 26624 ids
+// 12.6 us (four stages 22), 53248 13.2 (24), 106496 15.7 (25).  With cuts from a sample, not from an order sorted before,
+// 106496 ids take 18.9.
 // Returns which buffer of the set holds the order.
 int sort_now(het_cache *c, const int64_t *ids, uint32_t n, int set, int max_bits, int first_stage)
 {
@@ -438,8 +440,9 @@ void drop_oldest_announcement(het_cache *c)
     c->n_ann -= 1;
 }
 
-void use_order(het_cache *c, int set, int buf)
+void use_order(het_cache *c, int set, int buf, uint32_t n)
 {
+    c->sorted_n = n;
     c->sort_set = set;
     c->ws.skey = c->keys[set][buf];
     c->ws.perm = c->idx[set][buf];
@@ -601,9 +604,9 @@ int run_lookup(het_cache *c, const int64_t *ids, uint32_t n, const int64_t *offs
         for (int a = 0; a < match; ++a) drop_oldest_announcement(c);
         const Announced an = c->ann[0];
         drop_oldest_announcement(c);
-        use_order(c, an.set, an.result >= 0 ? an.result : sort_now(c, ids, n, an.set, an.max_bits, an.next_stage));
+        use_order(c, an.set, an.result >= 0 ? an.result : sort_now(c, ids, n, an.set, an.max_bits, an.next_stage), n);
     } else {
-        use_order(c, c->sort_set, sort_now(c, ids, n, c->sort_set, sort_bits_alone(n), 0));             // over the previous batch's order: it is not needed any more
+        use_order(c, c->sort_set, sort_now(c, ids, n, c->sort_set, sort_bits_alone(n), 0), n);             // over the previous batch's order: it is not needed any more
     }
     const uint32_t t_now = (uint32_t)c->t_host;
     if (c->cv.direct) {
@@ -837,7 +840,7 @@ int run_update(het_cache *c, const int64_t *ids, uint32_t n, const int64_t *offs
     const bool reuse = c->order_valid && ids == c->order_ids && n == c->order_n;
     if (!reuse) {
         if ((rc = settle_fetch(c)) != HET_OK) return rc;
-        use_order(c, c->sort_set, sort_now(c, ids, n, c->sort_set, sort_bits_alone(n), 0));
+        use_order(c, c->sort_set, sort_now(c, ids, n, c->sort_set, sort_bits_alone(n), 0), n);
         if (c->cv.direct)
             LAUNCH(c, K_PROBE, direct_probe_kernel<false, false><<<cdiv(n, PT_TILE), PT_THREADS, 0, c->stream>>>(c->cv, c->ws, n, (uint32_t)c->t_host, cdiv(n, PT_TILE), nullptr, nullptr, no_stage(), no_stage()));
         else {

@@ -464,17 +464,18 @@ __global__ __launch_bounds__(SOLO_THREADS) void sort_solo_kernel(const int64_t *
 }
 
 // The sort of a batch of middling size in two launches.  The keys are divided into ranges that hold about equally many:
-// a range begins at a quantile of a sample, which every workgroup draws for itself (the same one).  A key that
-// fills several ranges by itself gets one of its own.
+// a range begins at a quantile of the order sorted before this one or, if that turns out not to divide these keys
+// evenly, of a sample, which every workgroup draws for itself (the same one).  A key that fills several ranges by itself
+// gets one of its own.  Where the ranges begin decides nothing but how long this takes.
 // First (sort_part_kernel) every tile of 1024 keys is put in order of the ranges, in its own place, and leaves where each
 // range begins in it.  Then (sort_range_kernel) a workgroup per range collects its keys from all the tiles, whose
 // beginnings in the tiles add up to the range's beginning in the order, and sorts them as a small batch is sorted.
-// Against four stages of the general sort that is two kernel boundaries and one pass over memory less: 26624 ids 22 -> 12.4
-// us, 106496 ids 25 -> 18.9.  What bounds it: barriers, the ballots' vector instructions, the fullest range (at 106496 ids it
-// holds four times the mean and takes 9.7 us where the others take 5.4).
+// Against four stages of the general sort that is two kernel boundaries and one pass over memory less: 26624 ids 22 -> 12.6
+// us, 106496 ids 25 -> 15.7 (18.9 with cuts from the sample: the fullest range holds four times the mean).  What bounds it:
+// barriers and the ballots' vector instructions.
 constexpr uint32_t SR_SAMPLE = 256;                      // keys drawn
-constexpr uint32_t SR_MAX_RANGES = 128;
-constexpr uint32_t SR_MAX_TILES = 128;
+constexpr uint32_t SR_MAX_RANGES = 256;
+constexpr uint32_t SR_MAX_TILES = 256;
 constexpr uint32_t SR_MAX = SR_MAX_TILES * SORT_TILE;    // ids of a batch
 constexpr uint32_t SR_LIST = 8 * SOLO_THREADS;           // keys a workgroup sorts at a time
 
@@ -483,10 +484,13 @@ struct SortRanges {
     uint32_t *cuts;                          // [ranges]: where each begins
     uint16_t *begin;                         // [ranges][ntiles]: where each begins in each tile
     uint32_t *keys, *idx;                    // the tiles in order of the ranges
+    const uint32_t *known;                   // an order sorted before, or nullptr
+    uint32_t n_known;
 };
 
 struct SortPartLds {
     uint32_t sample[SR_SAMPLE], rank[SR_SAMPLE], at_rank[SR_SAMPLE], cuts[SR_MAX_RANGES];
+    uint32_t drawn_in[SR_MAX_RANGES];
     uint32_t base[SR_MAX_RANGES], scan[SOLO_WAVES];
     uint16_t hist[SOLO_WAVES * SR_MAX_RANGES];
 };
@@ -498,7 +502,8 @@ __global__ __launch_bounds__(SOLO_THREADS) void sort_part_kernel(const int64_t *
     const uint32_t t = threadIdx.x, w = t / WAVE, lane = lane_id(), tile = blockIdx.x, n = sr.n;
     const uint32_t i = tile * SORT_TILE + t;
     const bool in = i < n;
-    uint32_t key, drawn = 0;
+    uint32_t key, drawn = 0, known = 0;
+    if (sr.known && t && t < sr.ranges) known = sr.known[(uint64_t)t * sr.n_known / sr.ranges];
     {
         // (one position out of every n / SR_SAMPLE, not always the same: ids that come by fields have a period)
         uint32_t at = 0;
@@ -517,52 +522,71 @@ __global__ __launch_bounds__(SOLO_THREADS) void sort_part_kernel(const int64_t *
         }
     }
     if (t < SR_SAMPLE) { l.sample[t] = drawn; l.rank[t] = 0; l.at_rank[t] = 0; }
+    if (t < sr.ranges) { l.cuts[t] = known; l.drawn_in[t] = 0; }
     for (uint32_t b = t; b < SOLO_WAVES * sr.ranges / 2; b += SOLO_THREADS) reinterpret_cast<uint32_t *>(l.hist)[b] = 0;
     __syncthreads();
-    {   // how many drawn keys lie below each
-        const uint32_t mine = l.sample[t % SR_SAMPLE];
-        const uint4 *v = reinterpret_cast<const uint4 *>(l.sample) + t / SR_SAMPLE * (SR_SAMPLE / 16);
-        uint32_t r = 0;
-#pragma unroll
-        for (uint32_t q = 0; q < SR_SAMPLE / 16; ++q) {
-            const uint4 o = v[q];
-            r += (o.x < mine) + (o.y < mine) + (o.z < mine) + (o.w < mine);
+    // the range of a key: the last that begins at or below it, or, if the key fills several, the first that begins at it
+    const auto range_of = [&](uint32_t k) {
+        uint32_t lo = 0;
+        for (uint32_t step = sr.ranges / 2; step; step /= 2) if (l.cuts[lo + step] <= k) lo += step;
+        if (lo && l.cuts[lo] == k && l.cuts[lo - 1] == k) {
+            uint32_t first = 0, len = lo;
+            while (len) { const uint32_t half = len / 2; if (l.cuts[first + half] < k) { first += half + 1; len -= half + 1; } else len = half; }
+            lo = first;
         }
-        atomicAdd(&l.rank[t % SR_SAMPLE], r);
+        return lo;
+    };
+    // Cuts from an order sorted before do for keys like those: if a range of more than one key gets far more of the drawn
+    // keys than its share, the drawn keys make the cuts.
+    bool far_off = !sr.known;
+    if (!far_off) {
+        bool many = false;
+        if (t < SR_SAMPLE) {
+            const uint32_t r = range_of(drawn);
+            const bool one_key = r + 1 < sr.ranges && l.cuts[r] == drawn && l.cuts[r + 1] == drawn;
+            many = !one_key && atomicAdd(&l.drawn_in[r], 1u) >= SR_SAMPLE / sr.ranges * 2 + 8;
+        }
+        far_off = __syncthreads_or(many) != 0;
     }
-    __syncthreads();
-    if (t < SR_SAMPLE) l.at_rank[l.rank[t]] = drawn;     // (equal keys: the same to the same place)
-    __syncthreads();
-    if (w == 0) {        // the drawn key of a rank: the largest at it or before it
-        static_assert(SR_SAMPLE == 4 * WAVE, "four ranks to a lane");
-        const uint4 v = reinterpret_cast<const uint4 *>(l.at_rank)[lane];
-        uint32_t m[4];
-        m[0] = v.x; m[1] = max(m[0], v.y); m[2] = max(m[1], v.z); m[3] = max(m[2], v.w);
-        uint32_t top = m[3];
-        top = max(top, dpp_or_zero<0x111, 0xf>(top)); top = max(top, dpp_or_zero<0x112, 0xf>(top));
-        top = max(top, dpp_or_zero<0x114, 0xf>(top)); top = max(top, dpp_or_zero<0x118, 0xf>(top));
-        top = max(top, dpp_or_zero<0x142, 0xa>(top)); top = max(top, dpp_or_zero<0x143, 0xc>(top));
-        const uint32_t before = lane ? (uint32_t)__shfl_up(top, 1, WAVE) : 0u;
-        const uint32_t each = SR_SAMPLE / sr.ranges;     // 2 or 4
+    if (far_off) {
+        {   // how many drawn keys lie below each
+            const uint32_t mine = l.sample[t % SR_SAMPLE];
+            const uint4 *v = reinterpret_cast<const uint4 *>(l.sample) + t / SR_SAMPLE * (SR_SAMPLE / 16);
+            uint32_t r = 0;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const uint32_t r = lane * 4 + q;
-            if (r % each == 0) {
-                const uint32_t c = r ? max(before, m[q]) : 0u;
-                l.cuts[r / each] = c;
-                if (tile == 0) sr.cuts[r / each] = c;
+            for (uint32_t q = 0; q < SR_SAMPLE / 16; ++q) {
+                const uint4 o = v[q];
+                r += (o.x < mine) + (o.y < mine) + (o.z < mine) + (o.w < mine);
+            }
+            atomicAdd(&l.rank[t % SR_SAMPLE], r);
+        }
+        __syncthreads();
+        if (t < SR_SAMPLE) l.at_rank[l.rank[t]] = drawn;     // (equal keys: the same to the same place)
+        __syncthreads();
+        if (w == 0) {        // the drawn key of a rank: the largest at it or before it
+            static_assert(SR_SAMPLE == 4 * WAVE, "four ranks to a lane");
+            const uint4 v = reinterpret_cast<const uint4 *>(l.at_rank)[lane];
+            uint32_t m[4];
+            m[0] = v.x; m[1] = max(m[0], v.y); m[2] = max(m[1], v.z); m[3] = max(m[2], v.w);
+            uint32_t top = m[3];
+            top = max(top, dpp_or_zero<0x111, 0xf>(top)); top = max(top, dpp_or_zero<0x112, 0xf>(top));
+            top = max(top, dpp_or_zero<0x114, 0xf>(top)); top = max(top, dpp_or_zero<0x118, 0xf>(top));
+            top = max(top, dpp_or_zero<0x142, 0xa>(top)); top = max(top, dpp_or_zero<0x143, 0xc>(top));
+            const uint32_t before = lane ? (uint32_t)__shfl_up(top, 1, WAVE) : 0u;
+            const uint32_t each = SR_SAMPLE / sr.ranges;     // 1, 2 or 4
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const uint32_t r = lane * 4 + q;
+                if (r % each == 0) {
+                    const uint32_t c = r ? max(before, m[q]) : 0u;
+                    l.cuts[r / each] = c;
+                    if (tile == 0) sr.cuts[r / each] = c;
+                }
             }
         }
-    }
-    __syncthreads();
-    // the range of the key: the last that begins at or below it, or, if the key fills several, the first that begins at it
-    uint32_t lo = 0;
-    for (uint32_t step = sr.ranges / 2; step; step /= 2) if (l.cuts[lo + step] <= key) lo += step;
-    if (lo && l.cuts[lo] == key && l.cuts[lo - 1] == key) {
-        uint32_t first = 0, len = lo;
-        while (len) { const uint32_t half = len / 2; if (l.cuts[first + half] < key) { first += half + 1; len -= half + 1; } else len = half; }
-        lo = first;
-    }
+        __syncthreads();
+    } else if (tile == 0 && t < sr.ranges) sr.cuts[t] = known;
+    const uint32_t lo = range_of(key);
     uint32_t d[1] = {lo}, rank[1];
     const bool valid[1] = {in};
     const int width = 31 - __clz(sr.ranges);

@@ -89,10 +89,10 @@ def drawn_positions(n):
 
 
 @pytest.mark.parametrize("policy", [0, 2])
-@pytest.mark.parametrize("n,vocab", [(4_097, 2_100), (9_000, 3_000_000), (32_768, 1_000_000), (32_769, 4_000_000), (131_072, 70_000)])
+@pytest.mark.parametrize("n,vocab", [(4_097, 2_100), (16_384, 3_000_000), (16_385, 1_000_000), (65_537, 4_000_000), (262_144, 70_000)])
 def test_batches_sorted_in_ranges(n, vocab, policy):
     """Ranges of one key, of no key and of more keys than a workgroup sorts at a time (all drawn positions hold other keys
-    than the rest of the batch), ids outside the vocabulary, keys at both ends of it.  Whole numbers and lr 1, so rows are exact."""
+    than the rest of the batch), ids outside the vocabulary, keys at both ends of it, cut by orders like and unlike the batch's.  Whole numbers and lr 1, so rows are exact."""
     from paper_2112_07221_amd import hetcache as hc
     dev = torch.device("cuda:0")
     rng = np.random.default_rng(n)
@@ -130,9 +130,9 @@ def test_batches_sorted_in_ranges(n, vocab, policy):
 
 
 @pytest.mark.parametrize("policy,s", [(0, 3), (1, 3), (3, 0)])
-@pytest.mark.parametrize("batch,vocab,capacity", [(158, 60_000, 9_000), (1_260, 300_000, 20_000), (1_261, 300_000, 40_000)])
+@pytest.mark.parametrize("batch,vocab,capacity", [(158, 60_000, 9_000), (631, 300_000, 20_000), (2_521, 300_000, 40_000)])
 def test_lookups_of_batches_sorted_in_ranges(batch, vocab, capacity, policy, s):
-    """Classes, slots, clocks and victims of batches nobody announced, of 64 and of 128 ranges."""
+    """Classes, slots, clocks and victims of batches nobody announced, of 64, 128 and 256 ranges."""
     w = wl.WORKLOADS[1].scaled(batch=batch, vocab=vocab, capacity=capacity, s=s, policy=policy, dim=8)
     run_workload(w, 7, state_every=1)
 
