@@ -318,7 +318,7 @@ __device__ __forceinline__ void kept_remove_victims(const CacheView &cv, const T
 }
 
 // The kept histograms from nothing, for the rows cached before a Read (its probe moves on from there).
-__global__ __launch_bounds__(TRIM_THREADS) void kept_recount_kernel(CacheView cv, TrimPlan tp)
+static __global__ __launch_bounds__(TRIM_THREADS) void kept_recount_kernel(CacheView cv, TrimPlan tp)
 {
     for (uint32_t slot = blockIdx.x * TRIM_THREADS + threadIdx.x; slot < cv.n_slots; slot += gridDim.x * TRIM_THREADS) {
         const uint4 m = load_meta(cv.meta, slot);
@@ -329,7 +329,7 @@ __global__ __launch_bounds__(TRIM_THREADS) void kept_recount_kernel(CacheView cv
     }
 }
 
-__global__ __launch_bounds__(256) void clear_words_kernel(uint32_t *p, uint32_t words)
+static __global__ __launch_bounds__(256) void clear_words_kernel(uint32_t *p, uint32_t words)
 {
     for (uint32_t i = blockIdx.x * 256u + threadIdx.x; i < words; i += gridDim.x * 256u) p[i] = 0;
 }
@@ -383,10 +383,12 @@ __device__ __forceinline__ void load_slots(const CacheView &cv, uint32_t slot0, 
     }
 }
 
-// beside_fill: the count runs beside the lookup's fetches (the host allows it where no row of the batch but a
-// fetched one can be a victim: see count_beside_fill).  Slots that were free when the lookup began are being filled
+// beside_fill: the count runs beside the lookup's fetches.  Slots that were free when the lookup began are being filled
 // right now; those up to the last one taken hold the fetched rows, whose policy key is t_now and which hold no
-// updates yet (the eviction knows if they do by then).
+// updates yet (the eviction knows if they do by then).  Rows of the batch that were found can be victims under LRU, if the
+// batch has more keys than the capacity: all tied at t_now.  The stale ones among them are being refreshed right now and
+// hold no updates afterwards; CheckValid says which, whatever of the refresh is seen here: it leaves c_s = c_c = c_g = max(c_g, c_c),
+// so with the new c_s c_c does not exceed it, and with the old one c_c - c_s is still above the bound if either of the two conditions failed.
 __device__ __forceinline__ void trim_count_body(const CacheView &cv, const TrimPlan &tp, uint32_t vblock, TrimLds &l, bool beside_fill = false,
                                                 const uint32_t *tile_miss = nullptr, uint32_t ptiles = 0)
 {
@@ -416,7 +418,8 @@ __device__ __forceinline__ void trim_count_body(const CacheView &cv, const TrimP
     for (int i = 0; i < COUNT_ITEMS; ++i) {
         const bool cached = key[i] != KEY_NONE && evictable(tp, meta[i]);
         const uint32_t pk = policy_key(meta[i]);
-        const bool dirty = meta[i].y > meta[i].x || (tp.dirty_stamp && meta[i].z == tp.dirty_stamp);
+        bool dirty = meta[i].y > meta[i].x || (tp.dirty_stamp && meta[i].z == tp.dirty_stamp);
+        if (beside_fill && dirty && cached && pk == tp.t_now && pk == tau) dirty = check_valid(meta[i].x, meta[i].y, cv.Cg[key[i]], cv.s);
         if (cached && pk < tau) { lt += 1; dlt += dirty; }
         else if (cached && pk == tau) { eq += 1; deq += dirty; }
         else if (new_tied && key[i] == KEY_NONE && slot0 + i <= last_new) eq += 1;      // (a free slot up to the last one taken)
@@ -441,7 +444,7 @@ __device__ __forceinline__ void trim_count_body(const CacheView &cv, const TrimP
 }
 
 // The count where no kernel carries it.
-__global__ __launch_bounds__(TRIM_THREADS) void trim_stage_kernel(CacheView cv, TrimPlan tp)
+static __global__ __launch_bounds__(TRIM_THREADS) void trim_stage_kernel(CacheView cv, TrimPlan tp)
 {
     __shared__ TrimLds l;
     trim_count_body(cv, tp, blockIdx.x, l);
@@ -1253,7 +1256,7 @@ __global__ __launch_bounds__(256) void fill_gather_kernel(CacheView cv, Workspac
 }
 
 // Pooled update: the bag of every original position (its gradient row).
-__global__ __launch_bounds__(256) void pooled_index_kernel(Workspace ws, uint32_t n, const int64_t *__restrict__ offsets, uint32_t n_bags)
+static __global__ __launch_bounds__(256) void pooled_index_kernel(Workspace ws, uint32_t n, const int64_t *__restrict__ offsets, uint32_t n_bags)
 {
     for (uint32_t i = blockIdx.x * 256u + threadIdx.x; i < n; i += gridDim.x * 256u) {
         uint32_t lo = 0, hi = n_bags;            // largest b with offsets[b] <= i
@@ -1268,57 +1271,82 @@ __global__ __launch_bounds__(256) void pooled_index_kernel(Workspace ws, uint32_
 __device__ __forceinline__ float fast_sqrt(float v) { return __builtin_amdgcn_sqrtf(v); }
 __device__ __forceinline__ float fast_rcp(float v) { return __builtin_amdgcn_rcpf(v); }
 
+// x - step, the step rounded by itself in every variant of the kernel (no fused multiply-add): a row's value does not
+// depend on which of them it went through.
+__device__ __forceinline__ float minus(float x, float step)
+{
+#pragma clang fp contract(off)
+    return x - step;
+}
+
+// The optimizer of an update's kernel: known to it where rows have one piece per lane (registers), asked for beyond.
+constexpr int AO_SGD = 0, AO_ADAGRAD = 1, AO_ROWWISE = 2, AO_ANY = 3;
+template <int OPT> __device__ __forceinline__ bool by_adagrad(const CacheView &cv) { return OPT == AO_ANY ? cv.adagrad != 0 : OPT == AO_ADAGRAD; }
+template <int OPT> __device__ __forceinline__ bool by_rowwise(const CacheView &) { return OPT == AO_ROWWISE; }
+
 // The optimizer step on one cached row for chunk c of the row, and nothing else.
 // Row-wise Adagrad's denominator for the row in `slot`: the row group adds up the squares of the
 // gradient's pieces (every lane of the group calls, lanes beyond the row with zeros; the row has one
 // piece per lane), the accumulator takes their mean, and the group's first lane stores it.
 template <int VEC>
-__device__ __forceinline__ float rowwise_rcp(const CacheView &cv, uint32_t slot, const float (&G)[VEC], float eps)
+__device__ __forceinline__ float rowwise_rcp(const CacheView &cv, uint32_t slot, const float (&G)[VEC], float eps, uint32_t from_key, bool gone, uint32_t push_key)
 {
     double ss = 0.0;
 #pragma unroll
     for (int k = 0; k < VEC; ++k) ss += (double)G[k] * (double)G[k];
     for (int o = cv.geom.lanes / 2; o > 0; o >>= 1) ss += __shfl_xor(ss, o, WAVE);     // (the same tree in every lane: the same sum)
-    const float a = cv.acc[slot] + (float)(ss / (double)cv.geom.dim);
-    if (threadIdx.x % cv.geom.lanes == 0) cv.acc[slot] = a;
+    const float a = (from_key != KEY_NONE ? cv.A[from_key] : cv.acc[slot]) + (float)(ss / (double)cv.geom.dim);
+    if (threadIdx.x % cv.geom.lanes == 0) {
+        if (!gone) cv.acc[slot] = a;
+        if (push_key != KEY_NONE) cv.A[push_key] = a;
+    }
     return fast_rcp(fast_sqrt(a) + eps);
 }
 
 // `from_key` other than KEY_NONE: the row has not been fetched yet (see apply_kernel, "fresh"): it is
-// read from the global table at that key and written to the slot (EARLY: and to the global table), or, if
-// the trim that follows drops it (gone), to the global table alone.
-template <int VEC, bool EARLY = false>
-__device__ __forceinline__ void apply_step(const CacheView &cv, uint32_t slot, int c, const double *g64, float lr, float eps, bool act = true,
-                                           uint32_t from_key = KEY_NONE, bool gone = false)
+// read from the global table at that key.  The result goes to the slot, unless the trim beside the update drops the row
+// (gone), and to the global table at push_key, unless that is KEY_NONE (see push_key_of).
+template <int VEC, int OPT>
+__device__ __forceinline__ void apply_step(const CacheView &cv, uint32_t slot, int c, const double *g64, float lr, float eps, bool act,
+                                           uint32_t from_key, bool gone, uint32_t push_key)
 {
     using V = typename VecT<VEC>::type;
     float G[VEC];
 #pragma unroll
     for (int k = 0; k < VEC; ++k) G[k] = act ? (float)g64[k] : 0.f;           // the fp64 sum is rounded to fp32 once
     float row_rcp = 0.f;
-    if (cv.rowwise) row_rcp = rowwise_rcp<VEC>(cv, slot, G, eps);
+    if (by_rowwise<OPT>(cv)) row_rcp = rowwise_rcp<VEC>(cv, slot, G, eps, from_key, gone, push_key);
     if (!act) return;
     const bool fresh = from_key != KEY_NONE;
     V *xp = reinterpret_cast<V *>(cv.rows + (size_t)slot * cv.geom.dim) + c;
     V xv = fresh ? reinterpret_cast<const V *>(cv.W + (size_t)from_key * cv.geom.dim)[c] : *xp;
     float *x = reinterpret_cast<float *>(&xv);
-    if (cv.rowwise) {
+    if (by_rowwise<OPT>(cv)) {
 #pragma unroll
-        for (int k = 0; k < VEC; ++k) x[k] -= lr * G[k] * row_rcp;
-    } else if (cv.adagrad) {
+        for (int k = 0; k < VEC; ++k) x[k] = minus(x[k], lr * G[k] * row_rcp);
+    } else if (by_adagrad<OPT>(cv)) {
         V *ap = reinterpret_cast<V *>(cv.acc + (size_t)slot * cv.geom.dim) + c;
         V av = fresh ? reinterpret_cast<const V *>(cv.A + (size_t)from_key * cv.geom.dim)[c] : *ap;
         float *a = reinterpret_cast<float *>(&av);
 #pragma unroll
-        for (int k = 0; k < VEC; ++k) { a[k] += G[k] * G[k]; x[k] -= lr * G[k] * fast_rcp(fast_sqrt(a[k]) + eps); }
+        for (int k = 0; k < VEC; ++k) { a[k] += G[k] * G[k]; x[k] = minus(x[k], lr * G[k] * fast_rcp(fast_sqrt(a[k]) + eps)); }
         if (!gone) *ap = av;
-        if (gone || (EARLY && fresh)) reinterpret_cast<V *>(cv.A + (size_t)from_key * cv.geom.dim)[c] = av;
+        if (push_key != KEY_NONE) reinterpret_cast<V *>(cv.A + (size_t)push_key * cv.geom.dim)[c] = av;
     } else {
 #pragma unroll
-        for (int k = 0; k < VEC; ++k) x[k] -= lr * G[k];
+        for (int k = 0; k < VEC; ++k) x[k] = minus(x[k], lr * G[k]);
     }
     if (!gone) *xp = xv;
-    if (gone || (EARLY && fresh)) reinterpret_cast<V *>(cv.W + (size_t)from_key * cv.geom.dim)[c] = xv;     // the push
+    if (push_key != KEY_NONE) reinterpret_cast<V *>(cv.W + (size_t)push_key * cv.geom.dim)[c] = xv;     // the push
+}
+
+// Where an update puts a row besides, or instead of, its slot: the global table, if the trim beside it drops the row (TIED: any
+// row of the batch, else only rows it fetched); early push: also if it fetched the row.
+template <bool EARLY, bool TIED>
+__device__ __forceinline__ uint32_t push_key_of(uint32_t key, uint32_t from_key, bool gone)
+{
+    if constexpr (TIED) return gone || (EARLY && from_key != KEY_NONE) ? key : KEY_NONE;
+    return EARLY || gone ? from_key : KEY_NONE;
 }
 
 // Drops the victims among 1024 consecutive slots, four per thread: erase the key, free the slot,
@@ -1336,9 +1364,9 @@ struct EvictLds {
 };
 // MANY: several workers over the table (the push adds what this worker changed to the server's row:
 // three more rows in flight per victim, which the one-worker kernel does not pay registers for).
-// BESIDE: runs beside the update of the batch whose lookup left the overflow (see evict_beside in the host code).
-// No row of the batch is a victim but fetched ones tied at tau; those the update itself writes to the global
-// table (DState::cut_slot), and their clock will be the one they were fetched at plus one.  No other row's clock moves.
+// BESIDE: runs beside the update of the batch whose lookup left the overflow (see evict_beside_update in the host code).
+// The batch's rows that are victims are tied at tau = t_now (LFU: fetched ones only); those the update itself writes to
+// the global table (DState::cut_slot, tied_cut), and their clock will be the present one plus one.  No other victim's clock moves.
 // With a kernel less, and rows fetched and dropped by one step written once: 106496 ids 68.9 -> 60.4 us a step, 114688
 // ids of 128 floats 99.8 -> 92.7, 409600 ids in bags, 256 floats, 296 -> 251.
 // Runs in nblk_ workgroups of TRIM_THREADS threads; `blk` is this one's index.
@@ -1416,7 +1444,7 @@ __device__ __forceinline__ void evict_body(const CacheView &cv, const TrimPlan &
     for (int i = 0; i < EV_ITEMS; ++i) {
         if (victim[i]) {
         const bool by_update = BESIDE && meta[i].z == tp.t_now;
-        const uint32_t slot = slot0 + i, k = key[i], my_cc = by_update ? meta[i].x + 1u : meta[i].y;
+        const uint32_t slot = slot0 + i, k = key[i], my_cc = meta[i].y + (by_update ? 1u : 0u);
         tp.ev_ids[ev_at++] = k;
         const uint32_t cg = dirty[i] ? cv.Cg[k] : 0u;
         const uint32_t early = dirty[i] && cv.early_cc ? cv.early_cc[slot] : 0u;
@@ -1464,6 +1492,7 @@ __device__ __forceinline__ void evict_body(const CacheView &cv, const TrimPlan &
                 }
                 reinterpret_cast<RV *>(cv.W + t0)[c] = x0; reinterpret_cast<RV *>(cv.W + t1)[c] = x1;
             }
+            if (cv.rowwise && gl == 0) { cv.A[v_key[v0]] = cv.acc[v_slot[v0]]; cv.A[v_key[v1]] = cv.acc[v_slot[v1]]; }     // (one accumulator per row)
         }
     } else {
     constexpr int PUSH_ROWS = 4;
@@ -1588,10 +1617,12 @@ __global__ __launch_bounds__(TRIM_THREADS) void trim_evict_kernel(CacheView cv, 
 // MODE: AP_SORTED, the update sorted its own ids.  AP_REUSED, it reuses the preceding lookup's order: the ids must
 // be the ones that order was built from; extra workgroups compare them and flag any difference, others may count
 // the coming trim's rows.  AP_REUSED_EVICT, it also carries the eviction (a variant of its own, without the count, because
-// its arguments and registers made every other update 2 % slower).
-// MAXC: row pieces per lane (dim / VEC / lanes, rounded up).
+// its arguments and registers made every other update 2 % slower).  AP_REUSED_EVICT_TIED, the same where any row of the batch
+// may be a victim (tied_cut), found ones too: LRU, and more ids than the capacity (3328 ids over 1000 rows 36.8 -> 34.8
+// us a step; in the kernel above it would cost the others 2 %).
+// MAXC: row pieces per lane (dim / VEC / lanes, rounded up).  OPT: the optimizer.
 constexpr int AP_THREADS = 256;
-constexpr int AP_SORTED = 0, AP_REUSED = 1, AP_REUSED_EVICT = 2;
+constexpr int AP_SORTED = 0, AP_REUSED = 1, AP_REUSED_EVICT = 2, AP_REUSED_EVICT_TIED = 3;
 // Gradient rows in flight per row group, and waves per SIMD the kernel is held to (rows of one piece
 // per lane).  Tiles of 64 positions: seven waves (72 registers), so that all tiles of a batch of
 // config 2's or 4's size are resident from the start, with four rows in flight (three where the
@@ -1617,6 +1648,7 @@ template <int VEC, int AP_TILE> struct ApplyLds {
     uint32_t seg_start[AP_TILE + 1];     // first position of every segment, then the end of the last
     uint32_t wave_heads[WIN / WAVE];     // segments that begin in each wave's positions
     uint64_t fresh[WIN / WAVE];          // per position: a run head whose key missed in the lookup and whose row is fetched here
+    int32_t cut_slot;                    // (AP_REUSED_EVICT_TIED) the batch's rows in slots up to it are victims
     uint32_t front_open, back_open;      // a run of more than AP_SOLO positions comes in through the tile's front border / goes on behind its back border
 };
 
@@ -1636,7 +1668,7 @@ __device__ __forceinline__ uint32_t wave_count_leading(F cond)
 // Adds the gradient rows of tile positions [lo, hi) for row piece cidx to acc64, in order, in fp64.
 // If `with_row`, the cached row (and accumulator) of `slot` is requested together with the first
 // batch of gradients.
-template <int VEC, int BATCH>
+template <int VEC, int BATCH, int OPT>
 __device__ __forceinline__ void add_positions(const CacheView &cv, const float *__restrict__ grads, const uint32_t *grow, uint32_t lo, uint32_t hi,
                                               int cidx, bool act, double (&acc64)[VEC], bool with_row, uint32_t slot,
                                               typename VecT<VEC>::type &xr, typename VecT<VEC>::type &ar, uint32_t from_key = KEY_NONE)
@@ -1653,7 +1685,7 @@ __device__ __forceinline__ void add_positions(const CacheView &cv, const float *
         if (with_row && b0 == lo && act) {
             const bool fresh = from_key != KEY_NONE;          // not fetched yet: the global row
             xr = reinterpret_cast<const V *>(fresh ? cv.W + (size_t)from_key * dim : cv.rows + (size_t)slot * dim)[cidx];
-            if (cv.adagrad) ar = reinterpret_cast<const V *>(fresh ? cv.A + (size_t)from_key * dim : cv.acc + (size_t)slot * dim)[cidx];
+            if (by_adagrad<OPT>(cv)) ar = reinterpret_cast<const V *>(fresh ? cv.A + (size_t)from_key * dim : cv.acc + (size_t)slot * dim)[cidx];
         }
 #pragma unroll
         for (int r = 0; r < BATCH; ++r) {
@@ -1664,14 +1696,14 @@ __device__ __forceinline__ void add_positions(const CacheView &cv, const float *
     }
 }
 
-template <int VEC, int BATCH>
+template <int VEC, int BATCH, int OPT>
 __device__ __forceinline__ void sum_positions(const CacheView &cv, const float *__restrict__ grads, const uint32_t *grow, uint32_t lo, uint32_t hi,
                                               int cidx, bool act, double (&acc64)[VEC], bool with_row, uint32_t slot,
                                               typename VecT<VEC>::type &xr, typename VecT<VEC>::type &ar, uint32_t from_key = KEY_NONE)
 {
 #pragma unroll
     for (int e = 0; e < VEC; ++e) acc64[e] = 0.0;
-    add_positions<VEC, BATCH>(cv, grads, grow, lo, hi, cidx, act, acc64, with_row, slot, xr, ar, from_key);
+    add_positions<VEC, BATCH, OPT>(cv, grads, grow, lo, hi, cidx, act, acc64, with_row, slot, xr, ar, from_key);
 }
 
 struct SegWork {
@@ -1702,9 +1734,9 @@ __device__ __forceinline__ void store_piece(typename VecT<VEC>::type *p, const t
 }
 
 // The optimizer step from a row already in registers.
-template <int VEC, bool EARLY = false>
+template <int VEC, bool EARLY, int OPT>
 __device__ __forceinline__ void apply_loaded(const CacheView &cv, uint32_t slot, int cidx, const double *g64, float lr, float eps,
-                                             typename VecT<VEC>::type xv, typename VecT<VEC>::type av, bool act, uint32_t from_key, bool gone)
+                                             typename VecT<VEC>::type xv, typename VecT<VEC>::type av, bool act, uint32_t from_key, bool gone, uint32_t push_key)
 {
     using V = typename VecT<VEC>::type;
     float *x = reinterpret_cast<float *>(&xv), *a = reinterpret_cast<float *>(&av);
@@ -1712,23 +1744,61 @@ __device__ __forceinline__ void apply_loaded(const CacheView &cv, uint32_t slot,
 #pragma unroll
     for (int e = 0; e < VEC; ++e) Gs[e] = act ? (float)g64[e] : 0.f;          // the fp64 sum is rounded once
     float row_rcp = 0.f;
-    if (cv.rowwise) row_rcp = rowwise_rcp<VEC>(cv, slot, Gs, eps);            // (every lane of the row group)
+    if (by_rowwise<OPT>(cv)) row_rcp = rowwise_rcp<VEC>(cv, slot, Gs, eps, from_key, gone, push_key);            // (every lane of the row group)
     if (!act) return;
 #pragma unroll
     for (int e = 0; e < VEC; ++e) {
         const float G = Gs[e];
-        if (cv.rowwise) x[e] -= lr * G * row_rcp;
-        else if (cv.adagrad) { a[e] += G * G; x[e] -= lr * G * fast_rcp(fast_sqrt(a[e]) + eps); }
-        else x[e] -= lr * G;
+        if (by_rowwise<OPT>(cv)) x[e] = minus(x[e], lr * G * row_rcp);
+        else if (by_adagrad<OPT>(cv)) { a[e] += G * G; x[e] = minus(x[e], lr * G * fast_rcp(fast_sqrt(a[e]) + eps)); }
+        else x[e] = minus(x[e], lr * G);
     }
     if (!gone) {
         store_piece<VEC, EARLY>(reinterpret_cast<V *>(cv.rows + (size_t)slot * cv.geom.dim) + cidx, xv);
-        if (cv.adagrad) store_piece<VEC, EARLY>(reinterpret_cast<V *>(cv.acc + (size_t)slot * cv.geom.dim) + cidx, av);
+        if (by_adagrad<OPT>(cv)) store_piece<VEC, EARLY>(reinterpret_cast<V *>(cv.acc + (size_t)slot * cv.geom.dim) + cidx, av);
     }
-    if (gone || (EARLY && from_key != KEY_NONE)) {      // a row fetched by this update and dropped by the trim beside it goes to the global table; early push: any row fetched by it, too
-        store_piece<VEC, EARLY>(reinterpret_cast<V *>(cv.W + (size_t)from_key * cv.geom.dim) + cidx, xv);
-        if (cv.adagrad) store_piece<VEC, EARLY>(reinterpret_cast<V *>(cv.A + (size_t)from_key * cv.geom.dim) + cidx, av);
+    if (push_key != KEY_NONE) {
+        store_piece<VEC, EARLY>(reinterpret_cast<V *>(cv.W + (size_t)push_key * cv.geom.dim) + cidx, xv);
+        if (by_adagrad<OPT>(cv)) store_piece<VEC, EARLY>(reinterpret_cast<V *>(cv.A + (size_t)push_key * cv.geom.dim) + cidx, av);
     }
+}
+
+// LRU, and the batch may have more keys than the capacity: then the victims among them are the first tied ones in slot order,
+// up to the slot returned (-1: none).  Found from the eviction's counts, by one wave.  The slots' keys are being erased
+// by the eviction beside it, but not their metadata; a free slot's last use lies before t_now.
+__device__ __forceinline__ int32_t tied_cut(const CacheView &cv, const TrimPlan &tp)
+{
+    const DState *ds = cv.ds;
+    uint32_t take = ds->sel_take;
+    if (ds->over <= 0 || ds->sel_tau != tp.t_now || !take) return -1;
+    const uint32_t lane = lane_id(), nblocks = (cv.n_slots + EV_SLOTS - 1) / EV_SLOTS, nsup = (nblocks + EV_SUPER - 1) / EV_SUPER;
+    uint32_t sup = 0;
+    for (;; sup += WAVE) {
+        const uint32_t c = sup + lane < nsup ? tp.sup_cnt[sup + lane].y : 0u, inc = wave_incl_scan(c);
+        const uint64_t there = __ballot(inc >= take);
+        if (there || sup + WAVE >= nsup) {
+            const int at = there ? __builtin_ctzll(there) : WAVE - 1;
+            take -= (uint32_t)__builtin_amdgcn_readlane((int)(inc - c), at);
+            sup += (uint32_t)at;
+            break;
+        }
+        take -= (uint32_t)__builtin_amdgcn_readlane((int)inc, WAVE - 1);
+    }
+    static_assert(EV_SUPER <= WAVE && EV_SLOTS == 4 * WAVE, "a block per lane, then four slots per lane");
+    const uint32_t b = sup * EV_SUPER + lane, cb = lane < (uint32_t)EV_SUPER && b < nblocks ? tp.blk_cnt[b].y : 0u, incb = wave_incl_scan(cb);
+    const uint64_t thereb = __ballot(incb >= take);
+    const int atb = thereb ? __builtin_ctzll(thereb) : 0;
+    take -= (uint32_t)__builtin_amdgcn_readlane((int)(incb - cb), atb);
+    const uint32_t slot0 = (sup * EV_SUPER + (uint32_t)atb) * EV_SLOTS + 4 * lane;
+    uint32_t tied[4], mine = 0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) { tied[q] = slot0 + q < cv.n_slots && cv.meta[slot0 + q].last_use == tp.t_now ? 1u : 0u; }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) mine += tied[q];
+    uint32_t run = wave_incl_scan(mine) - mine, cut = 0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) { run += tied[q]; if (tied[q] && run == take) cut = slot0 + q + 1; }
+    return (int32_t)wave_sum(cut) - 1;                   // (one lane found it)
 }
 
 // What the tiles of one run tell each other inside the kernel goes through loads, stores and
@@ -1758,14 +1828,14 @@ struct ApplyBorders {
 };
 constexpr uint32_t AP_GROUP = 16;
 
-template <int VEC, int MAXC, int MODE, int AP_TILE, bool EARLY>
+template <int VEC, int MAXC, int MODE, int AP_TILE, bool EARLY, int OPT>
 __global__ __launch_bounds__(AP_THREADS) __attribute__((amdgpu_waves_per_eu(MAXC == 1 ? ap_waves(AP_TILE) : 1))) void apply_kernel(CacheView cv, Workspace ws, ApplyBorders bd, const int64_t *__restrict__ ids,
                                                            const float *__restrict__ grads, const uint32_t *__restrict__ grad_row,
                                                            float lr, float eps, uint32_t n_ids, uint32_t work_blocks, TrimPlan tp, uint32_t trim_blocks,
                                                            SortStage ride, SortStage ride2, KernelTrace tr, int fresh_rows)
 {
     using V = typename VecT<VEC>::type;
-    constexpr bool VERIFY = MODE != AP_SORTED;
+    constexpr bool VERIFY = MODE != AP_SORTED, TIED = MODE == AP_REUSED_EVICT_TIED, EVICT = MODE == AP_REUSED_EVICT || TIED;
     constexpr int BATCH = ap_batch(AP_TILE, EARLY);
     // The tiles' workgroups live longest, so they take the first places; the carried stages, the select
     // stage and the id check follow in the places they leave (the other way round the step was 1 to 2 %
@@ -1776,7 +1846,7 @@ __global__ __launch_bounds__(AP_THREADS) __attribute__((amdgpu_waves_per_eu(MAXC
     const uint32_t verify_blocks = VERIFY ? (n_ids + VERIFY_TILE - 1) / VERIFY_TILE : 0u;
     if (MODE != AP_SORTED) {             // extra workgroups: the eviction, or the count of the coming trim's rows
         if (bid < trim_blocks) {
-            if constexpr (MODE == AP_REUSED_EVICT) evict_body<VEC, false, true>(cv, tp, bid, trim_blocks);
+            if constexpr (EVICT) evict_body<VEC, false, true>(cv, tp, bid, trim_blocks);
             else trim_count_body(cv, tp, bid, lds_as<TrimLds>());
             tr.role(2); tr.end();
             return;
@@ -1803,8 +1873,8 @@ __global__ __launch_bounds__(AP_THREADS) __attribute__((amdgpu_waves_per_eu(MAXC
     const uint32_t group = threadIdx.x / g.lanes, ngroups = AP_THREADS / g.lanes;
     const int gl = threadIdx.x % g.lanes;
     const uint32_t nv = cv.ds->n_valid;
-    const int32_t cut_slot = MODE == AP_REUSED_EVICT ? cv.ds->cut_slot : -1;
-    auto is_gone = [&](uint32_t from_key, int32_t slot) { return MODE == AP_REUSED_EVICT && from_key != KEY_NONE && slot <= cut_slot; };
+    int32_t cut_slot = EVICT && !TIED ? cv.ds->cut_slot : -1;
+    auto is_gone = [&](uint32_t from_key, int32_t slot) { return TIED ? slot >= 0 && slot <= cut_slot : EVICT && from_key != KEY_NONE && slot <= cut_slot; };
     if (VERIFY && bid == 0 && threadIdx.x == 0) {
         // this call did not sort: its per-call counters start here, with the lookup's key count
         DState *ds = cv.ds;
@@ -1885,8 +1955,13 @@ __global__ __launch_bounds__(AP_THREADS) __attribute__((amdgpu_waves_per_eu(MAXC
     const bool through = front_open && back_open && nseg == 1;
     const bool do_front = wave == 0 && front_open, do_back = wave == 1 && back_open && !through;
     uint32_t T0 = T, T1 = T;
+    const uint32_t border_key = do_front ? l.key[W0] : l.key[W0 + AP_TILE - 1];
+    if (TIED && wave == AP_THREADS / WAVE - 1) {
+        const int32_t c = tied_cut(cv, tp);
+        if (lane_id() == 0) l.cut_slot = c;
+    }
     if (do_front || do_back) {
-        const uint32_t key = do_front ? l.key[W0] : l.key[W0 + AP_TILE - 1];
+        const uint32_t key = border_key;
         if (do_front)            // tiles before this one that the run also entered through their front border
             T0 = T - 1 - wave_count_leading([&](uint32_t i) { return i < T && skey[(size_t)(T - i) * AP_TILE - 1] == key; });
         if (do_back || through)  // tiles behind this one that the run also leaves through their back border
@@ -1895,6 +1970,7 @@ __global__ __launch_bounds__(AP_THREADS) __attribute__((amdgpu_waves_per_eu(MAXC
     tr.stamp(1);
     // (does any segment need the whole workgroup?  every thread looks at one)
     const bool any_long = __syncthreads_or(threadIdx.x < nseg && l.seg_start[threadIdx.x + 1] - l.seg_start[threadIdx.x] > AP_SOLO) != 0;
+    if (TIED) cut_slot = l.cut_slot;
 
     auto seg_work = [&](uint32_t sg) {
         SegWork w;
@@ -1909,7 +1985,7 @@ __global__ __launch_bounds__(AP_THREADS) __attribute__((amdgpu_waves_per_eu(MAXC
     auto finish_piece = [&](const SegWork &w, int cidx, bool act, const double (&acc64)[VEC], V xr, V ar) {
         const bool closed = !w.is_front && !w.is_back;
         if (closed) {
-            if (w.slot != SLOT_NONE) apply_loaded<VEC, EARLY>(cv, (uint32_t)w.slot, cidx, acc64, lr, eps, xr, ar, act, w.from_key, w.gone);
+            if (w.slot != SLOT_NONE) apply_loaded<VEC, EARLY, OPT>(cv, (uint32_t)w.slot, cidx, acc64, lr, eps, xr, ar, act, w.from_key, w.gone, push_key_of<EARLY, TIED>(TIED ? l.key[w.a] : 0u, w.from_key, w.gone));
         } else if (act) {
             double *mine = bd.part + ((size_t)T * 2 + (w.is_front ? 0 : 1)) * pstride + (size_t)cidx * VEC;
 #pragma unroll
@@ -1939,7 +2015,7 @@ __global__ __launch_bounds__(AP_THREADS) __attribute__((amdgpu_waves_per_eu(MAXC
                 const uint32_t lo = min(w.a + wave_group * per, w.b), hi = min(lo + per, w.b);
                 double acc64[VEC];
                 V xr{}, ar{};
-                sum_positions<VEC, BATCH>(cv, grads, l.grow, lo, hi, gl, act, acc64, step && wave_group == 0, (uint32_t)w.slot, xr, ar, w.from_key);
+                sum_positions<VEC, BATCH, OPT>(cv, grads, l.grow, lo, hi, gl, act, acc64, step && wave_group == 0, (uint32_t)w.slot, xr, ar, w.from_key);
                 for (int o = g.lanes; o < WAVE; o <<= 1)
 #pragma unroll
                     for (int e = 0; e < VEC; ++e) acc64[e] += __shfl_xor(acc64[e], o, WAVE);
@@ -1959,7 +2035,7 @@ __global__ __launch_bounds__(AP_THREADS) __attribute__((amdgpu_waves_per_eu(MAXC
                 const bool act = cidx < g.chunks;
                 double acc64[VEC];
                 V xr{}, ar{};
-                sum_positions<VEC, BATCH>(cv, grads, l.grow, w.a, w.b, cidx, act, acc64, step, (uint32_t)w.slot, xr, ar, w.from_key);
+                sum_positions<VEC, BATCH, OPT>(cv, grads, l.grow, w.a, w.b, cidx, act, acc64, step, (uint32_t)w.slot, xr, ar, w.from_key);
                 finish_piece(w, cidx, act, acc64, xr, ar);
             }
             finish_segment(w);
@@ -1985,7 +2061,7 @@ __global__ __launch_bounds__(AP_THREADS) __attribute__((amdgpu_waves_per_eu(MAXC
                 const bool act = cidx < g.chunks;
                 double acc64[VEC];
                 V xr{}, ar{};
-                sum_positions<VEC, BATCH>(cv, grads, l.grow, lo, hi, cidx, act, acc64, step && group == 0, (uint32_t)slot, xr, ar, from_key);
+                sum_positions<VEC, BATCH, OPT>(cv, grads, l.grow, lo, hi, cidx, act, acc64, step && group == 0, (uint32_t)slot, xr, ar, from_key);
                 __syncthreads();                            // (the shares of the piece before have been read)
 #pragma unroll
                 for (int e = 0; e < VEC; ++e) l.share[threadIdx.x * VEC + e] = acc64[e];
@@ -1997,7 +2073,7 @@ __global__ __launch_bounds__(AP_THREADS) __attribute__((amdgpu_waves_per_eu(MAXC
                     for (uint32_t gi = 0; gi < ngroups; ++gi)
 #pragma unroll
                         for (int e = 0; e < VEC; ++e) tot[e] += l.share[(gi * g.lanes + gl) * VEC + e];
-                    if (step) apply_loaded<VEC, EARLY>(cv, (uint32_t)slot, cidx, tot, lr, eps, xr, ar, act, from_key, gone);
+                    if (step) apply_loaded<VEC, EARLY, OPT>(cv, (uint32_t)slot, cidx, tot, lr, eps, xr, ar, act, from_key, gone, push_key_of<EARLY, TIED>(TIED ? l.key[a] : 0u, from_key, gone));
                     else if (!closed && act) {
                         double *mine = bd.part + ((size_t)T * 2 + (is_front ? 0 : 1)) * pstride + (size_t)cidx * VEC;
 #pragma unroll
@@ -2087,14 +2163,51 @@ __global__ __launch_bounds__(AP_THREADS) __attribute__((amdgpu_waves_per_eu(MAXC
     for (int q = 0; q < MAXC; ++q) {
         const int cidx = gl + q * g.lanes;
         const bool act = cidx < g.chunks;
-        if (!act && !cv.rowwise) continue;                  // (row-wise Adagrad: every lane of the group takes part in the row's sum)
+        if (!act && !by_rowwise<OPT>(cv)) continue;                  // (row-wise Adagrad: every lane of the group takes part in the row's sum)
         double sum[VEC];
         if (grouped) add_up(ngroups_run, [&](uint32_t i) { return (const double *)bd.part + ((size_t)work_blocks * 2 + (size_t)(T0 + i * AP_GROUP) * 2 + (i == 0 ? 1 : 0)) * pstride; }, cidx, act, sum);
         else add_up(m, [&](uint32_t i) { return (const double *)tile_sum(i); }, cidx, act, sum);
-        if (slot != SLOT_NONE) apply_step<VEC, EARLY>(cv, (uint32_t)slot, cidx, sum, lr, eps, act, from_key, is_gone(from_key, slot));
+        if (slot != SLOT_NONE) apply_step<VEC, OPT>(cv, (uint32_t)slot, cidx, sum, lr, eps, act, from_key, is_gone(from_key, slot), push_key_of<EARLY, TIED>(border_key, from_key, is_gone(from_key, slot)));
     }
     tr.end();
 }
+
+// The variants, compiled side by side (apply_variants.hip, fill_variants.hip): X(part, kernel arguments).
+#define HET_APPLY_MODES(X, part, VEC, MAXC, TILE, EARLY, OPT)                                                   \
+    X(part, VEC, MAXC, AP_SORTED, TILE, EARLY, OPT) X(part, VEC, MAXC, AP_REUSED, TILE, EARLY, OPT)              \
+    X(part, VEC, MAXC, AP_REUSED_EVICT, TILE, EARLY, OPT) X(part, VEC, MAXC, AP_REUSED_EVICT_TIED, TILE, EARLY, OPT)
+#define HET_APPLY_VARIANTS(X)                                                                                   \
+    HET_APPLY_MODES(X, 0, 4, 1, 64, false, AO_SGD) HET_APPLY_MODES(X, 0, 4, 1, 64, false, AO_ADAGRAD)            \
+    HET_APPLY_MODES(X, 0, 4, 1, 64, false, AO_ROWWISE) HET_APPLY_MODES(X, 1, 4, 1, 64, true, AO_SGD)             \
+    HET_APPLY_MODES(X, 1, 4, 1, 64, true, AO_ADAGRAD)                                                            \
+    HET_APPLY_MODES(X, 2, 4, 1, 128, false, AO_SGD) HET_APPLY_MODES(X, 2, 4, 1, 128, false, AO_ADAGRAD)          \
+    HET_APPLY_MODES(X, 2, 4, 1, 128, false, AO_ROWWISE) HET_APPLY_MODES(X, 1, 4, 1, 128, true, AO_SGD)           \
+    HET_APPLY_MODES(X, 1, 4, 1, 128, true, AO_ADAGRAD)                                                           \
+    HET_APPLY_MODES(X, 3, 4, 2, 128, false, AO_ANY) HET_APPLY_MODES(X, 3, 4, 2, 128, true, AO_ANY)               \
+    HET_APPLY_MODES(X, 4, 4, 4, 128, false, AO_ANY) HET_APPLY_MODES(X, 4, 4, 4, 128, true, AO_ANY)               \
+    HET_APPLY_MODES(X, 5, 4, 16, 128, false, AO_ANY) HET_APPLY_MODES(X, 6, 4, 16, 128, true, AO_ANY)             \
+    HET_APPLY_MODES(X, 7, 1, 1, 64, false, AO_SGD) HET_APPLY_MODES(X, 7, 1, 1, 64, false, AO_ADAGRAD)            \
+    HET_APPLY_MODES(X, 7, 1, 1, 64, false, AO_ROWWISE)                                                           \
+    HET_APPLY_MODES(X, 7, 1, 1, 128, false, AO_SGD) HET_APPLY_MODES(X, 7, 1, 1, 128, false, AO_ADAGRAD)          \
+    HET_APPLY_MODES(X, 7, 1, 1, 128, false, AO_ROWWISE)                                                          \
+    HET_APPLY_MODES(X, 3, 1, 2, 128, false, AO_ANY) HET_APPLY_MODES(X, 4, 1, 4, 128, false, AO_ANY)              \
+    HET_APPLY_MODES(X, 6, 1, 16, 128, false, AO_ANY)
+constexpr int HET_APPLY_PARTS = 8;
+#define HET_APPLY_KERNEL(VEC, MAXC, MODE, TILE, EARLY, OPT)                                                     \
+    template __global__ void apply_kernel<VEC, MAXC, MODE, TILE, EARLY, OPT>(                                     \
+        CacheView, Workspace, ApplyBorders, const int64_t *__restrict__, const float *__restrict__, const uint32_t *__restrict__, float, float, \
+        uint32_t, uint32_t, TrimPlan, uint32_t, SortStage, SortStage, KernelTrace, int);
+
+#define HET_FILL_RIDES(X, part, VEC, POOLED, TRACE) X(part, VEC, POOLED, 0, TRACE) X(part, VEC, POOLED, 1, TRACE) X(part, VEC, POOLED, 2, TRACE)
+#define HET_FILL_VARIANTS(X)                                                                                    \
+    HET_FILL_RIDES(X, 0, 4, false, false) HET_FILL_RIDES(X, 0, 4, true, false) HET_FILL_RIDES(X, 0, 1, false, false) \
+    HET_FILL_RIDES(X, 0, 1, true, false) HET_FILL_RIDES(X, 1, 4, false, true) HET_FILL_RIDES(X, 1, 4, true, true)  \
+    HET_FILL_RIDES(X, 1, 1, false, true) HET_FILL_RIDES(X, 1, 1, true, true)
+constexpr int HET_FILL_PARTS = 2;
+#define HET_FILL_KERNEL(VEC, POOLED, RIDE, TRACE)                                                               \
+    template __global__ void fill_gather_kernel<VEC, POOLED, RIDE, TRACE>(                                        \
+        CacheView, Workspace, uint32_t, uint32_t, uint32_t, uint32_t, TrimPlan, uint32_t, float *__restrict__, const int64_t *__restrict__, uint32_t, \
+        const uint32_t *__restrict__, SortStage, SortStage, uint32_t, int, uint32_t, Ahead, KernelTrace, int);
 
 // flush: push every cached row that holds updates and mark it clean (c_s = c_c = c_g).
 template <int VEC>
@@ -2138,7 +2251,7 @@ __global__ __launch_bounds__(256) void foreign_update_kernel(CacheView cv, const
 }
 
 // Initial free list (every slot free) and empty slots.
-__global__ __launch_bounds__(256) void init_cache_kernel(CacheView cv)
+static __global__ __launch_bounds__(256) void init_cache_kernel(CacheView cv)
 {
     const uint32_t i0 = blockIdx.x * 256u + threadIdx.x, stride = gridDim.x * 256u;
     for (uint32_t i = i0; i < cv.n_slots; i += stride) {

@@ -1,0 +1,19 @@
+// One part of the lookup's second kernel (HET_PART of HET_FILL_PARTS), see apply_variants.hip.
+#include "cache_kernels.hpp"
+
+namespace het {
+
+#if HET_PART == 0
+#define HET_PART_0(...) HET_FILL_KERNEL(__VA_ARGS__)
+#else
+#define HET_PART_0(...)
+#endif
+#if HET_PART == 1
+#define HET_PART_1(...) HET_FILL_KERNEL(__VA_ARGS__)
+#else
+#define HET_PART_1(...)
+#endif
+#define HET_HERE(part, ...) HET_PART_##part(__VA_ARGS__)
+HET_FILL_VARIANTS(HET_HERE)
+
+} // namespace het

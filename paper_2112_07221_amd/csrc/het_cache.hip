@@ -18,6 +18,15 @@
 #include "pattern_kernels.hpp"
 #include "static_lookup.hpp"
 
+namespace het {          // (compiled in parts of their own)
+#define HET_ELSEWHERE(part, ...) extern HET_APPLY_KERNEL(__VA_ARGS__)
+HET_APPLY_VARIANTS(HET_ELSEWHERE)
+#undef HET_ELSEWHERE
+#define HET_ELSEWHERE(part, ...) extern HET_FILL_KERNEL(__VA_ARGS__)
+HET_FILL_VARIANTS(HET_ELSEWHERE)
+#undef HET_ELSEWHERE
+} // namespace het
+
 using namespace het;
 
 // Kernels of the path, as named in profiles and by het_profile_kernel_name.
@@ -460,13 +469,16 @@ TrimPlan make_trim_plan(const het_cache *c)
     return tp;
 }
 
-// May the rows below and at tau be counted beside the fetches of a lookup of n ids?  What holds updates when the
-// trim comes must be known by then: no row of the batch may be a victim, or only fetched ones, all tied at tau.
-// LRU: as long as the batch's distinct keys fit the capacity, older rows are enough.  LFU: a row of the batch that was
-// found has been used twice, unless the light-weight policy stopped counting at 1.
-bool count_beside_fill(const het_cache *c, const TrimPlan &tp, uint32_t n)
+// May the rows below and at tau be counted beside the fetches of a lookup?  What holds updates when the trim comes must
+// follow from what is known by then.  LRU: rows of the batch are all tied at t_now (see trim_count_body), if they can be victims
+// at all.  LFU: a row of the batch that was found has been used twice, unless the light-weight policy stopped counting at 1.
+// (Where that held for LRU only up to a capacity of the batch's ids, lookups of 53248 ids over 50000 rows had a kernel for the count, 46.7 us.)
+bool count_beside_fill(const het_cache *c, const TrimPlan &tp) { return tp.passes == 2 && !(tp.lfu && c->cv.freq_cap == 1); }
+
+// May the eviction run beside the update?
+bool evict_beside_update(const het_cache *c, const TrimPlan &tp)
 {
-    return tp.passes == 2 && (tp.lfu ? c->cv.freq_cap != 1 : (int64_t)n <= c->capacity);
+    return count_beside_fill(c, tp) && c->location == HET_BACKING_HBM && !c->many;
 }
 
 uint32_t count_blocks(const het_cache *c) { return cdiv(c->cv.n_slots, COUNT_SLOTS); }
@@ -649,8 +661,7 @@ int run_lookup(het_cache *c, const int64_t *ids, uint32_t n, const int64_t *offs
     }
     {
         hash_find(c, c->ws.skey, n);
-        const bool beside = count_beside_fill(c, tp, n) && c->location == HET_BACKING_HBM && !c->many && !c->cv.rowwise;
-        const Rides ride = probe_must_ride(c, !beside) ? next_rides(c) : Rides{no_stage(), no_stage()};
+        const Rides ride = probe_must_ride(c, !evict_beside_update(c, tp)) ? next_rides(c) : Rides{no_stage(), no_stage()};
         const uint32_t blocks = ptiles + (match >= 0 ? ptiles : 0u) + stiles;
 #define PROBE(RIDE)                                                                                                                              \
     LAUNCH(c, K_PROBE, probe_kernel<true, RIDE><<<blocks + ride.blocks(), PT_THREADS, lds_bytes(0, ride, PT_THREADS), c->stream>>>(                \
@@ -660,7 +671,7 @@ int run_lookup(het_cache *c, const int64_t *ids, uint32_t n, const int64_t *offs
 #undef PROBE
     }
 
-    c->counted = count_beside_fill(c, tp, n);
+    c->counted = count_beside_fill(c, tp);
     c->recount = false;
     const uint32_t hist_blocks = c->counted ? count_blocks(c) : (tp.passes > 2 ? std::min(cdiv(c->cv.n_slots, TRIM_TILE), 1024u) : 0u);
     const uint32_t fill_blocks = std::min(cdiv(row_grid(c->cv.geom, n), (uint32_t)FILL_ROWS), FILL_MAX_BLOCKS);     // they come first: theirs is the longer chain
@@ -696,11 +707,10 @@ int run_lookup(het_cache *c, const int64_t *ids, uint32_t n, const int64_t *offs
         // them from the global table and writes them to their slots with its step applied); the fetch
         // workgroups that remain refresh the stale rows.
         const Rides ride = next_rides(c);
-        const bool owe = !c->cv.rowwise;
-        fetch_mode = owe ? 1 : 0;
-        const uint32_t fb = owe ? std::min(fill_blocks, STALE_BLOCKS) : fill_blocks;
+        fetch_mode = 1;
+        const uint32_t fb = std::min(fill_blocks, STALE_BLOCKS);
         FILL_GATHER_ANY(ride.blocks() + fb + ptiles + hist_blocks + gather_blocks, fb, hist_blocks, 0u);
-        if (owe) { c->fetch_owed = true; c->owed_n = n; c->owed_t = t_now; }
+        c->fetch_owed = true; c->owed_n = n; c->owed_t = t_now;
         hash_insert(c, n);
     } else {
         // Host-backed table: the fetches come over the host link, and the last trim's write-back
@@ -779,12 +789,12 @@ int run_lookup(het_cache *c, const int64_t *ids, uint32_t n, const int64_t *offs
 // carries that count in extra workgroups.  The count looks at the clocks the kernel is moving, which is sound
 // only when the update is known to touch exactly the rows the last Read touched (it reuses that Read's order): see
 // TrimPlan::dirty_stamp.
-// Where they were counted there, the eviction runs beside the update (see evict_body) if the update is the one the lookup left its fetches to (c->fetch_owed: table in HBM, one
-// worker, not row-wise Adagrad): by count_beside_fill no row it touches is a victim but rows it fetches, and those it
+// Where they were counted there, the eviction runs beside the update (see evict_body) if the update is the one the lookup left
+// its fetches to (c->fetch_owed: table in HBM, one worker): rows it touches that are victims it
 // writes to the global table itself, instead of to their slots.
 // `trim`: a trim follows.  Returns whether its rows have been counted.
-template <int VEC, int MAXC, int TILE, bool EARLY>
-bool launch_apply_tile2(het_cache *c, bool verify, const int64_t *ids, uint32_t n, const float *grads, const uint32_t *grad_row, float lr,
+template <int VEC, int MAXC, int TILE, bool EARLY, int OPT>
+bool launch_apply_opt(het_cache *c, bool verify, const int64_t *ids, uint32_t n, const float *grads, const uint32_t *grad_row, float lr,
                       bool trim)
 {
     const uint32_t grid = cdiv(n, TILE);
@@ -792,7 +802,7 @@ bool launch_apply_tile2(het_cache *c, bool verify, const int64_t *ids, uint32_t 
     bool counted = c->counted;
     const int fresh = verify && c->fetch_owed ? 1 : 0;          // (verify: this update reuses the lookup's order)
     if (fresh) c->fetch_owed = false;
-    const bool evict = trim && fresh && c->counted && !c->recount && !c->profiling;      // (per-kernel timing: in a kernel of its own, to tell the two apart)
+    const bool evict = trim && fresh && !c->recount && evict_beside_update(c, tp) && !c->profiling;      // (per-kernel timing: in a kernel of its own, to tell the two apart)
     uint32_t extra = 0;
     if (evict) { tp = plan_eviction(c, true); extra = evict_grid(c); }
     else if (trim && !counted && verify && c->cv.freq_cap != 1) {    // (light-weight LFU with a cap of 1 leaves rows of the batch unstamped that can be evicted; with a larger cap those it leaves unstamped cannot)
@@ -801,11 +811,27 @@ bool launch_apply_tile2(het_cache *c, bool verify, const int64_t *ids, uint32_t 
     const Rides ride = next_rides(c);
     const uint32_t lds = lds_bytes(std::max({sizeof(TrimLds), sizeof(EvictLds), sizeof(ApplyLds<VEC, TILE>)}), ride);
 #define APPLY(MODE)                                                                                                                              \
-    LAUNCH(c, K_APPLY, apply_kernel<VEC, MAXC, MODE, TILE, EARLY><<<ride.blocks() + grid + extra + (verify ? cdiv(n, VERIFY_TILE) : 0u), AP_THREADS, lds, c->stream>>>( \
+    LAUNCH(c, K_APPLY, apply_kernel<VEC, MAXC, MODE, TILE, EARLY, OPT><<<ride.blocks() + grid + extra + (verify ? cdiv(n, VERIFY_TILE) : 0u), AP_THREADS, lds, c->stream>>>( \
                            c->cv, c->ws, c->bd, ids, grads, grad_row, lr, c->eps, n, grid, tp, extra, ride.a, ride.b, c->trace[0], fresh))
-    if (evict) { APPLY(AP_REUSED_EVICT); hash_erase(c, tp); } else if (verify) APPLY(AP_REUSED); else APPLY(AP_SORTED);
+    if (evict) {
+        if (!tp.lfu && (int64_t)n > c->capacity) APPLY(AP_REUSED_EVICT_TIED); else APPLY(AP_REUSED_EVICT);
+        hash_erase(c, tp);
+    } else if (verify) APPLY(AP_REUSED); else APPLY(AP_SORTED);
 #undef APPLY
     return counted;
+}
+
+template <int VEC, int MAXC, int TILE, bool EARLY>
+bool launch_apply_early(het_cache *c, bool verify, const int64_t *ids, uint32_t n, const float *grads, const uint32_t *grad_row, float lr,
+                        bool trim)
+{
+    if constexpr (MAXC > 1) return launch_apply_opt<VEC, MAXC, TILE, EARLY, AO_ANY>(c, verify, ids, n, grads, grad_row, lr, trim);
+    else {
+        if constexpr (!EARLY)            // (row-wise Adagrad does not push early)
+            if (c->cv.rowwise) return launch_apply_opt<VEC, MAXC, TILE, EARLY, AO_ROWWISE>(c, verify, ids, n, grads, grad_row, lr, trim);
+        return c->cv.adagrad ? launch_apply_opt<VEC, MAXC, TILE, EARLY, AO_ADAGRAD>(c, verify, ids, n, grads, grad_row, lr, trim)
+                             : launch_apply_opt<VEC, MAXC, TILE, EARLY, AO_SGD>(c, verify, ids, n, grads, grad_row, lr, trim);
+    }
 }
 
 // EARLY: the variant that also pushes the rows it fetches (CacheView::early_cc in use).
@@ -814,8 +840,8 @@ bool launch_apply_tile(het_cache *c, bool verify, const int64_t *ids, uint32_t n
                       bool trim)
 {
     if constexpr (VEC == 4)          // (only rows of whole 16-byte pieces push early)
-        if (c->cv.early_cc) return launch_apply_tile2<VEC, MAXC, TILE, true>(c, verify, ids, n, grads, grad_row, lr, trim);
-    return launch_apply_tile2<VEC, MAXC, TILE, false>(c, verify, ids, n, grads, grad_row, lr, trim);
+        if (c->cv.early_cc) return launch_apply_early<VEC, MAXC, TILE, true>(c, verify, ids, n, grads, grad_row, lr, trim);
+    return launch_apply_early<VEC, MAXC, TILE, false>(c, verify, ids, n, grads, grad_row, lr, trim);
 }
 
 template <int VEC, int MAXC>

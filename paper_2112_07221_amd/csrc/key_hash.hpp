@@ -65,7 +65,7 @@ __device__ __forceinline__ int32_t key_find(const KeyHash &h, uint32_t key, size
 
 // The slot of the key at every sorted position where the probe asks for one: the head of every run of equal keys and
 // each wave's first lane.
-__global__ __launch_bounds__(256) void key_find_kernel(KeyHash h, const uint32_t *__restrict__ skey, uint32_t n, uint32_t vocab, int32_t *__restrict__ found)
+static __global__ __launch_bounds__(256) void key_find_kernel(KeyHash h, const uint32_t *__restrict__ skey, uint32_t n, uint32_t vocab, int32_t *__restrict__ found)
 {
     const uint32_t j = blockIdx.x * 256u + threadIdx.x;
     if (j >= n) return;
@@ -76,7 +76,7 @@ __global__ __launch_bounds__(256) void key_find_kernel(KeyHash h, const uint32_t
 }
 
 // The keys a lookup fetched (none of them is there yet).  cls and head_slot are valid at run heads.
-__global__ __launch_bounds__(256) void key_insert_kernel(KeyHash h, const uint32_t *__restrict__ skey, const uint8_t *__restrict__ cls,
+static __global__ __launch_bounds__(256) void key_insert_kernel(KeyHash h, const uint32_t *__restrict__ skey, const uint8_t *__restrict__ cls,
                                                          const int32_t *__restrict__ head_slot, uint32_t n, uint32_t vocab)
 {
     const uint32_t j = blockIdx.x * 256u + threadIdx.x;
@@ -104,7 +104,7 @@ __global__ __launch_bounds__(256) void key_insert_kernel(KeyHash h, const uint32
 }
 
 // The keys a trim dropped.
-__global__ __launch_bounds__(256) void key_erase_kernel(KeyHash h, const uint32_t *__restrict__ ev_ids, const uint32_t *__restrict__ ev_n)
+static __global__ __launch_bounds__(256) void key_erase_kernel(KeyHash h, const uint32_t *__restrict__ ev_ids, const uint32_t *__restrict__ ev_n)
 {
     const uint32_t n = *ev_n;
     for (uint32_t i = blockIdx.x * 256u + threadIdx.x; i < n; i += gridDim.x * 256u) {

@@ -13,7 +13,7 @@ constexpr int PAT_UPDATE_ROWS = 2;   // rows of x (and a, and their gradients) a
 
 // dst[i] = src[idx[i]] for n rows of `dim` floats (dim a multiple of 4): the gather's pattern
 // (idx == nullptr: dst[i] = src[i], a streaming copy of the same size).
-__global__ __launch_bounds__(256) void pattern_gather_kernel(const float *__restrict__ src, float *__restrict__ dst,
+static __global__ __launch_bounds__(256) void pattern_gather_kernel(const float *__restrict__ src, float *__restrict__ dst,
                                                              const uint32_t *__restrict__ idx, uint32_t n, int dim)
 {
     const int chunks = dim / 4, lanes = chunks < 64 ? chunks : 64;

@@ -495,7 +495,7 @@ struct SortPartLds {
     uint16_t hist[SOLO_WAVES * SR_MAX_RANGES];
 };
 
-__global__ __launch_bounds__(SOLO_THREADS) void sort_part_kernel(const int64_t *__restrict__ ids, const uint32_t *__restrict__ keys_in, SortRanges sr)
+static __global__ __launch_bounds__(SOLO_THREADS) void sort_part_kernel(const int64_t *__restrict__ ids, const uint32_t *__restrict__ keys_in, SortRanges sr)
 {
     static_assert(SR_SAMPLE * 4 == SOLO_THREADS && SOLO_THREADS == SORT_TILE, "four threads find a drawn key's rank; a key per thread");
     __shared__ SortPartLds l;
@@ -627,7 +627,7 @@ __device__ __forceinline__ void sort_listed(F source, const SortRanges &sr, uint
     solo_sort<ITEMS>(key, pay, valid, at0, m, first, 0, passes, width, lds, keys_out, idx_out);
 }
 
-__global__ __launch_bounds__(SOLO_THREADS) void sort_range_kernel(SortRanges sr, uint32_t *__restrict__ keys_out, uint32_t *__restrict__ idx_out)
+static __global__ __launch_bounds__(SOLO_THREADS) void sort_range_kernel(SortRanges sr, uint32_t *__restrict__ keys_out, uint32_t *__restrict__ idx_out)
 {
     extern __shared__ __align__(16) uint32_t sort_dyn_lds[];
     SortRangeLds &l = *reinterpret_cast<SortRangeLds *>(sort_dyn_lds);

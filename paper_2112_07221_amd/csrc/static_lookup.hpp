@@ -33,7 +33,7 @@ __device__ __forceinline__ void static_check_body(const int64_t *__restrict__ id
     if (threadIdx.x == 0) *err_bits = any ? ERRBIT_RANGE : 0u;
 }
 
-__global__ void static_clear_kernel(uint32_t *err_bits) { *err_bits = 0; }
+static __global__ void static_clear_kernel(uint32_t *err_bits) { *err_bits = 0; }
 
 // CHECK: the last workgroup checks the ids; otherwise a workgroup that meets a bad id sets the bit
 // itself (err_bits was cleared by a launch before this one).

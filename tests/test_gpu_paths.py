@@ -250,6 +250,23 @@ def test_evictions_counted_beside_the_fetches(policy, capacity, lfu_cap, dim, op
         p.close()
 
 
+@pytest.mark.parametrize("policy,capacity,dim,optimizer", [(0, 1, 16, 1), (0, 40, 3, 0), (0, 40, 16, 1), (0, 40, 128, 1), (0, 40, 260, 1), (0, 40, 16, 2), (0, 100, 128, 0),
+                                                           (0, 150, 16, 2), (0, 180, 64, 1), (0, 180, 130, 1), (0, 700, 16, 2), (1, 40, 128, 2), (1, 700, 3, 2), (3, 200, 16, 2), (0, 180, 1_100, 0)])
+def test_evictions_beside_the_update_of_any_row_of_the_batch(policy, capacity, dim, optimizer):
+    """LRU and fewer slots than the batch has keys: rows of the batch that were found are victims too (the update writes them to
+    the table itself); row-wise Adagrad, whose update fetches rows and whose evictions run beside it like the others'."""
+    test_evictions_counted_beside_the_fetches(policy, capacity, 2 if policy == 3 else None, dim, optimizer)
+
+
+def test_evictions_of_hundreds_of_thousands_of_tied_rows():
+    """The last victim's slot lies behind the first 64 groups of eviction blocks (524 288 slots)."""
+    w = wl.WORKLOADS[1].scaled(batch=26_924, vocab=2_000_000, capacity=650_000, s=100, policy=0, dim=4, optimizer=0)
+    rng = np.random.default_rng(5)
+    ids = np.stack([rng.permutation(w.vocab)[: w.n] for _ in range(3)])
+    ids[1, : w.n // 2] = ids[0, : w.n // 2]
+    run_workload(w, 3, ids=ids, state_every=1)
+
+
 @pytest.mark.parametrize("when", ["before", "between"])
 @pytest.mark.parametrize("policy", [0, 1, 2])
 @pytest.mark.parametrize("n,vocab", [(200, 3_000), (1_024, 5_000_000), (2_700, 5_000_000), (2_731, 100_000), (5_400, 5_000_000)])
