@@ -976,30 +976,43 @@ __global__ __launch_bounds__(256) void link_kernel(CacheView cv, int push_buf, i
     }
 }
 
-// Get for bags (sum pooling): one row group adds up one bag at a time, in bag order, in fp64, rounded
-// once (a bag may hold hundreds of rows).  Where the rows are is found for as many ids of the bag
-// as the group has lanes at once, one id per lane (its sorted position, then source and key there:
+// Get for bags (sum pooling): `split` row groups of a workgroup add up a bag, a contiguous share each, in bag order, in fp64;
+// the shares are added in a fixed order and rounded once (a bag may hold hundreds of rows).  Where the rows are is found
+// for as many ids of the share as the group has lanes at once, one id per lane (its sorted position, then source and key there:
 // two steps for the whole stretch, not two per POOL_ROWS rows), and handed from lane to lane
 // for the row loads; the next stretch is asked for behind the first rows of the present one.
 // A row's address carries "does not count" (an id outside the vocabulary) in its lowest bit.
+// split: see pool_split in the host code.
 template <int VEC>
 __device__ __forceinline__ void pooled_gather_body(const CacheView &cv, const Workspace &ws, uint32_t n, float *__restrict__ out,
                                                    const int64_t *__restrict__ offsets, uint32_t n_bags, const uint32_t *__restrict__ inv,
-                                                   uint32_t gid, uint32_t ngroups)
+                                                   uint32_t split, uint32_t blk, uint32_t nblk_)
 {
     using V = typename VecT<VEC>::type;
     const RowGeom g = cv.geom;
     const int gl = threadIdx.x % g.lanes;
     const int first_lane = (int)(threadIdx.x % WAVE) - gl;
+    const uint32_t group = threadIdx.x / g.lanes, part = group % split, bags = 256u / g.lanes / split;         // bags a workgroup has in hand
+    const uint32_t wave = threadIdx.x / WAVE, bag_waves = split * g.lanes / WAVE;                             // (0 or 1: a bag's groups share a wave)
+    double *wave_sums = reinterpret_cast<double *>(dyn_lds);               // [waves][lanes of a row][VEC]
     auto where = [&](uint32_t jj, bool in) -> unsigned long long {
         const int32_t sr = ws.src[jj];
         const uint32_t ky = ws.skey[jj];
         const float *row = sr == SRC_BACKING ? cv.W + (size_t)ky * g.dim : cv.rows + (size_t)(uint32_t)(sr < 0 ? 0 : sr) * g.dim;
         return (unsigned long long)(uintptr_t)row | (in && sr != SRC_ZERO ? 0ull : 1ull);
     };
-    for (uint32_t b = gid; b < n_bags; b += ngroups) {
-        int64_t lo = offsets[b], hi = offsets[b + 1];
-        lo = lo < 0 ? 0 : lo; hi = hi > (int64_t)n ? (int64_t)n : hi;
+    for (uint32_t b0 = blk * bags; b0 < n_bags; b0 += nblk_ * bags) {
+        const uint32_t b = b0 + group / split;
+        int64_t lo = 0, hi = 0;
+        if (b < n_bags) {
+            lo = offsets[b]; hi = offsets[b + 1];
+            lo = lo < 0 ? 0 : lo; hi = hi > (int64_t)n ? (int64_t)n : hi;
+            if (split > 1 && lo < hi) {
+                const int64_t share = (hi - lo + split - 1) / split;
+                lo += part * share;
+                hi = lo + share < hi ? lo + share : hi;
+            }
+        }
         for (int c0 = 0; c0 < g.chunks; c0 += g.lanes) {
             const bool mine = c0 + gl < g.chunks;
             const int c = mine ? c0 + gl : 0;    // (a lane beyond the row reads its first piece and stores nothing: every lane hands addresses on)
@@ -1036,19 +1049,38 @@ __device__ __forceinline__ void pooled_gather_body(const CacheView &cv, const Wo
                     cur = nxt; i0 = i1;
                 }
             }
+            // the shares: within the wave, then wave by wave
+            for (uint32_t o = g.lanes; o < min(split * g.lanes, (uint32_t)WAVE); o <<= 1) {
+#pragma unroll
+                for (int e = 0; e < VEC; ++e) sum[e] += __shfl_xor(sum[e], (int)o, WAVE);
+            }
+            if (bag_waves > 1) {
+                __syncthreads();                 // (the sums before have been read)
+                if (first_lane == 0) {
+#pragma unroll
+                    for (int e = 0; e < VEC; ++e) wave_sums[(wave * g.lanes + gl) * VEC + e] = sum[e];
+                }
+                __syncthreads();
+                if (part == 0) {
+                    for (uint32_t ww = 1; ww < bag_waves; ++ww)
+#pragma unroll
+                        for (int e = 0; e < VEC; ++e) sum[e] += wave_sums[((wave + ww) * g.lanes + gl) * VEC + e];
+                }
+            }
             V res;
             float *rf = reinterpret_cast<float *>(&res);
 #pragma unroll
             for (int e = 0; e < VEC; ++e) rf[e] = (float)sum[e];
-            if (mine) reinterpret_cast<V *>(out + (size_t)b * g.dim)[c] = res;
+            if (mine && part == 0 && b < n_bags) reinterpret_cast<V *>(out + (size_t)b * g.dim)[c] = res;
         }
     }
 }
 
-struct FillLds {
+struct FillLds {                             // (also what the pooled gather's workgroups have: a double per thread and float of a piece)
     uint32_t pre_miss[MAX_PROBE_TILES], pre_stale[MAX_PROBE_TILES];
     uint32_t scan[4 + 1];
 };
+static_assert(sizeof(FillLds) >= 256 * 4 * sizeof(double), "");
 // RIDE: 0 carries no sort stage, 1 a histogram stage (cheap in registers: the gather keeps its
 // occupancy), 2 any stage.
 // TRACE: time stamps (het_profile_trace); a kernel of its own, because the stamps' arguments cost the
@@ -1058,7 +1090,7 @@ __global__ __launch_bounds__(256) void fill_gather_kernel(CacheView cv, Workspac
                                                           TrimPlan tp, uint32_t hist_blocks, float *__restrict__ out, const int64_t *__restrict__ offsets, uint32_t n_bags,
                                                           const uint32_t *__restrict__ inv, SortStage ride, SortStage ride2,
                                                           uint32_t push_blocks, int push_buf, uint32_t push_seq, Ahead ah,
-                                                          KernelTrace tr_arg, int fetch_mode)
+                                                          KernelTrace tr_arg, int fetch_mode, uint32_t pool_split)
 {
     using V = typename VecT<VEC>::type;
     uint32_t bid = blockIdx.x, nblk = gridDim.x;
@@ -1080,7 +1112,7 @@ __global__ __launch_bounds__(256) void fill_gather_kernel(CacheView cv, Workspac
         const uint32_t bag_blocks = nblk - others;
         if (bid < bag_blocks) {
             if (fill_blocks == 0 && bid == 0 && threadIdx.x == 0) cv.ds->n_unique = (uint32_t)cv.last->unique;   // (no fetch workgroup does)
-            pooled_gather_body<VEC>(cv, ws, n, out, offsets, n_bags, inv, bid * groups_per_block + threadIdx.x / g.lanes, bag_blocks * groups_per_block);
+            pooled_gather_body<VEC>(cv, ws, n, out, offsets, n_bags, inv, pool_split, bid, bag_blocks);
             tr.role(5); tr.end();
             return;
         }
@@ -2207,7 +2239,7 @@ constexpr int HET_FILL_PARTS = 2;
 #define HET_FILL_KERNEL(VEC, POOLED, RIDE, TRACE)                                                               \
     template __global__ void fill_gather_kernel<VEC, POOLED, RIDE, TRACE>(                                        \
         CacheView, Workspace, uint32_t, uint32_t, uint32_t, uint32_t, TrimPlan, uint32_t, float *__restrict__, const int64_t *__restrict__, uint32_t, \
-        const uint32_t *__restrict__, SortStage, SortStage, uint32_t, int, uint32_t, Ahead, KernelTrace, int);
+        const uint32_t *__restrict__, SortStage, SortStage, uint32_t, int, uint32_t, Ahead, KernelTrace, int, uint32_t);
 
 // flush: push every cached row that holds updates and mark it clean (c_s = c_c = c_g).
 template <int VEC>

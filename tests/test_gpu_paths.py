@@ -267,6 +267,34 @@ def test_evictions_of_hundreds_of_thousands_of_tied_rows():
     run_workload(w, 3, ids=ids, state_every=1)
 
 
+@pytest.mark.parametrize("dim", [1, 4, 20, 64, 100, 128, 130, 256, 260])
+@pytest.mark.parametrize("bags", [1, 3, 37, 350])
+def test_bags_added_up_by_several_row_groups(bags, dim):
+    """A bag's rows shared out among 1 to 256 row groups, within a wave and over several, to bags that are empty, shorter
+    than the groups are many, and hundreds of rows long; ids outside the first and the last bag."""
+    w = wl.WORKLOADS[5].scaled(batch=bags, vocab=3_000, capacity=400, s=3, dim=dim, optimizer=0)
+    rng = np.random.default_rng(bags * 1000 + dim)
+    n, T = 1_400, 4
+    ids, table = rng.integers(0, w.vocab, (T, n)), wl.table_init(w)
+    p = Pair(w, table, max_ids=n)
+    try:
+        for t in range(T):
+            cuts = np.sort(rng.integers(0, n + 1, bags + 1))
+            cuts[0] = 0
+            if bags > 2:
+                cuts[bags // 2] = cuts[bags // 2 - 1]                     # (an empty bag)
+            if t % 2:
+                cuts[-1] = n
+            p.offsets_np, p.offsets = cuts, torch.from_numpy(cuts).to(p.dev)
+            d = torch.from_numpy(ids[t]).to(p.dev)
+            p.lookup(ids[t], ids_dev=d)
+            if t % 2:
+                p.update(ids[t], rng.standard_normal((bags, dim)).astype(np.float32), ids_dev=d)
+        p.flush_and_compare()
+    finally:
+        p.close()
+
+
 @pytest.mark.parametrize("when", ["before", "between"])
 @pytest.mark.parametrize("policy", [0, 1, 2])
 @pytest.mark.parametrize("n,vocab", [(200, 3_000), (1_024, 5_000_000), (2_700, 5_000_000), (2_731, 100_000), (5_400, 5_000_000)])
