@@ -1657,10 +1657,11 @@ constexpr int AP_THREADS = 256;
 constexpr int AP_SORTED = 0, AP_REUSED = 1, AP_REUSED_EVICT = 2, AP_REUSED_EVICT_TIED = 3;
 // Gradient rows in flight per row group, and waves per SIMD the kernel is held to (rows of one piece
 // per lane).  Tiles of 64 positions: seven waves (72 registers), so that all tiles of a batch of
-// config 2's or 4's size are resident from the start, with four rows in flight (three where the
-// kernel also pushes early: two more row addresses to keep).  Tiles of 128 positions (rows of more
+// config 2's or 4's size are resident from the start, with three rows in flight (Adagrad with four keeps twelve values in
+// scratch memory instead of four: 106496 ids 58.4 us a step, 57.8 with three; 40000 ids in bags of five 48.9 and 46.5) or four (SGD
+// without the early push; with five 200000 ids of 32 floats 83.7 us, with four 83.0).  Tiles of 128 positions (rows of more
 // than 128 floats): six waves and six rows (four with the early push); seven waves were slower there.
-__host__ __device__ constexpr int ap_batch(int ap_tile, bool early) { return ap_tile == 64 ? (early ? 3 : 4) : (early ? 4 : 6); }
+__host__ __device__ constexpr int ap_batch(int ap_tile, bool early, int opt) { return ap_tile == 64 ? (early || opt == AO_ADAGRAD ? 3 : 4) : (early ? 4 : 6); }
 __host__ __device__ constexpr int ap_waves(int ap_tile) { return ap_tile == 64 ? 7 : 6; }
 constexpr int AP_SOLO = 32;
 constexpr int AP_ROWS = 8;
@@ -1868,7 +1869,7 @@ __global__ __launch_bounds__(AP_THREADS) __attribute__((amdgpu_waves_per_eu(MAXC
 {
     using V = typename VecT<VEC>::type;
     constexpr bool VERIFY = MODE != AP_SORTED, TIED = MODE == AP_REUSED_EVICT_TIED, EVICT = MODE == AP_REUSED_EVICT || TIED;
-    constexpr int BATCH = ap_batch(AP_TILE, EARLY);
+    constexpr int BATCH = ap_batch(AP_TILE, EARLY, OPT);
     // The tiles' workgroups live longest, so they take the first places; the carried stages, the select
     // stage and the id check follow in the places they leave (the other way round the step was 1 to 2 %
     // longer on every config).
