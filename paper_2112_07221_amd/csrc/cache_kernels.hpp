@@ -250,17 +250,12 @@ template <typename T> __device__ __forceinline__ T &lds_as() { return *reinterpr
 
 // Up to two sort stages, of two different announced batches, travel in one kernel.  Returns
 // true if this workgroup ran one of them; otherwise bid / nblk number the kernel's own workgroups.
-// HIST_ONLY: both are known to be histogram stages (cheap in registers).
-template <bool HIST_ONLY = false, int THREADS = SORT_THREADS>
 __device__ __forceinline__ bool run_carried(const SortStage &a, const SortStage &b, uint32_t &bid, uint32_t &nblk)
 {
     uint32_t *lds = reinterpret_cast<uint32_t *>(dyn_lds);
     if (bid < a.blocks + b.blocks) {
         const bool first = bid < a.blocks;
-        const SortStage &st = first ? a : b;
-        const uint32_t tile = first ? bid : bid - a.blocks;
-        if (HIST_ONLY) { __builtin_amdgcn_s_setprio(3); sort_hist_body<THREADS>(st, tile, lds); }
-        else sort_stage_body<THREADS>(st, tile, lds);
+        sort_stage_body<SORT_THREADS>(first ? a : b, first ? bid : bid - a.blocks, lds);
         return true;
     }
     bid -= a.blocks + b.blocks; nblk -= a.blocks + b.blocks;
@@ -486,25 +481,14 @@ __device__ __forceinline__ void check_order_body(const CacheView &cv, const Work
     if (__any(changed) && lane_id() == 0) atomicOr(&cv.ds->err, ERRBIT_STATE);
 }
 
-// RIDE: carries sort stages of announced batches, in workgroups of a thread per key, behind its own (they end first).
-// (96 scalar registers: with the 102 that the stages' arguments would take, a SIMD holds seven waves, and a compute unit one workgroup instead of two.)
-template <bool LOOKUP, bool RIDE>
+template <bool LOOKUP>
 __global__ __launch_bounds__(PT_THREADS) __attribute__((amdgpu_num_sgpr(96))) void probe_kernel(CacheView cv, Workspace ws, uint32_t n, uint32_t t_now, uint32_t ptiles,
                                                            const uint32_t *tile_free, uint32_t *tile_free_idle, uint32_t ev_idle,
                                                            TrimPlan tp,
                                                            const int64_t *__restrict__ check_ids, int pf_idle,
-                                                           uint32_t *__restrict__ inv, SortStage ride, SortStage ride2)
+                                                           uint32_t *__restrict__ inv)
 {
     __shared__ uint32_t lds[PT_WAVES + 1];
-    uint32_t own_blocks = gridDim.x;
-    if (RIDE) {
-        own_blocks -= ride.blocks + ride2.blocks;
-        if (blockIdx.x >= own_blocks) {
-            uint32_t bid = blockIdx.x - own_blocks, nblk = gridDim.x;
-            run_carried<false, PT_THREADS>(ride, ride2, bid, nblk);
-            return;
-        }
-    }
     // rows entering (+) and leaving (-) the kept bins: by how many bins they lie before the present one, and by the
     // first digit the same way (the present one and the one before: what lies further back goes to memory at once)
     __shared__ uint32_t kept_delta[LOOKUP ? SEL_BINS : 1], coarse_delta[2];
@@ -519,7 +503,7 @@ __global__ __launch_bounds__(PT_THREADS) __attribute__((amdgpu_num_sgpr(96))) vo
     if (blockIdx.x >= ptiles) {          // extra workgroups of a lookup: the free list for the fill kernel
         // ... and clean counts for the trim that follows this lookup
         const uint32_t first = ptiles + check_blocks;
-        for (uint32_t i = (blockIdx.x - first) * PT_THREADS + threadIdx.x; i < tp.zero_words; i += (own_blocks - first) * PT_THREADS) tp.zero_from[i] = 0;
+        for (uint32_t i = (blockIdx.x - first) * PT_THREADS + threadIdx.x; i < tp.zero_words; i += (gridDim.x - first) * PT_THREADS) tp.zero_from[i] = 0;
         free_list_body(cv, tile_free, tile_free_idle, ev_idle, blockIdx.x - first, lds);
         return;
     }
@@ -643,19 +627,11 @@ __global__ __launch_bounds__(PT_THREADS) __attribute__((amdgpu_num_sgpr(96))) vo
 
 // No cache (the paper's baseline "Hybrid (w/o Cache)", Section 5): Read and Write go straight to
 // the global table.  The sorted order is used as it is; a key stands for its own row.
-template <bool LOOKUP, bool RIDE>
+template <bool LOOKUP>
 __global__ __launch_bounds__(PT_THREADS) __attribute__((amdgpu_num_sgpr(96))) void direct_probe_kernel(CacheView cv, Workspace ws, uint32_t n, uint32_t t_now, uint32_t ptiles,
-                                                                  const int64_t *__restrict__ check_ids, uint32_t *__restrict__ inv, SortStage ride, SortStage ride2)
+                                                                  const int64_t *__restrict__ check_ids, uint32_t *__restrict__ inv)
 {
     __shared__ uint32_t lds[PT_WAVES + 1];
-    if (RIDE) {
-        const uint32_t own_blocks = gridDim.x - (ride.blocks + ride2.blocks);
-        if (blockIdx.x >= own_blocks) {
-            uint32_t bid = blockIdx.x - own_blocks, nblk = gridDim.x;
-            run_carried<false, PT_THREADS>(ride, ride2, bid, nblk);
-            return;
-        }
-    }
     if (blockIdx.x >= ptiles) { check_order_body(cv, ws, check_ids, n, blockIdx.x - ptiles); return; }     // (an order sorted ahead, see probe_kernel)
     const uint32_t j = blockIdx.x * PT_TILE + threadIdx.x;
     if (LOOKUP && inv && j < n) inv[ws.perm[j]] = j;         // pooled lookup (see probe_kernel)
@@ -1081,11 +1057,10 @@ struct FillLds {                             // (also what the pooled gather's w
     uint32_t scan[4 + 1];
 };
 static_assert(sizeof(FillLds) >= 256 * 4 * sizeof(double), "");
-// RIDE: 0 carries no sort stage, 1 a histogram stage (cheap in registers: the gather keeps its
-// occupancy), 2 any stage.
+// RIDE: carries sort stages of announced batches.
 // TRACE: time stamps (het_profile_trace); a kernel of its own, because the stamps' arguments cost the
 // other one scalar registers it has no room for.
-template <int VEC, bool POOLED, int RIDE, bool TRACE>
+template <int VEC, bool POOLED, bool RIDE, bool TRACE>
 __global__ __launch_bounds__(256) void fill_gather_kernel(CacheView cv, Workspace ws, uint32_t n, uint32_t t_now, uint32_t ptiles, uint32_t fill_blocks,
                                                           TrimPlan tp, uint32_t hist_blocks, float *__restrict__ out, const int64_t *__restrict__ offsets, uint32_t n_bags,
                                                           const uint32_t *__restrict__ inv, SortStage ride, SortStage ride2,
@@ -1096,8 +1071,7 @@ __global__ __launch_bounds__(256) void fill_gather_kernel(CacheView cv, Workspac
     uint32_t bid = blockIdx.x, nblk = gridDim.x;
     const KernelTrace tr = TRACE ? tr_arg : KernelTrace{nullptr, 0u};
     tr.stamp(0);
-    if (RIDE == 1 && run_carried<true>(ride, ride2, bid, nblk)) { tr.role(1); tr.end(); return; }
-    if (RIDE == 2 && run_carried<false>(ride, ride2, bid, nblk)) { tr.role(1); tr.end(); return; }
+    if (RIDE && run_carried(ride, ride2, bid, nblk)) { tr.role(1); tr.end(); return; }
     if (bid < push_blocks) { deferred_push_body<VEC>(cv, push_buf, bid, push_blocks); tr.role(6); tr.end(); return; }    // host-backed table: the last trim's write-back
     bid -= push_blocks; nblk -= push_blocks;
     if (bid < ah.blocks) { ahead_list_body(cv, ah, bid); tr.role(6); tr.end(); return; }                                 // host-backed table: what to fetch ahead for the coming batch
@@ -2231,7 +2205,7 @@ constexpr int HET_APPLY_PARTS = 8;
         CacheView, Workspace, ApplyBorders, const int64_t *__restrict__, const float *__restrict__, const uint32_t *__restrict__, float, float, \
         uint32_t, uint32_t, TrimPlan, uint32_t, SortStage, SortStage, KernelTrace, int);
 
-#define HET_FILL_RIDES(X, part, VEC, POOLED, TRACE) X(part, VEC, POOLED, 0, TRACE) X(part, VEC, POOLED, 1, TRACE) X(part, VEC, POOLED, 2, TRACE)
+#define HET_FILL_RIDES(X, part, VEC, POOLED, TRACE) X(part, VEC, POOLED, false, TRACE) X(part, VEC, POOLED, true, TRACE)
 #define HET_FILL_VARIANTS(X)                                                                                    \
     HET_FILL_RIDES(X, 0, 4, false, false) HET_FILL_RIDES(X, 0, 4, true, false) HET_FILL_RIDES(X, 0, 1, false, false) \
     HET_FILL_RIDES(X, 0, 1, true, false) HET_FILL_RIDES(X, 1, 4, false, true) HET_FILL_RIDES(X, 1, 4, true, true)  \

@@ -48,9 +48,7 @@ struct Announced {
     const int64_t *ids = nullptr;
     uint32_t n = 0;
     int set = 0;
-    int max_bits = 0;                // widest digit its sort may use (see sort_bits_ahead)
-    int next_stage = 0;              // stages [0, next_stage) are enqueued; 2 * passes stages in all
-    int result = -1;                 // the buffer that holds the finished order (-1: not finished by sort_now)
+    int next_stage = 0;              // stages [0, next_stage) are enqueued (carried, or all of them)
 };
 
 struct het_cache {
@@ -75,8 +73,9 @@ struct het_cache {
     // three batches announced ahead by het_prefetch, whose sorts are carried by the kernels of the
     // calls in between (a sort is more stages long than a lookup and an update have kernels, so
     // in steady state two announced batches are being sorted and a third stands ready).
+    // Per set the tiles in order of the ranges, [0], and the order, [1].
     uint32_t *keys[SORT_SETS][2] = {}, *idx[SORT_SETS][2] = {};
-    uint32_t *sort_hist[SORT_SETS] = {};
+    uint32_t *sort_words[SORT_SETS] = {};     // SortPlan's cuts and beginnings
     int sort_set = 0;                // the set that holds the current batch's order
     uint32_t sorted_n = 0;           // how many ids that order has (0: there is none yet)
     Announced ann[SORT_SETS - 1];    // announced batches, oldest first
@@ -256,63 +255,22 @@ uint32_t row_grid(const RowGeom &g, uint64_t items)
     return std::max(1u, std::min(cdiv(items, per_block), 256u * 8u));      // at most 8 workgroups per CU
 }
 
-// A sort that runs in kernels of its own: up to 256 tiles digits of up to 11 bits and 1024 threads to a
-// tile, because a stage costs a kernel boundary and a chain of barriers whatever its width; beyond that adding
-// up the wide histograms' rows is most of a stage, and narrow digits (256 threads to a tile) are faster.
-// All stages together, us, wide / narrow: 106496 ids of 20 bits 25 / 31, 114688 of 22 bits 32 / 34,
-// 200000 of 20 bits 31 / 34, 409600 of 20 bits 56 / 43, 1048576 of 20 bits 118 / 94.
-constexpr int SORT_NARROW_BITS = 8;
-constexpr uint32_t SORT_WIDE_TILES = 256;
-int sort_bits_alone(uint32_t n) { return cdiv(n, SORT_TILE) <= SORT_WIDE_TILES ? SORT_MAX_BITS : SORT_NARROW_BITS; }
-
-// Digits of a sort: as few passes as max_bits allows, of equal width.
-SortPlan make_sort_plan(const het_cache *c, uint32_t n, int set, int max_bits)
-{
-    SortPlan sp{};
-    sp.n = n;
-    sp.vocab = c->cv.vocab;
-    const int bits = bit_width(sp.vocab);               // the key `vocab` itself marks a bad id
-    sp.passes = std::max(1, (bits + max_bits - 1) / max_bits);
-    sp.width = std::max(SORT_MIN_BITS, (bits + sp.passes - 1) / sp.passes);
-    sp.ntiles = cdiv(n, SORT_TILE);
-    // narrow digits: rows are short, and a histogram stage of one tile per workgroup is the quickest to carry (a
-    // step of 62393 ids without a cache 42 us, with 4 tiles 49 us) until there are hundreds of rows (a step of
-    // 409600 ids 327 us, with 4 tiles 314 us); wide ones: few rows to add up (106496 ids: 25.1 us with 4 tiles, 26.5 with 8)
-    sp.super = sp.width <= SORT_NARROW_BITS ? (sp.ntiles <= 128 ? 1u : 4u) : (sp.ntiles <= 128 ? 4u : 8u);
-    sp.nsupers = cdiv(sp.ntiles, sp.super);
-    sp.hist = c->sort_hist[set];
-    return sp;
-}
-
-// Digits of an announced batch's sort.  A step has two kernels that carry a stage (the lookup's second one and the
-// update), three where the eviction has one of its own, and the probe for what these cannot (probe_must_ride).
-// A batch announced one ahead meets them once: two wide passes are (nearly) all carried.  Announced two ahead
-// it meets them twice: six narrow stages are carried just as completely, and they are shorter and
-// need less LDS, so the carrying kernels keep their occupancy (114688 ids of 22 bits: the update 40 us with
-// stages of 8 bits, 48 us with stages of 11).  With the eviction beside the update that takes the probe in every
-// step (106496 ids: 12.1 us, 7.7 without a stage; 409600 ids: 29.8 and 18.2).
-int sort_bits_ahead(const het_cache *c, uint32_t n)
-{
-    const int carried = c->n_ann >= 2 ? 6 : 0;
-    return 2 * make_sort_plan(c, n, 0, SORT_NARROW_BITS).passes <= carried ? SORT_NARROW_BITS : sort_bits_alone(n);
-}
-
-int sort_stages(const het_cache *c, int max_bits) { return 2 * make_sort_plan(c, 1, 0, max_bits).passes; }
-int sort_result_buffer(const het_cache *c, int max_bits) { return (make_sort_plan(c, 1, 0, max_bits).passes - 1) & 1; }
-
-// Stage `stage` of the sort of ids[n] into buffer set `set`.  Pass p writes buffer p & 1 of the
-// set and reads the other one; stage 0 leaves the ids, converted to keys, where pass 0 reads.
-SortStage make_stage(const het_cache *c, const int64_t *ids, uint32_t n, int set, int max_bits, int stage)
+// Stage `stage` of the sort of ids[n] into buffer set `set`; carried: its first stage was, or is.  The order sorted last tells
+// where the ranges begin.
+SortStage make_stage(const het_cache *c, const int64_t *ids, uint32_t n, int set, int stage, bool carried)
 {
     SortStage s{};
-    s.sp = make_sort_plan(c, n, set, max_bits);
-    const int pass = stage >> 1, out = pass & 1, in = 1 - out;
+    SortPlan &sp = s.sp;
+    sp.n = n; sp.vocab = c->cv.vocab;
+    sp.ranges = sort_ranges(n, carried); sp.ntiles = cdiv(n, SORT_TILE);
+    sp.cuts = c->sort_words[set];
+    sp.begin = reinterpret_cast<uint16_t *>(sp.cuts + sp.ranges);
+    sp.keys = c->keys[set][0]; sp.idx = c->idx[set][0];
+    if (c->sorted_n) { sp.known = c->ws.skey; sp.n_known = c->sorted_n; }
     s.ids = ids;
-    s.keys_in = c->keys[set][in]; s.idx_in = c->idx[set][in];
-    s.keys_out = stage == 0 ? c->keys[set][in] : c->keys[set][out];
-    s.idx_out = c->idx[set][out];
+    s.keys_out = c->keys[set][1]; s.idx_out = c->idx[set][1];
     s.stage = stage;
-    s.blocks = stage & 1 ? s.sp.ntiles : s.sp.nsupers;
+    s.blocks = stage == SORT_PART ? sp.ntiles : sp.ranges;
     return s;
 }
 
@@ -331,74 +289,42 @@ void begin_call(het_cache *c)
     c->cv.next_call = &c->cv.ds->call[1 - c->cslot];
 }
 
-// The one-workgroup sort from where stages [0, s.stage) have left it (s: the first stage that is not enqueued).
 template <int ITEMS>
-void launch_solo(het_cache *c, const SortStage &s, uint32_t *keys_out, uint32_t *idx_out)
+void launch_solo(het_cache *c, const int64_t *ids, uint32_t n, int set)
 {
-    const int shift = (s.stage >> 1) * s.sp.width;
-    const int bits = std::max(SORT_MIN_BITS, bit_width(s.sp.vocab) - shift), passes = solo_passes(bits), width = (bits + passes - 1) / passes;
-    LAUNCH(c, K_SORT_STAGE, sort_solo_kernel<ITEMS><<<1, SOLO_THREADS, solo_lds_bytes(ITEMS, width), c->stream>>>(
-                                s.ids, s.stage > 0 ? s.keys_in : nullptr, s.stage > 1 ? s.idx_in : nullptr, s.sp.n, s.sp.vocab, shift, passes, width,
-                                keys_out, idx_out));
+    const int bits = std::max(SORT_MIN_BITS, bit_width(c->cv.vocab)), passes = solo_passes(bits, SORT_THREADS_ALONE), width = (bits + passes - 1) / passes;
+    LAUNCH(c, K_SORT_STAGE, sort_solo_kernel<ITEMS><<<1, SORT_THREADS_ALONE, solo_lds_bytes(ITEMS, width, SORT_THREADS_ALONE), c->stream>>>(
+                                ids, n, c->cv.vocab, passes, width, c->keys[set][1], c->idx[set][1]));
 }
 
-// A batch sorted in ranges (see SortRanges): its plan.  The tiles' order lies in buffer 0, the result in buffer 1, and what
-// the launches hand on where the general sort has its histograms.  Ranges for some 500 keys each.
-// The order sorted before tells where ranges begin, unless it lies where the tiles' order goes.
-SortRanges make_ranges(const het_cache *c, uint32_t n, int set)
+// What is left of a sort (stages [first_stage, end)), in kernels of its own.  Up to SOLO_MAX ids none of whose stages has run
+// by one workgroup in one launch: its time is the ballots' on one compute unit and grows with the ids (20 bits: 4.9 us
+// for 200, 7.7 for 2048, 11.9 for 4096, 19.9 for 8192); two launches take 10.8 us for 3328 ids, 11.7 for 8658.
+void sort_now(het_cache *c, const int64_t *ids, uint32_t n, int set, int first_stage)
 {
-    SortRanges sr{};
-    sr.n = n; sr.vocab = c->cv.vocab;
-    sr.ranges = n <= 16384 ? 64 : (n <= 65536 ? 128 : SR_MAX_RANGES);
-    sr.ntiles = cdiv(n, SORT_TILE);
-    sr.cuts = c->sort_hist[set];
-    sr.begin = reinterpret_cast<uint16_t *>(sr.cuts + SR_MAX_RANGES);
-    sr.keys = c->keys[set][0]; sr.idx = c->idx[set][0];
-    if (c->sorted_n && c->ws.skey != sr.keys) { sr.known = c->ws.skey; sr.n_known = c->sorted_n; }
-    return sr;
+    if (first_stage == 0 && n <= SOLO_MAX) {
+        if (n <= SORT_THREADS_ALONE) launch_solo<1>(c, ids, n, set);
+        else if (n <= 2 * SORT_THREADS_ALONE) launch_solo<2>(c, ids, n, set);
+        else launch_solo<4>(c, ids, n, set);
+        return;
+    }
+    for (int st = first_stage; st < SORT_STAGES; ++st) {
+        const SortStage s = make_stage(c, ids, n, set, st, first_stage > 0);
+        const uint32_t lds = sort_stage_lds_bytes(s, SORT_THREADS_ALONE);
+        if (st == SORT_PART) LAUNCH(c, K_SORT_STAGE, sort_part_kernel<<<s.blocks, SORT_THREADS_ALONE, lds, c->stream>>>(s));
+        else LAUNCH(c, K_SORT_STAGE, sort_range_kernel<<<s.blocks, SORT_THREADS_ALONE, lds, c->stream>>>(s));
+    }
 }
 
-// What is left of a sort (stages [first_stage, end)), in kernels of its own.  Up to SOLO_MAX ids by one workgroup in one
-// launch: its time is the ballots' on one compute unit and grows with the ids (20 bits: 4.9 us for 200,
-// 7.7 for 2048, 11.9 for 4096, 19.9 for 8192).  Up to SR_MAX ids in ranges, if three stages or more are left: two
-// launches from the ids, or the keys that stage 0 left, against a stage's 3.3 us (histogram) and 6.8 us (scatter): 26624 ids
-// 12.6 us (four stages 22), 53248 13.2 (24), 106496 15.7 (25).  With cuts from a sample, not from an order sorted before,
-// 106496 ids take 18.9.
-// Returns which buffer of the set holds the order.
-int sort_now(het_cache *c, const int64_t *ids, uint32_t n, int set, int max_bits, int first_stage)
-{
-    const int end = sort_stages(c, max_bits), result = sort_result_buffer(c, max_bits);
-    if (end - first_stage >= 3 && n > SOLO_ALONE && n <= SR_MAX) {
-        const SortRanges sr = make_ranges(c, n, set);
-        LAUNCH(c, K_SORT_STAGE, sort_part_kernel<<<sr.ntiles, SOLO_THREADS, 0, c->stream>>>(ids, first_stage > 0 ? c->keys[set][1] : nullptr, sr));
-        LAUNCH(c, K_SORT_STAGE, sort_range_kernel<<<sr.ranges, SOLO_THREADS, sizeof(SortRangeLds), c->stream>>>(sr, c->keys[set][1], c->idx[set][1]));
-        return 1;
-    }
-    if (3ull * n <= (uint64_t)SOLO_MAX * (uint32_t)std::max(0, std::min(3, end - first_stage - 1))) {
-        const SortStage s = make_stage(c, ids, n, set, max_bits, first_stage);
-        uint32_t *k = c->keys[set][result], *i = c->idx[set][result];
-        if (n <= SOLO_THREADS) launch_solo<1>(c, s, k, i);
-        else if (n <= 2 * SOLO_THREADS) launch_solo<2>(c, s, k, i);
-        else if (n <= 4 * SOLO_THREADS) launch_solo<4>(c, s, k, i);
-        else launch_solo<8>(c, s, k, i);
-        return result;
-    }
-    for (int st = first_stage; st < end; ++st) {
-        const SortStage s = make_stage(c, ids, n, set, max_bits, st);
-        if (s.sp.ntiles <= SORT_WIDE_TILES)
-            LAUNCH(c, K_SORT_STAGE, sort_stage_kernel<SORT_THREADS_ALONE><<<s.blocks, SORT_THREADS_ALONE, sort_stage_lds_bytes(s.sp.width, s.sp.super, s.stage, SORT_THREADS_ALONE), c->stream>>>(s));
-        else
-            LAUNCH(c, K_SORT_STAGE, sort_stage_kernel<SORT_THREADS><<<s.blocks, SORT_THREADS, sort_stage_lds_bytes(s.sp.width, s.sp.super, s.stage, SORT_THREADS), c->stream>>>(s));
-    }
-    return result;
-}
+// The largest batch whose sort is carried: beyond it ranges hold more keys than a workgroup of a carrying kernel sorts at once.
+constexpr uint32_t CARRY_MAX = SORT_MAX_RANGES * 512;
 
 // The next stage of the oldest announced batch whose sort is not complete yet, for the kernel
 // that is about to be launched to carry.
 SortStage next_ride_of(het_cache *c, int a)
 {
     Announced &an = c->ann[a];
-    return make_stage(c, an.ids, an.n, an.set, an.max_bits, an.next_stage++);
+    return make_stage(c, an.ids, an.n, an.set, an.next_stage++, true);
 }
 
 // What the kernel about to be launched carries: the next stage of the oldest announced batch whose
@@ -407,28 +333,15 @@ SortStage next_ride_of(het_cache *c, int a)
 struct Rides {
     SortStage a, b;
     uint32_t blocks() const { return a.blocks + b.blocks; }
-    // 0: nothing, 1: histogram stages only, 2: a scatter stage among them
-    int kind() const { return !blocks() ? 0 : (((a.blocks && (a.stage & 1)) || (b.blocks && (b.stage & 1))) ? 2 : 1); }
 };
 
 // LDS a kernel needs: its own roles' or, if larger, a carried stage's.
-uint32_t lds_bytes(size_t own, const Rides &r, int threads = SORT_THREADS)
+uint32_t lds_bytes(size_t own, const Rides &r)
 {
     uint32_t need = (uint32_t)own;
-    if (r.a.blocks) need = std::max(need, sort_stage_lds_bytes(r.a.sp.width, r.a.sp.super, r.a.stage, threads));
-    if (r.b.blocks) need = std::max(need, sort_stage_lds_bytes(r.b.sp.width, r.b.sp.super, r.b.stage, threads));
+    if (r.a.blocks) need = std::max(need, sort_stage_lds_bytes(r.a, SORT_THREADS));
+    if (r.b.blocks) need = std::max(need, sort_stage_lds_bytes(r.b, SORT_THREADS));
     return need;
-}
-
-// Must the probe carry a stage?  The kernels behind it carry them for less (the probe's workgroups are large ones of
-// its own size: 409600 ids 311 -> 328 us a step where nothing needed it, while the eviction still had a kernel of its
-// own), so only where an announced batch would meet too few of those before its lookup: 2 or 3 a step (with the
-// eviction beside the update, or none, or in a kernel of its own).
-bool probe_must_ride(const het_cache *c, bool evict_kernel)
-{
-    for (int a = 0; a < c->n_ann; ++a)
-        if (sort_stages(c, c->ann[a].max_bits) - c->ann[a].next_stage > (a + 1) * (evict_kernel ? 3 : 2)) return true;
-    return false;
 }
 
 Rides next_rides(het_cache *c)
@@ -436,7 +349,7 @@ Rides next_rides(het_cache *c)
     Rides r{no_stage(), no_stage()};
     int got = 0;
     for (int a = 0; a < c->n_ann && got < 2; ++a) {
-        if (c->ann[a].next_stage >= sort_stages(c, c->ann[a].max_bits)) continue;
+        if (c->ann[a].next_stage >= SORT_STAGES || c->ann[a].n > CARRY_MAX) continue;
         (got == 0 ? r.a : r.b) = next_ride_of(c, a);
         ++got;
     }
@@ -449,12 +362,12 @@ void drop_oldest_announcement(het_cache *c)
     c->n_ann -= 1;
 }
 
-void use_order(het_cache *c, int set, int buf, uint32_t n)
+void use_order(het_cache *c, int set, uint32_t n)
 {
     c->sorted_n = n;
     c->sort_set = set;
-    c->ws.skey = c->keys[set][buf];
-    c->ws.perm = c->idx[set][buf];
+    c->ws.skey = c->keys[set][1];
+    c->ws.perm = c->idx[set][1];
 }
 
 // The trim's select plan for the rows cached after the lookup that just ran.
@@ -515,7 +428,7 @@ int settle_fetch_impl(het_cache *c)
     const uint32_t fill_blocks = std::min(cdiv(row_grid(c->cv.geom, n), (uint32_t)FILL_ROWS), FILL_MAX_BLOCKS);
     const TrimPlan none{};
     const SortStage no = no_stage();
-    LAUNCH(c, K_FILL_GATHER, fill_gather_kernel<VEC, false, 0, false><<<fill_blocks, 256, sizeof(FillLds), c->stream>>>(
+    LAUNCH(c, K_FILL_GATHER, fill_gather_kernel<VEC, false, false, false><<<fill_blocks, 256, sizeof(FillLds), c->stream>>>(
                                  c->cv, c->ws, n, c->owed_t, ptiles, fill_blocks, none, 0u, nullptr, nullptr, 0u, nullptr, no, no,
                                  0u, 0, 0u, Ahead{}, KernelTrace{}, 2, 1u));
     c->fetch_owed = false;
@@ -629,23 +542,18 @@ int run_lookup(het_cache *c, const int64_t *ids, uint32_t n, const int64_t *offs
         for (int a = 0; a < match; ++a) drop_oldest_announcement(c);
         const Announced an = c->ann[0];
         drop_oldest_announcement(c);
-        use_order(c, an.set, an.result >= 0 ? an.result : sort_now(c, ids, n, an.set, an.max_bits, an.next_stage), n);
+        sort_now(c, ids, n, an.set, an.next_stage);
+        use_order(c, an.set, n);
     } else {
-        use_order(c, c->sort_set, sort_now(c, ids, n, c->sort_set, sort_bits_alone(n), 0), n);             // over the previous batch's order: it is not needed any more
+        sort_now(c, ids, n, c->sort_set, 0);             // over the previous batch's order: it is not needed any more
+        use_order(c, c->sort_set, n);
     }
     const uint32_t t_now = (uint32_t)c->t_host;
     const uint32_t split = offsets ? pool_split(c->cv.geom, n, n_bags) : 1u;
     if (c->cv.direct) {
         // no cache: mark the runs, then gather straight from the global table
         const uint32_t dtiles = cdiv(n, PT_TILE), dblocks = dtiles * (match >= 0 ? 2u : 1u);
-        {
-            const Rides ride = probe_must_ride(c, false) ? next_rides(c) : Rides{no_stage(), no_stage()};
-#define DIRECT_PROBE(RIDE)                                                                                                                       \
-    LAUNCH(c, K_PROBE, direct_probe_kernel<true, RIDE><<<dblocks + ride.blocks(), PT_THREADS, lds_bytes(0, ride, PT_THREADS), c->stream>>>(        \
-                           c->cv, c->ws, n, t_now, dtiles, match >= 0 ? ids : nullptr, offsets ? c->inv : nullptr, ride.a, ride.b))
-            if (ride.blocks()) DIRECT_PROBE(true); else DIRECT_PROBE(false);
-#undef DIRECT_PROBE
-        }
+        LAUNCH(c, K_PROBE, direct_probe_kernel<true><<<dblocks, PT_THREADS, 0, c->stream>>>(c->cv, c->ws, n, t_now, dtiles, match >= 0 ? ids : nullptr, offsets ? c->inv : nullptr));
         const Rides ride = next_rides(c);
         const uint32_t grid = ride.blocks() + row_grid(c->cv.geom, offsets ? (uint64_t)n_bags * split : cdiv(n, GATHER_ROWS));
         const uint32_t lds = lds_bytes(std::max(sizeof(FillLds), sizeof(TrimLds)), ride);
@@ -654,9 +562,8 @@ int run_lookup(het_cache *c, const int64_t *ids, uint32_t n, const int64_t *offs
     LAUNCH(c, K_FILL_GATHER, fill_gather_kernel<VEC, POOLED, RIDE, TRACE><<<grid, 256, lds, c->stream>>>(                   \
                                  c->cv, c->ws, n, t_now, 0u, 0u, none, 0u, out, offsets, n_bags, c->inv, ride.a, ride.b, 0u, 0, 0u, Ahead{}, c->trace[1], 0, split))
 #define GATHER_ONLY(POOLED, RIDE) do { if (c->trace[1].rec) GATHER_ONLY_T(POOLED, RIDE, true); else GATHER_ONLY_T(POOLED, RIDE, false); } while (0)
-        const int kind = ride.kind();
-        if (!offsets) { if (kind == 0) GATHER_ONLY(false, 0); else if (kind == 1) GATHER_ONLY(false, 1); else GATHER_ONLY(false, 2); }
-        else { if (kind == 0) GATHER_ONLY(true, 0); else if (kind == 1) GATHER_ONLY(true, 1); else GATHER_ONLY(true, 2); }
+        if (!offsets) { if (ride.blocks()) GATHER_ONLY(false, true); else GATHER_ONLY(false, false); }
+        else { if (ride.blocks()) GATHER_ONLY(true, true); else GATHER_ONLY(true, false); }
 #undef GATHER_ONLY
 #undef GATHER_ONLY_T
         if ((rc = launch_ok()) != HET_OK) return rc;
@@ -675,14 +582,10 @@ int run_lookup(het_cache *c, const int64_t *ids, uint32_t n, const int64_t *offs
     }
     {
         hash_find(c, c->ws.skey, n);
-        const Rides ride = probe_must_ride(c, !evict_beside_update(c, tp)) ? next_rides(c) : Rides{no_stage(), no_stage()};
         const uint32_t blocks = ptiles + (match >= 0 ? ptiles : 0u) + stiles;
-#define PROBE(RIDE)                                                                                                                              \
-    LAUNCH(c, K_PROBE, probe_kernel<true, RIDE><<<blocks + ride.blocks(), PT_THREADS, lds_bytes(0, ride, PT_THREADS), c->stream>>>(                \
-                           c->cv, c->ws, n, t_now, ptiles, c->tile_free[c->tf_last], c->tile_free[1 - c->tf_last], (uint32_t)(1 - c->tf_last),    \
-                           tp, match >= 0 ? ids : nullptr, c->side ? c->pf_slot_next : -1, offsets ? c->inv : nullptr, ride.a, ride.b))
-        if (ride.blocks()) PROBE(true); else PROBE(false);
-#undef PROBE
+        LAUNCH(c, K_PROBE, probe_kernel<true><<<blocks, PT_THREADS, 0, c->stream>>>(
+                               c->cv, c->ws, n, t_now, ptiles, c->tile_free[c->tf_last], c->tile_free[1 - c->tf_last], (uint32_t)(1 - c->tf_last),
+                               tp, match >= 0 ? ids : nullptr, c->side ? c->pf_slot_next : -1, offsets ? c->inv : nullptr));
     }
 
     c->counted = count_beside_fill(c, tp);
@@ -701,15 +604,12 @@ int run_lookup(het_cache *c, const int64_t *ids, uint32_t n, const int64_t *offs
     } while (0)
 #define FILL_GATHER_ANY(GRID, FILLB, HISTB, PUSHB)                                                                        \
     do {                                                                                                                  \
-        const int kind = ride.kind();                                                                                     \
         if (!offsets) {                                                                                                   \
-            if (kind == 0) FILL_GATHER(false, 0, GRID, FILLB, HISTB, PUSHB);                                              \
-            else if (kind == 1) FILL_GATHER(false, 1, GRID, FILLB, HISTB, PUSHB);                                         \
-            else FILL_GATHER(false, 2, GRID, FILLB, HISTB, PUSHB);                                                        \
+            if (ride.blocks()) FILL_GATHER(false, true, GRID, FILLB, HISTB, PUSHB);                                       \
+            else FILL_GATHER(false, false, GRID, FILLB, HISTB, PUSHB);                                                    \
         } else {                                                                                                          \
-            if (kind == 0) FILL_GATHER(true, 0, GRID, FILLB, HISTB, PUSHB);                                               \
-            else if (kind == 1) FILL_GATHER(true, 1, GRID, FILLB, HISTB, PUSHB);                                          \
-            else FILL_GATHER(true, 2, GRID, FILLB, HISTB, PUSHB);                                                         \
+            if (ride.blocks()) FILL_GATHER(true, true, GRID, FILLB, HISTB, PUSHB);                                        \
+            else FILL_GATHER(true, false, GRID, FILLB, HISTB, PUSHB);                                                     \
         }                                                                                                                 \
     } while (0)
     const uint32_t gather_blocks = row_grid(c->cv.geom, offsets ? (uint64_t)n_bags * split : cdiv(n, GATHER_ROWS));
@@ -753,12 +653,10 @@ int run_lookup(het_cache *c, const int64_t *ids, uint32_t n, const int64_t *offs
         hash_insert(c, n);
         ah = Ahead{};
         if (next) {
-            if (next->result < 0) {                                          // what is left of its sort runs now
-                next->result = sort_now(c, next->ids, next->n, next->set, next->max_bits, next->next_stage);
-                next->next_stage = sort_stages(c, next->max_bits);
-            }
+            sort_now(c, next->ids, next->n, next->set, next->next_stage);                                // what is left of its sort runs now
+            next->next_stage = SORT_STAGES;
             c->pf_serial = (c->pf_serial % 0x7FFFFFFFu) + 1;
-            ah.skey = c->keys[next->set][next->result];
+            ah.skey = c->keys[next->set][1];
             ah.n = next->n;
             ah.blocks = cdiv(next->n, 256);
             ah.list_tag = 0x80000000u | c->pf_serial;
@@ -880,13 +778,14 @@ int run_update(het_cache *c, const int64_t *ids, uint32_t n, const int64_t *offs
     const bool reuse = c->order_valid && ids == c->order_ids && n == c->order_n;
     if (!reuse) {
         if ((rc = settle_fetch(c)) != HET_OK) return rc;
-        use_order(c, c->sort_set, sort_now(c, ids, n, c->sort_set, sort_bits_alone(n), 0), n);
+        sort_now(c, ids, n, c->sort_set, 0);
+        use_order(c, c->sort_set, n);
         if (c->cv.direct)
-            LAUNCH(c, K_PROBE, direct_probe_kernel<false, false><<<cdiv(n, PT_TILE), PT_THREADS, 0, c->stream>>>(c->cv, c->ws, n, (uint32_t)c->t_host, cdiv(n, PT_TILE), nullptr, nullptr, no_stage(), no_stage()));
+            LAUNCH(c, K_PROBE, direct_probe_kernel<false><<<cdiv(n, PT_TILE), PT_THREADS, 0, c->stream>>>(c->cv, c->ws, n, (uint32_t)c->t_host, cdiv(n, PT_TILE), nullptr, nullptr));
         else {
             hash_find(c, c->ws.skey, n);
-            LAUNCH(c, K_PROBE, probe_kernel<false, false><<<cdiv(n, PT_TILE), PT_THREADS, 0, c->stream>>>(
-                                   c->cv, c->ws, n, (uint32_t)c->t_host, cdiv(n, PT_TILE), nullptr, nullptr, 0u, TrimPlan{}, nullptr, -1, nullptr, no_stage(), no_stage()));
+            LAUNCH(c, K_PROBE, probe_kernel<false><<<cdiv(n, PT_TILE), PT_THREADS, 0, c->stream>>>(
+                                   c->cv, c->ws, n, (uint32_t)c->t_host, cdiv(n, PT_TILE), nullptr, nullptr, 0u, TrimPlan{}, nullptr, -1, nullptr));
         }
     }
     const uint32_t *grad_row = nullptr;
@@ -1018,12 +917,11 @@ static int configure_impl(het_cache *c, int64_t max_batch_ids, int32_t optimizer
     Workspace &ws = c->ws;
     const size_t N = (size_t)max_batch_ids;
     const size_t ptiles = cdiv(N, PT_TILE);
-    const size_t sort_tiles = cdiv(N, SORT_TILE);
     const size_t ap_tiles = cdiv(N, (per_lane <= 1 ? ap_tile_for(g.lanes) : 128));
     for (int set = 0; set < SORT_SETS; ++set) {
         for (int i = 0; i < 2; ++i)
             if ((rc = dev_alloc(c, &c->keys[set][i], N)) || (rc = dev_alloc(c, &c->idx[set][i], N))) return rc;
-        if ((rc = dev_alloc(c, &c->sort_hist[set], std::max(2 * sort_tiles * ((size_t)1 << (SORT_NARROW_BITS - 1)), (sort_tiles + cdiv(sort_tiles, 4)) * (SORT_MAX_BINS / 2))))) return rc;
+        if ((rc = dev_alloc(c, &c->sort_words[set], sort_plan_words((uint32_t)N)))) return rc;
     }
     c->cv.last = &cv.ds->call[0];
     c->cv.next_call = &cv.ds->call[1];
@@ -1052,13 +950,10 @@ static int configure_impl(het_cache *c, int64_t max_batch_ids, int32_t optimizer
     }
     HIP_TRY(hipMemsetAsync(c->tile_free[1], 0, slot_tiles * sizeof(uint32_t), c->stream));
 
-    // the sort's own kernels, and those that carry wide digits in workgroups as large, ask for more LDS than a launch gets unasked
-    const int max_lds = 160 * 1024;
-    HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(&sort_stage_kernel<SORT_THREADS_ALONE>), hipFuncAttributeMaxDynamicSharedMemorySize, max_lds));
-    HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(&probe_kernel<true, true>), hipFuncAttributeMaxDynamicSharedMemorySize, max_lds - 16 * 1024));      // (it has LDS of its own)
-    HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(&direct_probe_kernel<true, true>), hipFuncAttributeMaxDynamicSharedMemorySize, max_lds - 16 * 1024));
+    // the sort's own kernels ask for more LDS than a launch gets unasked
+    const int max_lds = 144 * 1024;      // (of 160: some of it is taken by the compiler)
+    HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(&sort_part_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, max_lds));
     HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(&sort_range_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, max_lds));
-    HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(&sort_solo_kernel<8>), hipFuncAttributeMaxDynamicSharedMemorySize, max_lds));
     HIP_TRY(hipMemsetAsync(c->bd.arrived, 0, ap_tiles * 3 * sizeof(uint32_t), c->stream));
     HIP_TRY(hipMemsetAsync(cv.ds, 0, sizeof(DState), c->stream));
     init_cache_kernel<<<1024, 256, 0, c->stream>>>(cv);
@@ -1244,7 +1139,7 @@ int het_prefetch(het_cache *c, const int64_t *ids, int64_t n)
         for (int a = 0; a < c->n_ann; ++a) taken = taken || c->ann[a].set == set;
         if (taken) continue;
         Announced an;
-        an.ids = ids; an.n = (uint32_t)n; an.set = set; an.max_bits = sort_bits_ahead(c, an.n); an.next_stage = 0;
+        an.ids = ids; an.n = (uint32_t)n; an.set = set; an.next_stage = 0;
         c->ann[c->n_ann++] = an;
         break;
     }

@@ -82,17 +82,18 @@ def test_every_way_a_batch_is_sorted(n, vocab, ahead):
 
 
 def drawn_positions(n):
-    """The positions whose ids cut a batch into ranges (sort_part_kernel's sample)."""
+    """The positions whose ids cut a batch into ranges (sort_part_body's sample)."""
     t = np.arange(256, dtype=np.uint64)
     lo, hi = t * n // 256, (t + 1) * n // 256
     return (lo + ((t * 0x9E3779B9 % 2**32) * (hi - lo) >> np.uint64(32))).astype(np.int64)
 
 
-@pytest.mark.parametrize("policy", [0, 2])
-@pytest.mark.parametrize("n,vocab", [(4_097, 2_100), (16_384, 3_000_000), (16_385, 1_000_000), (65_537, 4_000_000), (262_144, 70_000)])
-def test_batches_sorted_in_ranges(n, vocab, policy):
+@pytest.mark.parametrize("policy,ahead", [(0, 0), (2, 0), (0, 1), (2, 2)])
+@pytest.mark.parametrize("n,vocab", [(300, 2_100), (4_097, 2_100), (16_384, 3_000_000), (16_385, 1_000_000), (65_537, 4_000_000), (262_144, 70_000)])
+def test_batches_sorted_in_ranges(n, vocab, policy, ahead):
     """Ranges of one key, of no key and of more keys than a workgroup sorts at a time (all drawn positions hold other keys
-    than the rest of the batch), ids outside the vocabulary, keys at both ends of it, cut by orders like and unlike the batch's.  Whole numbers and lr 1, so rows are exact."""
+    than the rest of the batch), keys that fill several ranges, ids outside the vocabulary, keys at both ends of it, cut by orders
+    like and unlike the batch's, in kernels of their own and carried.  Whole numbers and lr 1, so rows are exact."""
     from paper_2112_07221_amd import hetcache as hc
     dev = torch.device("cuda:0")
     rng = np.random.default_rng(n)
@@ -114,8 +115,11 @@ def test_batches_sorted_in_ranges(n, vocab, policy):
     try:
         cache.attach_backing(table, None, torch.zeros(vocab, dtype=torch.int32, device=dev))
         out = torch.empty(n, 4, device=dev)
+        dids = [torch.from_numpy(ids).to(dev) for ids in batches]
         for t, ids in enumerate(batches):
-            d, g = torch.from_numpy(ids).to(dev), rng.integers(-8, 9, (n, 4)).astype(np.float32)
+            d, g = dids[t], rng.integers(-8, 9, (n, 4)).astype(np.float32)
+            if ahead and t + ahead < len(batches):
+                cache.prefetch(dids[t + ahead])
             cache.lookup(d, out)
             ok = (ids >= 0) & (ids < vocab)
             got = out.cpu().numpy()
