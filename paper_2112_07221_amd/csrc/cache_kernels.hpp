@@ -111,7 +111,7 @@ struct Workspace {
     uint8_t *cls;                 // at heads: HIT / STALE / MISS (lookup)
     uint32_t *tile_miss, *tile_stale, *tile_hit;     // per probe tile counts
     uint2 *miss_stage, *stale_stage;      // per probe tile: (head position, key) of its missed / stale keys
-    uint32_t *bag_of;             // pooled: bag of each original position
+    uint32_t *bag_of;             // pooled: bag of each original position, as the lookup's offsets had it
 };
 
 // CheckValid (Section 3.1): c_c <= c_s + s and c_g <= c_c + s, as differences so that an
@@ -998,6 +998,7 @@ __device__ __forceinline__ void pooled_gather_body(const CacheView &cv, const Wo
             if (lo < hi) {
                 int64_t i0 = lo;
                 unsigned long long cur = where(inv[i0 + gl < hi ? i0 + gl : hi - 1], i0 + gl < hi);
+                if (c0 == 0) for (int64_t i = lo + gl; i < hi; i += g.lanes) ws.bag_of[i] = b;
                 while (i0 < hi) {
                     const int cnt = hi - i0 < (int64_t)g.lanes ? (int)(hi - i0) : g.lanes;
                     const int64_t i1 = i0 + g.lanes;
@@ -1261,14 +1262,17 @@ __global__ __launch_bounds__(256) void fill_gather_kernel(CacheView cv, Workspac
     tr.role(5); tr.end();
 }
 
-// Pooled update: the bag of every original position (its gradient row).
-static __global__ __launch_bounds__(256) void pooled_index_kernel(Workspace ws, uint32_t n, const int64_t *__restrict__ offsets, uint32_t n_bags)
+// Pooled update: the bag of an original position (its gradient row), the last that begins at or before it.  The lookup has
+// left a guess, which holds as long as the offsets are the lookup's; else it is searched for.  (A kernel of its own that searched for every
+// position's bag took 4 to 5 us.)
+__device__ __forceinline__ uint32_t bag_of_position(const uint32_t *bag_of, const int64_t *offsets, uint32_t n_bags, uint32_t i)
 {
-    for (uint32_t i = blockIdx.x * 256u + threadIdx.x; i < n; i += gridDim.x * 256u) {
-        uint32_t lo = 0, hi = n_bags;            // largest b with offsets[b] <= i
-        while (hi - lo > 1) { const uint32_t mid = (lo + hi) / 2; if (offsets[mid] <= (int64_t)i) lo = mid; else hi = mid; }
-        ws.bag_of[i] = lo;
-    }
+    const uint32_t guess = min(bag_of[i], n_bags - 1);
+    const int64_t from = offsets[guess], to = offsets[guess + 1];
+    if ((guess == 0 || from <= (int64_t)i) && (guess + 1 == n_bags || (int64_t)i < to)) return guess;
+    uint32_t lo = 0, hi = n_bags;            // largest b with offsets[b] <= i
+    while (hi - lo > 1) { const uint32_t mid = (lo + hi) / 2; if (offsets[mid] <= (int64_t)i) lo = mid; else hi = mid; }
+    return lo;
 }
 
 // Hardware square root and reciprocal (about one unit in the last place each): the Adagrad
@@ -1837,7 +1841,7 @@ constexpr uint32_t AP_GROUP = 16;
 
 template <int VEC, int MAXC, int MODE, int AP_TILE, bool EARLY, int OPT>
 __global__ __launch_bounds__(AP_THREADS) __attribute__((amdgpu_waves_per_eu(MAXC == 1 ? ap_waves(AP_TILE) : 1))) void apply_kernel(CacheView cv, Workspace ws, ApplyBorders bd, const int64_t *__restrict__ ids,
-                                                           const float *__restrict__ grads, const uint32_t *__restrict__ grad_row,
+                                                           const float *__restrict__ grads, const int64_t *__restrict__ offsets, uint32_t n_bags,
                                                            float lr, float eps, uint32_t n_ids, uint32_t work_blocks, TrimPlan tp, uint32_t trim_blocks,
                                                            SortStage ride, SortStage ride2, KernelTrace tr, int fresh_rows)
 {
@@ -1906,7 +1910,7 @@ __global__ __launch_bounds__(AP_THREADS) __attribute__((amdgpu_waves_per_eu(MAXC
             const int32_t hs = own ? ws.head_slot[j] : SLOT_NONE;
             // fresh_rows: the lookup left the fetch of its missed keys' rows to this kernel
             missed = fresh_rows && own && ws.cls[j] == (uint8_t)CLS_MISS;
-            if (grad_row && in) pm = grad_row[pm];
+            if (offsets && in && i >= W0) pm = bag_of_position(ws.bag_of, offsets, n_bags, pm);
             l.key[i] = j < nv ? k : KEY_NONE;
             l.grow[i] = pm;
             l.slot[i] = hs;
@@ -2202,7 +2206,7 @@ __global__ __launch_bounds__(AP_THREADS) __attribute__((amdgpu_waves_per_eu(MAXC
 constexpr int HET_APPLY_PARTS = 8;
 #define HET_APPLY_KERNEL(VEC, MAXC, MODE, TILE, EARLY, OPT)                                                     \
     template __global__ void apply_kernel<VEC, MAXC, MODE, TILE, EARLY, OPT>(                                     \
-        CacheView, Workspace, ApplyBorders, const int64_t *__restrict__, const float *__restrict__, const uint32_t *__restrict__, float, float, \
+        CacheView, Workspace, ApplyBorders, const int64_t *__restrict__, const float *__restrict__, const int64_t *__restrict__, uint32_t, float, float, \
         uint32_t, uint32_t, TrimPlan, uint32_t, SortStage, SortStage, KernelTrace, int);
 
 #define HET_FILL_RIDES(X, part, VEC, POOLED, TRACE) X(part, VEC, POOLED, false, TRACE) X(part, VEC, POOLED, true, TRACE)

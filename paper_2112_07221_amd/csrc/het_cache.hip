@@ -31,11 +31,11 @@ using namespace het;
 
 // Kernels of the path, as named in profiles and by het_profile_kernel_name.
 enum KernelId {
-    K_SORT_STAGE, K_PROBE, K_POOLED_INDEX, K_FILL_GATHER, K_APPLY, K_TRIM_STAGE,
+    K_SORT_STAGE, K_PROBE, K_FILL_GATHER, K_APPLY, K_TRIM_STAGE,
     K_TRIM_EVICT, K_DEFERRED_PUSH, K_LINK, K_FLUSH, K_MISC, K_NUM
 };
 static const char *const kKernelNames[K_NUM] = {
-    "sort_stage_kernel", "probe_kernel", "pooled_index_kernel", "fill_gather_kernel",
+    "sort_stage_kernel", "probe_kernel", "fill_gather_kernel",
     "apply_kernel", "trim_stage_kernel", "trim_evict_kernel", "deferred_push_kernel", "link_kernel", "flush_kernel", "misc"};
 
 struct ProfSpan { int id; hipEvent_t start, stop; };
@@ -706,7 +706,7 @@ int run_lookup(het_cache *c, const int64_t *ids, uint32_t n, const int64_t *offs
 // writes to the global table itself, instead of to their slots.
 // `trim`: a trim follows.  Returns whether its rows have been counted.
 template <int VEC, int MAXC, int TILE, bool EARLY, int OPT>
-bool launch_apply_opt(het_cache *c, bool verify, const int64_t *ids, uint32_t n, const float *grads, const uint32_t *grad_row, float lr,
+bool launch_apply_opt(het_cache *c, bool verify, const int64_t *ids, uint32_t n, const float *grads, const int64_t *offsets, uint32_t n_bags, float lr,
                       bool trim)
 {
     const uint32_t grid = cdiv(n, TILE);
@@ -724,7 +724,7 @@ bool launch_apply_opt(het_cache *c, bool verify, const int64_t *ids, uint32_t n,
     const uint32_t lds = lds_bytes(std::max({sizeof(TrimLds), sizeof(EvictLds), sizeof(ApplyLds<VEC, TILE>)}), ride);
 #define APPLY(MODE)                                                                                                                              \
     LAUNCH(c, K_APPLY, apply_kernel<VEC, MAXC, MODE, TILE, EARLY, OPT><<<ride.blocks() + grid + extra + (verify ? cdiv(n, VERIFY_TILE) : 0u), AP_THREADS, lds, c->stream>>>( \
-                           c->cv, c->ws, c->bd, ids, grads, grad_row, lr, c->eps, n, grid, tp, extra, ride.a, ride.b, c->trace[0], fresh))
+                           c->cv, c->ws, c->bd, ids, grads, offsets, n_bags, lr, c->eps, n, grid, tp, extra, ride.a, ride.b, c->trace[0], fresh))
     if (evict) {
         if (!tp.lfu && (int64_t)n > c->capacity) APPLY(AP_REUSED_EVICT_TIED); else APPLY(AP_REUSED_EVICT);
         hash_erase(c, tp);
@@ -734,36 +734,36 @@ bool launch_apply_opt(het_cache *c, bool verify, const int64_t *ids, uint32_t n,
 }
 
 template <int VEC, int MAXC, int TILE, bool EARLY>
-bool launch_apply_early(het_cache *c, bool verify, const int64_t *ids, uint32_t n, const float *grads, const uint32_t *grad_row, float lr,
+bool launch_apply_early(het_cache *c, bool verify, const int64_t *ids, uint32_t n, const float *grads, const int64_t *offsets, uint32_t n_bags, float lr,
                         bool trim)
 {
-    if constexpr (MAXC > 1) return launch_apply_opt<VEC, MAXC, TILE, EARLY, AO_ANY>(c, verify, ids, n, grads, grad_row, lr, trim);
+    if constexpr (MAXC > 1) return launch_apply_opt<VEC, MAXC, TILE, EARLY, AO_ANY>(c, verify, ids, n, grads, offsets, n_bags, lr, trim);
     else {
         if constexpr (!EARLY)            // (row-wise Adagrad does not push early)
-            if (c->cv.rowwise) return launch_apply_opt<VEC, MAXC, TILE, EARLY, AO_ROWWISE>(c, verify, ids, n, grads, grad_row, lr, trim);
-        return c->cv.adagrad ? launch_apply_opt<VEC, MAXC, TILE, EARLY, AO_ADAGRAD>(c, verify, ids, n, grads, grad_row, lr, trim)
-                             : launch_apply_opt<VEC, MAXC, TILE, EARLY, AO_SGD>(c, verify, ids, n, grads, grad_row, lr, trim);
+            if (c->cv.rowwise) return launch_apply_opt<VEC, MAXC, TILE, EARLY, AO_ROWWISE>(c, verify, ids, n, grads, offsets, n_bags, lr, trim);
+        return c->cv.adagrad ? launch_apply_opt<VEC, MAXC, TILE, EARLY, AO_ADAGRAD>(c, verify, ids, n, grads, offsets, n_bags, lr, trim)
+                             : launch_apply_opt<VEC, MAXC, TILE, EARLY, AO_SGD>(c, verify, ids, n, grads, offsets, n_bags, lr, trim);
     }
 }
 
 // EARLY: the variant that also pushes the rows it fetches (CacheView::early_cc in use).
 template <int VEC, int MAXC, int TILE>
-bool launch_apply_tile(het_cache *c, bool verify, const int64_t *ids, uint32_t n, const float *grads, const uint32_t *grad_row, float lr,
+bool launch_apply_tile(het_cache *c, bool verify, const int64_t *ids, uint32_t n, const float *grads, const int64_t *offsets, uint32_t n_bags, float lr,
                       bool trim)
 {
     if constexpr (VEC == 4)          // (only rows of whole 16-byte pieces push early)
-        if (c->cv.early_cc) return launch_apply_early<VEC, MAXC, TILE, true>(c, verify, ids, n, grads, grad_row, lr, trim);
-    return launch_apply_early<VEC, MAXC, TILE, false>(c, verify, ids, n, grads, grad_row, lr, trim);
+        if (c->cv.early_cc) return launch_apply_early<VEC, MAXC, TILE, true>(c, verify, ids, n, grads, offsets, n_bags, lr, trim);
+    return launch_apply_early<VEC, MAXC, TILE, false>(c, verify, ids, n, grads, offsets, n_bags, lr, trim);
 }
 
 template <int VEC, int MAXC>
-bool launch_apply(het_cache *c, bool verify, const int64_t *ids, uint32_t n, const float *grads, const uint32_t *grad_row, float lr,
+bool launch_apply(het_cache *c, bool verify, const int64_t *ids, uint32_t n, const float *grads, const int64_t *offsets, uint32_t n_bags, float lr,
                  bool trim)
 {
     // rows of more than 128 floats (64 lanes to a row) have one row piece per lane or more; narrower ones exactly one
     if constexpr (MAXC == 1)
-        if (ap_tile_for(c->cv.geom.lanes) == 64) return launch_apply_tile<VEC, MAXC, 64>(c, verify, ids, n, grads, grad_row, lr, trim);
-    return launch_apply_tile<VEC, MAXC, 128>(c, verify, ids, n, grads, grad_row, lr, trim);
+        if (ap_tile_for(c->cv.geom.lanes) == 64) return launch_apply_tile<VEC, MAXC, 64>(c, verify, ids, n, grads, offsets, n_bags, lr, trim);
+    return launch_apply_tile<VEC, MAXC, 128>(c, verify, ids, n, grads, offsets, n_bags, lr, trim);
 }
 
 template <int VEC>
@@ -788,19 +788,14 @@ int run_update(het_cache *c, const int64_t *ids, uint32_t n, const int64_t *offs
                                    c->cv, c->ws, n, (uint32_t)c->t_host, cdiv(n, PT_TILE), nullptr, nullptr, 0u, TrimPlan{}, nullptr, -1, nullptr));
         }
     }
-    const uint32_t *grad_row = nullptr;
-    if (offsets) {
-        LAUNCH(c, K_POOLED_INDEX, pooled_index_kernel<<<std::min(cdiv(n, 256), 4096u), 256, 0, c->stream>>>(c->ws, n, offsets, n_bags));
-        grad_row = c->ws.bag_of;
-    }
     // Only a lookup leaves rows above capacity; an update that follows no lookup has nothing to trim.
     const bool trim = c->overflow_pending;
     bool counted = false;
     switch (c->max_chunks_per_lane) {
-    case 1: counted = launch_apply<VEC, 1>(c, reuse, ids, n, grads, grad_row, lr, trim); break;
-    case 2: counted = launch_apply<VEC, 2>(c, reuse, ids, n, grads, grad_row, lr, trim); break;
-    case 4: counted = launch_apply<VEC, 4>(c, reuse, ids, n, grads, grad_row, lr, trim); break;
-    default: counted = launch_apply<VEC, 16>(c, reuse, ids, n, grads, grad_row, lr, trim); break;
+    case 1: counted = launch_apply<VEC, 1>(c, reuse, ids, n, grads, offsets, n_bags, lr, trim); break;
+    case 2: counted = launch_apply<VEC, 2>(c, reuse, ids, n, grads, offsets, n_bags, lr, trim); break;
+    case 4: counted = launch_apply<VEC, 4>(c, reuse, ids, n, grads, offsets, n_bags, lr, trim); break;
+    default: counted = launch_apply<VEC, 16>(c, reuse, ids, n, grads, offsets, n_bags, lr, trim); break;
     }
     if ((rc = launch_ok()) != HET_OK) return rc;
     if (!trim) { c->last_trim_skipped = true; c->order_valid = false; return HET_OK; }

@@ -299,6 +299,35 @@ def test_bags_added_up_by_several_row_groups(bags, dim):
         p.close()
 
 
+@pytest.mark.parametrize("bags,other", [(5, 5), (40, 3), (3, 40), (700, 1)])
+def test_updates_by_other_bags_than_the_lookups(bags, other):
+    """The lookup leaves the bag of every position for the update; an update with other offsets, or of ids no lookup had, finds
+    its own."""
+    w = wl.WORKLOADS[5].scaled(batch=bags, vocab=3_000, capacity=600, s=3, dim=16, optimizer=1)
+    rng = np.random.default_rng(bags)
+    n = 1_000
+    ids, table = rng.integers(0, 500, (4, n)), wl.table_init(w)
+
+    def offsets(p, k):
+        cuts = np.sort(rng.integers(0, n + 1, k + 1))
+        cuts[0] = 0
+        p.offsets_np, p.offsets = cuts, torch.from_numpy(cuts).to(p.dev)
+
+    p = Pair(w, table, max_ids=n)
+    try:
+        for t in range(4):
+            d = torch.from_numpy(ids[t]).to(p.dev)
+            offsets(p, bags)
+            p.lookup(ids[t], ids_dev=d)
+            offsets(p, other if t else bags)
+            b = ids[t] if t < 2 else np.roll(ids[t], 7)
+            p.update(b, rng.standard_normal((len(p.offsets_np) - 1, 16)).astype(np.float32), ids_dev=d if t < 2 else None)
+            p.compare_state(values=True)
+        p.flush_and_compare()
+    finally:
+        p.close()
+
+
 @pytest.mark.parametrize("when", ["before", "between"])
 @pytest.mark.parametrize("policy", [0, 1, 2])
 @pytest.mark.parametrize("n,vocab", [(200, 3_000), (1_024, 5_000_000), (2_700, 5_000_000), (2_731, 100_000), (5_400, 5_000_000)])
