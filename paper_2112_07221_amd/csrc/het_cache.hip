@@ -398,7 +398,10 @@ uint32_t count_blocks(const het_cache *c) { return cdiv(c->cv.n_slots, COUNT_SLO
 
 constexpr uint32_t STALE_BLOCKS = 128;     // fetch workgroups of a lookup that leaves the missed rows to the update: they refresh the stale rows
 constexpr uint32_t PUSH_BLOCKS = 256;      // few workgroups keep the host link full; more only contend
-constexpr uint32_t LINK_BLOCKS = 32;       // workgroups of the kernel that works the host link beside the update (half write back, half fetch ahead)
+// Workgroups of the kernel that works the host link beside the update: a third of them write back, the others, which mostly
+// have more rows to move, fetch ahead (four minibatches and a flush of 106496 ids of 128 floats: 2 691 us with 16 and 16, 2 694
+// with 12 and 20, 2 718 with 8 and 24, 2 648 with 16 and 32).
+constexpr uint32_t LINK_BLOCKS = 48, LINK_PUSH_BLOCKS = 16;
 
 // Host-backed table: the main stream goes on only when the kernel on the stream beside it is done.
 void wait_link(het_cache *c)
@@ -677,8 +680,8 @@ int run_lookup(het_cache *c, const int64_t *ids, uint32_t n, const int64_t *offs
             // serves its other waves' memory requests behind those that wait, so every compute unit that
             // hosts a workgroup of this kernel is slow for the update's kernels meanwhile (measured: with
             // 512 workgroups the optimizer step took as long as the whole transfer).
-            if (VEC == 4) LAUNCH_ON(c, c->side, K_LINK, link_kernel<4><<<LINK_BLOCKS, 256, 0, c->side>>>(c->cv, pbuf, ah.list_slot, c->push_buf, LINK_BLOCKS / 2));
-            else LAUNCH_ON(c, c->side, K_LINK, link_kernel<1><<<LINK_BLOCKS, 256, 0, c->side>>>(c->cv, pbuf, ah.list_slot, c->push_buf, LINK_BLOCKS / 2));
+            if (VEC == 4) LAUNCH_ON(c, c->side, K_LINK, link_kernel<4><<<LINK_BLOCKS, 256, 0, c->side>>>(c->cv, pbuf, ah.list_slot, c->push_buf, LINK_PUSH_BLOCKS));
+            else LAUNCH_ON(c, c->side, K_LINK, link_kernel<1><<<LINK_BLOCKS, 256, 0, c->side>>>(c->cv, pbuf, ah.list_slot, c->push_buf, LINK_PUSH_BLOCKS));
             if ((rc = launch_ok()) != HET_OK) return rc;
             HIP_TRY(hipEventRecord(c->ev_link, c->side));
             c->link_outstanding = true;
