@@ -915,17 +915,16 @@ __device__ __forceinline__ void ahead_list_body(const CacheView &cv, const Ahead
     }
 }
 
-// On the stream beside the main one: the first half of the workgroups write the rows a trim staged
-// back to the table (push_buf < 0: nothing to write), the second half bring the listed rows in.
+// On the stream beside the main one: the first push_blocks workgroups write the rows a trim staged
+// back to the table (push_buf < 0: nothing to write), the others bring the listed rows in.
 template <int VEC>
 __global__ __launch_bounds__(256) void link_kernel(CacheView cv, int push_buf, int list_slot, int staged_buf, uint32_t push_blocks)
 {
-    const uint32_t half = push_blocks;
-    if (blockIdx.x < half) { if (push_buf >= 0) deferred_push_body<VEC>(cv, push_buf, blockIdx.x, half); return; }
+    if (blockIdx.x < push_blocks) { if (push_buf >= 0) deferred_push_body<VEC>(cv, push_buf, blockIdx.x, push_blocks); return; }
     if (list_slot < 0) return;
     const RowGeom g = cv.geom;
     const uint32_t n = cv.ds->pf_n[list_slot];
-    const uint32_t gid = ((blockIdx.x - half) * 256u + threadIdx.x) / g.lanes, ngroups = (gridDim.x - half) * 256u / g.lanes;
+    const uint32_t gid = ((blockIdx.x - push_blocks) * 256u + threadIdx.x) / g.lanes, ngroups = (gridDim.x - push_blocks) * 256u / g.lanes;
     const int gl = threadIdx.x % g.lanes;
     using V = typename VecT<VEC>::type;
     for (uint32_t r0 = gid * LINK_ROWS; r0 < n; r0 += ngroups * LINK_ROWS) {

@@ -78,7 +78,7 @@ __device__ __forceinline__ uint32_t id_to_key(int64_t id, uint32_t vocab)
 // First all the ballots (registers only, all items of a bit together), then the running counts (LDS
 // only): interleaved, every item would wait for both in turn.  The counts pass between the wave's lanes
 // under wavefront fences, not through a volatile pointer: that made every access a flat one that
-// waits for memory (a scatter stage of 1024 keys 4.5 us, most of it these accesses).
+// waits for memory (a stage over 1024 keys 4.5 us, most of it these accesses).
 template <int ITEMS>
 __device__ __forceinline__ void rank_in_wave(const uint32_t (&d)[ITEMS], const bool (&valid)[ITEMS], int width, uint16_t *my_hist, uint32_t (&rank)[ITEMS])
 {
