@@ -352,7 +352,7 @@ def main():
         # sort); lookup t; update t
         pf = not args.no_prefetch and t + 1 < total
         if pf and args.prefetch_order == "before":
-            # two ahead: a sort has more stages than one step has kernels to carry them
+            # two ahead (one would do: a sort has two stages, and a step two kernels that carry one)
             if t == 0:
                 cache.prefetch(ids[1])
             if t + 2 < total:
