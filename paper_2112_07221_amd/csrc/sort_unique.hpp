@@ -12,8 +12,11 @@
 // workgroup per range collects its keys from all the tiles, whose beginnings in the tiles add up to the range's beginning in
 // the order, and sorts them in LDS.  No workgroup ever waits for another one, and nothing is counted with global atomics.
 // A range begins at a quantile of the order sorted before this one or, if that turns out not to divide these keys evenly, of a
-// sample, which every workgroup draws for itself (the same one).  A key that fills several ranges by itself gets
-// ranges of its own, a stretch of the tiles each.  Where the ranges begin decides nothing but how long this takes.
+// sample, which every workgroup draws for itself (the same one), or at either.  A key that fills several ranges by itself gets
+// ranges of its own, a stretch of the tiles each.  Where the ranges begin decides nothing but how long this takes, and a range that
+// holds too many keys takes time in proportion to them (sort_packed, part_popular, sort_through_memory).  A step of 106496 ids, announced, 49.7 us;
+// if a rare key makes up 1, 2 or 4 % of every second batch 50.1, 52.2 and 53.3 (166 to 263 where such a range's keys were
+// searched again and again); of 409600 ids in bags 225 us, and 226, 227 and 228 (560 to 907).
 // In the place of a radix sort over the vocabulary's bits, of four to six stages: 26624 ids 22 -> 12.6 us, 106496 ids 25 -> 15.7
 // (18.9 with cuts from the sample: then the fullest range holds four times the mean).  What bounds it: a kernel boundary, barriers
 // and the ballots' vector instructions.
@@ -32,7 +35,8 @@ constexpr int SORT_THREADS = 256;                        // workgroups of the ke
 constexpr int SORT_THREADS_ALONE = 1024;                 // workgroups of a stage's own kernel
 constexpr int SORT_TILE = 1024;                          // keys per workgroup of a part stage
 constexpr int SORT_MIN_BITS = 3;
-constexpr uint32_t SORT_SAMPLE = 256;                    // keys drawn
+constexpr uint32_t SORT_SAMPLE = 256;                    // keys drawn to look whether an order's cuts will do
+constexpr uint32_t SORT_CUT_SAMPLE = 1024;               // keys drawn to make cuts of
 constexpr uint32_t SORT_MAX_RANGES = 1024;
 
 // How many ranges.  Carried: of up to 512 keys on average, half of what a workgroup of 256 threads sorts at a time (with up to
@@ -131,40 +135,99 @@ __device__ __forceinline__ uint32_t waves_before(uint16_t *count, uint32_t bins)
     return run;
 }
 
+// Keys a workgroup of a range stage sorts at a time, per thread and in all.
+__host__ __device__ constexpr int sort_range_items(int threads) { return threads == SORT_THREADS ? 4 : 8; }
+__host__ __device__ constexpr uint32_t sort_list(int threads) { return (uint32_t)(threads * sort_range_items(threads)); }
+
+// ---- sort in LDS ------------------------------------------------------------------------------
+// By one workgroup: the keys stay in registers, ITEMS per thread, and change places through LDS between the passes of a radix sort.
+__host__ __device__ constexpr int solo_max_bits(int threads) { return threads == SORT_THREADS ? 8 : 9; }        // (no more digits than threads)
+__host__ __device__ inline int solo_passes(int bits, int threads) { return (bits + solo_max_bits(threads) - 1) / solo_max_bits(threads); }
+__host__ __device__ constexpr uint32_t solo_lds_bytes(int items, int width, int threads)
+{
+    return (uint32_t)(threads * items * 8 + threads / WAVE * (2 << width) + (4 << width) + threads / WAVE * 4);
+}
+
+// The passes: keys (and their payload) of list places at0 + 64 * it, in place order; `n` of them.  The digits are taken
+// of key - first.  `lds` holds solo_lds_bytes(ITEMS, width, THREADS) bytes.  The order has a gap of `gap` places before its place gap_at.
+template <int ITEMS, int THREADS>
+__device__ __forceinline__ void solo_sort(uint32_t (&key)[ITEMS], uint32_t (&pay)[ITEMS], const bool (&valid)[ITEMS], uint32_t at0, uint32_t n,
+                                          uint32_t first, int passes, int width, uint32_t *lds, uint32_t *keys_out, uint32_t *idx_out,
+                                          uint32_t gap_at = 0, uint32_t gap = 0)
+{
+    constexpr int WAVES = THREADS / WAVE;
+    const uint32_t bins = 1u << width, mask = bins - 1u, w = threadIdx.x / WAVE;
+    uint32_t *xkey = lds, *xpay = xkey + THREADS * ITEMS;
+    uint32_t *base = xpay + THREADS * ITEMS, *scan = base + bins;
+    uint16_t *hist = reinterpret_cast<uint16_t *>(scan + WAVES);
+    uint32_t d[ITEMS], rank[ITEMS];
+    for (int p = 0; p < passes; ++p) {
+        for (uint32_t b = threadIdx.x; b < WAVES * bins / 2; b += THREADS) reinterpret_cast<uint32_t *>(hist)[b] = 0;
+        __syncthreads();                                   // (also: the keys of the pass before have been read back)
+#pragma unroll
+        for (int it = 0; it < ITEMS; ++it) d[it] = ((key[it] - first) >> (p * width)) & mask;
+        if (at0 - lane_id() < n) rank_in_wave<ITEMS>(d, valid, width, hist + w * bins, rank);     // (a wave without keys leaves its counts at zero)
+        __syncthreads();
+        uint32_t run = 0;
+        if (threadIdx.x < bins) run = waves_before<WAVES>(hist + threadIdx.x, bins);     // (bins <= threads)
+        uint32_t total;
+        const uint32_t excl = block_excl_scan<WAVES>(run, scan, total);
+        if (threadIdx.x < bins) base[threadIdx.x] = excl;
+        __syncthreads();
+        const bool last = p + 1 == passes;
+#pragma unroll
+        for (int it = 0; it < ITEMS; ++it) {
+            if (valid[it]) {
+                const uint32_t pos = base[d[it]] + hist[w * bins + d[it]] + rank[it];
+                if (last) { const uint32_t to = pos < gap_at ? pos : pos + gap; keys_out[to] = key[it]; idx_out[to] = pay[it]; }
+                else { xkey[pos] = key[it]; xpay[pos] = pay[it]; }
+            }
+        }
+        if (last) return;
+        __syncthreads();
+#pragma unroll
+        for (int it = 0; it < ITEMS; ++it)
+            if (valid[it]) { key[it] = xkey[at0 + it * WAVE]; pay[it] = xpay[at0 + it * WAVE]; }
+    }
+}
+
 // ---- part -------------------------------------------------------------------------------------
-// LDS: sample, its ranks, the drawn keys by rank; cuts; offsets (first: how many drawn keys a range gets); the scan's words; 16-bit
-// counts per wave and range.
+// LDS: cuts; offsets (first: how many drawn keys a range gets); the scan's words; 16-bit counts per wave and range (first: the sort of the drawn keys).
 __host__ __device__ inline uint32_t sort_part_lds_bytes(uint32_t ranges, int threads)
 {
-    return 4u * (3u * SORT_SAMPLE + 2u * ranges + (uint32_t)threads / WAVE) + 2u * (uint32_t)threads / WAVE * ranges;
+    const uint32_t waves = (uint32_t)threads / WAVE, counts = 2u * waves * ranges;
+    const uint32_t drawn = threads == SORT_THREADS ? solo_lds_bytes((int)SORT_CUT_SAMPLE / threads, solo_max_bits(threads), threads) : 12u * SORT_SAMPLE;
+    return 4u * (2u * ranges + waves) + (counts > drawn ? counts : drawn);
+}
+
+// A position of the j-th of `draws` equal stretches of the batch, not always the same: ids that come by fields have a period.
+__device__ __forceinline__ uint32_t drawn_position(uint32_t j, uint32_t draws, uint32_t n)
+{
+    const uint32_t lo = (uint32_t)((uint64_t)j * n / draws), hi = (uint32_t)((uint64_t)(j + 1) * n / draws);
+    return lo + (hi > lo ? __umulhi(j * 0x9E3779B9u, hi - lo) : 0u);
 }
 
 template <int THREADS>
 __device__ __forceinline__ void sort_part_body(const SortStage &s, uint32_t tile, uint32_t *lds)
 {
     constexpr int ITEMS = SORT_TILE / THREADS, WAVES = THREADS / WAVE;
-    constexpr uint32_t PARTS = THREADS / SORT_SAMPLE;             // threads that find one drawn key's rank
     const SortPlan &sp = s.sp;
     const uint32_t t = threadIdx.x, w = t / WAVE, lane = lane_id(), n = sp.n, ranges = sp.ranges;
-    uint32_t *sample = lds, *rank_of = sample + SORT_SAMPLE, *at_rank = rank_of + SORT_SAMPLE, *cuts = at_rank + SORT_SAMPLE;
-    uint32_t *base = cuts + ranges, *scan = base + ranges;
+    uint32_t *cuts = lds, *base = cuts + ranges, *scan = base + ranges;
     uint16_t *hist = reinterpret_cast<uint16_t *>(scan + WAVES);
+    const auto clear_hist = [&] { for (uint32_t b = t; b < WAVES * ranges / 2; b += THREADS) reinterpret_cast<uint32_t *>(hist)[b] = 0; };
     // A wave owns ITEMS * 64 consecutive keys and walks them 64 at a time, so (wave, item, lane) order is position order.
     const uint32_t at0 = tile * SORT_TILE + w * (WAVE * ITEMS) + lane;
     uint32_t key[ITEMS], drawn = 0;
     bool valid[ITEMS];
     {
         int64_t id[ITEMS], d = 0;
-        // (one position out of every n / SORT_SAMPLE, not always the same: ids that come by fields have a period)
-        if (t < SORT_SAMPLE) {
-            const uint32_t lo = (uint32_t)((uint64_t)t * n / SORT_SAMPLE), hi = (uint32_t)((uint64_t)(t + 1) * n / SORT_SAMPLE);
-            d = s.ids[lo + (hi > lo ? __umulhi(t * 0x9E3779B9u, hi - lo) : 0u)];
-        }
+        if (t < SORT_SAMPLE) d = s.ids[drawn_position(t, SORT_SAMPLE, n)];
 #pragma unroll
         for (int it = 0; it < ITEMS; ++it) { const uint32_t i = at0 + it * WAVE; valid[it] = i < n; id[it] = s.ids[valid[it] ? i : 0u]; }
         for (uint32_t r = t; r < ranges; r += THREADS) { cuts[r] = sp.known && r ? sp.known[(uint64_t)r * sp.n_known / ranges] : 0u; base[r] = 0; }
-        if (t < SORT_SAMPLE) { drawn = id_to_key(d, sp.vocab); sample[t] = drawn; rank_of[t] = 0; at_rank[t] = 0; }
-        for (uint32_t b = t; b < WAVES * ranges / 2; b += THREADS) reinterpret_cast<uint32_t *>(hist)[b] = 0;
+        drawn = id_to_key(d, sp.vocab);
+        clear_hist();
 #pragma unroll
         for (int it = 0; it < ITEMS; ++it) key[it] = id_to_key(id[it], sp.vocab);
     }
@@ -184,49 +247,94 @@ __device__ __forceinline__ void sort_part_body(const SortStage &s, uint32_t tile
         return lo;
     };
     // Cuts from an order sorted before do for keys like those: if a range of more than one key gets far more of the drawn
-    // keys than its share, the drawn keys make the cuts.
+    // keys than its share, cuts are made anew.  In a kernel that carries this: if the range holds, by the draws, more than a workgroup sorts
+    // twice, and they are more than chance gives a range of up to two shares (106496 ids, 256 ranges: 8 of 256; a step with a key
+    // at 4 % of the batch 53.3 us, and 56.2 if only 11 will do).  New cuts cost such a workgroup 5 us.
     bool far_off = !sp.known;
     if (!far_off) {
         bool many = false;
         if (t < SORT_SAMPLE) {
             const uint32_t r = last_at_or_below(drawn);
             const bool one_key = r && cuts[r] == drawn && cuts[r - 1] == drawn;
-            many = !one_key && atomicAdd(&base[r], 1u) >= SORT_SAMPLE * 2 / ranges + 8;
+            const uint32_t got = one_key ? 0u : atomicAdd(&base[r], 1u) + 1u;
+            const uint32_t lists = got * n / (SORT_SAMPLE * sort_list(THREADS));
+            many = THREADS == SORT_THREADS ? lists > 1 && got >= SORT_SAMPLE * 3 / ranges + 5 : got >= SORT_SAMPLE * 2 / ranges + 9;
         }
         far_off = __syncthreads_or(many) != 0;
     }
     if (far_off) {
-        {   // how many drawn keys lie below each
+        uint32_t *work = scan + WAVES;
+        // In a kernel that carries this, with ranges of more than a quarter of what a workgroup sorts at a time, ranges from 256 drawn keys are too
+        // uneven: more are drawn.  Half of the cuts stay where the order before had them, and divide what has not changed (409600
+        // ids in bags, a key at 4 %: 224 us a step, with all cuts from the drawn keys 233).
+        const bool finely = THREADS == SORT_THREADS && n > sort_list(THREADS) / 4 * ranges;
+        if (finely) {
+            constexpr int DRAWS = SORT_CUT_SAMPLE / THREADS;
+            static_assert(SORT_MAX_RANGES <= SORT_CUT_SAMPLE, "a drawn key to a range");
+            uint32_t k[DRAWS], unused[DRAWS];
+            int64_t id[DRAWS];
+            bool all[DRAWS];
+#pragma unroll
+            for (int q = 0; q < DRAWS; ++q) { id[q] = s.ids[drawn_position(q * THREADS + t, SORT_CUT_SAMPLE, n)]; all[q] = true; unused[q] = 0; }
+#pragma unroll
+            for (int q = 0; q < DRAWS; ++q) k[q] = id_to_key(id[q], sp.vocab);
+            const int bits = max(SORT_MIN_BITS, 32 - __clz(sp.vocab)), passes = solo_passes(bits, THREADS);
+            solo_sort<DRAWS, THREADS>(k, unused, all, w * (WAVE * DRAWS) + lane, SORT_CUT_SAMPLE, 0u, passes, (bits + passes - 1) / passes, work, work, work + SORT_CUT_SAMPLE);
+            __syncthreads();
+            if (!sp.known) {
+                for (uint32_t r = t; r < ranges; r += THREADS) cuts[r] = r ? work[r * (SORT_CUT_SAMPLE / ranges)] : 0u;
+            } else {                                     // half of the cuts by the order before, half by the drawn keys
+                const uint32_t half = ranges / 2, per = SORT_CUT_SAMPLE / half;
+                for (uint32_t r = t; r < ranges; r += THREADS) {
+                    const bool of_known = r < half;
+                    const uint32_t cut = of_known ? cuts[2 * r] : work[(r - half) * per];
+                    uint32_t at = 0;                     // how many of the others come before it (of equal ones the known)
+                    for (uint32_t len = half; len;) {
+                        const uint32_t mid = at + len / 2, other = of_known ? work[mid * per] : cuts[2 * mid];
+                        if (of_known ? other < cut : other <= cut) { at = mid + 1; len -= len / 2 + 1; } else len /= 2;
+                    }
+                    base[(of_known ? r : r - half) + at] = cut;
+                }
+                __syncthreads();
+                for (uint32_t r = t; r < ranges; r += THREADS) cuts[r] = base[r];
+            }
+        } else {                                         // those drawn already
+            uint32_t *sample = work, *rank_of = sample + SORT_SAMPLE, *at_rank = rank_of + SORT_SAMPLE;
+            if (t < SORT_SAMPLE) { sample[t] = drawn; rank_of[t] = 0; at_rank[t] = 0; }
+            __syncthreads();
+            constexpr uint32_t PARTS = THREADS / SORT_SAMPLE;             // threads that find one drawn key's rank
             const uint32_t mine = sample[t % SORT_SAMPLE];
             const uint4 *v = reinterpret_cast<const uint4 *>(sample) + t / SORT_SAMPLE * (SORT_SAMPLE / PARTS / 4);
-            uint32_t r = 0;
+            uint32_t below = 0;
 #pragma unroll 8
             for (uint32_t q = 0; q < SORT_SAMPLE / PARTS / 4; ++q) {
                 const uint4 o = v[q];
-                r += (o.x < mine) + (o.y < mine) + (o.z < mine) + (o.w < mine);
+                below += (o.x < mine) + (o.y < mine) + (o.z < mine) + (o.w < mine);
             }
-            atomicAdd(&rank_of[t % SORT_SAMPLE], r);
+            atomicAdd(&rank_of[t % SORT_SAMPLE], below);
+            __syncthreads();
+            if (t < SORT_SAMPLE) at_rank[rank_of[t]] = drawn;     // (equal keys: the same to the same place)
+            __syncthreads();
+            if (w == 0) {        // the drawn key of a rank: the largest at it or before it
+                static_assert(SORT_SAMPLE == 4 * WAVE, "four ranks to a lane");
+                uint4 v = reinterpret_cast<const uint4 *>(at_rank)[lane];
+                v.y = max(v.x, v.y); v.z = max(v.y, v.z); v.w = max(v.z, v.w);
+                uint32_t top = v.w;
+                top = max(top, dpp_or_zero<0x111, 0xf>(top)); top = max(top, dpp_or_zero<0x112, 0xf>(top));
+                top = max(top, dpp_or_zero<0x114, 0xf>(top)); top = max(top, dpp_or_zero<0x118, 0xf>(top));
+                top = max(top, dpp_or_zero<0x142, 0xa>(top)); top = max(top, dpp_or_zero<0x143, 0xc>(top));
+                const uint32_t before = lane ? (uint32_t)__shfl_up(top, 1, WAVE) : 0u;
+                reinterpret_cast<uint4 *>(at_rank)[lane] = make_uint4(max(before, v.x), max(before, v.y), max(before, v.z), max(before, v.w));
+            }
+            __syncthreads();
+            for (uint32_t r = t; r < ranges; r += THREADS) {     // (more ranges than drawn keys: evenly between two of them)
+                const uint32_t at = (uint32_t)((uint64_t)r * SORT_SAMPLE / ranges), rest = r * SORT_SAMPLE % ranges;
+                const uint32_t lo = at_rank[at], hi = at + 1 < SORT_SAMPLE ? at_rank[at + 1] : sp.vocab;
+                cuts[r] = r ? lo + (uint32_t)((uint64_t)(hi - lo) * rest / ranges) : 0u;
+            }
         }
         __syncthreads();
-        if (t < SORT_SAMPLE) at_rank[rank_of[t]] = drawn;     // (equal keys: the same to the same place)
-        __syncthreads();
-        if (w == 0) {        // the drawn key of a rank: the largest at it or before it
-            static_assert(SORT_SAMPLE == 4 * WAVE, "four ranks to a lane");
-            uint4 v = reinterpret_cast<const uint4 *>(at_rank)[lane];
-            v.y = max(v.x, v.y); v.z = max(v.y, v.z); v.w = max(v.z, v.w);
-            uint32_t top = v.w;
-            top = max(top, dpp_or_zero<0x111, 0xf>(top)); top = max(top, dpp_or_zero<0x112, 0xf>(top));
-            top = max(top, dpp_or_zero<0x114, 0xf>(top)); top = max(top, dpp_or_zero<0x118, 0xf>(top));
-            top = max(top, dpp_or_zero<0x142, 0xa>(top)); top = max(top, dpp_or_zero<0x143, 0xc>(top));
-            const uint32_t before = lane ? (uint32_t)__shfl_up(top, 1, WAVE) : 0u;
-            reinterpret_cast<uint4 *>(at_rank)[lane] = make_uint4(max(before, v.x), max(before, v.y), max(before, v.z), max(before, v.w));
-        }
-        __syncthreads();
-        for (uint32_t r = t; r < ranges; r += THREADS) {     // (more ranges than drawn keys: evenly between two of them)
-            const uint32_t at = (uint32_t)((uint64_t)r * SORT_SAMPLE / ranges), rest = r * SORT_SAMPLE % ranges;
-            const uint32_t lo = at_rank[at], hi = at + 1 < SORT_SAMPLE ? at_rank[at + 1] : sp.vocab;
-            cuts[r] = r ? lo + (uint32_t)((uint64_t)(hi - lo) * rest / ranges) : 0u;
-        }
+        clear_hist();
         __syncthreads();
     }
     if (tile == 0) for (uint32_t r = t; r < ranges; r += THREADS) sp.cuts[r] = cuts[r];
@@ -264,57 +372,7 @@ __device__ __forceinline__ void sort_part_body(const SortStage &s, uint32_t tile
     }
 }
 
-// ---- sort in LDS ------------------------------------------------------------------------------
-// By one workgroup: the keys stay in registers, ITEMS per thread, and change places through LDS between the passes of a radix sort.
-__host__ __device__ constexpr int solo_max_bits(int threads) { return threads == SORT_THREADS ? 8 : 9; }        // (no more digits than threads)
-__host__ __device__ inline int solo_passes(int bits, int threads) { return (bits + solo_max_bits(threads) - 1) / solo_max_bits(threads); }
-__host__ __device__ constexpr uint32_t solo_lds_bytes(int items, int width, int threads)
-{
-    return (uint32_t)(threads * items * 8 + threads / WAVE * (2 << width) + (4 << width) + threads / WAVE * 4);
-}
-
-// The passes: keys (and their payload) of list places at0 + 64 * it, in place order; `n` of them.  The digits are taken
-// of key - first.  `lds` holds solo_lds_bytes(ITEMS, width, THREADS) bytes.
-template <int ITEMS, int THREADS>
-__device__ __forceinline__ void solo_sort(uint32_t (&key)[ITEMS], uint32_t (&pay)[ITEMS], const bool (&valid)[ITEMS], uint32_t at0, uint32_t n,
-                                          uint32_t first, int passes, int width, uint32_t *lds, uint32_t *keys_out, uint32_t *idx_out)
-{
-    constexpr int WAVES = THREADS / WAVE;
-    const uint32_t bins = 1u << width, mask = bins - 1u, w = threadIdx.x / WAVE;
-    uint32_t *xkey = lds, *xpay = xkey + THREADS * ITEMS;
-    uint32_t *base = xpay + THREADS * ITEMS, *scan = base + bins;
-    uint16_t *hist = reinterpret_cast<uint16_t *>(scan + WAVES);
-    uint32_t d[ITEMS], rank[ITEMS];
-    for (int p = 0; p < passes; ++p) {
-        for (uint32_t b = threadIdx.x; b < WAVES * bins / 2; b += THREADS) reinterpret_cast<uint32_t *>(hist)[b] = 0;
-        __syncthreads();                                   // (also: the keys of the pass before have been read back)
-#pragma unroll
-        for (int it = 0; it < ITEMS; ++it) d[it] = ((key[it] - first) >> (p * width)) & mask;
-        if (at0 - lane_id() < n) rank_in_wave<ITEMS>(d, valid, width, hist + w * bins, rank);     // (a wave without keys leaves its counts at zero)
-        __syncthreads();
-        uint32_t run = 0;
-        if (threadIdx.x < bins) run = waves_before<WAVES>(hist + threadIdx.x, bins);     // (bins <= threads)
-        uint32_t total;
-        const uint32_t excl = block_excl_scan<WAVES>(run, scan, total);
-        if (threadIdx.x < bins) base[threadIdx.x] = excl;
-        __syncthreads();
-        const bool last = p + 1 == passes;
-#pragma unroll
-        for (int it = 0; it < ITEMS; ++it) {
-            if (valid[it]) {
-                const uint32_t pos = base[d[it]] + hist[w * bins + d[it]] + rank[it];
-                if (last) { keys_out[pos] = key[it]; idx_out[pos] = pay[it]; }
-                else { xkey[pos] = key[it]; xpay[pos] = pay[it]; }
-            }
-        }
-        if (last) return;
-        __syncthreads();
-#pragma unroll
-        for (int it = 0; it < ITEMS; ++it)
-            if (valid[it]) { key[it] = xkey[at0 + it * WAVE]; pay[it] = xpay[at0 + it * WAVE]; }
-    }
-}
-
+// ---- alone ------------------------------------------------------------------------------------
 constexpr uint32_t SOLO_MAX = 4 * SORT_THREADS_ALONE;
 
 // A small batch.
@@ -337,8 +395,6 @@ __global__ __launch_bounds__(SORT_THREADS_ALONE) void sort_solo_kernel(const int
 }
 
 // ---- range ------------------------------------------------------------------------------------
-// Keys a workgroup sorts at a time (per thread).
-__host__ __device__ constexpr int sort_range_items(int threads) { return threads == SORT_THREADS ? 4 : 8; }
 // LDS: of a tile's keys in this range, the list place of the first, and where it lies less that place; the scan's words; the
 // list, then the passes'.
 __host__ __device__ inline uint32_t sort_range_lds_bytes(uint32_t ntiles, int threads)
@@ -346,26 +402,255 @@ __host__ __device__ inline uint32_t sort_range_lds_bytes(uint32_t ntiles, int th
     return 8u * ((ntiles + 1u) / 2u * 2u) + 64u + solo_lds_bytes(sort_range_items(threads), solo_max_bits(threads), threads);
 }
 
-template <int ITEMS, int THREADS, typename S>
-__device__ __forceinline__ void sort_listed(S source, const SortPlan &sp, uint32_t m, uint32_t first, int bits, uint32_t *lds, uint32_t *keys_out, uint32_t *idx_out)
+// The keys of a range, in the order of the tiles: where those at some list places lie.
+struct RangeList {
+    const uint32_t *first_of, *where;
+    uint32_t ntiles, top;                                // top: the highest power of two below ntiles (0: there is one tile)
+    template <int N>
+    __device__ __forceinline__ void operator()(const uint32_t (&place)[N], uint32_t (&from)[N]) const
+    {
+        uint32_t tile[N];
+#pragma unroll
+        for (int q = 0; q < N; ++q) tile[q] = 0;
+        for (uint32_t step = top; step; step /= 2) {     // (all the places' searches together)
+#pragma unroll
+            for (int q = 0; q < N; ++q) {
+                const uint32_t at = tile[q] + step;
+                if (first_of[min(at, ntiles - 1)] <= place[q] && at < ntiles) tile[q] = at;
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < N; ++q) from[q] = where[tile[q]] + place[q];
+    }
+};
+
+template <int ITEMS, int THREADS, typename L>
+__device__ __forceinline__ void sort_listed(const L &list, const SortPlan &sp, uint32_t m, uint32_t first, int bits, uint32_t *lds, uint32_t *keys_out, uint32_t *idx_out,
+                                            uint32_t gap_at, uint32_t gap)
 {
     const uint32_t at0 = threadIdx.x / WAVE * (WAVE * ITEMS) + lane_id();
     uint32_t key[ITEMS], pay[ITEMS], from[ITEMS];
     bool valid[ITEMS];
 #pragma unroll
-    for (int it = 0; it < ITEMS; ++it) { const uint32_t i = at0 + it * WAVE; valid[it] = i < m; from[it] = source(valid[it] ? i : 0u); }
+    for (int it = 0; it < ITEMS; ++it) { const uint32_t i = at0 + it * WAVE; valid[it] = i < m; key[it] = valid[it] ? i : 0u; }
+    list(key, from);
 #pragma unroll
     for (int it = 0; it < ITEMS; ++it) { key[it] = sp.keys[from[it]]; pay[it] = sp.idx[from[it]]; }
     const int passes = solo_passes(bits, THREADS), width = max(SORT_MIN_BITS, (bits + passes - 1) / passes);
     __syncthreads();                                     // (every place has been read)
-    solo_sort<ITEMS, THREADS>(key, pay, valid, at0, m, first, passes, width, lds, keys_out, idx_out);
+    solo_sort<ITEMS, THREADS>(key, pay, valid, at0, m, first, passes, width, lds, keys_out, idx_out, gap_at, gap);
+}
+
+// Twice as many keys, of few enough bits: a word holds a key and its list place, and only words change places.  (1024 to 2048 keys in a
+// kernel that carries this: 18 us, through memory 25.)
+template <int THREADS>
+__device__ __forceinline__ void sort_packed(const RangeList &list, const SortPlan &sp, uint32_t m, uint32_t first, int bits, uint32_t *lds, uint32_t *keys_out, uint32_t *idx_out)
+{
+    constexpr int ITEMS = 2 * sort_range_items(THREADS), WAVES = THREADS / WAVE;
+    constexpr uint32_t PLACES = THREADS * ITEMS;         // (a power of two)
+    const int passes = solo_passes(bits, THREADS), width = max(SORT_MIN_BITS, (bits + passes - 1) / passes);
+    const uint32_t bins = 1u << width, mask = bins - 1u, t = threadIdx.x, w = t / WAVE, at0 = w * (WAVE * ITEMS) + lane_id();
+    uint32_t *x = lds, *base = x + PLACES, *scan = base + bins;
+    uint16_t *hist = reinterpret_cast<uint16_t *>(scan + WAVES);
+    uint32_t word[ITEMS], rank[ITEMS];
+    bool valid[ITEMS];
+#pragma unroll
+    for (int it = 0; it < ITEMS; ++it) { const uint32_t i = at0 + it * WAVE; valid[it] = i < m; word[it] = valid[it] ? i : 0u; }
+    list(word, rank);
+#pragma unroll
+    for (int it = 0; it < ITEMS; ++it) word[it] = sp.keys[rank[it]];
+#pragma unroll
+    for (int it = 0; it < ITEMS; ++it) word[it] = (word[it] - first) * PLACES + at0 + it * WAVE;
+    for (int p = 0; p < passes; ++p) {
+        for (uint32_t b = t; b < WAVES * bins / 2; b += THREADS) reinterpret_cast<uint32_t *>(hist)[b] = 0;
+        __syncthreads();                                 // (also: the words of the pass before have been read back)
+        uint32_t d[ITEMS];
+#pragma unroll
+        for (int it = 0; it < ITEMS; ++it) d[it] = (word[it] / PLACES >> (p * width)) & mask;
+        rank_in_wave<ITEMS>(d, valid, width, hist + w * bins, rank);
+        __syncthreads();
+        const uint32_t run = t < bins ? waves_before<WAVES>(hist + t, bins) : 0u;
+        uint32_t total;
+        const uint32_t excl = block_excl_scan<WAVES>(run, scan, total);
+        if (t < bins) base[t] = excl;
+        __syncthreads();
+#pragma unroll
+        for (int it = 0; it < ITEMS; ++it) rank[it] += base[d[it]] + hist[w * bins + d[it]];
+        if (p + 1 == passes) break;
+#pragma unroll
+        for (int it = 0; it < ITEMS; ++it) if (valid[it]) x[rank[it]] = word[it];
+        __syncthreads();
+#pragma unroll
+        for (int it = 0; it < ITEMS; ++it) if (valid[it]) word[it] = x[at0 + it * WAVE];
+    }
+    uint32_t from[ITEMS];
+#pragma unroll
+    for (int it = 0; it < ITEMS; ++it) {
+        if (valid[it]) keys_out[rank[it]] = word[it] / PLACES + first;
+        word[it] = valid[it] ? word[it] % PLACES : 0u;
+    }
+    list(word, from);
+#pragma unroll
+    for (int it = 0; it < ITEMS; ++it) word[it] = sp.idx[from[it]];
+#pragma unroll
+    for (int it = 0; it < ITEMS; ++it) if (valid[it]) idx_out[rank[it]] = word[it];
+}
+
+// The most popular of the first keys of a range, if what else is in the range can be sorted at a time: its copies are put in their
+// places, where the other keys lie is listed.  (4700 keys: 30 us, through memory 60.  Four keys of a thread at a time and everything read
+// twice: with eight, or with the keys kept, the kernels that carry this have 100 scalar registers or more in scratch memory, and every step takes 1 % longer.)
+struct SortPopular { uint32_t copies, below; };          // (copies 0: there is none)
+template <int THREADS>
+__device__ __forceinline__ SortPopular part_popular(const RangeList &list, const SortPlan &sp, uint32_t m, uint32_t *scan, uint32_t *others, uint32_t *keys_out, uint32_t *idx_out)
+{
+    constexpr int ITEMS = 4, WAVES = THREADS / WAVE, TRIED = 8;
+    const uint32_t t = threadIdx.x, w = t / WAVE, first = w * (WAVE * ITEMS) + lane_id();
+    uint32_t popular = 0, copies = 0, below = 0;
+    for (uint32_t at0 = first; at0 - first < m; at0 += THREADS * ITEMS) {
+        uint32_t key[ITEMS], from[ITEMS];
+#pragma unroll
+        for (int it = 0; it < ITEMS; ++it) key[it] = min(at0 + it * WAVE, m - 1);
+        list(key, from);
+#pragma unroll
+        for (int it = 0; it < ITEMS; ++it) key[it] = sp.keys[from[it]];
+        if (at0 == first) {
+            if (w == 0) {
+                uint32_t most = 0;
+#pragma unroll
+                for (int j = 0; j < TRIED; ++j) {
+                    const uint32_t k = (uint32_t)__builtin_amdgcn_readlane((int)key[0], j * (WAVE / TRIED));
+                    const uint32_t c = (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(key[0] == k));
+                    if (c > most) { most = c; popular = k; }
+                }
+                if (t == 0) { others[0] = popular; others[1] = most; }
+            }
+            __syncthreads();
+            popular = others[0];
+            const uint32_t most = others[1];
+            __syncthreads();
+            if (most < WAVE / 8) return {0u, 0u};        // (one in eight)
+        }
+#pragma unroll
+        for (int it = 0; it < ITEMS; ++it) {
+            const bool in = at0 + it * WAVE < m;
+            copies += in && key[it] == popular; below += in && key[it] < popular;
+        }
+    }
+    copies = block_sum<WAVES>(copies, scan);
+    below = block_sum<WAVES>(below, scan);
+    if (m - copies > sort_list(THREADS)) return {0u, 0u};
+    uint32_t copy_at = below, other_at = 0;
+    for (uint32_t at0 = first; at0 - first < m; at0 += THREADS * ITEMS) {
+        uint32_t key[ITEMS], from[ITEMS], pos[ITEMS];
+#pragma unroll
+        for (int it = 0; it < ITEMS; ++it) key[it] = min(at0 + it * WAVE, m - 1);
+        list(key, from);
+#pragma unroll
+        for (int it = 0; it < ITEMS; ++it) { key[it] = sp.keys[from[it]]; pos[it] = sp.idx[from[it]]; }
+        uint32_t mine = 0, rank[ITEMS];                  // the wave's copies, and above them its other keys; of a key's kind, how many before it
+#pragma unroll
+        for (int it = 0; it < ITEMS; ++it) {
+            const bool in = at0 + it * WAVE < m, same = key[it] == popular;
+            const uint64_t bc = __builtin_amdgcn_ballot_w64(in && same), bo = __builtin_amdgcn_ballot_w64(in && !same);
+            rank[it] = same ? (mine & 0xFFFFu) + mask_rank(bc) : (mine >> 16) + mask_rank(bo);
+            mine += (uint32_t)__popcll(bc) + ((uint32_t)__popcll(bo) << 16);
+        }
+        __syncthreads();                                 // (the words have been read)
+        if (lane_id() == 0) scan[w] = mine;
+        __syncthreads();
+        uint32_t before = 0, all = 0;
+#pragma unroll
+        for (int ww = 0; ww < WAVES; ++ww) { const uint32_t c = scan[ww]; before += (uint32_t)ww < w ? c : 0u; all += c; }
+        const uint32_t to_copy = copy_at + (before & 0xFFFFu), to_other = other_at + (before >> 16);
+#pragma unroll
+        for (int it = 0; it < ITEMS; ++it) {
+            if (at0 + it * WAVE >= m) continue;
+            if (key[it] == popular) { keys_out[to_copy + rank[it]] = popular; idx_out[to_copy + rank[it]] = pos[it]; }
+            else others[to_other + rank[it]] = from[it];
+        }
+        copy_at += all & 0xFFFFu; other_at += all >> 16;
+    }
+    __syncthreads();
+    return {copies, below};
+}
+
+// Any number of keys: a radix sort through memory, its time in proportion to the keys whatever they are.  The range's places in the tiles
+// and those in the order are this workgroup's alone, and take the keys in turn, an odd number of times.
+template <int THREADS>
+__device__ __forceinline__ void sort_through_memory(const RangeList &list, const SortPlan &sp, uint32_t m, uint32_t first, int bits, uint32_t *lds, uint32_t *keys_out, uint32_t *idx_out)
+{
+    constexpr int ITEMS = 4, COUNT = 8, WAVES = THREADS / WAVE;
+    const int passes = bits <= 8 ? 1 : (bits <= 24 ? 3 : 5), width = (bits + passes - 1) / passes;
+    const uint32_t bins = 1u << width, mask = bins - 1u, t = threadIdx.x, w = t / WAVE;
+    uint32_t *next = lds, *base = next + passes * bins, *scan = base + bins;         // next: by pass and digit, where its next key goes
+    uint16_t *hist = reinterpret_cast<uint16_t *>(scan + WAVES);
+    for (uint32_t b = t; b < passes * bins; b += THREADS) next[b] = 0;
+    __syncthreads();
+    for (uint32_t i0 = t; i0 < m; i0 += COUNT * THREADS) {
+        uint32_t key[COUNT], from[COUNT];
+#pragma unroll
+        for (int k = 0; k < COUNT; ++k) key[k] = min(i0 + k * THREADS, m - 1);
+        list(key, from);
+#pragma unroll
+        for (int k = 0; k < COUNT; ++k) key[k] = sp.keys[from[k]] - first;
+#pragma unroll
+        for (int k = 0; k < COUNT; ++k) {
+            if (i0 + k * THREADS >= m) continue;
+            for (int p = 0; p < passes; ++p) {           // (the first lane's digit by one addition: mostly a popular key's)
+                const uint32_t d = (key[k] >> (p * width)) & mask, d0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)d);
+                const uint64_t same = __builtin_amdgcn_ballot_w64(d == d0);
+                const bool leads = d == d0 && mask_rank(same) == 0;
+                if (leads || d != d0) atomicAdd(&next[p * bins + d], leads ? (uint32_t)__popcll(same) : 1u);
+            }
+        }
+    }
+    for (int p = 0; p < passes; ++p) {
+        const bool back = p & 1;                         // (from the order's places to the tiles')
+        const uint32_t *key_in = back ? keys_out : sp.keys, *pay_in = back ? idx_out : sp.idx;
+        uint32_t *key_to = back ? sp.keys : keys_out, *pay_to = back ? sp.idx : idx_out;
+        uint32_t key[ITEMS], pay[ITEMS], total;
+        bool valid[ITEMS];
+        const auto load = [&](uint32_t at0) {
+            uint32_t from[ITEMS];
+#pragma unroll
+            for (int it = 0; it < ITEMS; ++it) from[it] = key[it] = min(at0 + it * WAVE, m - 1);
+            if (!back) list(key, from);
+#pragma unroll
+            for (int it = 0; it < ITEMS; ++it) { key[it] = key_in[from[it]]; pay[it] = pay_in[from[it]]; }
+        };
+        __syncthreads();                                 // (the keys have been counted, or have all moved)
+        const uint32_t mine = t < bins ? next[p * bins + t] : 0u, excl = block_excl_scan<WAVES>(mine, scan, total);
+        if (t < bins) next[p * bins + t] = excl;
+        uint32_t at0 = w * (WAVE * ITEMS) + lane_id();
+        load(at0);
+        for (uint32_t c0 = 0; c0 < m; c0 += THREADS * ITEMS, at0 += THREADS * ITEMS) {
+            uint32_t d[ITEMS], rank[ITEMS], k[ITEMS], q[ITEMS];
+            for (uint32_t b = t; b < WAVES * bins / 2; b += THREADS) reinterpret_cast<uint32_t *>(hist)[b] = 0;
+#pragma unroll
+            for (int it = 0; it < ITEMS; ++it) { k[it] = key[it]; q[it] = pay[it]; valid[it] = at0 + it * WAVE < m; d[it] = ((k[it] - first) >> (p * width)) & mask; }
+            if (c0 + THREADS * ITEMS < m) load(at0 + THREADS * ITEMS);               // (under way while these are ranked)
+            __syncthreads();
+            rank_in_wave<ITEMS>(d, valid, width, hist + w * bins, rank);
+            __syncthreads();
+            if (t < bins) { const uint32_t run = waves_before<WAVES>(hist + t, bins), at = next[p * bins + t]; base[t] = at; next[p * bins + t] = at + run; }
+            __syncthreads();
+#pragma unroll
+            for (int it = 0; it < ITEMS; ++it) rank[it] = valid[it] ? rank[it] + base[d[it]] + hist[w * bins + d[it]] : 0u;
+#pragma unroll
+            for (int it = 0; it < ITEMS; ++it) d[it] = rank[it];
+            if (back) list(rank, d);
+#pragma unroll
+            for (int it = 0; it < ITEMS; ++it) if (valid[it]) { key_to[d[it]] = k[it]; pay_to[d[it]] = q[it]; }
+            __syncthreads();
+        }
+    }
 }
 
 template <int THREADS>
 __device__ __forceinline__ void sort_range_body(const SortStage &s, uint32_t range, uint32_t *lds)
 {
     constexpr int WAVES = THREADS / WAVE;
-    constexpr uint32_t LIST = THREADS * sort_range_items(THREADS);
+    constexpr uint32_t LIST = sort_list(THREADS);
     const SortPlan &sp = s.sp;
     uint32_t *first_of = lds, *where = first_of + (sp.ntiles + 1) / 2 * 2, *scan = where + (sp.ntiles + 1) / 2 * 2, *work = scan + 16;
     const uint32_t t = threadIdx.x;
@@ -386,19 +671,16 @@ __device__ __forceinline__ void sort_range_body(const SortStage &s, uint32_t ran
     }
     begin = block_sum<WAVES>(begin, scan);               // (its barriers make the tiles' places visible)
     if (!m) return;
-    const auto source = [&](uint32_t i) {                // where list place i's key lies
-        uint32_t lo = 0, hi = sp.ntiles;
-        while (hi - lo > 1) { const uint32_t mid = (lo + hi) / 2; if (first_of[mid] <= i) lo = mid; else hi = mid; }
-        return where[lo] + i;
-    };
+    const RangeList list{first_of, where, sp.ntiles, sp.ntiles > 1 ? 1u << (31 - __clz(sp.ntiles - 1)) : 0u};
     uint32_t *keys_out = s.keys_out + begin, *idx_out = s.idx_out + begin;
-    uint32_t cur = range && before == a ? a + 1 : a;     // (key a has ranges of its own before this one)
+    const uint32_t cur = range && before == a ? a + 1 : a;         // (key a has ranges of its own before this one)
     if (a == behind) {                                   // this is one
         constexpr int COPY = 8;
         for (uint32_t i0 = t; i0 < m; i0 += COPY * THREADS) {
             uint32_t from[COPY], pos[COPY];
 #pragma unroll
-            for (int k = 0; k < COPY; ++k) from[k] = source(min(i0 + k * THREADS, m - 1));
+            for (int k = 0; k < COPY; ++k) pos[k] = min(i0 + k * THREADS, m - 1);
+            list(pos, from);
 #pragma unroll
             for (int k = 0; k < COPY; ++k) pos[k] = sp.idx[from[k]];
 #pragma unroll
@@ -406,44 +688,24 @@ __device__ __forceinline__ void sort_range_body(const SortStage &s, uint32_t ran
         }
         return;
     }
-    const auto sort = [&](auto place, uint32_t count, uint32_t hi, uint32_t *ko, uint32_t *io) {
-        const int bits = max(1, 32 - __clz(hi - 1 - cur));
+    const int bits = max(1, 32 - __clz(behind - 1 - cur));
+    const auto sort = [&](const auto &which, uint32_t count, uint32_t gap_at, uint32_t gap) {
         if constexpr (THREADS == SORT_THREADS) {
-            if (count <= 2 * THREADS) sort_listed<2, THREADS>(place, sp, count, cur, bits, work, ko, io);
-            else sort_listed<4, THREADS>(place, sp, count, cur, bits, work, ko, io);
+            if (count <= 2 * THREADS) sort_listed<2, THREADS>(which, sp, count, cur, bits, work, keys_out, idx_out, gap_at, gap);
+            else sort_listed<4, THREADS>(which, sp, count, cur, bits, work, keys_out, idx_out, gap_at, gap);
         } else {
-            if (count <= THREADS) sort_listed<1, THREADS>(place, sp, count, cur, bits, work, ko, io);
-            else if (count <= 2 * THREADS) sort_listed<2, THREADS>(place, sp, count, cur, bits, work, ko, io);
-            else if (count <= 4 * THREADS) sort_listed<4, THREADS>(place, sp, count, cur, bits, work, ko, io);
-            else sort_listed<8, THREADS>(place, sp, count, cur, bits, work, ko, io);
+            if (count <= THREADS) sort_listed<1, THREADS>(which, sp, count, cur, bits, work, keys_out, idx_out, gap_at, gap);
+            else if (count <= 2 * THREADS) sort_listed<2, THREADS>(which, sp, count, cur, bits, work, keys_out, idx_out, gap_at, gap);
+            else if (count <= 4 * THREADS) sort_listed<4, THREADS>(which, sp, count, cur, bits, work, keys_out, idx_out, gap_at, gap);
+            else sort_listed<8, THREADS>(which, sp, count, cur, bits, work, keys_out, idx_out, gap_at, gap);
         }
     };
-    if (m <= LIST) { sort(source, m, behind, keys_out, idx_out); return; }
-    // More than a workgroup sorts at a time (the cuts were far off): part after part of the range, or key by key.
-    while (cur < behind) {
-        uint32_t hi = behind, here;
-        for (;;) {
-            here = 0;
-            for (uint32_t i0 = 0; i0 < m; i0 += THREADS) {
-                const uint32_t from = source(min(i0 + t, m - 1)), key = sp.keys[from];
-                const bool in = i0 + t < m && key - cur < hi - cur;
-                uint32_t tot;
-                const uint32_t to = here + block_excl_scan<WAVES>(in ? 1u : 0u, scan, tot);
-                if (in) {
-                    if (hi - cur == 1) { keys_out[to] = key; idx_out[to] = sp.idx[from]; }
-                    else if (to < LIST) work[to] = from;
-                }
-                here += tot;
-            }
-            if (here <= LIST || hi - cur == 1) break;
-            hi = cur + (hi - cur) / 2;
-        }
-        __syncthreads();
-        if (hi - cur > 1 && here) sort([&](uint32_t i) { return work[i]; }, here, hi, keys_out, idx_out);
-        keys_out += here; idx_out += here;
-        cur = hi;
-        __syncthreads();
-    }
+    if (m <= LIST) { sort(list, m, 0u, 0u); return; }
+    if (m <= 2 * LIST && bits + 32 - __clz(2 * LIST - 1) <= 32) { sort_packed<THREADS>(list, sp, m, cur, bits, work, keys_out, idx_out); return; }
+    const SortPopular pop = part_popular<THREADS>(list, sp, m, scan, work, keys_out, idx_out);
+    if (!pop.copies) sort_through_memory<THREADS>(list, sp, m, cur, bits, work, keys_out, idx_out);
+    else if (pop.copies < m)
+        sort([&](const auto &place, auto &from) { for (uint32_t q = 0; q < sizeof(place) / 4; ++q) from[q] = work[place[q]]; }, m - pop.copies, pop.below, pop.copies);
 }
 
 // ---- stages -----------------------------------------------------------------------------------

@@ -81,10 +81,10 @@ def test_every_way_a_batch_is_sorted(n, vocab, ahead):
         cache.close()
 
 
-def drawn_positions(n):
-    """The positions whose ids cut a batch into ranges (sort_part_body's sample)."""
-    t = np.arange(256, dtype=np.uint64)
-    lo, hi = t * n // 256, (t + 1) * n // 256
+def drawn_positions(n, draws=256):
+    """The positions whose ids cut a batch into ranges (sort_part_body's samples)."""
+    t = np.arange(draws, dtype=np.uint64)
+    lo, hi = t * n // draws, (t + 1) * n // draws
     return (lo + ((t * 0x9E3779B9 % 2**32) * (hi - lo) >> np.uint64(32))).astype(np.int64)
 
 
@@ -129,6 +129,137 @@ def test_batches_sorted_in_ranges(n, vocab, policy, ahead):
             np.add.at(want, ids[ok], -g[ok].astype(np.float64))
         assert cache.flush() == hc.HET_ERANGE                          # (the ids outside)
         assert np.array_equal(table.cpu().numpy(), want.astype(np.float32))
+    finally:
+        cache.close()
+
+
+def over_full_batch(kind, n, vocab, times, rng):
+    """A batch whose ids are spread over the vocabulary at the positions that decide where ranges begin, and elsewhere make one range far
+    too full: `kind` says by what, `times` how many workgroups of 256 threads could sort as much as what sorts it."""
+    ids = rng.integers(0, vocab, n)
+    plain = np.ones(n, dtype=bool)
+    for draws in (256, 1024):
+        plain[drawn_positions(n, draws)] = False
+    free = rng.permutation(np.flatnonzero(plain))
+    at = vocab // 2 + 11
+    for count, first, keys in {"some": [(1_300, at, vocab // 400)], "popular": [(4_700, at, 1)], "popular_and_some": [(2_500, at, 1), (700, at - 60, 120)],
+                               "two_popular": [(1_900, at, 1), (1_900, at + 1, 1)], "many": [(6_000, at, vocab // 400)], "many_close": [(6_000, at, 150)],
+                               "first": [(3_000, 0, 1)], "last": [(3_000, vocab - 1, 1)], "outside": [(3_000, -1, 1)]}[kind]:
+        ids[free[:count * times]] = rng.integers(first, first + keys, count * times)
+        free = free[count * times:]
+    return ids
+
+
+@pytest.mark.parametrize("kind", ["some", "popular", "popular_and_some", "two_popular", "many", "many_close", "first", "last", "outside"])
+@pytest.mark.parametrize("n,vocab,ahead", [(30_000, 20_000, 1), (30_000, 300_000, 1), (30_000, 1 << 23, 1), (70_000, 5_000_000, 1), (200_000, 5_000_000, 0)])
+def test_ranges_that_hold_too_many_keys(n, vocab, ahead, kind):
+    """Sorted in kernels that carry it or in their own, with cuts from a batch unlike: the distinct keys, whole-number gradient sums, and, against
+    a run that sorts the other way, every bit of sums that depend on the order of a key's gradients."""
+    from paper_2112_07221_amd import hetcache as hc
+    dev = torch.device("cuda:0")
+    rng = np.random.default_rng(n + vocab)
+    batches = [rng.integers(0, vocab, n)] + [over_full_batch(kind, n, vocab, 1 if ahead else 8, rng) if t % 2 else rng.integers(0, vocab, n) for t in range(1, 5)]
+    whole = [rng.integers(-8, 9, (n, 1)).astype(np.float32) for _ in batches]
+    wide = [(rng.standard_normal((n, 1)) * 2.0 ** rng.integers(-60, 60, (n, 1))).astype(np.float32) for _ in batches]
+    tables = []
+    for announced, grads in ((ahead, whole), (ahead, wide), (1 - ahead, wide)):
+        table, want = torch.zeros(vocab, 1, device=dev), np.zeros((vocab, 1))
+        cache = hc.HetCache(1, 1, 0, hc.POLICY_NONE, n, hc.OPT_SGD)
+        try:
+            cache.attach_backing(table, None, torch.zeros(vocab, dtype=torch.int32, device=dev))
+            out = torch.empty(n, 1, device=dev)
+            dids = [torch.from_numpy(ids).to(dev) for ids in batches]
+            for t, ids in enumerate(batches):
+                if announced and t + 1 < len(batches):
+                    cache.prefetch(dids[t + 1])
+                cache.lookup(dids[t], out)
+                ok = ids >= 0
+                assert np.array_equal(cache.last_lookup()[0], np.unique(ids[ok])), t
+                cache.update(dids[t], torch.from_numpy(grads[t]).to(dev), 1.0)
+                if grads is whole:
+                    assert np.array_equal(out.cpu().numpy()[ok], want[ids[ok]]), t
+                    np.add.at(want, ids[ok], -grads[t][ok].astype(np.float64))
+            torch.cuda.synchronize()
+            tables.append(table.cpu().numpy())
+            if grads is whole:
+                assert np.array_equal(tables[-1], want.astype(np.float32))
+        finally:
+            cache.close()
+    assert np.array_equal(tables[1].view(np.uint32), tables[2].view(np.uint32))
+
+
+def test_a_range_of_a_wide_interval_that_holds_too_many_keys():
+    """Keys of 26 bits in the last range, whose beginning came from a batch of small keys: five passes through memory."""
+    from paper_2112_07221_amd import hetcache as hc
+    dev = torch.device("cuda:0")
+    n, vocab, rng = 30_000, 60_000_000, np.random.default_rng(1)
+    small, large = [rng.integers(0, 900, n) for _ in range(3)], [rng.integers(0, 900, n) for _ in range(2)]
+    for ids in large:
+        plain = np.ones(n, dtype=bool)
+        plain[drawn_positions(n, 256)] = plain[drawn_positions(n, 1024)] = False
+        some = rng.permutation(np.flatnonzero(plain))[:5_000]
+        ids[some] = rng.integers(900, vocab, 5_000)
+    batches = [small[0], large[0], small[1], large[1], small[2]]
+    table, want = torch.zeros(vocab, 1, device=dev), np.zeros((vocab, 1))
+    cache = hc.HetCache(1, 1, 0, hc.POLICY_NONE, n, hc.OPT_SGD)
+    try:
+        cache.attach_backing(table, None, torch.zeros(vocab, dtype=torch.int32, device=dev))
+        out = torch.empty(n, 1, device=dev)
+        dids = [torch.from_numpy(ids).to(dev) for ids in batches]
+        for t, ids in enumerate(batches):
+            if t + 1 < len(batches):
+                cache.prefetch(dids[t + 1])
+            cache.lookup(dids[t], out)
+            assert np.array_equal(out.cpu().numpy(), want[ids]) and np.array_equal(cache.last_lookup()[0], np.unique(ids)), t
+            g = rng.integers(-8, 9, (n, 1)).astype(np.float32)
+            cache.update(dids[t], torch.from_numpy(g).to(dev), 1.0)
+            np.add.at(want, ids, -g.astype(np.float64))
+        assert np.array_equal(table.cpu().numpy(), want.astype(np.float32))
+    finally:
+        cache.close()
+
+
+@pytest.mark.parametrize("share", [0.01, 0.02, 0.04])
+def test_a_rare_key_that_becomes_popular_does_not_hold_up_the_step(share):
+    """The sort of a batch of 106496 ids, a new one of which makes up 1 to 4 %, carried by the update with cuts from the batch before: its longest
+    workgroup lives 13 to 40 us (11 to 13 if the popularity stays).  Bound: 100 us; where a range's keys were searched again for every
+    part of it, 160 us and more."""
+    from paper_2112_07221_amd import hetcache as hc
+    dev = torch.device("cuda:0")
+    n, vocab, steps = 106_496, 1_000_000, 12
+    rng = np.random.default_rng(3)
+    p = np.cumsum(np.arange(1, vocab // 26 + 1) ** -1.05)
+    perm = [rng.permutation(vocab // 26) for _ in range(26)]
+
+    def batch(t):
+        ids = np.stack([f * (vocab // 26) + perm[f][np.searchsorted(p, rng.random(n // 26) * p[-1])] for f in range(26)], axis=1).reshape(-1)
+        if t % 2:
+            ids[rng.random(n) < share] = rng.integers(0, vocab)
+        return torch.from_numpy(ids).to(dev)
+
+    ids = [batch(t) for t in range(steps)]
+    table = torch.zeros(vocab, 64, device=dev)
+    out, grads = torch.empty(n, 64, device=dev), torch.zeros(n, 64, device=dev)
+    cache = hc.HetCache(1, 64, 0, hc.POLICY_NONE, n, hc.OPT_SGD)
+    try:
+        cache.attach_backing(table, None, torch.zeros(vocab, dtype=torch.int32, device=dev))
+        rec = torch.zeros(1 << 13, hc.TRACE_WORDS, dtype=torch.int64, device=dev)
+        longest = []
+        for t in range(steps):
+            if t + 1 < steps:
+                cache.prefetch(ids[t + 1])
+            cache.lookup(ids[t], out)
+            rec.zero_()
+            cache.profile_trace(rec, "apply_kernel")
+            cache.update(ids[t], grads, 0.1)
+            torch.cuda.synchronize()
+            cache.profile_trace(None, "apply_kernel")
+            r = rec.cpu().numpy()
+            stage = r[r[:, 6] == 1]
+            if t % 2 == 0 and t > 1 and t + 1 < steps:          # (the next batch has the new key)
+                assert len(stage) > 0
+                longest.append((stage[:, 5] - stage[:, 0]).max() / 100.0)      # (the counter runs at 100 MHz)
+        assert np.median(longest) < 100.0, longest
     finally:
         cache.close()
 
