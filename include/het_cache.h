@@ -171,8 +171,7 @@ int het_lookup(het_cache *c, const int64_t *ids, int64_t n, float *out);
  * kernels of the calls made between this call and that lookup carry it in extra workgroups, one
  * stage per kernel (two, if two announced batches are under way); whatever is still missing runs
  * when the lookup comes.  A sort has two stages, and a lookup plus an update have two or three kernels that carry
- * one (batches of more than 524 288 ids are sorted when their lookup comes): announce a batch before the lookup of the batch
- * before it, and its sort is never seen.  ids[n] (device) must be complete in stream order when this call is made and stay
+ * one: announce a batch before the lookup of the batch before it, and its sort is never seen.  ids[n] (device) must be complete in stream order when this call is made and stay
  * unchanged until the lookup that passes the same pointer and n.  That lookup checks the order sorted ahead
  * against the ids as they are then: ids that changed after the sort began set error bit 2, HET_ESTATE,
  * and its results are not meaningful (ids that changed before, with no call in between to carry its first

@@ -317,9 +317,6 @@ void sort_now(het_cache *c, const int64_t *ids, uint32_t n, int set, int first_s
     }
 }
 
-// The largest batch whose sort is carried: beyond it ranges hold more keys than a workgroup of a carrying kernel sorts at once.
-constexpr uint32_t CARRY_MAX = SORT_MAX_RANGES * 512;
-
 // The next stage of the oldest announced batch whose sort is not complete yet, for the kernel
 // that is about to be launched to carry.
 SortStage next_ride_of(het_cache *c, int a)
@@ -355,7 +352,7 @@ Rides next_rides(het_cache *c, bool lookup = false)
     Rides r{no_stage(), no_stage()};
     int got = 0;
     for (int a = 0; a < c->n_ann && got < 2; ++a) {
-        if (c->ann[a].next_stage >= SORT_STAGES || c->ann[a].n > CARRY_MAX) continue;
+        if (c->ann[a].next_stage >= SORT_STAGES) continue;
         if (lookup && c->updated && !c->side && c->ann[a].n <= LEAVE_MAX && SORT_STAGES - c->ann[a].next_stage <= a + 1) continue;
         (got == 0 ? r.a : r.b) = next_ride_of(c, a);
         ++got;

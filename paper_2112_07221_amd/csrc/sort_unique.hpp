@@ -39,8 +39,9 @@ constexpr uint32_t SORT_SAMPLE = 256;                    // keys drawn to look w
 constexpr uint32_t SORT_CUT_SAMPLE = 1024;               // keys drawn to make cuts of
 constexpr uint32_t SORT_MAX_RANGES = 1024;
 
-// How many ranges.  Carried: of up to 512 keys on average, half of what a workgroup of 256 threads sorts at a time (with up to
-// 832 many hold more, and a step of 409600 ids takes 265 us, not 226).  Alone a workgroup sorts eight times as
+// How many ranges.  Carried: of up to 512 keys on average, half of what a workgroup of 256 threads sorts at a time, as long as there
+// are enough (of up to 256 keys: 60000 ids 36.2 us a step instead of 35.7, 114688 75.9 instead of 75.2); beyond 524288 ids many hold more (600000 ids announced 157 us a
+// step, sorted at their lookup 198; 1048576 ids 268 and 303).  Alone a workgroup sorts eight times as
 // many, and ranges cost the part stage: 200000 ids in bulk 84.4 us a step with 512, 77.8 with 256.
 __host__ __device__ inline uint32_t sort_ranges(uint32_t n, bool carried)
 {

@@ -264,6 +264,71 @@ def test_a_rare_key_that_becomes_popular_does_not_hold_up_the_step(share):
         cache.close()
 
 
+@pytest.mark.parametrize("ahead", [1, 2])
+@pytest.mark.parametrize("n", [400, 4_096, 4_097, 16_384, 16_385, 32_768, 32_769, 65_536, 65_537, 131_072, 131_073, 262_144, 262_145, 524_288, 524_289, 1 << 20])
+def test_the_sort_of_an_announced_batch_has_no_kernel_of_its_own(n, ahead):
+    """Table in HBM, lookups and updates in turn: both stages are carried, for one and two batches ahead, on either side of the sizes at
+    which the ranges' number and who carries a stage change.  Whole numbers and lr 1, so rows are exact."""
+    from paper_2112_07221_amd import hetcache as hc
+    dev = torch.device("cuda:0")
+    rng = np.random.default_rng(n)
+    vocab, steps = 1_000_000, 6
+    ids = [np.minimum((rng.random(n) ** 3 * vocab).astype(np.int64), vocab - 1) for _ in range(steps)]
+    dids = [torch.from_numpy(x).to(dev) for x in ids]
+    table, want = torch.zeros(vocab, 1, device=dev), np.zeros(vocab)
+    cache = hc.HetCache(1, 1, 0, hc.POLICY_NONE, n, hc.OPT_SGD)
+    try:
+        cache.attach_backing(table, None, torch.zeros(vocab, dtype=torch.int32, device=dev))
+        out = torch.empty(n, 1, device=dev)
+        for t in range(1, ahead):
+            cache.prefetch(dids[t])
+        for t in range(steps):
+            if t + ahead < steps:
+                cache.prefetch(dids[t + ahead])
+            if t == 1:                                   # (the first batch was not announced)
+                cache.profile_begin()
+            cache.lookup(dids[t], out)
+            assert np.array_equal(out.cpu().numpy()[:, 0], want[ids[t]]), t
+            g = rng.integers(-8, 9, n).astype(np.float32)
+            cache.update(dids[t], torch.from_numpy(g[:, None]).to(dev), 1.0)
+            np.subtract.at(want, ids[t], g.astype(np.float64))
+        assert "sort_stage_kernel" not in cache.profile_end()
+        assert np.array_equal(table.cpu().numpy()[:, 0], want.astype(np.float32))
+    finally:
+        cache.close()
+
+
+def test_announced_batches_of_all_sizes_in_turn():
+    """Small batches behind the largest and before them, two ahead, with updates left out and lookups nobody announced in between."""
+    from paper_2112_07221_amd import hetcache as hc
+    dev = torch.device("cuda:0")
+    rng = np.random.default_rng(9)
+    vocab, sizes = 500_000, [600_000, 300, 32_768, 1 << 20, 32_769, 5_000, 4_096, 1, 524_289, 70_000, 20_000, 900, 700_000, 20_000, 20_000, 20_000, 20_000]
+    ids = [rng.integers(0, vocab, n) for n in sizes]
+    dids = [torch.from_numpy(x).to(dev) for x in ids]
+    table, want = torch.zeros(vocab, 1, device=dev), np.zeros(vocab)
+    cache = hc.HetCache(60_000, 1, 100, hc.POLICY_LRU, 1 << 20, hc.OPT_SGD)
+    try:
+        cache.attach_backing(table, None, torch.zeros(vocab, dtype=torch.int32, device=dev))
+        cache.prefetch(dids[1])
+        for t, n in enumerate(sizes):
+            if t + 2 < len(sizes):
+                cache.prefetch(dids[t + 2])
+            out = torch.empty(n, 1, device=dev)
+            if t % 5 == 2:
+                other = torch.from_numpy(rng.integers(0, vocab, 9_000)).to(dev)
+                cache.lookup(other, torch.empty(9_000, 1, device=dev))
+            cache.lookup(dids[t], out)
+            assert np.array_equal(out.cpu().numpy()[:, 0], want[ids[t]]), t
+            if t % 3 != 1 and t < 13:
+                g = rng.integers(-8, 9, n).astype(np.float32)
+                cache.update(dids[t], torch.from_numpy(g[:, None]).to(dev), 1.0)
+                np.subtract.at(want, ids[t], g.astype(np.float64))
+        assert cache.flush() == 0
+        assert np.array_equal(table.cpu().numpy()[:, 0], want.astype(np.float32))
+    finally:
+        cache.close()
+
 @pytest.mark.parametrize("policy,s", [(0, 3), (1, 3), (3, 0)])
 @pytest.mark.parametrize("batch,vocab,capacity", [(158, 60_000, 9_000), (631, 300_000, 20_000), (2_521, 300_000, 40_000)])
 def test_lookups_of_batches_sorted_in_ranges(batch, vocab, capacity, policy, s):
