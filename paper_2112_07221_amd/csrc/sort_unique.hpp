@@ -443,7 +443,8 @@ __device__ __forceinline__ void sort_listed(const L &list, const SortPlan &sp, u
 }
 
 // Twice as many keys, of few enough bits: a word holds a key and its list place, and only words change places.  (1024 to 2048 keys in a
-// kernel that carries this: 18 us, through memory 25.)
+// kernel that carries this: 18 us, through memory 25.  Not in the sort's own kernel, which has eight times the list and whose every
+// range would pay for the registers: 8000 ids 34.4 -> 35.5 us a step.)
 template <int THREADS>
 __device__ __forceinline__ void sort_packed(const RangeList &list, const SortPlan &sp, uint32_t m, uint32_t first, int bits, uint32_t *lds, uint32_t *keys_out, uint32_t *idx_out)
 {
@@ -702,7 +703,7 @@ __device__ __forceinline__ void sort_range_body(const SortStage &s, uint32_t ran
         }
     };
     if (m <= LIST) { sort(list, m, 0u, 0u); return; }
-    if (m <= 2 * LIST && bits + 32 - __clz(2 * LIST - 1) <= 32) { sort_packed<THREADS>(list, sp, m, cur, bits, work, keys_out, idx_out); return; }
+    if (THREADS == SORT_THREADS && m <= 2 * LIST && bits + 32 - __clz(2 * LIST - 1) <= 32) { sort_packed<THREADS>(list, sp, m, cur, bits, work, keys_out, idx_out); return; }
     const SortPopular pop = part_popular<THREADS>(list, sp, m, scan, work, keys_out, idx_out);
     if (!pop.copies) sort_through_memory<THREADS>(list, sp, m, cur, bits, work, keys_out, idx_out);
     else if (pop.copies < m)
