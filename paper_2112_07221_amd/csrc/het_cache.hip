@@ -112,7 +112,7 @@ struct het_cache {
     uint64_t t_host = 0;             // non-empty lookups so far (equals the device's t)
     bool overflow_pending = false;   // a lookup ran and no trim since
     uint32_t last_lookup_n = 0;
-    bool updated = false;            // the lookup before the present one was followed by an update
+    bool updated = false;            // an update has come since the last lookup
     const int64_t *order_ids = nullptr;   // ids the current sorted order was built from (by a lookup)
     uint32_t order_n = 0;
     bool order_valid = false;
@@ -342,18 +342,24 @@ uint32_t lds_bytes(size_t own, const Rides &r)
     return need;
 }
 
-// A lookup's kernels leave the stages of batches of up to LEAVE_MAX ids to the updates that come before the batch is looked up,
-// if these are enough (announced two ahead; updated: the last call was an update): with so few ids they are shorter
-// than a stage's chain, the update is not (two ahead, a step carried by both kernels and by the updates alone: 400 ids 22.0 and 18.8 us,
-// 4000 27.8 and 26.0, 30000 32.1 and 29.5).
+// Which kernel is about to be launched: stages of batches of up to LEAVE_MAX ids are left to those that hide them better, if these come
+// often enough before the batch is looked up (table in HBM).  With so few ids a lookup's kernels are shorter than a stage's chain.
+//   FILL, a lookup's second kernel: leaves them to the updates (if the last call was one; two ahead, a step carried by both
+//     kernels and by the updates alone: 400 ids 22.0 and 18.8 us, 4000 27.8 and 26.0, 30000 32.1 and 29.5).
+//   READ_TRIM, the eviction of a lookup that follows a lookup: leaves them to the lookups' second kernels, which have two stages of two
+//     batches side by side where each kernel had one (lookups only, two ahead: 2000 ids 23.3 and 22.9 us, 8000 24.3 and 22.8, 20000 30.7 and 27.6).
+//     The lookup's own batch may be among the announced ones, so the a-th has a of them before it.
+enum Carrier { UPDATE, FILL, READ_TRIM };
 constexpr uint32_t LEAVE_MAX = 32768;
-Rides next_rides(het_cache *c, bool lookup = false)
+Rides next_rides(het_cache *c, Carrier who = UPDATE)
 {
     Rides r{no_stage(), no_stage()};
     int got = 0;
     for (int a = 0; a < c->n_ann && got < 2; ++a) {
-        if (c->ann[a].next_stage >= SORT_STAGES) continue;
-        if (lookup && c->updated && !c->side && c->ann[a].n <= LEAVE_MAX && SORT_STAGES - c->ann[a].next_stage <= a + 1) continue;
+        const int left = SORT_STAGES - c->ann[a].next_stage;
+        if (!left) continue;
+        const int later = c->side || c->ann[a].n > LEAVE_MAX ? 0 : who == FILL ? (c->updated ? a + 1 : 0) : who == READ_TRIM ? a : 0;
+        if (left <= later) continue;
         (got == 0 ? r.a : r.b) = next_ride_of(c, a);
         ++got;
     }
@@ -498,7 +504,7 @@ int run_trim(het_cache *c, bool counted, bool updated)
     }
     if (!counted) LAUNCH(c, K_TRIM_STAGE, trim_stage_kernel<<<count_blocks(c), TRIM_THREADS, 0, c->stream>>>(c->cv, c->sel_tp));
     const TrimPlan tp = plan_eviction(c, counted && c->counted && updated);
-    const Rides ride = next_rides(c);
+    const Rides ride = next_rides(c, c->updated ? UPDATE : READ_TRIM);
     const uint32_t ev_blocks = evict_grid(c);
     // Rows of a kilobyte or more: the pushes run at the memory's limit, and a fourth workgroup per
     // compute unit only gets in the others' way (config 5: 107 us against 97).  Asking for more LDS
@@ -561,7 +567,7 @@ int run_lookup(het_cache *c, const int64_t *ids, uint32_t n, const int64_t *offs
         // no cache: mark the runs, then gather straight from the global table
         const uint32_t dtiles = cdiv(n, PT_TILE), dblocks = dtiles * (match >= 0 ? 2u : 1u);
         LAUNCH(c, K_PROBE, direct_probe_kernel<true><<<dblocks, PT_THREADS, 0, c->stream>>>(c->cv, c->ws, n, t_now, dtiles, match >= 0 ? ids : nullptr, offsets ? c->inv : nullptr));
-        const Rides ride = next_rides(c, true);
+        const Rides ride = next_rides(c, FILL);
         const uint32_t grid = ride.blocks() + row_grid(c->cv.geom, offsets ? (uint64_t)n_bags * split : cdiv(n, GATHER_ROWS));
         const uint32_t lds = lds_bytes(std::max(sizeof(FillLds), sizeof(TrimLds)), ride);
         const TrimPlan none{};
@@ -628,7 +634,7 @@ int run_lookup(het_cache *c, const int64_t *ids, uint32_t n, const int64_t *offs
         // The missed keys' rows themselves are left to the update that is expected to follow (it reads
         // them from the global table and writes them to their slots with its step applied); the fetch
         // workgroups that remain refresh the stale rows.
-        const Rides ride = next_rides(c, true);
+        const Rides ride = next_rides(c, FILL);
         fetch_mode = 1;
         const uint32_t fb = std::min(fill_blocks, STALE_BLOCKS);
         FILL_GATHER_ANY(ride.blocks() + fb + ptiles + hist_blocks + gather_blocks, fb, hist_blocks, 0u);
@@ -654,7 +660,7 @@ int run_lookup(het_cache *c, const int64_t *ids, uint32_t n, const int64_t *offs
         const uint32_t push_blocks = c->push_pending && !next ? PUSH_BLOCKS : 0u;
         const uint32_t fetch_blocks = c->location == HET_BACKING_HBM ? fill_blocks : std::min(fill_blocks, PUSH_BLOCKS);
         {
-            const Rides ride = next_rides(c, true);
+            const Rides ride = next_rides(c, FILL);
             FILL_GATHER_ANY(ride.blocks() + push_blocks + fetch_blocks + ptiles + hist_blocks, fetch_blocks, hist_blocks, push_blocks);
         }
         if (push_blocks) c->push_pending = false;
@@ -673,7 +679,7 @@ int run_lookup(het_cache *c, const int64_t *ids, uint32_t n, const int64_t *offs
             hash_find(c, ah.skey, ah.n);
         }
         {
-            const Rides ride = next_rides(c, true);
+            const Rides ride = next_rides(c, FILL);
             FILL_GATHER_ANY(ride.blocks() + ah.blocks + gather_blocks, 0u, 0u, 0u);
         }
         if (next) {

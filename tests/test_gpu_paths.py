@@ -298,6 +298,36 @@ def test_the_sort_of_an_announced_batch_has_no_kernel_of_its_own(n, ahead):
         cache.close()
 
 
+@pytest.mark.parametrize("n", [2_000, 8_000, 32_768, 32_769])
+def test_lookups_alone_leave_the_sorts_of_small_batches_to_one_kernel_each(n):
+    """Lookups only, two batches ahead: the second kernel of a lookup carries the first stage of one batch and the second of another (up
+    to 32768 ids), instead of the eviction before it one and itself the other."""
+    from paper_2112_07221_amd import hetcache as hc
+    dev = torch.device("cuda:0")
+    vocab, steps = 300_000, 8
+    rng = np.random.default_rng(n)
+    ids = [torch.from_numpy(rng.integers(0, vocab, n)).to(dev) for _ in range(steps + 2)]
+    table = torch.randn(vocab, 16, device=dev)
+    out = torch.empty(n, 16, device=dev)
+    rec = torch.zeros(1 << 13, hc.TRACE_WORDS, dtype=torch.int64, device=dev)
+    tiles, ranges = -(-n // 1024), 64 if n <= 16_384 else 128
+    cache = hc.HetCache(40_000, 16, 100, hc.POLICY_LRU, n, hc.OPT_SGD)
+    try:
+        cache.attach_backing(table, None, torch.zeros(vocab, dtype=torch.int32, device=dev))
+        cache.prefetch(ids[1])
+        for t in range(steps):
+            cache.prefetch(ids[t + 2])
+            rec.zero_()
+            cache.profile_trace(rec, "fill_gather_kernel")
+            cache.lookup(ids[t], out)
+            torch.cuda.synchronize()
+            cache.profile_trace(None, "fill_gather_kernel")
+            assert torch.equal(out, table[ids[t]]), t
+            if t >= 4:
+                assert int((rec[:, 6] == 1).sum()) == (tiles + ranges if n <= 32_768 else ranges), t
+    finally:
+        cache.close()
+
 def test_announced_batches_of_all_sizes_in_turn():
     """Small batches behind the largest and before them, two ahead, with updates left out and lookups nobody announced in between."""
     from paper_2112_07221_amd import hetcache as hc
