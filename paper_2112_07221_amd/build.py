@@ -10,7 +10,7 @@ from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
-# (source, parts it is compiled in): the parts run side by side
+# (source, parts it is compiled in): the parts run side by side; the sources check that they are as many as they have
 SOURCES = [("het_cache.hip", 1), ("apply_variants.hip", 8), ("fill_variants.hip", 2)]
 OUT = os.path.join(HERE, "libhet_cache.so")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -40,7 +40,7 @@ def build(verbose: bool = False, flags=()) -> str:
         for name, parts in SOURCES:
             for part in range(parts):
                 objects.append(os.path.join(tmp, f"{name}.{part}.o"))
-                jobs.append([HIPCC, *FLAGS, *flags, "-c", f'-DHET_BUILD_ID="{source_id()}"', f"-DHET_PART={part}", os.path.join(CSRC, name), "-o", objects[-1]])
+                jobs.append([HIPCC, *FLAGS, *flags, "-c", f'-DHET_BUILD_ID="{source_id()}"', f"-DHET_PART={part}", f"-DHET_PARTS={parts}", os.path.join(CSRC, name), "-o", objects[-1]])
         if verbose:
             print("\n".join(" ".join(j) for j in jobs))
         with ThreadPoolExecutor(max(1, min(len(jobs), os.cpu_count() or 1))) as pool:

@@ -3,6 +3,11 @@
 
 namespace het {
 
+static_assert(HET_PARTS == HET_APPLY_PARTS, "the build compiles other parts than there are: kernels would be missing in the library");
+#define HET_LISTED(part, ...) static_assert(part < HET_APPLY_PARTS, "a part beyond the last");
+HET_APPLY_VARIANTS(HET_LISTED)
+#undef HET_LISTED
+
 #if HET_PART == 0
 #define HET_PART_0(...) HET_APPLY_KERNEL(__VA_ARGS__)
 #else

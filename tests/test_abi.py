@@ -39,3 +39,18 @@ def test_argument_errors_need_no_gpu():
     assert lib.het_cache_destroy(h) == hc.HET_OK
     assert lib.het_cache_destroy(None) == hc.HET_OK
     assert hc.strerror(hc.HET_ESTATE) and hc.strerror(-99) == "unknown status"
+
+
+def test_the_build_compiles_every_part_of_the_kernels():
+    """The sources that are compiled in parts refuse to be compiled as fewer or more than they have; build.py compiles as many."""
+    import subprocess
+    from paper_2112_07221_amd import build
+    for name, parts in build.SOURCES:
+        if parts == 1:
+            continue
+        for said in (parts - 1, parts, parts + 1):
+            cmd = [build.HIPCC, "-std=c++17", "--offload-arch=gfx950", "--cuda-host-only", "-fsyntax-only", "-DHET_PART=0", f"-DHET_PARTS={said}",
+                   os.path.join(build.CSRC, name)]
+            done = subprocess.run(cmd, capture_output=True, text=True)
+            assert (done.returncode == 0) == (said == parts), (name, said, done.stderr[-2000:])
+            assert said == parts or "the build compiles other parts than there are" in done.stderr
