@@ -488,7 +488,7 @@ __device__ __forceinline__ void sort_packed(const RangeList &list, const SortPla
     uint32_t from[ITEMS];
 #pragma unroll
     for (int it = 0; it < ITEMS; ++it) {
-        if (valid[it]) keys_out[rank[it]] = word[it] / PLACES + first;
+        if (valid[it]) keys_out[rank[it]] = min(word[it] / PLACES + first, sp.vocab);      // (a key outside the range, of ids that were changed under the part stage, has lost its upper bits)
         word[it] = valid[it] ? word[it] % PLACES : 0u;
     }
     list(word, from);
