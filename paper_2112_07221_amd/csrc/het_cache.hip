@@ -634,11 +634,14 @@ int run_lookup(het_cache *c, const int64_t *ids, uint32_t n, const int64_t *offs
         // The missed keys' rows themselves are left to the update that is expected to follow (it reads
         // them from the global table and writes them to their slots with its step applied); the fetch
         // workgroups that remain refresh the stale rows.
+        // Row-wise Adagrad: only if an update came since the lookup before; where lookups follow lookups the rows left would take a kernel
+        // of their own (settle_fetch): lookups alone of 3000 ids of 64 floats 32.5 us, 27.3 with the rows fetched here.
         const Rides ride = next_rides(c, FILL);
-        fetch_mode = 1;
-        const uint32_t fb = std::min(fill_blocks, STALE_BLOCKS);
+        const bool owe = !c->cv.rowwise || c->updated;
+        fetch_mode = owe ? 1 : 0;
+        const uint32_t fb = owe ? std::min(fill_blocks, STALE_BLOCKS) : fill_blocks;
         FILL_GATHER_ANY(ride.blocks() + fb + ptiles + hist_blocks + gather_blocks, fb, hist_blocks, 0u);
-        c->fetch_owed = true; c->owed_n = n; c->owed_t = t_now;
+        if (owe) { c->fetch_owed = true; c->owed_n = n; c->owed_t = t_now; }
         hash_insert(c, n);
     } else {
         // Host-backed table: the fetches come over the host link, and the last trim's write-back

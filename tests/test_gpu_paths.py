@@ -328,6 +328,46 @@ def test_lookups_alone_leave_the_sorts_of_small_batches_to_one_kernel_each(n):
     finally:
         cache.close()
 
+@pytest.mark.parametrize("ahead", [0, 1])
+def test_lookups_alone_fetch_their_rows_themselves_under_rowwise_adagrad(ahead):
+    """Lookups only, row-wise Adagrad: one launch of the second kernel for each (rows left to an update that does not come take another), and
+    with updates again their fetches are the updates'.  Rows and accumulators against a run that looks up once per update."""
+    from paper_2112_07221_amd import hetcache as hc
+    dev = torch.device("cuda:0")
+    n, vocab, steps = 3_000, 60_000, 6
+    rng = np.random.default_rng(ahead)
+    ids = [torch.from_numpy(rng.integers(0, vocab, n)).to(dev) for _ in range(3 * steps)]
+    grads = torch.from_numpy(rng.standard_normal((n, 64)).astype(np.float32)).to(dev)
+    start = torch.randn(vocab, 64, device=dev)
+    results = []
+    for extra in (True, False):
+        table, state = start.clone(), torch.zeros(vocab, 1, device=dev)
+        cache = hc.HetCache(5_000, 64, 100, hc.POLICY_LFU, n, hc.OPT_ADAGRAD_ROWWISE, 1e-8)
+        try:
+            cache.attach_backing(table, state, torch.zeros(vocab, dtype=torch.int32, device=dev))
+            out = torch.empty(n, 64, device=dev)
+            if extra:
+                for t in range(steps):
+                    if ahead:
+                        cache.prefetch(ids[t + 1])
+                    if t == 1:
+                        cache.profile_begin()
+                    cache.lookup(ids[t], out)
+                    assert torch.equal(out, table[ids[t]]), t
+                assert cache.profile_end()["fill_gather_kernel"][1] == steps - 1
+            for t in range(steps, 2 * steps):            # lookup and update in turn; now and then a lookup more
+                if extra and t % 3 == 0:
+                    cache.lookup(ids[t + steps], out)
+                    cache.lookup(ids[t + 1], out)
+                cache.lookup(ids[t], out)
+                cache.update(ids[t], grads, 0.1)
+            assert cache.flush() == 0
+            results.append((table.cpu(), state.cpu()))
+        finally:
+            cache.close()
+    assert torch.equal(results[0][0], results[1][0]) and torch.equal(results[0][1], results[1][1])
+
+
 def test_announced_batches_of_all_sizes_in_turn():
     """Small batches behind the largest and before them, two ahead, with updates left out and lookups nobody announced in between."""
     from paper_2112_07221_amd import hetcache as hc
