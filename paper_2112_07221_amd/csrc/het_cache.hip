@@ -78,6 +78,8 @@ struct het_cache {
     uint32_t *sort_words[SORT_SETS] = {};     // SortPlan's cuts and beginnings
     int sort_set = 0;                // the set that holds the current batch's order
     uint32_t sorted_n = 0;           // how many ids that order has (0: there is none yet)
+    int older_set = -1;              // the set that still holds the order before it (-1: none does), and how many ids that has
+    uint32_t older_n = 0;
     Announced ann[SORT_SETS - 1];    // announced batches, oldest first
     int n_ann = 0;
     TrimPlan sel_tp{};               // the select plan of the rows now cached (fixed at the lookup)
@@ -256,9 +258,9 @@ uint32_t row_grid(const RowGeom &g, uint64_t items)
     return std::max(1u, std::min(cdiv(items, per_block), 256u * 8u));      // at most 8 workgroups per CU
 }
 
-// Stage `stage` of the sort of ids[n] into buffer set `set`; carried: its first stage was, or is.  The order sorted last tells
-// where the ranges begin.
-SortStage make_stage(const het_cache *c, const int64_t *ids, uint32_t n, int set, int stage, bool carried)
+// Stage `stage` of the sort of ids[n] into buffer set `set`; carried: its first stage was, or is.  The orders sorted last tell
+// where the ranges begin.  (A batch's first stage may read the order that its second one, in a kernel behind it, overwrites.)
+SortStage make_stage(het_cache *c, const int64_t *ids, uint32_t n, int set, int stage, bool carried)
 {
     SortStage s{};
     SortPlan &sp = s.sp;
@@ -268,6 +270,8 @@ SortStage make_stage(const het_cache *c, const int64_t *ids, uint32_t n, int set
     sp.begin = reinterpret_cast<uint16_t *>(sp.cuts + sp.ranges);
     sp.keys = c->keys[set][0]; sp.idx = c->idx[set][0];
     if (c->sorted_n) { sp.known = c->ws.skey; sp.n_known = c->sorted_n; }
+    if (c->older_set >= 0) { sp.older = c->keys[c->older_set][1]; sp.n_older = c->older_n; }
+    if (set == c->older_set) c->older_set = -1;
     s.ids = ids;
     s.keys_out = c->keys[set][1]; s.idx_out = c->idx[set][1];
     s.stage = stage;
@@ -304,6 +308,7 @@ void launch_solo(het_cache *c, const int64_t *ids, uint32_t n, int set)
 void sort_now(het_cache *c, const int64_t *ids, uint32_t n, int set, int first_stage)
 {
     if (first_stage == 0 && n <= SOLO_MAX) {
+        if (set == c->older_set) c->older_set = -1;
         if (n <= SORT_THREADS_ALONE) launch_solo<1>(c, ids, n, set);
         else if (n <= 2 * SORT_THREADS_ALONE) launch_solo<2>(c, ids, n, set);
         else launch_solo<4>(c, ids, n, set);
@@ -374,6 +379,7 @@ void drop_oldest_announcement(het_cache *c)
 
 void use_order(het_cache *c, int set, uint32_t n)
 {
+    if (set != c->sort_set && c->sorted_n) { c->older_set = c->sort_set; c->older_n = c->sorted_n; }
     c->sorted_n = n;
     c->sort_set = set;
     c->ws.skey = c->keys[set][1];

@@ -11,12 +11,12 @@
 // keys is put in order of the ranges, in its own place, and leaves where each range begins in it.  Then (range) a
 // workgroup per range collects its keys from all the tiles, whose beginnings in the tiles add up to the range's beginning in
 // the order, and sorts them in LDS.  No workgroup ever waits for another one, and nothing is counted with global atomics.
-// A range begins at a quantile of the order sorted before this one or, if that turns out not to divide these keys evenly, of a
-// sample, which every workgroup draws for itself (the same one), or at either.  A key that fills several ranges by itself gets
+// A range begins at a quantile of the order sorted before this one or, if that turns out not to divide these keys evenly, of the order before
+// that or of a sample, which every workgroup draws for itself (the same one), or at either.  A key that fills several ranges by itself gets
 // ranges of its own, a stretch of the tiles each.  Where the ranges begin decides nothing but how long this takes, and a range that
-// holds too many keys takes time in proportion to them (sort_packed, part_popular, sort_through_memory).  A step of 106496 ids, announced, 49.7 us;
-// if a rare key makes up 1, 2 or 4 % of every second batch 50.1, 52.2 and 53.3 (166 to 263 where such a range's keys were
-// searched again and again); of 409600 ids in bags 225 us, and 226, 227 and 228 (560 to 907).
+// holds too many keys takes time in proportion to them (sort_packed, part_popular, sort_through_memory).  A step of 106496 ids, announced one
+// ahead, 48.7 us; if a rare key makes up 1, 2 or 4 % of every second batch 48.7, 50.6 and 53.1 (165 to 256 where such a range's keys were
+// searched again and again), of two populations in turn 49.8 (138); of 409600 ids in bags 221 us, and 223, 224, 225 (566 to 1001) and 220 (1048).
 // In the place of a radix sort over the vocabulary's bits, of four to six stages: 26624 ids 22 -> 12.6 us, 106496 ids 25 -> 15.7
 // (18.9 with cuts from the sample: then the fullest range holds four times the mean).  What bounds it: a kernel boundary, barriers
 // and the ballots' vector instructions.
@@ -56,8 +56,8 @@ struct SortPlan {
     uint32_t *cuts;                          // [ranges]: where each begins
     uint16_t *begin;                         // [ntiles][ranges]: where each begins in each tile
     uint32_t *keys, *idx;                    // the tiles in order of the ranges
-    const uint32_t *known;                   // an order sorted before, or nullptr
-    uint32_t n_known;
+    const uint32_t *known, *older;           // the order sorted before this one and the one before that, or nullptr
+    uint32_t n_known, n_older;
 };
 // Words that the cuts and the beginnings of up to n ids take.
 __host__ __device__ inline size_t sort_plan_words(uint32_t n) { return sort_ranges(n, true) + ((size_t)sort_ranges(n, true) * ((n + SORT_TILE - 1) / SORT_TILE) + 1) / 2; }
@@ -249,10 +249,12 @@ __device__ __forceinline__ void sort_part_body(const SortStage &s, uint32_t tile
     };
     // Cuts from an order sorted before do for keys like those: if a range of more than one key gets far more of the drawn
     // keys than its share, cuts are made anew.  In a kernel that carries this: if the range holds, by the draws, more than a workgroup sorts
-    // twice, and they are more than chance gives a range of up to two shares (106496 ids, 256 ranges: 8 of 256; a step with a key
-    // at 4 % of the batch 53.3 us, and 56.2 if only 11 will do).  New cuts cost such a workgroup 5 us.
-    bool far_off = !sp.known;
-    if (!far_off) {
+    // twice, and they are more than chance gives a range of up to two shares (106496 ids, 256 ranges: 8 of 256; measured before the order before was looked at, a step
+    // with a key at 4 % of the batch 53.3 us, and 56.2 if only 11 will do).  New cuts cost such a workgroup 5 us.
+    // If they will not do, those of the order before are looked at: batches of two populations in turn, a step with cuts of
+    // drawn keys 56.4 us, with these 49.8 (106496 ids; of 409600 in bags 233.1 and 219.8); a new key at 4 % pays for the look (51.8 and 53.1, 223.4 and 224.5).
+    bool far_off = true;
+    for (const uint32_t *order = sp.known; order;) {
         bool many = false;
         if (t < SORT_SAMPLE) {
             const uint32_t r = last_at_or_below(drawn);
@@ -262,6 +264,11 @@ __device__ __forceinline__ void sort_part_body(const SortStage &s, uint32_t tile
             many = THREADS == SORT_THREADS ? lists > 1 && got >= SORT_SAMPLE * 3 / ranges + 5 : got >= SORT_SAMPLE * 2 / ranges + 9;
         }
         far_off = __syncthreads_or(many) != 0;
+        order = far_off && order != sp.older ? sp.older : nullptr;
+        if (order) {
+            for (uint32_t r = t; r < ranges; r += THREADS) { cuts[r] = r ? order[(uint64_t)r * sp.n_older / ranges] : 0u; base[r] = 0; }
+            __syncthreads();
+        }
     }
     if (far_off) {
         uint32_t *work = scan + WAVES;

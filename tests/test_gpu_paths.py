@@ -264,6 +264,89 @@ def test_a_rare_key_that_becomes_popular_does_not_hold_up_the_step(share):
         cache.close()
 
 
+def test_batches_of_two_kinds_in_turn_are_divided_as_evenly_as_of_one():
+    """The sort of batches of 400000 ids of two populations in turn, one ahead, carried by the update: the cuts come from the order before the
+    last one.  Its longest workgroup lives 12 us, as that of one population; with cuts made anew of drawn keys 54 to 68.
+    Bound: twice that of one population, measured beside it."""
+    from paper_2112_07221_amd import hetcache as hc
+    dev = torch.device("cuda:0")
+    n, vocab, steps = 400_000, 500_000, 14
+    rng = np.random.default_rng(4)
+    p = np.cumsum(np.arange(1, vocab + 1) ** -1.05)
+    perm = rng.permutation(vocab)
+    longest = []
+    for kinds in (1, 2):
+        ids = [perm[np.searchsorted(p, rng.random(n) * p[-1])] for t in range(steps)]
+        ids = [torch.from_numpy(x // 4 + vocab // 2 if kinds == 2 and t % 2 else x).to(dev) for t, x in enumerate(ids)]
+        table = torch.zeros(vocab, 16, device=dev)
+        out, grads = torch.empty(n, 16, device=dev), torch.zeros(n, 16, device=dev)
+        cache = hc.HetCache(1, 16, 0, hc.POLICY_NONE, n, hc.OPT_SGD)
+        try:
+            cache.attach_backing(table, None, torch.zeros(vocab, dtype=torch.int32, device=dev))
+            rec = torch.zeros(1 << 14, hc.TRACE_WORDS, dtype=torch.int64, device=dev)
+            lives = []
+            for t in range(steps):
+                if t + 1 < steps:
+                    cache.prefetch(ids[t + 1])
+                cache.lookup(ids[t], out)
+                rec.zero_()
+                cache.profile_trace(rec, "apply_kernel")
+                cache.update(ids[t], grads, 0.1)
+                torch.cuda.synchronize()
+                cache.profile_trace(None, "apply_kernel")
+                r = rec.cpu().numpy()
+                stage = r[r[:, 6] == 1]
+                if 2 < t < steps - 1:
+                    assert len(stage) > 0
+                    lives.append((stage[:, 5] - stage[:, 0]).max() / 100.0)      # (the counter runs at 100 MHz)
+            longest.append(np.median(lives))
+        finally:
+            cache.close()
+    assert longest[1] < 2 * longest[0], longest
+
+
+@pytest.mark.parametrize("ahead", [1, 2, 3])
+@pytest.mark.parametrize("host", [False, True])
+def test_batches_of_two_kinds_and_of_several_sizes(ahead, host):
+    """Cuts from the order before the last one while announcements take the buffers it lies in: batches of two populations and of three sizes, one
+    to three ahead, announcements withdrawn, lookups nobody announced, updates of other ids.  Whole numbers and lr 1, so rows are exact."""
+    from paper_2112_07221_amd import hetcache as hc
+    dev = torch.device("cuda:0")
+    rng = np.random.default_rng(ahead)
+    vocab, steps = 200_000, 24
+    sizes = [(30_000, 30_000, 45_000, 9_000)[t // 2 % 4] for t in range(steps)]
+    ids = [rng.integers(0, vocab, n) if t % 2 else np.minimum((rng.random(n) ** 3 * vocab / 8).astype(np.int64), vocab - 1) for t, n in enumerate(sizes)]
+    dids = [torch.from_numpy(x).to(dev) for x in ids]
+    table = torch.zeros(vocab, 1, pin_memory=True) if host else torch.zeros(vocab, 1, device=dev)
+    clock = torch.zeros(vocab, dtype=torch.int32, pin_memory=True) if host else torch.zeros(vocab, dtype=torch.int32, device=dev)
+    want = np.zeros(vocab)
+    cache = hc.HetCache(20_000, 1, 100, hc.POLICY_LFU, max(sizes), hc.OPT_SGD)
+    try:
+        cache.attach_backing(table, None, clock, hc.BACKING_PINNED_HOST if host else hc.BACKING_HBM)
+        for t in range(1, ahead):
+            cache.prefetch(dids[t])
+        for t, n in enumerate(sizes):
+            if t % 11 == 10:
+                cache.prefetch_cancel()
+            if t + ahead < steps:
+                cache.prefetch(dids[t + ahead])
+            out = torch.empty(n, 1, device=dev)
+            if t % 7 == 5:
+                other = torch.from_numpy(rng.integers(0, vocab, 12_000)).to(dev)
+                cache.lookup(other, torch.empty(12_000, 1, device=dev))
+            cache.lookup(dids[t], out)
+            assert np.array_equal(out.cpu().numpy()[:, 0], want[ids[t]]), t
+            assert np.array_equal(cache.last_lookup()[0], np.unique(ids[t])), t
+            g = rng.integers(-8, 9, n).astype(np.float32)
+            mine = dids[t].clone() if t % 5 == 3 else dids[t]
+            cache.update(mine, torch.from_numpy(g[:, None]).to(dev), 1.0)
+            np.subtract.at(want, ids[t], g.astype(np.float64))
+        assert cache.flush() == 0
+        assert np.array_equal(table.cpu().numpy()[:, 0], want.astype(np.float32))
+    finally:
+        cache.close()
+
+
 @pytest.mark.parametrize("ahead", [1, 2])
 @pytest.mark.parametrize("n", [400, 4_096, 4_097, 16_384, 16_385, 32_768, 32_769, 65_536, 65_537, 131_072, 131_073, 262_144, 262_145, 524_288, 524_289, 1 << 20])
 def test_the_sort_of_an_announced_batch_has_no_kernel_of_its_own(n, ahead):
