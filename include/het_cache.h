@@ -171,7 +171,10 @@ int het_lookup(het_cache *c, const int64_t *ids, int64_t n, float *out);
  * kernels of the calls made between this call and that lookup carry it in extra workgroups, one
  * stage per kernel (two, if two announced batches are under way); whatever is still missing runs
  * when the lookup comes.  A sort has two stages, and a lookup plus an update have two or three kernels that carry
- * one: announce a batch before the lookup of the batch before it, and its sort is never seen.  ids[n] (device) must be complete in stream order when this call is made and stay
+ * one: with the table in HBM, and lookups and updates in turn, announce a batch before the lookup of the batch before it,
+ * and its sort is never seen.  (Elsewhere a stage may be left to kernels of its own: with the table in host memory, where a lookup
+ * needs the next batch's order before its end, and where updates stop coming, because stages of batches of up to 32768 ids
+ * announced two ahead are left to them.)  ids[n] (device) must be complete in stream order when this call is made and stay
  * unchanged until the lookup that passes the same pointer and n.  That lookup checks the order sorted ahead
  * against the ids as they are then: ids that changed after the sort began set error bit 2, HET_ESTATE,
  * and its results are not meaningful (ids that changed before, with no call in between to carry its first
@@ -202,8 +205,10 @@ int het_backing_foreign_update(het_cache *c, const int64_t *ids, const float *de
 
 /*
  * Pooled Read for multi-hot inputs: bag b holds ids[offsets[b] .. offsets[b+1]) and
- * out[b][:] = sum of its rows, added in bag order in fp64 and rounded once (device,
- * float[n_bags][dim]).
+ * out[b][:] = sum of its rows in fp64, rounded once (device, float[n_bags][dim]).  The rows are added in a
+ * fixed order: in bag order within each of 1 to 256 contiguous shares of the bag, then the shares' sums.  How many
+ * shares depends on n, n_bags and dim alone, so the same call gives the same bits, but a bag's last
+ * bit may differ between calls of different n or n_bags.
  * offsets: device, int64[n_bags + 1], non-decreasing, offsets[0] = 0, offsets[n_bags] = n.
  */
 int het_lookup_pooled(het_cache *c, const int64_t *ids, int64_t n, const int64_t *offsets,

@@ -1358,7 +1358,7 @@ __device__ __forceinline__ uint32_t push_key_of(uint32_t key, uint32_t from_key,
     return EARLY || gone ? from_key : KEY_NONE;
 }
 
-// Drops the victims among 1024 consecutive slots, four per thread: erase the key, free the slot,
+// Drops the victims among EV_SLOTS consecutive slots, EV_ITEMS per thread: erase the key, free the slot,
 // raise c_g; then one row group per victim that holds updates copies its row (and accumulator)
 // to the global table: Evict's push (Section 3.1).  Where a victim goes in the evicted-id list
 // and (host-backed table) in the staging buffer follows from the select's per-block counts, so

@@ -71,8 +71,8 @@ struct het_cache {
     TrimPlan tp{};
     // Four sets of sort buffers: the order of the current batch (kept for its update) and up to
     // three batches announced ahead by het_prefetch, whose sorts are carried by the kernels of the
-    // calls in between (a sort is more stages long than a lookup and an update have kernels, so
-    // in steady state two announced batches are being sorted and a third stands ready).
+    // calls in between.  (With batches announced two ahead three stand announced when a lookup is called: its own, sorted by
+    // then, the next one and the one after that.)
     // Per set the tiles in order of the ranges, [0], and the order, [1].
     uint32_t *keys[SORT_SETS][2] = {}, *idx[SORT_SETS][2] = {};
     uint32_t *sort_words[SORT_SETS] = {};     // SortPlan's cuts and beginnings
