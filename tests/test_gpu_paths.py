@@ -45,10 +45,13 @@ def test_light_weight_lfu_over_a_border_of_the_first_digit(cap):
 @pytest.mark.parametrize("ahead", [0, 1, 2])
 @pytest.mark.parametrize("n,vocab", [(1, 5), (1_024, 2_047), (1_025, 2_048), (2_730, 300), (2_731, 300), (5_461, 70_000), (5_462, 70_000),
                                      (8_192, 1_000_000), (8_193, 1_000_000), (131_072, 4_000_000), (131_073, 4_194_304),
-                                     (262_144, 100_000), (262_145, 100_000), (262_145, 17_000_000), (20_000, 8_400_000)])
+                                     (262_144, 100_000), (262_145, 100_000), (262_145, 17_000_000), (20_000, 8_400_000),
+                                     (4_096, 1_000_000), (4_097, 1_000_000), (16_384, 50_000), (16_385, 50_000), (32_768, 300_000), (32_769, 300_000),
+                                     (65_536, 1_000_000), (65_537, 1_000_000), (524_288, 900_000), (524_289, 900_000)])
 def test_every_way_a_batch_is_sorted(n, vocab, ahead):
-    """One workgroup or stages, one to four passes, wide and narrow digits, super-tiles of 1, 4 and 8 tiles,
-    stages carried or alone: the distinct keys and the gradient sums of a no-cache step.  Gradients are
+    """One workgroup or two stages, carried or alone, on either side of the sizes at which one gives way to the other (4096 ids that nobody
+    announced), a tile ends (1024) and there are more ranges (from 64, at 16384 ids, to 1024), of vocabularies whose ranges take one
+    to four passes: the distinct keys and the gradient sums of a no-cache step.  Gradients are
     small integers and lr is 1, so every sum is exact."""
     from paper_2112_07221_amd import hetcache as hc
     dev = torch.device("cuda:0")
